@@ -1,4 +1,4 @@
-// fp32 MFMA GEMM family for gfx950 (v_mfma_f32_32x32x2_f32), used by every
+// fp32 MFMA GEMM family for gfx950 (v_mfma_f32_16x16x4_f32), used by every
 // fp32 workload: MLR logits, DML projections, the two ISTA contractions of
 // sparse coding, and the reconstruction + application of the SF sum.
 //
@@ -7,39 +7,42 @@
 // Either operand may be k-contiguous ([rows][k], e.g. W[J][D] against the
 // feature index) or k-strided ([k][rows], e.g. the SF matrices U[N][J], V[N][D]
 // against the SF index), so "U^T V" needs no transposed copy: a k-strided tile
-// is kept in LDS as it sits in memory and each MFMA lane picks one float.
+// is kept in LDS as it sits in memory.
 //
-// Workgroup: 256 threads = 2x2 wavefronts, tile BT x BT x 32 (BT = 64 or 128),
-// one LDS stage plus a register prefetch of the next k-slice.
+// One workgroup of eight wavefronts (two per SIMD) owns one output tile.  Operands
+// go from global memory straight into LDS, several k-slices ahead; the wavefronts
+// divide the tile between them, and the k of every slice as well where the tile is
+// too small for eight (their partial sums meet in LDS at the end), so that a
+// contraction with few outputs and a long k fills the chip in one launch.
 //
-// Shapes with few output tiles and a long k (the residual x - W^T a of sparse
-// coding: 512 x 1024 over k = 4096; the DML projections) are split along k over
-// several workgroups: each writes its partial sums to a scratch buffer and a
-// second kernel adds them in a fixed order and applies the epilogue, so results
-// stay bit-reproducible (no float atomics).
+// What bounds it (MI355X, us of one launch in a row of dependent ones; in front of the
+// arrow the kernel this one replaced: four wavefronts of 32x32x2 MFMAs, a k-split over
+// workgroups with a second launch, rows off 16-byte alignment through a scalar path):
+//   1000 x 2048 x 2048 (both k-strided)      92 -> 74   64.7 us in the k-loop (54.5 at 2.4 GHz; the clock is 2.2
+//                                                       in kernels this short), 2.3 first loads, 2.5 epilogue
+//   512 x 4096 x 1024  (both k-contiguous)   45 -> 40   32 in the loop, 27.9 at 2.4 GHz
+//   512 x 1024 x 4096  (k-contiguous x strided) 47 -> 43   k divided inside the workgroup, no second launch
+//   256 x 1000 x 2048                        21 -> 12
+//   100 x 1000 x 300                         14 -> 6.6  launch, first loads, epilogue: 5 us
+//   100 x 300 x 1000                         14 -> 5.7
+//   1003 x 2047 x 800 (nothing aligned)      60 -> 41
+//   100 x 1003 x 2047 (nothing aligned)      20 -> 14
+// 16x16x4 MFMAs rather than 32x32x2: in a kernel of 60 us a loop of nothing but MFMAs on
+// random operands runs at 2.40 GHz with the former and 2.23 with the latter.  Two
+// wavefronts per SIMD hide each other's LDS latency, barriers and load issue: without any
+// loads or reads the loop of T1 below takes 68 instead of 74 us.
 #include "kernels.h"
 
 #include <cmath>
+#include <type_traits>
 
 namespace sfb {
 namespace {
 
-typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-constexpr int NT = 256;
-constexpr int BK = 32;
-constexpr int KC_PITCH = BK + 4;  // floats; 144-byte rows keep 16-byte reads of 16 rows on distinct banks
-
-template <int BT>
-struct TileGeom {
-    static constexpr int KS_PITCH = BT + 32;
-    static constexpr int KC_FLOATS = BT * KC_PITCH;
-    static constexpr int KS_FLOATS = BK * KS_PITCH;
-    static constexpr int FLOATS = KC_FLOATS > KS_FLOATS ? KC_FLOATS : KS_FLOATS;
-    static constexpr int UNITS = BT * BK / 4;  // float4 units per operand tile
-    static constexpr int PER_THREAD = UNITS / NT;
-};
+constexpr int NWAVES = 8, NT = 64 * NWAVES;
+constexpr int LDS_MAX = 152 * 1024;      // of the 160 KB of a CU
 
 struct Params {
     const float* A;
@@ -50,602 +53,662 @@ struct Params {
     int64_t lda, ldb, ldc;
     int64_t M, N, K;
     float eta, lambda;
-    int vecA, vecB;
-    int tiles_n;
-    int split_k;       // > 1: workgroup z of a tile covers k-slices [z * slabs, (z + 1) * slabs) and writes partial[z]
-    int64_t slabs;     // k-slices of BK per split
-    float* partial;    // [split_k][M][N]
-};
-
-// Global -> registers for one operand tile.  `outer` is the strided index
-// (rows for k-contiguous, k for k-strided), `inner` the contiguous one.
-template <int BT, bool KS>
-__device__ __forceinline__ void fetch_tile(floatx4 (&r)[TileGeom<BT>::PER_THREAD], const float* __restrict__ P,
-                                           int64_t ld, int64_t row0, int64_t rows, int64_t k0, int64_t K,
-                                           int vec, int tid)
-{
-    constexpr int INNER4 = KS ? BT / 4 : BK / 4;
-#pragma unroll
-    for (int i = 0; i < TileGeom<BT>::PER_THREAD; ++i) {
-        const int u = tid + NT * i;
-        const int o = u / INNER4;
-        const int c = (u % INNER4) * 4;
-        const int64_t outer = (KS ? k0 : row0) + o;
-        const int64_t inner = (KS ? row0 : k0) + c;
-        const int64_t outer_end = KS ? K : rows;
-        const int64_t inner_end = KS ? rows : K;
-        floatx4 v = {0.f, 0.f, 0.f, 0.f};
-        if (outer < outer_end) {
-            const float* src = P + outer * ld + inner;
-            if (vec && inner + 3 < inner_end) {
-                v = *reinterpret_cast<const floatx4*>(src);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (inner + e < inner_end) v[e] = src[e];
-            }
-        }
-        r[i] = v;
-    }
-}
-
-template <int BT, bool KS>
-__device__ __forceinline__ void stash_tile(float* lds, const floatx4 (&r)[TileGeom<BT>::PER_THREAD], int tid)
-{
-    constexpr int INNER4 = KS ? BT / 4 : BK / 4;
-    constexpr int PITCH = KS ? TileGeom<BT>::KS_PITCH : KC_PITCH;
-#pragma unroll
-    for (int i = 0; i < TileGeom<BT>::PER_THREAD; ++i) {
-        const int u = tid + NT * i;
-        const int o = u / INNER4;
-        const int c = (u % INNER4) * 4;
-        *reinterpret_cast<floatx4*>(lds + o * PITCH + c) = r[i];
-    }
-}
-
-// MFMA operand values of one lane for k-group t (8 consecutive k): lane group g
-// (lane / 32) owns k = 8t + 4g + e, e = 0..3; the e-th MFMA of the group
-// consumes element e from both lane groups, i.e. two distinct k per MFMA.
-template <int BT, bool KS, int TILES>
-__device__ __forceinline__ void read_frags(float (&f)[TILES][4], const float* lds, int w0, int l32, int g, int t)
-{
-#pragma unroll
-    for (int x = 0; x < TILES; ++x) {
-        const int row = w0 + x * 32 + l32;
-        if (KS) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) f[x][e] = lds[(8 * t + 4 * g + e) * TileGeom<BT>::KS_PITCH + row];
-        } else {
-            const floatx4 v = *reinterpret_cast<const floatx4*>(lds + row * KC_PITCH + 8 * t + 4 * g);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) f[x][e] = v[e];
-        }
-    }
-}
-
-template <int EPI>
-__device__ __forceinline__ void epilogue_elem(const Params& p, int64_t row, int64_t col, float acc, float invL)
-{
-    const int64_t idx = row * p.ldc + col;
-    if (EPI == EPI_STORE) {
-        p.C[idx] = acc;
-    } else if (EPI == EPI_RMW) {
-        p.C[idx] = p.C[idx] - p.eta * acc;
-    } else if (EPI == EPI_RESID) {
-        p.C[idx] = p.aux[idx] - acc;
-    } else {
-        const float t = p.aux[idx] + acc * invL;
-        const float th = p.lambda * invL;
-        p.C[idx] = t > th ? t - th : (t < -th ? t + th : 0.f);
-    }
-}
-
-template <int BT, bool A_KS, bool B_KS, int EPI>
-__global__ __launch_bounds__(NT) void gemm_f32_kernel(Params p)
-{
-    constexpr int TM = BT / 64;  // 32x32 MFMA tiles per wave along m (and n)
-    __shared__ __attribute__((aligned(16))) float ldsA[TileGeom<BT>::FLOATS];
-    __shared__ __attribute__((aligned(16))) float ldsB[TileGeom<BT>::FLOATS];
-
-    const int tid = threadIdx.x;
-    const int wave = tid >> 6;
-    const int lane = tid & 63;
-    const int l32 = lane & 31;
-    const int g = lane >> 5;
-    const int wm0 = (wave >> 1) * (BT / 2);
-    const int wn0 = (wave & 1) * (BT / 2);
-
-    const int64_t tile = blockIdx.x;
-    const int64_t m0 = (tile / p.tiles_n) * BT;
-    const int64_t n0 = (tile % p.tiles_n) * BT;
-    const int64_t z = blockIdx.y;
-
-    floatx16 acc[TM][TM];
-#pragma unroll
-    for (int a = 0; a < TM; ++a)
-#pragma unroll
-        for (int b = 0; b < TM; ++b)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
-
-    floatx4 ra[TileGeom<BT>::PER_THREAD], rb[TileGeom<BT>::PER_THREAD];
-    const int64_t nk_all = (p.K + BK - 1) / BK;
-    const int64_t k_first = p.split_k > 1 ? z * p.slabs : 0;
-    const int64_t nk = p.split_k > 1 ? (k_first + p.slabs < nk_all ? k_first + p.slabs : nk_all) : nk_all;
-    if (k_first < nk) {
-        fetch_tile<BT, A_KS>(ra, p.A, p.lda, m0, p.M, k_first * BK, p.K, p.vecA, tid);
-        fetch_tile<BT, B_KS>(rb, p.B, p.ldb, n0, p.N, k_first * BK, p.K, p.vecB, tid);
-    }
-    for (int64_t kt = k_first; kt < nk; ++kt) {
-        stash_tile<BT, A_KS>(ldsA, ra, tid);
-        stash_tile<BT, B_KS>(ldsB, rb, tid);
-        __syncthreads();
-        if (kt + 1 < nk) {
-            fetch_tile<BT, A_KS>(ra, p.A, p.lda, m0, p.M, (kt + 1) * BK, p.K, p.vecA, tid);
-            fetch_tile<BT, B_KS>(rb, p.B, p.ldb, n0, p.N, (kt + 1) * BK, p.K, p.vecB, tid);
-        }
-#pragma unroll
-        for (int t = 0; t < BK / 8; ++t) {
-            float fa[TM][4], fb[TM][4];
-            read_frags<BT, A_KS, TM>(fa, ldsA, wm0, l32, g, t);
-            read_frags<BT, B_KS, TM>(fb, ldsB, wn0, l32, g, t);
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-                for (int a = 0; a < TM; ++a)
-#pragma unroll
-                    for (int b = 0; b < TM; ++b)
-                        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[a][e], fb[b][e], acc[a][b], 0, 0, 0);
-        }
-        __syncthreads();
-    }
-
-    float invL = 0.f;
-    if (EPI == EPI_SHRINK) invL = 1.0f / p.L_ptr[0];
-    // Accumulator layout of the 32x32 MFMA: register i of lane (g, l32) holds
-    // row 8*(i/4) + 4*g + (i%4), column l32.
-#pragma unroll
-    for (int a = 0; a < TM; ++a)
-#pragma unroll
-        for (int b = 0; b < TM; ++b) {
-            const int64_t col = n0 + wn0 + b * 32 + l32;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int64_t row = m0 + wm0 + a * 32 + 8 * (i / 4) + 4 * g + (i % 4);
-                if (row < p.M && col < p.N) {
-                    if (p.split_k > 1)
-                        p.partial[(z * p.M + row) * p.N + col] = acc[a][b][i];
-                    else
-                        epilogue_elem<EPI>(p, row, col, acc[a][b][i], invL);
-                }
-            }
-        }
-}
-
-// Sum of the k-splits in index order, then the epilogue.
-template <int EPI>
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(Params p)
-{
-    float invL = 0.f;
-    if (EPI == EPI_SHRINK) invL = 1.0f / p.L_ptr[0];
-    const int64_t total = p.M * p.N, stride = (int64_t)gridDim.x * 256;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += stride) {
-        float sum = p.partial[i];
-        for (int z = 1; z < p.split_k; ++z) sum += p.partial[z * total + i];
-        epilogue_elem<EPI>(p, i / p.N, i % p.N, sum, invL);
-    }
-}
-
-// ---------------------------------------------------------------------------
-// The pipelined kernel: operands whose rows are 16-byte aligned go from global
-// memory straight into LDS (global_load_lds_dwordx4, 16 bytes a lane, no staging
-// registers), three LDS stages of one k-slice (32 of k) each, one workgroup
-// barrier per slice: at slice s the loads of slice s + 1 are in flight, those of
-// slice s + 2 are issued right after the barrier into the stage slice s - 1 was
-// read from (every wavefront has passed its reads of s - 1 before it arrives at
-// the barrier).  256 threads = 2 x 2 wavefronts, tile BM x BN.
-//   k-contiguous operand: LDS rows of 32 floats (128 bytes), the eight 16-byte
-//     chunks of row r XOR-swizzled by r & 7 (applied on the global side: a lane
-//     fetches the chunk that belongs in its slot), so that the 16-byte fragment
-//     reads of 8 consecutive rows hit 8 different bank groups;
-//   k-strided operand: LDS as in memory, [k][rows]; a fragment is four 4-byte reads.
-// Rows past the end of the matrix are clamped (they feed accumulators that are not
-// stored).  A last partial k-slice (K % 32 != 0) goes through registers with zero
-// fill, like every slice of the plain kernel above.
-// ---------------------------------------------------------------------------
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-constexpr int DL_STAGES = 4;     // LDS stages: the loads of three k-slices are in flight while one is multiplied
-
-struct DlParams {
-    Params g;
+    int tiles_m, tiles_n;
+    int split_k;          // > 1: workgroup z of a tile covers k-slices [z * per_split, (z + 1) * per_split) and writes partial[z]
+    int64_t per_split;    // k-slices per split
+    float* partial;       // [split_k][M][N]
     int num_xcd;
-    int tiles_m;
-    int group_m;    // raster: groups of group_m row-tiles, row-tile index fastest inside a group
+    int group_m;          // raster: groups of group_m row-tiles, row-tile index fastest inside a group
 };
 
-__device__ __forceinline__ void dl_load_16(uint32_t lds_addr, uint64_t gbase, uint32_t voff)
+// A workgroup tile of BM x BN, WM x WN wavefronts over it and KW over k: each wavefront multiplies a block of
+// 16 TA x 16 TB over its 16 of the KB = 16 KW values of k of a slice.
+template <int BM_, int BN_, int WM_, int WN_, int KW_, int MAX_NS = 5>
+struct Tile {
+    static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, KW = KW_, KB = 16 * KW;
+    static constexpr int TA = BM / WM / 16, TB = BN / WN / 16;  // 16 x 16 MFMA tiles of a wavefront
+    static constexpr int A_BYTES = BM * KB * 4, B_BYTES = BN * KB * 4, STAGE = A_BYTES + B_BYTES;
+    static constexpr int MEET = KW > 1 ? NWAVES * TA * TB * 1024 : 0;      // LDS of the partial sums
+    static constexpr int NS = LDS_MAX / STAGE < MAX_NS ? LDS_MAX / STAGE : MAX_NS;   // LDS stages
+    static constexpr int NSR = NS > 5 ? NS : 3;                            // the same where slices wait in registers first
+    static constexpr int lds(bool direct) { return (direct ? NS : NSR) * STAGE > MEET ? (direct ? NS : NSR) * STAGE : MEET; }
+    static_assert(WM * WN * KW == NWAVES && KW % 2 == 0 && NS >= 3 && MEET <= LDS_MAX, "tile");
+};
+
+__device__ __forceinline__ void load_to_lds_16(uint32_t lds_addr, uint64_t gbase, uint32_t voff)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(voff), "s"(gbase) : "memory");
 }
-__device__ __forceinline__ uint64_t dl_uniform64(uint64_t a)
+__device__ __forceinline__ void load_to_lds_4(uint32_t lds_addr, uint64_t vaddr)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_addr), "v"(vaddr) : "memory");
+}
+__device__ __forceinline__ uint64_t uniform64(uint64_t a)
 {
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
     return ((uint64_t)hi << 32) | (uint64_t)lo;
 }
 
-template <int LX, bool KS, int ROWS_TILE>
-__device__ __forceinline__ void dl_lane_offsets(uint32_t (&off)[LX], int wave, int lane, int64_t row0, int64_t rows, int64_t ld)
+// LDS image of one operand's slice (ROWS x KB floats):
+//   k-contiguous: per 32 of k, ROWS rows of 32 floats (128 bytes), the eight 16-byte chunks of row r XOR-swizzled by
+//     (r ^ r / 8) & 7, so that the 16-byte fragment reads of 16 consecutive rows meet every bank once;
+//   k-strided: [k][rows] as in memory; a fragment is four reads of T consecutive floats.
+// MFMA tile x, lane l of a wavefront's block of 16 T rows is row T l + x of the block in both images (LDS row 16 x + l
+// of a k-contiguous block holds it): a lane's T columns of C are neighbours and its fragments of a k-strided operand
+// one read.  Rows past the end of the matrix are clamped (they feed accumulators that are not stored).
+__device__ __forceinline__ int swz(int r) { return (r ^ (r >> 3)) & 7; }
+template <int T>
+__device__ __forceinline__ int tile_row(int r) { return (r / (16 * T)) * (16 * T) + T * (r % 16) + (r % (16 * T)) / 16; }
+
+// T consecutive floats, at any float of global memory.
+template <int T> struct Vec;
+template <> struct Vec<1> { typedef float type __attribute__((ext_vector_type(1), aligned(4))); };
+template <> struct Vec<2> { typedef float type __attribute__((ext_vector_type(2), aligned(4))); };
+template <> struct Vec<4> { typedef float type __attribute__((ext_vector_type(4), aligned(4))); };
+
+// Which 16 bytes of the operand lane `lane` of 1 KB unit u of a slice takes: row (k-contiguous) or k (k-strided) and the
+// first of four floats along the other index, relative to the tile and the slice.
+template <int ROWS, bool KS, int T>
+__device__ __forceinline__ void unit_place(int u, int lane, int& row, int& k)
 {
-#pragma unroll
-    for (int i = 0; i < LX; ++i) {
-        if (!KS) {
-            const int r = 8 * (LX * wave + i) + (lane >> 3);
-            int64_t rr = row0 + r;
-            if (rr >= rows) rr = rows - 1;
-            off[i] = (uint32_t)((rr - row0) * ld * 4) + (uint32_t)((((lane & 7) ^ (r & 7)) << 4));
-        } else {
-            const int byte = 1024 * (LX * wave + i) + 16 * lane;
-            const int k = byte / (ROWS_TILE * 4);
-            int64_t m = row0 + (byte % (ROWS_TILE * 4)) / 4;
-            if (m + 4 > rows) m = rows - 4;               // (rows % 4 == 0 and rows >= 4 on this path)
-            off[i] = (uint32_t)(k * ld * 4) + (uint32_t)((m - row0) * 4);
-        }
+    if (KS) {
+        const int f = 256 * u + 4 * lane;
+        k = f / ROWS;
+        row = f % ROWS;
+    } else {
+        const int r = 8 * (u % (ROWS / 8)) + (lane >> 3);
+        row = tile_row<T>(r);
+        k = 32 * (u / (ROWS / 8)) + 4 * ((lane & 7) ^ swz(r));
     }
 }
 
-template <int BM, int BN, bool A_KS, bool B_KS, int EPI>
-__global__ __launch_bounds__(NT) void gemm_f32_dl_kernel(DlParams dp)
-{
-    const Params& p = dp.g;
-    constexpr int TMA = BM / 64, TNB = BN / 64;          // 32 x 32 MFMA tiles per wavefront
-    constexpr int A_BYTES = BM * BK * 4, B_BYTES = BN * BK * 4, STAGE = A_BYTES + B_BYTES, NS = DL_STAGES;
-    constexpr int LA = A_BYTES / 1024 / 4, LB = B_BYTES / 1024 / 4;   // 1 KB loads per wavefront and slice
-    extern __shared__ u32x4 dl_smem[];
-    char* const lds = reinterpret_cast<char*>(dl_smem);
-    const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)dl_smem;
+// Direct loads of one operand whose rows are 16-byte aligned.
+template <int ROWS, int KB, bool KS, int T>
+struct DirectLoader {
+    static constexpr int L = ROWS * KB * 4 / 1024 / NWAVES;
+    static_assert(L * 1024 * NWAVES == ROWS * KB * 4, "loads per wavefront");
+    uint64_t base[L];      // uniform: the address of the unit's first row and k
+    uint32_t voff[L];
+    uint64_t step;
 
-    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
+    __device__ __forceinline__ void init(const float* P, int64_t ld, int64_t row0, int64_t rows, int64_t k0, int wave, int lane)
+    {
+        step = (uint64_t)(KS ? KB * ld : KB) * 4;
+#pragma unroll
+        for (int i = 0; i < L; ++i) {
+            int r, k, r_first, k_first;
+            unit_place<ROWS, KS, T>(L * wave + i, lane, r, k);
+            if (KS) {
+                k_first = 256 * (L * wave + i) / ROWS;
+                int64_t m = row0 + r;
+                if (m + 4 > rows) m = rows - 4;               // (rows % 4 == 0 and rows >= 4 here)
+                base[i] = uniform64(reinterpret_cast<uint64_t>(P) + (uint64_t)((k0 + k_first) * ld + row0) * 4);
+                voff[i] = (uint32_t)((k - k_first) * ld * 4) + (uint32_t)((m - row0) * 4);
+            } else {
+                r_first = tile_row<T>(8 * ((L * wave + i) % (ROWS / 8)));
+                k_first = 32 * ((L * wave + i) / (ROWS / 8));
+                int64_t br = row0 + r_first, gr = row0 + r;
+                if (br >= rows) br = rows - 1;
+                if (gr >= rows) gr = rows - 1;
+                base[i] = uniform64(reinterpret_cast<uint64_t>(P) + (uint64_t)(br * ld + k0 + k_first) * 4);
+                voff[i] = (uint32_t)((gr - br) * ld * 4) + (uint32_t)((k - k_first) * 4);
+            }
+        }
+    }
+    __device__ __forceinline__ void issue(int i, uint32_t dst, int wave)
+    {
+        load_to_lds_16(dst + (uint32_t)(L * wave + i) * 1024u, base[i], voff[i]);
+        base[i] += step;
+    }
+};
+
+// The same for rows at any alignment: 16-byte loads at 4-byte alignment into registers, then to LDS.  (Direct loads of
+// 4 bytes a lane, the alternative, keep the address unit busy four times as long per byte.)
+template <int ROWS, int KB, bool KS, int T>
+struct RegLoader {
+    static constexpr int L = ROWS * KB * 4 / 1024 / NWAVES;
+    uint64_t at[L];        // the lane's own address
+    int shift[L];          // k-strided, last rows: the four floats are loaded `shift` floats early (they end with the row)
+    uint64_t step;
+    int last;              // k-strided with fewer than four rows in all: the last row (float by float); otherwise -1
+
+    __device__ __forceinline__ void init(const float* P, int64_t ld, int64_t row0, int64_t rows, int64_t k0, int wave, int lane)
+    {
+        step = (uint64_t)(KS ? KB * ld : KB) * 4;
+        last = KS && rows < 4 ? (int)rows - 1 : -1;
+#pragma unroll
+        for (int i = 0; i < L; ++i) {
+            int r, k;
+            unit_place<ROWS, KS, T>(L * wave + i, lane, r, k);
+            int64_t m = row0 + r;
+            shift[i] = 0;
+            if (KS && last < 0) {
+                if (m >= rows) m = rows - 1;
+                if (m + 4 > rows) {
+                    shift[i] = (int)(m + 4 - rows);
+                    m = rows - 4;
+                }
+            } else if (m >= rows) {
+                m = KS ? 0 : rows - 1;
+            }
+            at[i] = reinterpret_cast<uint64_t>(P) + (uint64_t)(KS ? (k0 + k) * ld + m : m * ld + k0 + k) * 4;
+        }
+    }
+    __device__ __forceinline__ floatx4 fetch(int i)
+    {
+        const float* src = reinterpret_cast<const float*>(at[i]);
+        at[i] += step;
+        if (KS && last >= 0) return floatx4{src[0], src[last < 1 ? last : 1], src[last < 2 ? last : 2], src[last]};
+        const typename Vec<4>::type v = *reinterpret_cast<const typename Vec<4>::type*>(src);
+        return floatx4{v[0], v[1], v[2], v[3]};
+    }
+    __device__ __forceinline__ void store(int i, char* dst, int wave, int lane, floatx4 v) const
+    {
+        if (KS) {
+            const bool one = shift[i] & 1, two = shift[i] & 2;
+            const float a0 = one ? v[1] : v[0], a1 = one ? v[2] : v[1], a2 = one ? v[3] : v[2], a3 = v[3];
+            v = floatx4{two ? a2 : a0, two ? a3 : a1, a2, a3};
+        }
+        *reinterpret_cast<floatx4*>(dst + (L * wave + i) * 1024 + lane * 16) = v;
+    }
+};
+
+// The values of a partial slice (k0 .. K) that this thread puts into LDS itself, zero past K.
+template <int ROWS, int KB, bool KS, int T>
+struct TailPart {
+    static_assert(ROWS * KB % NT == 0, "whole parts");
+    static constexpr int PER = ROWS * KB / NT;
+    float v[PER];
+    __device__ __forceinline__ void fetch(const float* P, int64_t ld, int64_t row0, int64_t rows, int64_t k0, int64_t K, int tid)
+    {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int f = tid + NT * i;
+            const int kk = KS ? f / ROWS : (f / (ROWS * 32)) * 32 + f % 32;
+            int64_t row = row0 + (KS ? f % ROWS : tile_row<T>((f / 32) % ROWS));
+            if (row >= rows) row = rows - 1;
+            v[i] = k0 + kk < K ? P[KS ? (k0 + kk) * ld + row : row * ld + k0 + kk] : 0.f;
+        }
+    }
+    __device__ __forceinline__ void store(char* dst, int tid) const
+    {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int f = tid + NT * i, r = (f / 32) % ROWS, pos = f % 32;
+            const int at = KS ? f : (f / 32) * 32 + (((pos >> 2) ^ swz(r)) << 2) + (pos & 3);
+            *reinterpret_cast<float*>(dst + at * 4) = v[i];
+        }
+    }
+};
+
+template <int EPI>
+__device__ __forceinline__ float combine(float old, float acc, float eta, float invL, float th)
+{
+    if (EPI == EPI_RMW) return old - eta * acc;
+    if (EPI == EPI_RESID) return old - acc;
+    if (EPI == EPI_SHRINK) {
+        const float t = old + acc * invL;
+        return t > th ? t - th : (t < -th ? t + th : 0.f);
+    }
+    return acc;
+}
+
+template <class TL, bool A_KS, bool B_KS, int EPI, bool DIRECT>
+__global__ __launch_bounds__(NT, 2) void gemm_f32_kernel(Params p)
+{
+    constexpr int BM = TL::BM, BN = TL::BN, WM = TL::WM, WN = TL::WN, KW = TL::KW, KB = TL::KB;
+    constexpr int TA = TL::TA, TB = TL::TB, STAGE = TL::STAGE, A_BYTES = TL::A_BYTES, NS = DIRECT ? TL::NS : TL::NSR;
+    extern __shared__ floatx4 gemm_smem[];
+    char* const lds = reinterpret_cast<char*>(gemm_smem);
+    const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)gemm_smem;
+
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, quad = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm0 = (wave >> 1) * (BM / 2), wn0 = (wave & 1) * (BN / 2);
+    const int kw = wave / (WM * WN), wm0 = ((wave / WN) % WM) * (16 * TA), wn0 = (wave % WN) * (16 * TB);
 
     // tiles: each XCD (one L2) takes a contiguous range of a raster in which consecutive tiles form compact blocks
     // (group_m row-tiles x as many column-tiles): the workgroups of an XCD walk k together, so a line of an operand
     // panel is fetched into that L2 once and found there by the other tiles that share the panel
-    const int64_t tiles = (int64_t)gridDim.x;
     int64_t m0, n0;
-    {
-        const int64_t x = blockIdx.x % dp.num_xcd, wi = blockIdx.x / dp.num_xcd;
-        const int64_t q = tiles / dp.num_xcd, r = tiles % dp.num_xcd;
-        const int64_t L = x * q + (x < r ? x : r) + wi;
-        const int64_t per_group = (int64_t)dp.group_m * p.tiles_n;
-        const int64_t grp = L / per_group, rr = L % per_group;
-        const int64_t rem = dp.tiles_m - grp * dp.group_m;
-        const int64_t gm = rem < dp.group_m ? rem : dp.group_m;
-        m0 = (grp * dp.group_m + rr % gm) * BM;
-        n0 = (rr / gm) * BN;
+    {   // (32-bit: a 64-bit division is some hundred instructions in front of the first load)
+        const uint32_t tiles = gridDim.x, xcds = (uint32_t)p.num_xcd, tiles_n = (uint32_t)p.tiles_n, tiles_m = (uint32_t)p.tiles_m;
+        const uint32_t x = blockIdx.x % xcds, wi = blockIdx.x / xcds, q = tiles / xcds, r = tiles % xcds;
+        const uint32_t t = x * q + (x < r ? x : r) + wi;
+        const uint32_t per_group = (uint32_t)p.group_m * tiles_n;      // (<= tiles)
+        const uint32_t grp = t / per_group, rr = t % per_group, first = grp * (uint32_t)p.group_m;
+        const uint32_t gm = tiles_m - first < (uint32_t)p.group_m ? tiles_m - first : (uint32_t)p.group_m;
+        m0 = (int64_t)(first + rr % gm) * BM;
+        n0 = (int64_t)(rr / gm) * BN;
     }
     const int64_t z = blockIdx.y;
-    const int64_t nk_full = p.K / BK;                     // whole slices
-    const int64_t nk_all = (p.K + BK - 1) / BK;
-    const int64_t k_first = p.split_k > 1 ? z * p.slabs : 0;
-    const int64_t k_end = p.split_k > 1 ? (k_first + p.slabs < nk_all ? k_first + p.slabs : nk_all) : nk_all;
-    const int64_t k_end_full = k_end < nk_full ? k_end : nk_full;     // direct loads cover [k_first, k_end_full)
+    // slices of this workgroup: the whole ones [k_first, k_end) and, for the last split, the partial one, which comes
+    // first (stage 0, through registers, under the latency of the direct loads of the others)
+    const int64_t whole = p.K / KB, all = (p.K + KB - 1) / KB;
+    const int64_t k_first = p.split_k > 1 ? z * p.per_split : 0;
+    int64_t k_end = p.split_k > 1 ? k_first + p.per_split : all;
+    const bool tail = k_end >= all && all > whole;
+    if (k_end > whole) k_end = whole;
+    const int64_t n = (k_end > k_first ? k_end - k_first : 0) + (tail ? 1 : 0);
 
-    // ---- loader: per-lane byte offsets within a slice, relative to the operand's base of the slice ----
-    // k-contiguous: load i of a wavefront fills LDS rows 8 (LX * wave + i) .. + 7; lane l fills slot l & 7 of row
-    //   + (l >> 3), i.e. fetches chunk (l & 7) ^ (row & 7) of that row.
-    // k-strided: the slice is BK rows of BM (BN) floats; 1 KB pieces in order.
-    uint32_t offA[LA], offB[LB];
-    dl_lane_offsets<LA, A_KS, BM>(offA, wave, lane, m0, p.M, p.lda);
-    dl_lane_offsets<LB, B_KS, BN>(offB, wave, lane, n0, p.N, p.ldb);
-    // base address of the operand's first element of slice kt (may be "before" the tile's clamped rows: offsets are >= 0)
-    auto baseA = [&](int64_t kt) {
-        return dl_uniform64(reinterpret_cast<uint64_t>(p.A) + (uint64_t)(A_KS ? (kt * BK * p.lda + m0) : (m0 * p.lda + kt * BK)) * 4);
-    };
-    auto baseB = [&](int64_t kt) {
-        return dl_uniform64(reinterpret_cast<uint64_t>(p.B) + (uint64_t)(B_KS ? (kt * BK * p.ldb + n0) : (n0 * p.ldb + kt * BK)) * 4);
-    };
-    auto issue = [&](int64_t kt, int stage) {            // all loads of slice kt (clamped to the last whole slice)
-        if (kt >= k_end_full) kt = k_end_full - 1;
-        const uint64_t ga = baseA(kt), gb = baseB(kt);
-        const uint32_t dst = lds_base + stage * STAGE;
+    floatx4 acc[TA][TB];
 #pragma unroll
-        for (int i = 0; i < LA; ++i) dl_load_16(dst + (LA * wave + i) * 1024u, ga, offA[i]);
+    for (int a = 0; a < TA; ++a)
 #pragma unroll
-        for (int i = 0; i < LB; ++i) dl_load_16(dst + A_BYTES + (LB * wave + i) * 1024u, gb, offB[i]);
-    };
+        for (int b = 0; b < TB; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-    floatx16 acc[TMA][TNB];
-#pragma unroll
-    for (int a = 0; a < TMA; ++a)
-#pragma unroll
-        for (int b = 0; b < TNB; ++b)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
-
-    // one k-slice from stage `st`: 4 groups of 8 k, each 4 MFMAs per tile pair.  The fragments of group t + 1 are
-    // read while the MFMAs of group t run (two register sets), a few reads after each MFMA; the order is pinned,
-    // otherwise the compiler puts each 4-byte read of a k-strided operand right before the MFMA that uses it and
-    // the wavefront waits out the LDS latency with an idle matrix pipe.
-    constexpr int NRA = A_KS ? TMA * 4 : TMA, NRB = B_KS ? TNB * 4 : TNB, NR = NRA + NRB;   // LDS reads per group
+    // ---- fragments of a slice: this wavefront's 16 k are 16 kw .. + 15; lane quad q owns k = 4 q + e, the e-th MFMA
+    // takes element e of all four
     struct Frag {
-        float a[TMA][4], b[TNB][4];
+        float a[TA][4], b[TB][4];
     };
-    auto read_op = [&](const char* sa, const char* sb, int t, int q, Frag& f) {    // q: compile-time after unrolling
-        if (q < NRA) {
-            const int x = A_KS ? q / 4 : q, r = wm0 + 32 * x + l32;
-            if (A_KS) {
-                const int e = q % 4;
-                f.a[x][e] = *reinterpret_cast<const float*>(sa + (8 * t + 4 * g + e) * (BM * 4) + r * 4);
-            } else {
-                const floatx4 v = *reinterpret_cast<const floatx4*>(sa + r * 128 + (((2 * t + g) ^ (r & 7)) << 4));
+    uint32_t ra[A_KS ? 1 : TA], rb[B_KS ? 1 : TB];
+    if (A_KS) {
+        ra[0] = (uint32_t)((16 * kw + 4 * quad) * BM + wm0 + TA * l16) * 4u;
+    } else {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) f.a[x][e] = v[e];
+        for (int x = 0; x < TA; ++x) {
+            const int r = wm0 + 16 * x + l16;
+            ra[A_KS ? 0 : x] = (uint32_t)((kw / 2) * (BM * 128) + r * 128 + (((4 * (kw & 1) + quad) ^ swz(r)) << 4));
+        }
+    }
+    if (B_KS) {
+        rb[0] = (uint32_t)(A_BYTES + ((16 * kw + 4 * quad) * BN + wn0 + TB * l16) * 4);
+    } else {
+#pragma unroll
+        for (int x = 0; x < TB; ++x) {
+            const int r = wn0 + 16 * x + l16;
+            rb[B_KS ? 0 : x] = (uint32_t)(A_BYTES + (kw / 2) * (BN * 128) + r * 128 + (((4 * (kw & 1) + quad) ^ swz(r)) << 4));
+        }
+    }
+    constexpr int NRA = A_KS ? 4 : TA, NRB = B_KS ? 4 : TB, NR = NRA + NRB;   // LDS reads per slice
+    auto read_op = [&](const char* stage, int q, Frag& f) {    // q: a constant after unrolling
+        if (q < NRA) {
+            if (A_KS) {
+                typedef float V __attribute__((ext_vector_type(TA)));
+                const V v = *reinterpret_cast<const V*>(stage + ra[0] + q * (BM * 4));
+#pragma unroll
+                for (int x = 0; x < TA; ++x) f.a[x][A_KS ? q : 0] = v[x];
+            } else {
+                const floatx4 v = *reinterpret_cast<const floatx4*>(stage + ra[A_KS ? 0 : q]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) f.a[A_KS ? 0 : q][e] = v[e];
             }
         } else {
-            const int qq = q - NRA, x = B_KS ? qq / 4 : qq, r = wn0 + 32 * x + l32;
+            const int qq = q - NRA;
             if (B_KS) {
-                const int e = qq % 4;
-                f.b[x][e] = *reinterpret_cast<const float*>(sb + (8 * t + 4 * g + e) * (BN * 4) + r * 4);
+                typedef float V __attribute__((ext_vector_type(TB)));
+                const V v = *reinterpret_cast<const V*>(stage + rb[0] + qq * (BN * 4));
+#pragma unroll
+                for (int x = 0; x < TB; ++x) f.b[x][B_KS ? qq : 0] = v[x];
             } else {
-                const floatx4 v = *reinterpret_cast<const floatx4*>(sb + r * 128 + (((2 * t + g) ^ (r & 7)) << 4));
+                const floatx4 v = *reinterpret_cast<const floatx4*>(stage + rb[B_KS ? 0 : qq]);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) f.b[x][e] = v[e];
+                for (int e = 0; e < 4; ++e) f.b[B_KS ? 0 : qq][e] = v[e];
             }
         }
-    };
-    Frag f[2];
-    constexpr int NM = 4 * TMA * TNB;                                  // MFMAs per group
-    // groups t0, t0 + 1 of the slice in stage `st`; the reads interleaved with the MFMAs of a group fetch the next
-    // group, which for the slice's last group is group 0 of the slice in stage `st_next`
-    auto compute_half = [&](int st, int st_next, int t0) {
-        const char* sa = lds + st * STAGE;
-        const char* sb = sa + A_BYTES;
-        const char* na = lds + st_next * STAGE;
-        const char* nb = na + A_BYTES;
-#pragma unroll
-        for (int t = t0; t < t0 + 2; ++t) {
-            const bool last = t + 1 == BK / 8;
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int i = 0; i < NM; ++i) {
-                const int e = i / (TMA * TNB), a = (i / TNB) % TMA, b = i % TNB;
-                acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(f[t & 1].a[a][e], f[t & 1].b[b][e], acc[a][b], 0, 0, 0);
-#pragma unroll
-                for (int q = i * NR / NM; q < (i + 1) * NR / NM; ++q)
-                    read_op(last ? na : sa, last ? nb : sb, last ? 0 : t + 1, q, f[(t + 1) & 1]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-    };
-    auto compute = [&](int st) {      // a whole slice on its own (the partial last slice)
-        const char* sa = lds + st * STAGE;
-        const char* sb = sa + A_BYTES;
-#pragma unroll
-        for (int q = 0; q < NR; ++q) read_op(sa, sb, 0, q, f[0]);
-        compute_half(st, st, 0);
-        compute_half(st, st, 2);
     };
 
-    // The values the epilogue combines with (W, the samples, the previous codes): requested during the last
-    // k-slice, so that their latency runs under its MFMAs.
-    float old[TMA][TNB][16];
-    auto load_old = [&]() {
-        if (EPI == EPI_STORE || p.split_k > 1) return;
+    typename std::conditional<DIRECT, DirectLoader<BM, KB, A_KS, TA>, RegLoader<BM, KB, A_KS, TA>>::type la;
+    typename std::conditional<DIRECT, DirectLoader<BN, KB, B_KS, TB>, RegLoader<BN, KB, B_KS, TB>>::type lb;
+    constexpr int LA = decltype(la)::L, LB = decltype(lb)::L, LL = LA + LB;
+    [[maybe_unused]] auto issue_one = [&](int i, int stage) {
+        if constexpr (DIRECT) {
+            const uint32_t dst = lds_base + (uint32_t)stage * STAGE;
+            if (i < LA)
+                la.issue(i, dst, wave);
+            else
+                lb.issue(i - LA, dst + A_BYTES, wave);
+        }
+    };
+    [[maybe_unused]] floatx4 held[2][DIRECT ? 1 : LL];       // (not DIRECT) the next two slices to go to LDS, on their way
+    [[maybe_unused]] auto fetch_one = [&](int i) -> floatx4 {
+        if constexpr (DIRECT)
+            return floatx4{};
+        else
+            return i < LA ? la.fetch(i < LA ? i : 0) : lb.fetch(i < LA ? 0 : i - LA);
+    };
+    [[maybe_unused]] auto store_one = [&](int i, int stage, floatx4 v) {
+        if constexpr (!DIRECT) {
+            if (i < LA)
+                la.store(i < LA ? i : 0, lds + stage * STAGE, wave, lane, v);
+            else
+                lb.store(i < LA ? 0 : i - LA, lds + stage * STAGE + A_BYTES, wave, lane, v);
+        }
+    };
+
+    // Slice s lives in stage s % NS and is multiplied in two halves (elements 0, 1 and 2, 3 of the fragments).
+    // Between them every wavefront waits until slice s + 1 has landed and meets the others: after that barrier the
+    // stage of slice s - 1 is free (the loads of slice s + NS - 1 go there) and the fragments of slice s + 1 can be
+    // read, so that the MFMA pipe does not drain at a slice boundary.  Direct loads complete in order: "slice s + 1
+    // has landed" = at most the loads of the NS - 3 slices after it are outstanding.  (Through registers: slice
+    // s + NS - 1, requested two slices earlier, is written to that stage, and slice s + NS + 1 requested.)  Reads and loads
+    // follow the MFMAs one at a time (a burst of loads blocks the wavefront in the memory-issue stage); the order is
+    // pinned.
+    constexpr int HM = 2 * TA * TB;
+    auto mfma = [&](const Frag& f, int j) {
+        const int e = j / (TA * TB), a = (j / TB) % TA, b = j % TB;
+        acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(f.a[a][e], f.b[b][e], acc[a][b], 0, 0, 0);
+    };
+    // FEED 2: everything above; 1: write the held slice, request none; 0: no slice left to bring
+    auto slice = [&](const Frag& cur, Frag& next, floatx4* hold, int st, int st_next, auto feed_tag) {
+        constexpr int FEED = decltype(feed_tag)::value, OVER = DIRECT ? HM : HM / 2;
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int a = 0; a < TMA; ++a)
+        for (int j = 0; j < HM; ++j) mfma(cur, j);
+        __builtin_amdgcn_sched_barrier(0);
+        if (DIRECT && FEED)
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 3) * LL) : "memory");
+        else if (DIRECT)
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        const char* nxt = lds + st_next * STAGE;
+        const int st_load = st >= 1 ? st - 1 : NS - 1;
 #pragma unroll
-            for (int b = 0; b < TNB; ++b) {
-                const int64_t col = n0 + wn0 + b * 32 + l32, row_first = m0 + wm0 + a * 32 + 4 * g;
-                const float* src = (EPI == EPI_RMW ? p.C : p.aux) + row_first * p.ldc + col;
+        for (int j = 0; j < HM; ++j) {
+            mfma(cur, HM + j);
 #pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int dr = 8 * (i / 4) + (i % 4);
-                    old[a][b][i] = (col < p.N && row_first + dr < p.M) ? src[(int64_t)dr * p.ldc] : 0.f;
+            for (int q = j * NR / (HM / 2); q < (j + 1) * NR / (HM / 2) && q < NR; ++q) read_op(nxt, q, next);
+            if (FEED) {
+#pragma unroll
+                for (int q = j * LL / OVER; q < (j + 1) * LL / OVER && q < LL; ++q) {
+                    if (DIRECT) {
+                        issue_one(q, st_load);
+                    } else {
+                        store_one(q, st_load, hold[DIRECT ? 0 : q]);
+                        if (FEED == 2) hold[DIRECT ? 0 : q] = fetch_one(q);
+                    }
                 }
             }
+            __builtin_amdgcn_sched_barrier(0);
+        }
     };
-    const bool tail = k_end > k_end_full;
-    if (k_first < k_end_full) {
-        // Slice s lives in stage s % NS.  In the middle of slice s every wavefront waits until slice s + 1 has landed
-        // and meets the others: after that barrier the stage of slice s - 1 is free (the loads of slice s + NS - 1
-        // go there) and the second half of slice s can fetch the first fragments of slice s + 1, so that the MFMA
-        // pipe does not drain at a slice boundary.  Loads complete in order: "slice s + 1 has landed" = at most the
-        // loads of the NS - 3 slices after it are outstanding.
+
+    // ---- epilogue units: EU accumulator registers e of one a (rows TA (4 quad + e) + a of the wavefront's block) and
+    // all TB tiles along n (columns TB l16 .. + TB - 1); the KW wavefronts of a block share its units
+    constexpr int EU = TA >= KW ? 4 : (2 * TA >= KW ? 2 : 1), UNITS = TA * 4 / EU, PER = (UNITS + KW - 1) / KW;
+    typedef typename Vec<TB>::type VecC;
+    float* const out = p.split_k > 1 ? p.partial + z * p.M * p.N : p.C;
+    const int64_t ldo = p.split_k > 1 ? p.N : p.ldc;
+    const int64_t col = n0 + wn0 + TB * l16;
+    const bool direct = EPI == EPI_STORE || p.split_k > 1;
+    constexpr int PO = EPI == EPI_STORE ? 1 : PER;
+    float old[PO][EU][TB];
+    auto unit_row = [&](int unit, int e) { return m0 + wm0 + TA * (4 * quad + (unit % (4 / EU)) * EU + e) + unit / (4 / EU); };
+    auto load_old = [&]() {
+        if (direct) return;
+        const float* src = EPI == EPI_RMW ? p.C : p.aux;
 #pragma unroll
-        for (int i = 0; i < NS - 1; ++i) issue(k_first + i, i);
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * (LA + LB)) : "memory");
-        __syncthreads();
-        {
-            const char* sa = lds;
-            const char* sb = sa + A_BYTES;
+        for (int i = 0; i < PO; ++i) {
+            const int unit = kw * PER + i;
 #pragma unroll
-            for (int q = 0; q < NR; ++q) read_op(sa, sb, 0, q, f[0]);
-        }
-        int st = 0;
-        for (int64_t kt = k_first; kt < k_end_full; ++kt) {
-            const int st_next = st + 1 == NS ? 0 : st + 1;
-            compute_half(st, st_next, 0);
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 3) * (LA + LB)) : "memory");
-            __syncthreads();
-            issue(kt + NS - 1, st >= 1 ? st - 1 : NS - 1);    // into the stage slice kt - 1 was read from
-            if (kt + 1 == k_end_full && !tail) load_old();
-            compute_half(st, st_next, 2);
-            st = st_next;
-        }
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no direct load in flight when LDS is reused or released
-        __syncthreads();
-    }
-    if (k_end > k_end_full) {
-        // the partial last slice: through registers, zero-filled past K, into stage 0 in the layouts above
-        const int64_t k0 = nk_full * BK;
-        constexpr int PA = BM * BK / 4 / NT, PB = BN * BK / 4 / NT;
-        auto stage_partial = [&](char* dst, const float* P, int64_t ld, bool ks, int rows_tile, int64_t row0, int64_t rows,
-                                 int per) {
-            for (int i = 0; i < per; ++i) {
-                const int u = tid + NT * i;
-                floatx4 v = {0.f, 0.f, 0.f, 0.f};
-                if (!ks) {
-                    const int r = u / 8, c = u % 8;           // row, 16-byte chunk
-                    const int64_t rr = row0 + r, k = k0 + 4 * c;
-                    if (rr < rows) {
+            for (int e = 0; e < EU; ++e) {
+                const int64_t row = unit_row(unit, e);
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (k + e < p.K) v[e] = P[rr * ld + k + e];
+                for (int b = 0; b < TB; ++b) old[i][e][b] = 0.f;
+                if (unit < UNITS && row < p.M) {
+                    const float* s = src + row * p.ldc + col;
+                    if (col + TB <= p.N) {
+                        const VecC v = *reinterpret_cast<const VecC*>(s);
+#pragma unroll
+                        for (int b = 0; b < TB; ++b) old[i][e][b] = v[b];
+                    } else {
+#pragma unroll
+                        for (int b = 0; b < TB; ++b)
+                            if (col + b < p.N) old[i][e][b] = s[b];
                     }
-                    *reinterpret_cast<floatx4*>(dst + r * 128 + ((c ^ (r & 7)) << 4)) = v;
-                } else {
-                    const int per_row = rows_tile / 4, kk = u / per_row, m4 = (u % per_row) * 4;
-                    const int64_t k = k0 + kk;
-                    if (k < p.K) {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (row0 + m4 + e < rows) v[e] = P[k * ld + row0 + m4 + e];
-                    }
-                    *reinterpret_cast<floatx4*>(dst + kk * (rows_tile * 4) + m4 * 4) = v;
                 }
+            }
+        }
+    };
+
+    if (n > 0) {
+        const int64_t k0 = k_first * KB;
+        la.init(p.A, p.lda, m0, p.M, k0, wave, lane);
+        lb.init(p.B, p.ldb, n0, p.N, k0, wave, lane);
+        auto bring = [&](int first) {      // slices first .. NS - 2 on their way, and (through registers) NS - 1 and NS held
+            if constexpr (DIRECT) {
+#pragma unroll
+                for (int s = 0; s < NS - 1; ++s)
+                    if (s >= first && s < n) {
+#pragma unroll
+                        for (int i = 0; i < LL; ++i) issue_one(i, s);
+                    }
+            } else {
+                floatx4 early[NS - 1][LL];
+#pragma unroll
+                for (int s = 0; s < NS + 1; ++s)
+                    if (s >= first && s < n) {
+#pragma unroll
+                        for (int i = 0; i < LL; ++i) {
+                            if (s < NS - 1)
+                                early[s < NS - 1 ? s : 0][i] = fetch_one(i);
+                            else
+                                held[(s - NS + 1) & 1][i] = fetch_one(i);
+                        }
+                    }
+#pragma unroll
+                for (int s = 0; s < NS - 1; ++s)
+                    if (s >= first && s < n) {
+#pragma unroll
+                        for (int i = 0; i < LL; ++i) store_one(i, s, early[s][i]);
+                    }
             }
         };
-        stage_partial(lds, p.A, p.lda, A_KS, BM, m0, p.M, PA);
-        stage_partial(lds + A_BYTES, p.B, p.ldb, B_KS, BN, n0, p.N, PB);
+        if (tail) {
+            TailPart<BM, KB, A_KS, TA> ta;
+            TailPart<BN, KB, B_KS, TB> tb;
+            ta.fetch(p.A, p.lda, m0, p.M, whole * KB, p.K, tid);
+            tb.fetch(p.B, p.ldb, n0, p.N, whole * KB, p.K, tid);
+            bring(1);
+            ta.store(lds, tid);
+            tb.store(lds + A_BYTES, tid);
+        } else {
+            bring(0);
+            if (DIRECT && n >= NS - 1)
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * LL) : "memory");
+            else if (DIRECT)
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        }
         __syncthreads();
-        load_old();
-        compute(0);
-    } else if (k_first >= k_end_full) {
+        Frag f0, f1;
+#pragma unroll
+        for (int q = 0; q < NR; ++q) read_op(lds, q, f0);
+        int st = 0;
+        auto next_of = [](int x) { return x + 1 == NS ? 0 : x + 1; };
+        typedef std::integral_constant<int, 2> Feed;
+        int64_t s = 0;
+        const int64_t feeds = n - NS - (DIRECT ? 0 : 2);       // slices 0 .. feeds bring another one
+        for (; s < feeds; s += 2) {
+            const int s1 = next_of(st), s2 = next_of(s1);
+            slice(f0, f1, held[0], st, s1, Feed{});
+            slice(f1, f0, held[1], s1, s2, Feed{});
+            st = s2;
+        }
+        auto single = [&](auto feed_tag) {
+            slice(f0, f1, held[0], st, next_of(st), feed_tag);
+            f0 = f1;
+            if (!DIRECT) {
+#pragma unroll
+                for (int i = 0; i < LL; ++i) {
+                    const floatx4 t = held[0][DIRECT ? 0 : i];
+                    held[0][DIRECT ? 0 : i] = held[1][DIRECT ? 0 : i];
+                    held[1][DIRECT ? 0 : i] = t;
+                }
+            }
+            st = next_of(st);
+            ++s;
+        };
+        if (s <= feeds) single(Feed{});
+        if (!DIRECT)
+            while (s + NS - 1 < n) single(std::integral_constant<int, 1>{});
+        while (s + 1 < n) single(std::integral_constant<int, 0>{});
+        load_old();      // (their latency runs under the last slice)
+#pragma unroll
+        for (int j = 0; j < 2 * HM; ++j) mfma(f0, j);
+    } else {
         load_old();
     }
 
-    // Epilogue.  Register i of lane (g, l32) of MFMA tile (a, b) is row 32 a + 8 (i / 4) + 4 g + i % 4, column
-    // 32 b + l32 of the wavefront's block: for fixed (a, b, i) a half-wave covers 128 contiguous bytes of one row.
-    // The 16 values a tile combines with (W, the samples, the previous codes) are all requested before the first
-    // is used.
     float invL = 0.f, th = 0.f;
     if (EPI == EPI_SHRINK) {
         invL = 1.0f / p.L_ptr[0];
         th = p.lambda * invL;
     }
+    // partial sums: EU floats a lane per (tile, unit of it), added in the order of kw
+    typedef float VecE __attribute__((ext_vector_type(EU)));
+    VecE* const meet = reinterpret_cast<VecE*>(gemm_smem);
+    if (KW > 1) {
+        __syncthreads();
 #pragma unroll
-    for (int a = 0; a < TMA; ++a)
+        for (int t = 0; t < TA * TB; ++t)
 #pragma unroll
-        for (int b = 0; b < TNB; ++b) {
-            const int64_t col = n0 + wn0 + b * 32 + l32;
-            const int64_t row_first = m0 + wm0 + a * 32 + 4 * g;
-            const bool col_ok = col < p.N;
-            if (p.split_k > 1) {
-                float* dst = p.partial + (z * p.M + row_first) * p.N + col;
+            for (int q = 0; q < 4 / EU; ++q) {
+                VecE v;
 #pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int dr = 8 * (i / 4) + (i % 4);
-                    if (col_ok && row_first + dr < p.M) dst[(int64_t)dr * p.N] = acc[a][b][i];
-                }
-                continue;
+                for (int e = 0; e < EU; ++e) v[e] = acc[t / TB][t % TB][q * EU + e];
+                meet[((wave * TA * TB + t) * (4 / EU) + q) * 64 + lane] = v;
             }
-            float* dst = p.C + row_first * p.ldc + col;
+        __syncthreads();
+    }
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int dr = 8 * (i / 4) + (i % 4);
-                float v = acc[a][b][i];
-                if (EPI == EPI_RMW) {
-                    v = old[a][b][i] - p.eta * v;
-                } else if (EPI == EPI_RESID) {
-                    v = old[a][b][i] - v;
-                } else if (EPI == EPI_SHRINK) {
-                    const float t = old[a][b][i] + v * invL;
-                    v = t > th ? t - th : (t < -th ? t + th : 0.f);
-                }
-                if (col_ok && row_first + dr < p.M) dst[(int64_t)dr * p.ldc] = v;
+    for (int i = 0; i < PER; ++i) {
+        const int unit = KW > 1 ? kw * PER + i : i;
+        if (unit >= UNITS) break;
+        float v[TB][EU];
+#pragma unroll
+        for (int b = 0; b < TB; ++b) {
+            if (KW > 1) {
+                const int w0 = wave % (WM * WN), t = unit / (4 / EU) * TB + b, q = unit % (4 / EU);
+                VecE sum = meet[((w0 * TA * TB + t) * (4 / EU) + q) * 64 + lane];
+#pragma unroll
+                for (int k = 1; k < KW; ++k) sum += meet[(((w0 + k * WM * WN) * TA * TB + t) * (4 / EU) + q) * 64 + lane];
+#pragma unroll
+                for (int e = 0; e < EU; ++e) v[b][e] = sum[e];
+            } else {
+#pragma unroll
+                for (int e = 0; e < EU; ++e) v[b][e] = acc[i / (4 / EU)][b][(i % (4 / EU)) * EU + e];
             }
         }
-}
-
-template <int BT, bool A_KS, bool B_KS, int EPI>
-hipError_t launch_one(Params p, hipStream_t stream)
-{
-    const int64_t tm = (p.M + BT - 1) / BT, tn = (p.N + BT - 1) / BT;
-    p.tiles_n = (int)tn;
-    if (tm * tn > 0x7fffffffLL) return hipErrorInvalidValue;
-    const unsigned gz = p.split_k > 1 ? (unsigned)p.split_k : 1u;
-    hipLaunchKernelGGL((gemm_f32_kernel<BT, A_KS, B_KS, EPI>), dim3((unsigned)(tm * tn), gz), dim3(NT), 0, stream, p);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || p.split_k <= 1) return e;
-    int64_t g = (p.M * p.N + 255) / 256;
-    if (g > 4096) g = 4096;
-    hipLaunchKernelGGL((splitk_reduce_kernel<EPI>), dim3((unsigned)g), dim3(256), 0, stream, p);
-    return hipGetLastError();
-}
-
-template <bool A_KS, bool B_KS, int EPI>
-hipError_t launch_sized(Params p, hipStream_t stream)
-{
-    const int64_t t128 = ((p.M + 127) / 128) * ((p.N + 127) / 128);
-    if (t128 >= 256) {
-        p.split_k = 1;
-        return launch_one<128, A_KS, B_KS, EPI>(p, stream);
+#pragma unroll
+        for (int e = 0; e < EU; ++e) {
+            const int64_t row = unit_row(unit, e);
+            if (row >= p.M) continue;
+            float r[TB];
+#pragma unroll
+            for (int b = 0; b < TB; ++b)
+                r[b] = direct ? v[b][e] : combine<EPI>(old[EPI == EPI_STORE ? 0 : i][e][b], v[b][e], p.eta, invL, th);
+            float* dst = out + row * ldo + col;
+            if (col + TB <= p.N) {
+                VecC w;
+#pragma unroll
+                for (int b = 0; b < TB; ++b) w[b] = r[b];
+                *reinterpret_cast<VecC*>(dst) = w;
+            } else {
+#pragma unroll
+                for (int b = 0; b < TB; ++b)
+                    if (col + b < p.N) dst[b] = r[b];
+            }
+        }
     }
-    return launch_one<64, A_KS, B_KS, EPI>(p, stream);
 }
 
-// ---- the pipelined kernel: tile shape and k-split by a small cost model ----
-struct DlPlan {
-    int bm, bn, split;
+// Sum of the k-splits in index order, then the epilogue.
+template <int EPI>
+__global__ __launch_bounds__(256) void splitk_reduce_kernel(Params p)
+{
+    float invL = 0.f, th = 0.f;
+    if (EPI == EPI_SHRINK) {
+        invL = 1.0f / p.L_ptr[0];
+        th = p.lambda * invL;
+    }
+    const int64_t total = p.M * p.N, stride = (int64_t)gridDim.x * 256;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += stride) {
+        float sum = p.partial[i];
+        for (int z = 1; z < p.split_k; ++z) sum += p.partial[z * total + i];
+        const int64_t idx = i / p.N * p.ldc + i % p.N;
+        const float old = EPI == EPI_RMW ? p.C[idx] : (EPI == EPI_STORE ? 0.f : p.aux[idx]);
+        p.C[idx] = combine<EPI>(old, sum, p.eta, invL, th);
+    }
+}
+
+// ---- tile shape and k-split by a small cost model ----
+typedef Tile<128, 128, 2, 2, 2> T0;
+typedef Tile<128, 64, 2, 2, 2> T1;
+typedef Tile<64, 64, 2, 1, 4> T2;
+typedef Tile<64, 32, 2, 1, 4> T3;
+typedef Tile<32, 32, 1, 1, 8> T4;
+typedef Tile<16, 16, 1, 1, 8, 9> T5;
+constexpr int NTILES = 6;
+
+struct Plan {
+    int cfg, split;
 };
 
-// Estimated duration (seconds) of a contraction as `rounds` of one workgroup per CU, each walking its k-slices at
-// the fp32 MFMA rate of a CU times an efficiency that falls with the tile (smaller tiles move more operand bytes per
-// flop through the L2), plus, when k is split, the second pass that adds the partial sums.
-static DlPlan dl_plan(int64_t M, int64_t N, int64_t K, int cus, int max_split)
+// Estimated duration (us) of a contraction as `rounds` of one workgroup per CU, each walking its k-slices.  Per tile
+// shape: us per slice with every CU busy, and us per tile beside the slices (first loads, partial sums, epilogue).
+// Measured (direct, us of one launch, 2.5 of them between dependent launches): 1000 x 2048 x 2048 73 with T1, 78 T2,
+// 89 T3, 100 T4; 256 x 1000 x 2048 12.0 T4, 20.5 T3, 20.7 T5, 16 T3 split in two; 100 x 300 x 1000 5.7 T5, 9.4 T4,
+// 13 T3; 4096 x 4096 x 1024 260 T0, 283 T1.  The smallest tile waits for memory rather than for the matrix pipes, and
+// waits less where it leaves CUs idle.
+template <class TL>
+double plan_time(int64_t M, int64_t N, int64_t K, int cus, int s, double slice_us, double tile_us, double idle_gain)
 {
-    static const int shapes[3][2] = {{128, 128}, {128, 64}, {64, 64}};
-    static const double eff[3] = {0.85, 0.80, 0.70};
-    const int64_t nk = (K + BK - 1) / BK;
-    DlPlan best = {64, 64, 1};
+    const int64_t tiles = ((M + TL::BM - 1) / TL::BM) * ((N + TL::BN - 1) / TL::BN), nk = (K + TL::KB - 1) / TL::KB;
+    const double rounds = (double)((tiles * s + cus - 1) / cus), slices = (double)((nk + s - 1) / s);
+    const double busy = (double)(tiles * s) / (double)cus;
+    if (busy < 1.0) slice_us *= 1.0 - idle_gain * (1.0 - busy);
+    double t = 2.5 + rounds * (slices * slice_us + tile_us);
+    if (s > 1) t += 4.5 + (double)(s + 1) * (double)M * (double)N * 4.0 / 3e6;      // the second pass
+    return t;
+}
+
+Plan plan_gemm(int64_t M, int64_t N, int64_t K, int cus, int max_split, bool direct)
+{
+    static const double us[2][NTILES][2] = {{{2.10, 6.5}, {1.22, 5.0}, {1.25, 4.7}, {0.69, 3.5}, {0.80, 3.0}, {0.40, 1.2}},
+                                            {{1.82, 6.5}, {1.01, 5.0}, {1.03, 4.7}, {0.55, 3.5}, {0.55, 3.0}, {0.38, 1.2}}};
+    const double(*u)[2] = us[direct ? 1 : 0];
+    Plan best = {0, 1};
     double best_t = 1e30;
-    for (int sh = 0; sh < 3; ++sh) {
-        const int bm = shapes[sh][0], bn = shapes[sh][1];
-        const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
-        for (int s = 1; s <= max_split; ++s) {
-            if (s > 1 && nk / s < 8) break;
-            const int64_t slabs = (nk + s - 1) / s;
-            const double rounds = (double)((tiles * s + cus - 1) / cus);
-            const double slice = 2.0 * bm * bn * BK / (157.3e12 / 256.0 * eff[sh]);      // one workgroup, one k-slice
-            double t = rounds * ((double)slabs * slice + 4e-6);                             // + pipeline fill and epilogue of a round
-            if (s > 1) t += 3e-6 + (double)(s + 1) * (double)M * (double)N * 4.0 / 3e12;
-            if (t < best_t) {
-                best_t = t;
-                best = DlPlan{bm, bn, s};
+    for (int s = 1; s <= max_split; ++s) {
+        const double t[NTILES] = {plan_time<T0>(M, N, K, cus, s, u[0][0], u[0][1], 0.05), plan_time<T1>(M, N, K, cus, s, u[1][0], u[1][1], 0.05),
+                                  plan_time<T2>(M, N, K, cus, s, u[2][0], u[2][1], 0.1), plan_time<T3>(M, N, K, cus, s, u[3][0], u[3][1], 0.2),
+                                  plan_time<T4>(M, N, K, cus, s, u[4][0], u[4][1], 0.0), plan_time<T5>(M, N, K, cus, s, u[5][0], u[5][1], 1.0)};
+        for (int c = 0; c < NTILES; ++c)
+            if (t[c] < best_t) {
+                best_t = t[c];
+                best = Plan{c, s};
             }
-        }
     }
     return best;
 }
 
-template <int BM, int BN, bool A_KS, bool B_KS, int EPI>
-hipError_t launch_dl_one(Params p, DeviceInfo& dev, int slot, hipStream_t stream)
+template <class TL, bool A_KS, bool B_KS, int EPI, bool DIRECT>
+hipError_t launch_tile(Params p, DeviceInfo& dev, int slot, int split, hipStream_t stream)
 {
-    const int64_t tm = (p.M + BM - 1) / BM, tn = (p.N + BN - 1) / BN;
-    p.tiles_n = (int)tn;
+    const int64_t tm = (p.M + TL::BM - 1) / TL::BM, tn = (p.N + TL::BN - 1) / TL::BN;
     if (tm * tn > 0x7fffffffLL) return hipErrorInvalidValue;
-    constexpr int LDS = DL_STAGES * (BM + BN) * BK * 4;
     if (!dev.gemm_f32_lds_set[slot]) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_f32_dl_kernel<BM, BN, A_KS, B_KS, EPI>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_f32_kernel<TL, A_KS, B_KS, EPI, DIRECT>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, TL::lds(DIRECT));
         if (e != hipSuccess) return e;
         dev.gemm_f32_lds_set[slot] = true;
     }
-    DlParams dp;
-    dp.g = p;
-    dp.num_xcd = dev.xcds > 0 ? dev.xcds : 1;
-    dp.tiles_m = (int)tm;
+    const int64_t nk = (p.K + TL::KB - 1) / TL::KB;
+    p.per_split = split > 1 ? (nk + split - 1) / split : nk;
+    p.split_k = split > 1 ? (int)((nk + p.per_split - 1) / p.per_split) : 1;      // (no empty split)
+    p.tiles_m = (int)tm;
+    p.tiles_n = (int)tn;
+    p.num_xcd = dev.xcds > 0 ? dev.xcds : 1;
     {   // block of tiles per XCD with the fewest operand rows: group_m ~ sqrt(tiles per XCD * BN / BM)
-        const double per_xcd = (double)(tm * tn) / dp.num_xcd;
-        int gm = (int)(sqrt(per_xcd * BN / BM) + 0.5);
+        const double per_xcd = (double)(tm * tn) / p.num_xcd;
+        int gm = (int)(sqrt(per_xcd * TL::BN / TL::BM) + 0.5);
         if (gm < 1) gm = 1;
         if (gm > tm) gm = (int)tm;
-        dp.group_m = gm;
+        p.group_m = gm;
     }
-    const unsigned gz = p.split_k > 1 ? (unsigned)p.split_k : 1u;
-    hipLaunchKernelGGL((gemm_f32_dl_kernel<BM, BN, A_KS, B_KS, EPI>), dim3((unsigned)(tm * tn), gz), dim3(NT), LDS, stream, dp);
+    hipLaunchKernelGGL((gemm_f32_kernel<TL, A_KS, B_KS, EPI, DIRECT>), dim3((unsigned)(tm * tn), (unsigned)p.split_k), dim3(NT), TL::lds(DIRECT),
+                       stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.split_k <= 1) return e;
     int64_t g = (p.M * p.N + 255) / 256;
@@ -654,43 +717,45 @@ hipError_t launch_dl_one(Params p, DeviceInfo& dev, int slot, hipStream_t stream
     return hipGetLastError();
 }
 
-template <bool A_KS, bool B_KS, int EPI>
-hipError_t launch_dl(Params p, DeviceInfo& dev, int combo, int max_split, hipStream_t stream)
+template <bool A_KS, bool B_KS, int EPI, bool DIRECT>
+hipError_t launch_vec(Params p, DeviceInfo& dev, int combo, int max_split, hipStream_t stream)
 {
-    const DlPlan plan = dl_plan(p.M, p.N, p.K, dev.cus > 0 ? dev.cus : 256, max_split);
-    p.split_k = plan.split;
-    const int64_t nk = (p.K + BK - 1) / BK;
-    p.slabs = plan.split > 1 ? (nk + plan.split - 1) / plan.split : nk;
-    if (plan.bm == 128 && plan.bn == 128) return launch_dl_one<128, 128, A_KS, B_KS, EPI>(p, dev, combo * 3 + 0, stream);
-    if (plan.bm == 128) return launch_dl_one<128, 64, A_KS, B_KS, EPI>(p, dev, combo * 3 + 1, stream);
-    return launch_dl_one<64, 64, A_KS, B_KS, EPI>(p, dev, combo * 3 + 2, stream);
+    const Plan plan = plan_gemm(p.M, p.N, p.K, dev.cus > 0 ? dev.cus : 256, max_split, DIRECT);
+    const int slot = (combo * 2 + (DIRECT ? 1 : 0)) * NTILES + plan.cfg;
+    switch (plan.cfg) {
+        case 0: return launch_tile<T0, A_KS, B_KS, EPI, DIRECT>(p, dev, slot, plan.split, stream);
+        case 1: return launch_tile<T1, A_KS, B_KS, EPI, DIRECT>(p, dev, slot, plan.split, stream);
+        case 2: return launch_tile<T2, A_KS, B_KS, EPI, DIRECT>(p, dev, slot, plan.split, stream);
+        case 3: return launch_tile<T3, A_KS, B_KS, EPI, DIRECT>(p, dev, slot, plan.split, stream);
+        case 4: return launch_tile<T4, A_KS, B_KS, EPI, DIRECT>(p, dev, slot, plan.split, stream);
+        default: return launch_tile<T5, A_KS, B_KS, EPI, DIRECT>(p, dev, slot, plan.split, stream);
+    }
 }
 
-}  // namespace
+template <bool A_KS, bool B_KS, int EPI>
+hipError_t launch_any(const Params& p, DeviceInfo& dev, int combo, int max_split, hipStream_t stream)
+{
+    // 16-byte loads: every operand row 16-byte aligned, 32-bit byte offsets between the rows of a load
+    auto rows16 = [](const float* P, int64_t ld, bool ks, int64_t rows) {
+        return ld % 4 == 0 && reinterpret_cast<uintptr_t>(P) % 16 == 0 && (!ks || rows % 4 == 0) && ld < (1LL << 25);
+    };
+    if (rows16(p.A, p.lda, A_KS, p.M) && rows16(p.B, p.ldb, B_KS, p.N)) return launch_vec<A_KS, B_KS, EPI, true>(p, dev, combo, max_split, stream);
+    return launch_vec<A_KS, B_KS, EPI, false>(p, dev, combo, max_split, stream);
+}
 
 // How many ways a contraction may be split along k at most: only when there are few output tiles and every
 // split still gets at least 8 k-slices.  The scratch is sized for this bound; the launcher picks the split.
-static int gemm_f32_max_split(int64_t M, int64_t N, int64_t K)
+int gemm_f32_max_split(int64_t M, int64_t N, int64_t K)
 {
     if (M <= 0 || N <= 0 || K <= 0) return 1;
-    const int64_t t128 = ((M + 127) / 128) * ((N + 127) / 128), nk = (K + BK - 1) / BK;
+    const int64_t t128 = ((M + 127) / 128) * ((N + 127) / 128), nk = (K + 31) / 32;
     if (t128 >= 256) return 1;
     int64_t s = nk / 8;
     if (s > 8) s = 8;
     return s < 2 ? 1 : (int)s;
 }
 
-// The plain kernel's split: only when 64 x 64 tiles leave most CUs idle.
-int gemm_f32_split_k(int64_t M, int64_t N, int64_t K)
-{
-    const int max_split = gemm_f32_max_split(M, N, K);
-    if (max_split <= 1) return 1;
-    const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64);
-    if (tiles >= 256) return 1;
-    int64_t s = (512 + tiles - 1) / tiles;
-    if (s > max_split) s = max_split;
-    return s < 2 ? 1 : (int)s;
-}
+}  // namespace
 
 int64_t gemm_f32_partial_bytes(int64_t M, int64_t N, int64_t K)
 {
@@ -701,36 +766,19 @@ int64_t gemm_f32_partial_bytes(int64_t M, int64_t N, int64_t K)
 hipError_t launch_gemm_f32(const GemmF32Args& a, hipStream_t stream)
 {
     if (a.M <= 0 || a.N <= 0) return hipSuccess;
-    Params p;
-    p.split_k = a.partial ? gemm_f32_split_k(a.M, a.N, a.K) : 1;
-    p.partial = a.partial;
-    {
-        const int64_t nk = (a.K + BK - 1) / BK;
-        p.slabs = p.split_k > 1 ? (nk + p.split_k - 1) / p.split_k : nk;
-    }
+    if (!a.dev) return hipErrorInvalidValue;
+    Params p = {};
     p.A = a.A; p.B = a.B; p.C = a.C; p.aux = a.aux; p.L_ptr = a.L_ptr;
     p.lda = a.lda; p.ldb = a.ldb; p.ldc = a.ldc;
     p.M = a.M; p.N = a.N; p.K = a.K;
     p.eta = a.eta; p.lambda = a.lambda;
-    p.vecA = ((a.lda % 4) == 0 && (reinterpret_cast<uintptr_t>(a.A) % 16) == 0) ? 1 : 0;
-    p.vecB = ((a.ldb % 4) == 0 && (reinterpret_cast<uintptr_t>(a.B) % 16) == 0) ? 1 : 0;
-    p.tiles_n = 0;
+    p.partial = a.partial;
+    const int max_split = a.partial ? gemm_f32_max_split(a.M, a.N, a.K) : 1;
     const bool aks = a.a_kstrided, bks = a.b_kstrided;
-    // the pipelined kernel: 16-byte aligned operand rows, at least one whole k-slice, 32-bit in-tile offsets
-    const bool dl = a.dev && p.vecA && p.vecB && a.K >= BK && (!aks || a.M % 4 == 0) && (!bks || a.N % 4 == 0) &&
-                    a.lda * 4 * 128 < (1LL << 31) && a.ldb * 4 * 128 < (1LL << 31);
-    if (dl) {
-        const int max_split = a.partial ? gemm_f32_max_split(a.M, a.N, a.K) : 1;
-        if (!aks && !bks && a.epilogue == EPI_STORE) return launch_dl<false, false, EPI_STORE>(p, *a.dev, 0, max_split, stream);
-        if (!aks && !bks && a.epilogue == EPI_SHRINK) return launch_dl<false, false, EPI_SHRINK>(p, *a.dev, 1, max_split, stream);
-        if (!aks && bks && a.epilogue == EPI_RESID) return launch_dl<false, true, EPI_RESID>(p, *a.dev, 2, max_split, stream);
-        if (aks && bks && a.epilogue == EPI_RMW) return launch_dl<true, true, EPI_RMW>(p, *a.dev, 3, max_split, stream);
-        return hipErrorInvalidValue;
-    }
-    if (!aks && !bks && a.epilogue == EPI_STORE) return launch_sized<false, false, EPI_STORE>(p, stream);
-    if (!aks && !bks && a.epilogue == EPI_SHRINK) return launch_sized<false, false, EPI_SHRINK>(p, stream);
-    if (!aks && bks && a.epilogue == EPI_RESID) return launch_sized<false, true, EPI_RESID>(p, stream);
-    if (aks && bks && a.epilogue == EPI_RMW) return launch_sized<true, true, EPI_RMW>(p, stream);
+    if (!aks && !bks && a.epilogue == EPI_STORE) return launch_any<false, false, EPI_STORE>(p, *a.dev, 0, max_split, stream);
+    if (!aks && !bks && a.epilogue == EPI_SHRINK) return launch_any<false, false, EPI_SHRINK>(p, *a.dev, 1, max_split, stream);
+    if (!aks && bks && a.epilogue == EPI_RESID) return launch_any<false, true, EPI_RESID>(p, *a.dev, 2, max_split, stream);
+    if (aks && bks && a.epilogue == EPI_RMW) return launch_any<true, true, EPI_RMW>(p, *a.dev, 3, max_split, stream);
     return hipErrorInvalidValue;
 }
 
