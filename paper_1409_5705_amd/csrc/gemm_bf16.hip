@@ -774,8 +774,8 @@ hipError_t launch_shadow_from_w(const float* W, uint16_t* shadow, int64_t J, int
     return hipGetLastError();
 }
 
-hipError_t launch_mlr_forward_bf16(const uint16_t* X, const uint16_t* W_shadow, float* Z, uint16_t* X_aligned,
-                                   int64_t B, int64_t J, int64_t D, DeviceInfo& dev, hipStream_t stream)
+hipError_t launch_mlr_forward_bf16(const MlrForwardPlan& plan, const uint16_t* X, const float* W, const uint16_t* W_shadow, float* Z,
+                                   uint16_t* X_aligned, int64_t B, int64_t J, int64_t D, DeviceInfo& dev, hipStream_t stream)
 {
     if (B <= 0 || J <= 0) return hipSuccess;
     const int64_t pitch = bf16_pitch(D);
@@ -785,6 +785,7 @@ hipError_t launch_mlr_forward_bf16(const uint16_t* X, const uint16_t* W_shadow, 
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
+    if (plan.mt > 0) return launch_fwd_stream(plan, X_aligned, W, W_shadow, Z, B, J, D, dev, stream);
     Params p = {};
     p.A = X_aligned; p.lda = pitch; p.M = B;
     p.B = W_shadow; p.ldb = pitch; p.N = J;

@@ -12,6 +12,7 @@ struct DeviceInfo {
     int xcds = 0;                                  // accelerator dies, one L2 each (workgroup ids go round-robin over them)
     bool gemm_bf16_lds_set[3] = {false, false, false};   // dynamic-LDS attribute of sf_gemm_kernel<mode> set on this device
     bool gemm_f32_lds_set[48] = {};                      // the same for the fp32 kernels (operand combination x load width x tile shape)
+    bool fwd_stream_lds_set[6] = {};                     // and of the streaming bf16 forward
     int softmax_wait_polls = 1000;                 // bound of the one-read softmax's wait for a partner's word
 };
 
@@ -62,13 +63,21 @@ int64_t bf16_pitch(int64_t cols);
 int64_t bf16_operand_bytes(int64_t rows, int64_t cols);
 // shadow = bf16(W) (round to nearest even), J x D, in that layout.
 hipError_t launch_shadow_from_w(const float* W, uint16_t* shadow, int64_t J, int64_t D, hipStream_t stream);
-// z(b, j) = sum_d X[b][d] * shadow(j, d);  X bf16 [B][D] row-major, or null if X_aligned (B x D in the operand
+// z(b, j) = sum_d X[b][d] * bf16(W[j][d]);  X bf16 [B][D] row-major, or null if X_aligned (B x D in the operand
 // layout, bf16_operand_bytes(B, D)) has already been filled.  The logits are stored tile by tile:
 // Z is an array of 256 x 256 tiles (mlr_logits_floats(B, J) floats), tile (b / 256, j / 256) at index
-// (j / 256) * ceil(B / 256) + b / 256, rows of 256 floats inside a tile; launch_mlr_softmax(..., blocked = true)
-// reads that layout.
-hipError_t launch_mlr_forward_bf16(const uint16_t* X, const uint16_t* W_shadow, float* Z, uint16_t* X_aligned,
-                                   int64_t B, int64_t J, int64_t D, DeviceInfo& dev, hipStream_t stream);
+// (j / 256) * ceil(B / 256) + b / 256, rows of 256 floats inside a tile; launch_mlr_softmax(blocked) reads that layout.
+// The plan says which kernel: mt == 0, the 256 x 256 tiles of gemm_bf16.hip (W_shadow, the bf16 copy of W, is needed);
+// otherwise the streaming kernel of forward_bf16.hip, which reads W_shadow or, if that is null, the fp32 array W, and
+// leaves `split` planes of partial sums, one behind the other, for the softmax to add up.
+struct MlrForwardPlan {
+    int mt = 0, ntl = 0, split = 1;
+};
+MlrForwardPlan mlr_forward_plan(int64_t B, int64_t J, int64_t D, bool have_copy);
+hipError_t launch_mlr_forward_bf16(const MlrForwardPlan& plan, const uint16_t* X, const float* W, const uint16_t* W_shadow, float* Z,
+                                   uint16_t* X_aligned, int64_t B, int64_t J, int64_t D, DeviceInfo& dev, hipStream_t stream);
+hipError_t launch_fwd_stream(const MlrForwardPlan& plan, const uint16_t* X_aligned, const float* W, const uint16_t* W_shadow, float* Z,
+                             int64_t B, int64_t J, int64_t D, DeviceInfo& dev, hipStream_t stream);
 // W[j][d] -= eta * sum_i U[i][j] * V[i][d];  U bf16 [N][J], V bf16 [N][D], W fp32 [J][D].
 // Two steps: launch_apply_bf16_transpose writes U^T and V^T into `workspace`
 // (apply_bf16_workspace_bytes, 256-byte aligned), launch_apply_bf16 consumes them.
@@ -120,15 +129,28 @@ hipError_t launch_csr_check(const int64_t* indptr, const int32_t* indices, int64
 // Row-wise kernels.
 // ---------------------------------------------------------------------------
 // U[i][j] = exp(Z[i][j] - max_i) / sum_i - [j == y[i]];  out_bf16 selects the U dtype.
-// blocked: Z is the tile-blocked array written by launch_mlr_forward_bf16 instead of a row-major [B][J].
-// scratch: mlr_softmax_scratch_bytes(B, J) bytes (8-byte aligned; contents irrelevant) or null; with it, blocked
-// logits of long rows are read once, by several workgroups per row that exchange their partial sums through it.
+constexpr int64_t MLR_SOFTMAX_ROW_MAX = 16384;   // longest row that one workgroup keeps in registers
+struct MlrSoftmaxArgs {
+    const float* Z;
+    const int32_t* y;
+    void* U;
+    bool out_bf16;
+    int64_t B, J;
+    bool blocked;            // Z is the tile-blocked array written by launch_mlr_forward_bf16 instead of a row-major [B][J]
+    int planes;              // the logits are the sum of this many arrays, plane_floats apart (more than 1: J <= MLR_SOFTMAX_ROW_MAX)
+    int64_t plane_floats;
+    // mlr_softmax_scratch_bytes(B, J) bytes (8-byte aligned; contents irrelevant) or null; with it, blocked logits of
+    // long rows are read once, by several workgroups per row that exchange their partial sums through it
+    void* scratch;
+    // (needed with scratch) CU count for the grid of that kernel, and the polls of a partner's word before a workgroup
+    // does the partner's part itself.  Every such event is counted on the device (softmax_fallbacks).
+    const DeviceInfo* dev;
+    const void* copy_src;    // nullable: copy_bytes (a multiple of 4) from here to copy_dst by the same launch where there is room
+    void* copy_dst;
+    int64_t copy_bytes;
+};
 int64_t mlr_softmax_scratch_bytes(int64_t B, int64_t J);
-// dev (needed with scratch): CU count for the grid of that kernel, and the polls of a partner's word before a
-// workgroup does the partner's part itself.  Every such event is counted on the device (softmax_fallbacks).
-hipError_t launch_mlr_softmax(const float* Z, const int32_t* y, void* U, bool out_bf16, int64_t B, int64_t J,
-                              hipStream_t stream, bool blocked = false, void* scratch = nullptr,
-                              const DeviceInfo* dev = nullptr);
+hipError_t launch_mlr_softmax(const MlrSoftmaxArgs& a, hipStream_t stream);
 // Partner pairs that workgroups of the one-read softmax computed themselves instead of receiving them, on the
 // current device since the library was loaded (copies a device counter: the caller synchronises first).
 hipError_t softmax_fallbacks(unsigned long long* count);

@@ -5,6 +5,8 @@
 // shuffle reductions.
 #include "kernels.h"
 
+#include <type_traits>
+
 namespace sfb {
 namespace {
 
@@ -148,6 +150,102 @@ __global__ __launch_bounds__(NT) void mlr_softmax_kernel(const float* __restrict
             reinterpret_cast<uint16_t*>(Uv)[row * J + j] = (uint16_t)(pack_bf16(p, 0.f) & 0xffffu);
         } else {
             reinterpret_cast<float*>(Uv)[row * J + j] = p;
+        }
+    }
+}
+
+// Rows of at most PER floats per thread: the row stays in registers between the maximum, the exponentials and the
+// output, every logit is read once and exponentiated once (the elements of a thread and the order of the sums are those
+// of the kernel above).  PLANES: the logits are the sum of several partial arrays.  Workgroups past the B rows copy
+// copy_bytes from copy_src to copy_dst (the samples that become the second factors): one launch less.
+template <int PER, bool OUT_BF16, bool VEC, bool PLANES>
+__global__ __launch_bounds__(256) void mlr_softmax_row_kernel(const float* __restrict__ Z, const int32_t* __restrict__ y,
+                                                            void* __restrict__ Uv, int64_t B, int64_t J, int64_t tiles_m, int planes,
+                                                            int64_t plane_floats, const u32x4* __restrict__ copy_src,
+                                                            u32x4* __restrict__ copy_dst, int64_t copy_bytes)
+{
+    constexpr int NT = 256;
+    __shared__ float sm[NT / 64];
+    const int tid = threadIdx.x;
+    const int64_t row = blockIdx.x;
+    if (row >= B) {
+        const int64_t n = copy_bytes / 16, stride = (int64_t)(gridDim.x - B) * NT, first = (row - B) * NT + tid;
+        for (int64_t i = first; i < n; i += stride) copy_dst[i] = copy_src[i];
+        if (first < (copy_bytes % 16) / 4)
+            reinterpret_cast<uint32_t*>(copy_dst)[n * 4 + first] = reinterpret_cast<const uint32_t*>(copy_src)[n * 4 + first];
+        return;
+    }
+    const bool blocked = tiles_m > 0;
+    const float* z = blocked ? Z + (row / 256) * 65536 + (row % 256) * 256 : Z + row * J;
+    constexpr int E = VEC ? 4 : 1, CH = PER / E;             // elements of a chunk; chunks of a thread
+    float v[CH][E];
+    auto load = [&](const float* at, float* dst) {
+        if constexpr (VEC) {
+            const floatx4 t = *reinterpret_cast<const floatx4*>(at);
+            const float t0 = t[0], t1 = t[1], t2 = t[2], t3 = t[3];
+            dst[0] = t0; dst[1] = t1; dst[2] = t2; dst[3] = t3;
+        } else {
+            dst[0] = at[0];
+        }
+    };
+    float m = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+        const int64_t j = (int64_t)(tid + NT * i) * E;
+#pragma unroll
+        for (int e = 0; e < E; ++e) v[i][e] = -INFINITY;
+        if (j < J) load(z + (blocked ? (j >> 8) * (tiles_m * 65536) + (j & 255) : j), v[i]);
+    }
+    if (PLANES)
+        for (int k = 1; k < planes; ++k) {
+            const float* zk = z + k * plane_floats;
+            float t[CH][E];
+#pragma unroll
+            for (int i = 0; i < CH; ++i) {
+                const int64_t j = (int64_t)(tid + NT * i) * E;
+                if (j < J) load(zk + (blocked ? (j >> 8) * (tiles_m * 65536) + (j & 255) : j), t[i]);
+            }
+#pragma unroll
+            for (int i = 0; i < CH; ++i)
+                if ((int64_t)(tid + NT * i) * E < J) {
+#pragma unroll
+                    for (int e = 0; e < E; ++e) v[i][e] += t[i][e];
+                }
+        }
+#pragma unroll
+    for (int i = 0; i < CH; ++i)
+#pragma unroll
+        for (int e = 0; e < E; ++e) m = fmaxf(m, v[i][e]);
+    const float M = block_max<NT>(m, sm);
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) v[i][e] = expf(v[i][e] - M);
+        s += VEC ? (v[i][0] + v[i][E > 1 ? 1 : 0]) + (v[i][E > 2 ? 2 : 0] + v[i][E > 3 ? 3 : 0]) : v[i][0];
+    }
+    s = block_sum<NT>(s, sm);
+    const float inv = 1.0f / s;
+    const int64_t lab = y[row];
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+        const int64_t j = (int64_t)(tid + NT * i) * E;
+        if (j >= J) continue;
+        float p[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) p[e] = v[i][e] * inv - ((j + e == lab) ? 1.0f : 0.0f);
+        if (OUT_BF16) {
+            uint16_t* u = reinterpret_cast<uint16_t*>(Uv) + row * J + j;
+            if constexpr (VEC)
+                *reinterpret_cast<u32x2*>(u) = u32x2{pack_bf16(p[0], p[1]), pack_bf16(p[2], p[3])};
+            else
+                *u = (uint16_t)(pack_bf16(p[0], 0.f) & 0xffffu);
+        } else {
+            float* u = reinterpret_cast<float*>(Uv) + row * J + j;
+            if constexpr (VEC)
+                *reinterpret_cast<floatx4*>(u) = floatx4{p[0], p[1], p[2], p[3]};
+            else
+                *u = p[0];
         }
     }
 }
@@ -628,41 +726,63 @@ hipError_t softmax_fallbacks(unsigned long long* count)
 
 int64_t mlr_softmax_scratch_bytes(int64_t B, int64_t J) { return softmax_cluster(J) ? B * softmax_cluster(J) * 8 : 0; }
 
-hipError_t launch_mlr_softmax(const float* Z, const int32_t* y, void* U, bool out_bf16, int64_t B, int64_t J,
-                              hipStream_t stream, bool blocked, void* scratch, const DeviceInfo* dev)
+template <int PER>
+static hipError_t launch_softmax_row(const MlrSoftmaxArgs& a, bool vec, hipStream_t stream)
 {
-    if (B <= 0 || J <= 0) return hipSuccess;
-    const int cl = (blocked && out_bf16 && B <= 65536) ? softmax_cluster(J) : 0;   // (32-bit offsets of a thread)
-    if (cl && scratch && dev && reinterpret_cast<uintptr_t>(Z) % 16 == 0 && reinterpret_cast<uintptr_t>(U) % 16 == 0) {
-        // one workgroup per CU so that all are resident together; whole clusters only
-        int grid = dev->cus / cl * cl;
-        if (grid < cl) return hipErrorInvalidValue;
-        if ((int64_t)grid / cl > B) grid = (int)B * cl;
-        const int64_t tn = (J + 255) / 256;
-        const int tiles_per_wg = (int)((tn + cl - 1) / cl);
-        hipError_t e = launch_fill_u32(scratch, 0u, B * cl * 2, stream);
+    constexpr int NT = 256;
+    int64_t copies = a.copy_src ? (a.copy_bytes / 16 + NT * 4 - 1) / (NT * 4) : 0;       // (at least four 16-byte pieces a thread)
+    if (a.copy_src && copies < 1) copies = 1;
+    if (copies > 1024) copies = 1024;
+    const dim3 grid((unsigned)(a.B + copies));
+    const int64_t tiles_m = a.blocked ? (a.B + 255) / 256 : 0;
+    auto go = [&](auto bf16, auto v, auto planes) {
+        hipLaunchKernelGGL((mlr_softmax_row_kernel<PER, decltype(bf16)::value, decltype(v)::value, decltype(planes)::value>), grid,
+                           dim3(NT), 0, stream, a.Z, a.y, a.U, a.B, a.J, tiles_m, a.planes, a.plane_floats,
+                           static_cast<const u32x4*>(a.copy_src), static_cast<u32x4*>(a.copy_dst), a.copy_bytes);
+        return hipGetLastError();
+    };
+    typedef std::true_type Y;
+    typedef std::false_type N;
+    if (a.planes > 1) return vec && a.out_bf16 ? go(Y{}, Y{}, Y{}) : hipErrorInvalidValue;     // (only the bf16 path leaves several)
+    return vec ? (a.out_bf16 ? go(Y{}, Y{}, N{}) : go(N{}, Y{}, N{})) : (a.out_bf16 ? go(Y{}, N{}, N{}) : go(N{}, N{}, N{}));
+}
+
+hipError_t launch_mlr_softmax(const MlrSoftmaxArgs& a, hipStream_t stream)
+{
+    if (a.B <= 0 || a.J <= 0) return hipSuccess;
+    // Vector path: rows of Z (and of U) must start 16-byte (8-byte for bf16 U) aligned.
+    const bool vec = a.J % 4 == 0 && reinterpret_cast<uintptr_t>(a.Z) % 16 == 0 && reinterpret_cast<uintptr_t>(a.U) % 16 == 0 &&
+                     a.plane_floats % 4 == 0;
+    if (a.J <= MLR_SOFTMAX_ROW_MAX) {
+        if (a.B > 0x7fff0000LL) return hipErrorInvalidValue;
+        return a.J <= 4096 ? launch_softmax_row<16>(a, vec, stream) : launch_softmax_row<64>(a, vec, stream);
+    }
+    if (a.planes > 1) return hipErrorInvalidValue;
+    if (a.copy_src) {
+        hipError_t e = hipMemcpyAsync(a.copy_dst, a.copy_src, (size_t)a.copy_bytes, hipMemcpyDeviceToDevice, stream);
         if (e != hipSuccess) return e;
-        unsigned long long* slots = static_cast<unsigned long long*>(scratch);
-        hipLaunchKernelGGL(mlr_softmax_cluster_kernel, dim3((unsigned)grid), dim3(1024), 0, stream, Z, y,
-                           static_cast<uint16_t*>(U), B, J, (B + 255) / 256, cl, tiles_per_wg, slots, dev->softmax_wait_polls);
+    }
+    const int cl = (a.blocked && a.out_bf16 && a.B <= 65536) ? softmax_cluster(a.J) : 0;   // (32-bit offsets of a thread)
+    if (cl && a.scratch && a.dev && vec) {
+        // one workgroup per CU so that all are resident together; whole clusters only
+        int grid = a.dev->cus / cl * cl;
+        if (grid < cl) return hipErrorInvalidValue;
+        if ((int64_t)grid / cl > a.B) grid = (int)a.B * cl;
+        const int64_t tn = (a.J + 255) / 256;
+        const int tiles_per_wg = (int)((tn + cl - 1) / cl);
+        hipError_t e = launch_fill_u32(a.scratch, 0u, a.B * cl * 2, stream);
+        if (e != hipSuccess) return e;
+        unsigned long long* slots = static_cast<unsigned long long*>(a.scratch);
+        hipLaunchKernelGGL(mlr_softmax_cluster_kernel, dim3((unsigned)grid), dim3(1024), 0, stream, a.Z, a.y, static_cast<uint16_t*>(a.U),
+                           a.B, a.J, (a.B + 255) / 256, cl, tiles_per_wg, slots, a.dev->softmax_wait_polls);
         return hipGetLastError();
     }
-    // Vector path: rows of Z (and of U) must start 16-byte (8-byte for bf16 U) aligned.
-    const int vec = (J % 4 == 0) && (reinterpret_cast<uintptr_t>(Z) % 16 == 0) &&
-                    (reinterpret_cast<uintptr_t>(U) % 16 == 0);
-    const dim3 grid((unsigned)B);
-    const int64_t tiles_m = blocked ? (B + 255) / 256 : 0;
-    if (J > 16384) {
-        if (out_bf16)
-            hipLaunchKernelGGL((mlr_softmax_kernel<1024, true>), grid, dim3(1024), 0, stream, Z, y, U, J, vec, tiles_m);
-        else
-            hipLaunchKernelGGL((mlr_softmax_kernel<1024, false>), grid, dim3(1024), 0, stream, Z, y, U, J, vec, tiles_m);
-    } else {
-        if (out_bf16)
-            hipLaunchKernelGGL((mlr_softmax_kernel<256, true>), grid, dim3(256), 0, stream, Z, y, U, J, vec, tiles_m);
-        else
-            hipLaunchKernelGGL((mlr_softmax_kernel<256, false>), grid, dim3(256), 0, stream, Z, y, U, J, vec, tiles_m);
-    }
+    const dim3 grid((unsigned)a.B);
+    const int64_t tiles_m = a.blocked ? (a.B + 255) / 256 : 0;
+    if (a.out_bf16)
+        hipLaunchKernelGGL((mlr_softmax_kernel<1024, true>), grid, dim3(1024), 0, stream, a.Z, a.y, a.U, a.J, (int)vec, tiles_m);
+    else
+        hipLaunchKernelGGL((mlr_softmax_kernel<1024, false>), grid, dim3(1024), 0, stream, a.Z, a.y, a.U, a.J, (int)vec, tiles_m);
     return hipGetLastError();
 }
 

@@ -143,15 +143,22 @@ int64_t sc_partial_bytes(int64_t B, int64_t J, int64_t D)
     return round_up(a > b ? a : b);
 }
 
-// Front of the workspace on the bf16 multiclass-logistic path: the tile-blocked logits, then the words the
-// workgroups of the one-read softmax exchange.
-int64_t bf16_logits_bytes(int64_t B, int64_t J)
+// Front of the workspace on the bf16 multiclass-logistic path: the tile-blocked logits (as many planes of partial sums
+// as the forward may leave, with or without a bf16 copy of W), then the words the workgroups of the one-read softmax
+// exchange.
+int64_t bf16_logits_bytes(int64_t B, int64_t J, int64_t D)
 {
-    return round_up(sfb::mlr_logits_floats(B, J) * 4) + round_up(sfb::mlr_softmax_scratch_bytes(B, J));
+    int planes = 1;
+    for (bool copy : {false, true}) {
+        const int s = sfb::mlr_forward_plan(B, J, D, copy).split;
+        if (s > planes) planes = s;
+    }
+    return round_up(planes * sfb::mlr_logits_floats(B, J) * 4) + round_up(sfb::mlr_softmax_scratch_bytes(B, J));
 }
-void* bf16_softmax_scratch(sfb_ctx* ctx, int64_t B, int64_t J)
+void* bf16_softmax_scratch(sfb_ctx* ctx, int64_t B, int64_t J, int64_t D)
 {
-    return sfb::mlr_softmax_scratch_bytes(B, J) ? ctx->ws + round_up(sfb::mlr_logits_floats(B, J) * 4) : nullptr;
+    const int64_t bytes = round_up(sfb::mlr_softmax_scratch_bytes(B, J));
+    return bytes ? ctx->ws + bf16_logits_bytes(B, J, D) - bytes : nullptr;
 }
 
 // True if W is currently kept as two planes by this context: its fp32 array is stale.
@@ -301,7 +308,7 @@ int64_t sfb_workspace_bytes(int32_t model, int64_t J, int64_t D, const sfb_batch
     switch (model) {
         case SFB_MLR:
             if (batch->in_dtype == SFB_BF16)   // logits (tile-blocked), aligned copy of X, bf16 copy of W
-                return bf16_logits_bytes(B, J) + round_up(sfb::bf16_operand_bytes(B, D)) + sfb_shadow_bytes(J, D);
+                return bf16_logits_bytes(B, J, D) + round_up(sfb::bf16_operand_bytes(B, D)) + sfb_shadow_bytes(J, D);
             return round_up(B * J * 4) + round_up(sfb::gemm_f32_partial_bytes(B, J, D));   // logits, k-split scratch
         case SFB_DML:
             return round_up(B * J * 4) + round_up(sfb::gemm_f32_partial_bytes(B, J, D));   // projections Q[B][K], k-split scratch
@@ -428,7 +435,16 @@ int sfb_compute_sf(sfb_ctx* ctx, int32_t model, const float* W, int64_t J, int64
         if (!batch->Y) return SFB_EINVAL;
         const int32_t* y = static_cast<const int32_t*>(batch->Y);
         float* Z = reinterpret_cast<float*>(ctx->ws);
-        const int64_t esz = batch->in_dtype == SFB_BF16 ? 2 : 4;
+        sfb::MlrSoftmaxArgs sm = {};
+        sm.Z = Z; sm.y = y; sm.U = U;
+        sm.B = B; sm.J = J;
+        sm.planes = 1;
+        sm.dev = &ctx->dev;
+        if (V && V != batch->X) {      // the second factors are the samples
+            sm.copy_src = batch->X;
+            sm.copy_dst = V;
+            sm.copy_bytes = B * D * (batch->in_dtype == SFB_BF16 ? 2 : 4);
+        }
         if (batch->in_dtype == SFB_F32) {
             sfb::GemmF32Args g = {};
             g.dev = &ctx->dev;
@@ -439,21 +455,23 @@ int sfb_compute_sf(sfb_ctx* ctx, int32_t model, const float* W, int64_t J, int64
             g.epilogue = sfb::EPI_STORE;
             if (sfb::gemm_f32_partial_bytes(B, J, D) > 0) g.partial = reinterpret_cast<float*>(ctx->ws + round_up(B * J * 4));
             SFB_RUN(KID_GEMM_F32_STORE, sfb::launch_gemm_f32(g, st));
-            SFB_RUN(KID_SOFTMAX, sfb::launch_mlr_softmax(Z, y, U, false, B, J, st));
         } else {
-            uint16_t* Xa = reinterpret_cast<uint16_t*>(ctx->ws + bf16_logits_bytes(B, J));
-            const uint16_t* Wb = ctx->shadow_buf;
-            if (!has_shadow) {   // no working copy attached: make one for this call
+            uint16_t* Xa = reinterpret_cast<uint16_t*>(ctx->ws + bf16_logits_bytes(B, J, D));
+            const uint16_t* Wb = has_shadow ? ctx->shadow_buf : nullptr;
+            const sfb::MlrForwardPlan plan = sfb::mlr_forward_plan(B, J, D, has_shadow);
+            if (!has_shadow && plan.mt == 0) {   // no working copy attached: make one for this call
                 uint16_t* tmp = Xa + round_up(sfb::bf16_operand_bytes(B, D)) / 2;
                 SFB_RUN(KID_SHADOW, sfb::launch_shadow_from_w(W, tmp, J, D, st));
                 Wb = tmp;
             }
-            SFB_RUN(KID_FORWARD_BF16,
-                    sfb::launch_mlr_forward_bf16(static_cast<const uint16_t*>(batch->X), Wb, Z, Xa, B, J, D, ctx->dev, st));
-            SFB_RUN(KID_SOFTMAX, sfb::launch_mlr_softmax(Z, y, U, true, B, J, st, true, bf16_softmax_scratch(ctx, B, J), &ctx->dev));
+            SFB_RUN(KID_FORWARD_BF16, sfb::launch_mlr_forward_bf16(plan, static_cast<const uint16_t*>(batch->X), W, Wb, Z, Xa, B, J, D,
+                                                                   ctx->dev, st));
+            sm.out_bf16 = sm.blocked = true;
+            sm.planes = plan.split;
+            sm.plane_floats = sfb::mlr_logits_floats(B, J);
+            sm.scratch = bf16_softmax_scratch(ctx, B, J, D);
         }
-        if (V && V != batch->X)
-            SFB_RUN(KID_COPY, hipMemcpyAsync(V, batch->X, (size_t)(B * D * esz), hipMemcpyDeviceToDevice, st));
+        SFB_RUN(KID_SOFTMAX, sfb::launch_mlr_softmax(sm, st));
         return SFB_OK;
     }
 
@@ -714,6 +732,11 @@ int sfb_mlr_sf_csr(sfb_ctx* ctx, const float* W, int64_t J, int64_t D, const sfb
     hipStream_t st = ctx->stream;
     float* Z = reinterpret_cast<float*>(ctx->ws);
     const bool gather = csr_use_gather(ctx, B, J, D, X->nnz, bf16);
+    sfb::MlrSoftmaxArgs sm = {};
+    sm.Z = Z; sm.y = y; sm.U = U;
+    sm.B = B; sm.J = J;
+    sm.planes = 1;
+    sm.dev = &ctx->dev;
     if (!bf16) {
         const int64_t part = round_up(sfb::gemm_f32_partial_bytes(B, J, D));
         char* region = ctx->ws + round_up(B * J * 4) + part;
@@ -734,13 +757,14 @@ int sfb_mlr_sf_csr(sfb_ctx* ctx, const float* W, int64_t J, int64_t D, const sfb
             if (part > 0) g.partial = reinterpret_cast<float*>(ctx->ws + round_up(B * J * 4));
             SFB_RUN(KID_GEMM_F32_STORE, sfb::launch_gemm_f32(g, st));
         }
-        SFB_RUN(KID_SOFTMAX, sfb::launch_mlr_softmax(Z, y, U, false, B, J, st));
+        SFB_RUN(KID_SOFTMAX, sfb::launch_mlr_softmax(sm, st));
         return SFB_OK;
     }
     const int64_t pitch = sfb::bf16_pitch(D);
-    char* region = ctx->ws + bf16_logits_bytes(B, J);
-    const uint16_t* Wb = ctx->shadow_buf;
-    if (!has_shadow) {
+    char* region = ctx->ws + bf16_logits_bytes(B, J, D);
+    const uint16_t* Wb = has_shadow ? ctx->shadow_buf : nullptr;
+    const sfb::MlrForwardPlan plan = sfb::mlr_forward_plan(B, J, D, has_shadow);
+    if (!has_shadow && (gather || plan.mt == 0)) {
         uint16_t* tmp = reinterpret_cast<uint16_t*>(region + csr_operand_bytes(J, D, B, true));
         SFB_RUN(KID_SHADOW, sfb::launch_shadow_from_w(W, tmp, J, D, st));
         Wb = tmp;
@@ -752,9 +776,13 @@ int sfb_mlr_sf_csr(sfb_ctx* ctx, const float* W, int64_t J, int64_t D, const sfb
         uint16_t* Xa = reinterpret_cast<uint16_t*>(region);
         SFB_RUN(KID_FILL, sfb::launch_fill_u32(Xa, 0u, sfb::bf16_operand_bytes(B, D) / 4, st));
         SFB_RUN(KID_CSR, sfb::launch_csr_scatter(X->indptr, X->indices, X->values, true, nullptr, Xa, B, D, X->nnz, -pitch, 1, st));
-        SFB_RUN(KID_FORWARD_BF16, sfb::launch_mlr_forward_bf16(nullptr, Wb, Z, Xa, B, J, D, ctx->dev, st));
+        SFB_RUN(KID_FORWARD_BF16, sfb::launch_mlr_forward_bf16(plan, nullptr, W, Wb, Z, Xa, B, J, D, ctx->dev, st));
+        sm.planes = plan.split;
     }
-    SFB_RUN(KID_SOFTMAX, sfb::launch_mlr_softmax(Z, y, U, true, B, J, st, true, bf16_softmax_scratch(ctx, B, J), &ctx->dev));
+    sm.out_bf16 = sm.blocked = true;
+    sm.plane_floats = sfb::mlr_logits_floats(B, J);
+    sm.scratch = bf16_softmax_scratch(ctx, B, J, D);
+    SFB_RUN(KID_SOFTMAX, sfb::launch_mlr_softmax(sm, st));
     return SFB_OK;
 }
 

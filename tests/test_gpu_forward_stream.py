@@ -1,0 +1,56 @@
+"""The bf16 logits by the streaming kernel (few 256 x 256 tiles): every tile shape of it, W as fp32 and from its bf16 copy, partial
+k-slices, ragged samples and classes, and the k-split whose partial sums the softmax adds up."""
+import numpy as np
+import pytest
+
+import sfb_synth as S
+from parity import TOL_BF16, mlr_u_check
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sfb():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1409_5705_amd as m
+    m.lib()
+    return m
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+
+
+def dev_bf16(a):
+    return dev(S.bf16_bits(a)).view(torch.bfloat16)
+
+
+@pytest.mark.parametrize("J,D,B", [
+    (8, 8, 1), (72, 136, 17), (264, 72, 64),     # one slice, partial slices; up to 64 samples
+    (1000, 2056, 65), (1504, 520, 128),          # up to 128 samples
+    (1504, 3000, 200), (2040, 1032, 256),        # up to 256, k-split
+    (520, 1000, 300), (1000, 4104, 520),         # several tiles of samples, the last one ragged
+    (8192, 264, 100), (16400, 72, 40),           # rows at and past the longest that one workgroup keeps in registers
+])
+@pytest.mark.parametrize("layout", ["plain", "copy", "planes"])
+def test_stream_forward(sfb, oracle, J, D, B, layout):
+    print("stream forward", J, D, B, layout, flush=True)
+    ctx = sfb.Context(0)
+    W0 = S.normal_matrix(J, D, 0.05, seed=31)
+    X, y = S.mlr_batch(J, D, B, seed=31, zero_frac=0.5, bf16=True)
+    W = dev(W0)
+    if layout == "copy":
+        ctx.sfb_shadow_attach(W)
+    elif layout == "planes":
+        ctx.sfb_split_attach(W)
+    U = torch.empty((B, J), dtype=torch.bfloat16, device="cuda:0")
+    V = torch.empty((B, D), dtype=torch.bfloat16, device="cuda:0")
+    Xd = dev_bf16(X)
+    ctx.sfb_compute_sf(sfb.SFB_MLR, W, Xd, Y=dev(y), U=U, V=V)
+    torch.cuda.synchronize()
+    assert torch.equal(V.view(torch.int16), Xd.view(torch.int16))
+    Uo, _ = oracle.mlr_sf(W0, X, y)
+    mlr_u_check(U.float().cpu().numpy(), Uo, y, TOL_BF16)
+    ctx.close()
