@@ -177,7 +177,9 @@ hipError_t launch_prox_rows(float* W, int64_t J, int64_t D, int mode, hipStream_
 // Power iteration on W^T W: writes the norm estimate to *L_out (device).
 // scratch: float[D (b) + J (c) + chunks*D (partials) + D (g)] with chunks = power_chunks(J).
 int64_t power_chunks(int64_t J);
-hipError_t launch_power_iteration(const float* W, int64_t J, int64_t D, int iters, float* scratch,
+// spare (nullable, 16-byte aligned, spare_floats floats): another array it may overwrite; with room for chunks * D floats and
+// few of them an iteration is one launch.
+hipError_t launch_power_iteration(const float* W, int64_t J, int64_t D, int iters, float* scratch, float* spare, int64_t spare_floats,
                                   float* L_out, hipStream_t stream);
 
 }  // namespace sfb

@@ -16,17 +16,30 @@ typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
+// Reductions over the 64 lanes (all active): four DPP steps inside rows of 16 lanes, then the four rows through scalar
+// registers.  (The shuffles through the LDS unit that stood here cost six round trips of some 50 ns each.)
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float lane_value(float v, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); }
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140;
 __device__ __forceinline__ float wave_sum(float v)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    v += dpp<DPP_XOR1>(v);
+    v += dpp<DPP_XOR2>(v);
+    v += dpp<DPP_HALF_MIRROR>(v);
+    v += dpp<DPP_MIRROR>(v);
+    return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
 }
 __device__ __forceinline__ float wave_max(float v)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-    return v;
+    v = fmaxf(v, dpp<DPP_XOR1>(v));
+    v = fmaxf(v, dpp<DPP_XOR2>(v));
+    v = fmaxf(v, dpp<DPP_HALF_MIRROR>(v));
+    v = fmaxf(v, dpp<DPP_MIRROR>(v));
+    return fmaxf(fmaxf(lane_value(v, 0), lane_value(v, 16)), fmaxf(lane_value(v, 32), lane_value(v, 48)));
 }
 // Block reductions; `sm` has NT/64 floats.  Every thread gets the result.
 template <int NT>
@@ -433,12 +446,16 @@ __global__ __launch_bounds__(1024) void mlr_softmax_cluster_kernel(const float* 
 }
 
 // V = X - Y; also clears *counter (nullable): the count of active pairs a later kernel of the same call adds to.
+// E floats an access.
+template <int E>
 __global__ __launch_bounds__(256) void diff_kernel(const float* __restrict__ X, const float* __restrict__ Y,
                                                    float* __restrict__ V, int64_t n, int32_t* __restrict__ counter)
 {
+    typedef float F __attribute__((ext_vector_type(E)));
     if (counter && blockIdx.x == 0 && threadIdx.x == 0) *counter = 0;
     const int64_t stride = (int64_t)gridDim.x * 256;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += stride) V[i] = X[i] - Y[i];
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n / E; i += stride)
+        reinterpret_cast<F*>(V)[i] = reinterpret_cast<const F*>(X)[i] - reinterpret_cast<const F*>(Y)[i];
 }
 
 __global__ __launch_bounds__(256) void scale_rows_kernel(const float* __restrict__ V, const float* __restrict__ coef,
@@ -456,11 +473,14 @@ __global__ __launch_bounds__(256) void fill_u32_kernel(uint32_t* __restrict__ p,
 
 // W = Z / lambda: the primal matrix from the auxiliary one for the squared l2
 // regulariser (W = grad h^*(Z), Section 2.1, Stochastic DCA).
+template <int E>
 __global__ __launch_bounds__(256) void div_scalar_kernel(const float* __restrict__ Z, float* __restrict__ W,
                                                          float lambda, int64_t n)
 {
+    typedef float F __attribute__((ext_vector_type(E)));
     const int64_t stride = (int64_t)gridDim.x * 256;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += stride) W[i] = Z[i] / lambda;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n / E; i += stride)
+        reinterpret_cast<F*>(W)[i] = reinterpret_cast<const F*>(Z)[i] / lambda;
 }
 
 // w > 0 with w + log w = L (w = W0(e^L), the principal Lambert function).  The
@@ -495,51 +515,110 @@ __device__ __forceinline__ float lambert_w_exp(float L)
 // and the root lies in [lse(theta) - c, lse(theta)], theta = z + c p_old.  nu is
 // found by Newton's iteration on log(sum p) kept inside that bracket (bisection
 // when a step leaves it).  Outputs: dU = beta (p - p_old), P += dU.
-__global__ __launch_bounds__(256) void sdca_mlr_kernel(const float* __restrict__ Zl, const float* __restrict__ X,
-                                                       float* __restrict__ P, float* __restrict__ dU, int64_t J,
-                                                       int64_t D, float inv_lambda_n, float beta)
+//
+// Rows of at most PER classes a thread: logits and dual point stay in registers for all the passes (seven on average),
+// every pass takes one barrier (two sums reduced together, alternating LDS slots); what bounds it is the chain of
+// exponentials and logarithms of a Newton step, hence two to four classes a thread rather than more (256 samples of 1000
+// classes: 27.7 us re-reading the rows with four barriers a step, 16.0 now).  PER == 0: rows of any length, re-read
+// from the cache.
+template <int NT, int PER>
+__global__ __launch_bounds__(NT) void sdca_mlr_kernel(const float* __restrict__ Zl, const float* __restrict__ X,
+                                                      float* __restrict__ P, float* __restrict__ dU, int64_t J,
+                                                      int64_t D, float inv_lambda_n, float beta)
 {
-    __shared__ float sm[4];
+    constexpr int NWV = NT / 64, R = PER > 0 ? PER : 1;
+    __shared__ float sm[2][2][NWV];
     const int64_t i = blockIdx.x;
     const float* z = Zl + i * J;
     float* p_old = P + i * J;
     float* du = dU + i * J;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, wave = tid >> 6;
+    int turn = 0;
+    auto sum2 = [&](float& a, float& b) {      // (a slot is rewritten two calls later: the barrier between has been passed)
+        a = wave_sum(a);
+        b = wave_sum(b);
+        if ((tid & 63) == 0) {
+            sm[turn][0][wave] = a;
+            sm[turn][1][wave] = b;
+        }
+        __syncthreads();
+        a = 0.f;
+        b = 0.f;
+#pragma unroll
+        for (int w = 0; w < NWV; ++w) {
+            a += sm[turn][0][w];
+            b += sm[turn][1][w];
+        }
+        turn ^= 1;
+    };
+    auto max1 = [&](float v) {
+        v = wave_max(v);
+        if ((tid & 63) == 0) sm[turn][0][wave] = v;
+        __syncthreads();
+        v = sm[turn][0][0];
+#pragma unroll
+        for (int w = 1; w < NWV; ++w) v = fmaxf(v, sm[turn][0][w]);
+        turn ^= 1;
+        return v;
+    };
+    float rz[R], rp[R];
+    if (PER > 0) {
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            const int64_t j = tid + (int64_t)NT * k;
+            rz[k] = j < J ? z[j] : 0.f;
+            rp[k] = j < J ? p_old[j] : 0.f;
+        }
+    }
+    // f(class, logit, dual point) over the classes of this thread
+    auto each = [&](auto&& f) {
+        if (PER > 0) {
+#pragma unroll
+            for (int k = 0; k < R; ++k) {
+                const int64_t j = tid + (int64_t)NT * k;
+                if (j < J) f(j, rz[k], rp[k]);
+            }
+        } else {
+            for (int64_t j = tid; j < J; j += NT) f(j, z[j], p_old[j]);
+        }
+    };
 
-    float acc = 0.f;
-    for (int64_t d = tid; d < D; d += 256) {
+    float acc = 0.f, none = 0.f;
+    for (int64_t d = tid; d < D; d += NT) {
         const float x = X[i * D + d];
         acc += x * x;
     }
-    const float c = block_sum<256>(acc, sm) * inv_lambda_n;
+    sum2(acc, none);
+    const float c = acc * inv_lambda_n;
 
     float m = -INFINITY;
-    for (int64_t j = tid; j < J; j += 256) m = fmaxf(m, z[j] + c * p_old[j]);
-    m = block_max<256>(m, sm);
+    each([&](int64_t, float zj, float pj) { m = fmaxf(m, zj + c * pj); });
+    m = max1(m);
     float s = 0.f;
-    for (int64_t j = tid; j < J; j += 256) s += expf(z[j] + c * p_old[j] - m);
-    s = block_sum<256>(s, sm);
+    each([&](int64_t, float zj, float pj) { s += expf(zj + c * pj - m); });
+    sum2(s, none);
     const float lse = m + logf(s);
 
     if (!(c > 1e-30f)) {   // a zero sample: the class equations decouple, p = softmax(z)
-        for (int64_t j = tid; j < J; j += 256) {
-            const float po = p_old[j], d = beta * (expf(z[j] - lse) - po);
+        each([&](int64_t j, float zj, float po) {
+            const float d = beta * (expf(zj - lse) - po);
             du[j] = d;
             p_old[j] = po + d;
-        }
+        });
         return;
     }
     const float logc = logf(c), inv_c = 1.f / c;
     float lo = lse - c, hi = lse, nu = lo;
     for (int it = 0; it < 32; ++it) {
         float S = 0.f, T = 0.f;
-        for (int64_t j = tid; j < J; j += 256) {
-            const float w = lambert_w_exp(logc + (z[j] + c * p_old[j] - nu));
+        each([&](int64_t, float zj, float pj) {
+            const float w = lambert_w_exp(logc + (zj + c * pj - nu));
             S += w;                 // c p_j
             T += w / (1.f + w);     // c p_j / (1 + c p_j)
-        }
-        S = block_sum<256>(S, sm) * inv_c;
-        T = block_sum<256>(T, sm) * inv_c;
+        });
+        sum2(S, T);
+        S *= inv_c;
+        T *= inv_c;
         if (fabsf(S - 1.f) <= 1e-6f) break;          // (every thread holds the same S: a uniform exit)
         if (S > 1.f) lo = nu; else hi = nu;
         float cand = nu + S * logf(S) / T;
@@ -547,16 +626,16 @@ __global__ __launch_bounds__(256) void sdca_mlr_kernel(const float* __restrict__
         if (cand == nu) break;                        // bracket exhausted at fp32 resolution
         nu = cand;
     }
-    for (int64_t j = tid; j < J; j += 256) {
-        const float po = p_old[j];
-        const float p = lambert_w_exp(logc + (z[j] + c * po - nu)) * inv_c;
+    each([&](int64_t j, float zj, float po) {
+        const float p = lambert_w_exp(logc + (zj + c * po - nu)) * inv_c;
         const float d = beta * (p - po);
         du[j] = d;
         p_old[j] = po + d;
-    }
+    });
 }
 
-// DML: one workgroup per pair.
+// DML: one workgroup per pair; PER > 0: rows of at most 256 PER floats, in registers between the norm and the product.
+template <int PER>
 __global__ __launch_bounds__(256) void dml_scale_kernel(const float* __restrict__ Q, const int8_t* __restrict__ sim,
                                                         float* __restrict__ U, int32_t* __restrict__ n_active,
                                                         float margin, int64_t K)
@@ -564,15 +643,30 @@ __global__ __launch_bounds__(256) void dml_scale_kernel(const float* __restrict_
     __shared__ float sm[4];
     const int64_t row = blockIdx.x;
     const float* q = Q + row * K;
-    float d = 0.f;
-    for (int64_t k = threadIdx.x; k < K; k += 256) d += q[k] * q[k];
+    float* const u = U + row * K;
+    const int s = sim[row];
+    float d = 0.f, v[PER > 0 ? PER : 1];
+    if (PER > 0) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) v[i] = threadIdx.x + 256 * i < K ? q[threadIdx.x + 256 * i] : 0.f;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) d += v[i] * v[i];
+    } else {
+        for (int64_t k = threadIdx.x; k < K; k += 256) d += q[k] * q[k];
+    }
     d = block_sum<256>(d, sm);
     float c;
-    if (sim[row] > 0)
+    if (s > 0)
         c = 2.0f;
     else
         c = (d < margin) ? -2.0f : 0.0f;
-    for (int64_t k = threadIdx.x; k < K; k += 256) U[row * K + k] = c * q[k];
+    if (PER > 0) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+            if (threadIdx.x + 256 * i < K) u[threadIdx.x + 256 * i] = c * v[i];
+    } else {
+        for (int64_t k = threadIdx.x; k < K; k += 256) u[k] = c * q[k];
+    }
     if (threadIdx.x == 0 && c != 0.0f && n_active) atomicAdd(n_active, 1);
 }
 
@@ -588,6 +682,35 @@ __global__ __launch_bounds__(256) void prox_rows_kernel(float* __restrict__ W, i
     const bool scale = (mode == 0) ? (nrm > 1.0f) : (nrm > 0.0f);
     if (scale)
         for (int64_t d = threadIdx.x; d < D; d += 256) w[d] = w[d] / nrm;
+}
+// The same for rows of at most 1024 floats: one wavefront a row, the row in its registers (4096 x 1024: 18.6 -> 15.7 us).
+template <bool VEC>
+__global__ __launch_bounds__(256) void prox_rows_wave_kernel(float* __restrict__ W, int64_t J, int64_t D, int mode)
+{
+    const int lane = threadIdx.x & 63, d_count = (int)D;
+    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (row >= J) return;
+    float* const w = W + row * D;
+    constexpr int E = VEC ? 4 : 1, CH = 16 / E;
+    typedef float V __attribute__((ext_vector_type(E)));
+    V v[CH];
+    float nn = 0.f;
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+        const int d = (lane + 64 * i) * E;
+        v[i] = V(0.f);
+        if (d < d_count) v[i] = *reinterpret_cast<const V*>(w + d);
+#pragma unroll
+        for (int e = 0; e < E; ++e) nn += v[i][e] * v[i][e];
+    }
+    const float nrm = sqrtf(wave_sum(nn));
+    const bool scale = (mode == 0) ? (nrm > 1.0f) : (nrm > 0.0f);
+    if (!scale) return;
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+        const int d = (lane + 64 * i) * E;
+        if (d < d_count) *reinterpret_cast<V*>(w + d) = v[i] / nrm;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -624,25 +747,71 @@ __global__ __launch_bounds__(256) void power_step_kernel(const float* __restrict
         part[(int64_t)blockIdx.x * D + d] = s;
     }
 }
-// The same for rows of at most 1024 floats, 16-byte aligned (D % 4 == 0): a workgroup keeps its 16 rows in
-// registers (thread t holds columns 4 t .. 4 t + 3 of every row: one 16-byte load per row, all in flight
-// together), so W is read once and nothing waits on a chain of dependent loads.
-__global__ __launch_bounds__(256) void power_step16_kernel(const float* __restrict__ W, const float* __restrict__ g,
+// The same for rows of at most 1024 floats: a workgroup keeps its 16 rows in registers, all loads in flight together, so W
+// is read once and nothing waits on a chain of dependent loads.  VEC (rows 16-byte aligned): thread t holds columns
+// 4 t .. 4 t + 3 of every row; otherwise columns t, t + 256, t + 512, t + 768.
+// `g` is gchunks partial vectors of D floats; every workgroup adds them up itself (in the same order).  With few
+// partials that costs less than the launch of power_reduce_kernel; with many the caller passes their sum (gchunks 1).
+// One iteration: 1000 x 300 10.4 -> 7.3 us (in one launch), 4096 x 1024 12.1 -> 10.1 us (in two; the rest is the reductions).
+template <bool VEC>
+__global__ __launch_bounds__(256) void power_step16_kernel(const float* __restrict__ W, const float* __restrict__ g, int gchunks,
                                                            float* __restrict__ part, int64_t J, int64_t D)
 {
     __shared__ float sm[16];
     __shared__ float cw[16][4];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t d0 = 4 * (int64_t)tid, j0 = (int64_t)blockIdx.x * 16;
-    const bool have = d0 < D;
+    __shared__ float ps[1024];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, d_count = (int)D;
+    const int64_t j0 = (int64_t)blockIdx.x * 16;
+    constexpr int CW = VEC ? 4 : 1;                                          // floats of an access
+    auto column = [&](int e) { return VEC ? 4 * tid + e : tid + 256 * e; };
+    auto load4 = [&](const float* row) {
+        floatx4 v = {0.f, 0.f, 0.f, 0.f};
+        if (VEC) {
+            if (4 * tid < d_count) v = *reinterpret_cast<const floatx4*>(row + 4 * tid);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (tid + 256 * e < d_count) v[e] = row[tid + 256 * e];
+        }
+        return v;
+    };
     floatx4 w[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         w[r] = floatx4{0.f, 0.f, 0.f, 0.f};
-        if (have && j0 + r < J) w[r] = *reinterpret_cast<const floatx4*>(W + (j0 + r) * D + d0);
+        if (j0 + r < J) w[r] = load4(W + (j0 + r) * D);
     }
     floatx4 g4 = {0.f, 0.f, 0.f, 0.f};
-    if (have) g4 = *reinterpret_cast<const floatx4*>(g + d0);
+    if (gchunks == 1) {
+        g4 = load4(g);
+    } else {
+        // the threads are `groups` times the columns (in units of CW): group k adds partials k, k + groups, ...
+        typedef float V __attribute__((ext_vector_type(CW)));
+        const int units = d_count / CW, groups = units < 256 ? 256 / units : 1;
+        const int grp = units < 256 ? tid / units : 0;
+        if (grp < groups)
+            for (int u = units < 256 ? tid - grp * units : tid; u < units; u += 256) {      // (units < 256: once)
+                V sum = V(0.f);
+                int ch = grp;
+                for (; ch + 7 * groups < gchunks; ch += 8 * groups) {
+                    V v[8];
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) v[q] = reinterpret_cast<const V*>(g + (int64_t)(ch + q * groups) * D)[u];
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) sum += v[q];
+                }
+                for (; ch < gchunks; ch += groups) sum += reinterpret_cast<const V*>(g + (int64_t)ch * D)[u];
+                reinterpret_cast<V*>(ps)[grp * units + u] = sum;
+            }
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (column(e) < d_count) {
+                float t = ps[column(e)];
+                for (int k = 1; k < groups; ++k) t += ps[k * d_count + column(e)];
+                g4[e] = t;
+            }
+    }
     const float inv = 1.0f / sqrtf(block_sum<256>(g4[0] * g4[0] + g4[1] * g4[1] + g4[2] * g4[2] + g4[3] * g4[3], sm));
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -656,7 +825,14 @@ __global__ __launch_bounds__(256) void power_step16_kernel(const float* __restri
         const float c = (((cw[r][0] + cw[r][1]) + cw[r][2]) + cw[r][3]) * inv;
         out += w[r] * c;
     }
-    if (have) *reinterpret_cast<floatx4*>(part + (int64_t)blockIdx.x * D + d0) = out;
+    float* const to = part + (int64_t)blockIdx.x * D;
+    if (VEC) {
+        if (4 * tid < d_count) *reinterpret_cast<floatx4*>(to + 4 * tid) = out;
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (column(e) < d_count) to[column(e)] = out[e];
+    }
 }
 // g[d] = sum of the chunks' partials in a fixed order: 16 columns a workgroup, 16 interleaved groups of chunks
 // per column (eight loads in flight per thread), combined in order.
@@ -687,12 +863,35 @@ __global__ __launch_bounds__(256) void power_reduce_kernel(const float* __restri
         g[d] = t;
     }
 }
-// L = ||g||.  One workgroup.
-__global__ __launch_bounds__(1024) void vec_norm_kernel(const float* __restrict__ g, float* __restrict__ L_out, int64_t D)
+// L = ||sum of the partials||.  One workgroup.
+__global__ __launch_bounds__(1024) void vec_norm_kernel(const float* __restrict__ g, int gchunks, float* __restrict__ L_out, int64_t D)
 {
     __shared__ float sm[16];
+    __shared__ float ps[1024];
     float nn = 0.f;
-    for (int64_t d = threadIdx.x; d < D; d += 1024) nn += g[d] * g[d];
+    if (gchunks == 1) {
+        for (int64_t d = threadIdx.x; d < D; d += 1024) nn += g[d] * g[d];
+    } else {                                        // (D <= 1024)
+        const int d_count = (int)D, groups = 1024 / d_count, grp = (int)threadIdx.x / d_count, d = (int)threadIdx.x % d_count;
+        float t = 0.f;
+        if (grp < groups) {
+            int ch = grp;
+            for (; ch + 7 * groups < gchunks; ch += 8 * groups) {
+                float v[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) v[q] = g[(int64_t)(ch + q * groups) * D + d];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) t += v[q];
+            }
+            for (; ch < gchunks; ch += groups) t += g[(int64_t)ch * D + d];
+        }
+        ps[threadIdx.x] = t;
+        __syncthreads();
+        if (grp == 0) {
+            for (int k = 1; k < groups; ++k) t += ps[k * d_count + d];
+            nn = t * t;
+        }
+    }
     nn = block_sum<1024>(nn, sm);
     if (threadIdx.x == 0) L_out[0] = sqrtf(nn);
 }
@@ -789,7 +988,11 @@ hipError_t launch_mlr_softmax(const MlrSoftmaxArgs& a, hipStream_t stream)
 hipError_t launch_diff(const float* X, const float* Y, float* V, int64_t n, int32_t* counter, hipStream_t stream)
 {
     if (n <= 0) return counter ? launch_fill_u32(counter, 0u, 1, stream) : hipSuccess;
-    hipLaunchKernelGGL(diff_kernel, dim3(grid_for(n)), dim3(256), 0, stream, X, Y, V, n, counter);
+    auto aligned = [](const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; };
+    if (n % 4 == 0 && aligned(X) && aligned(Y) && aligned(V))
+        hipLaunchKernelGGL(diff_kernel<4>, dim3(grid_for(n / 4)), dim3(256), 0, stream, X, Y, V, n, counter);
+    else
+        hipLaunchKernelGGL(diff_kernel<1>, dim3(grid_for(n)), dim3(256), 0, stream, X, Y, V, n, counter);
     return hipGetLastError();
 }
 
@@ -803,7 +1006,10 @@ hipError_t launch_scale_rows(const float* V, const float* coef, float* Vs, int64
 hipError_t launch_div_scalar(const float* Z, float* W, float lambda, int64_t n, hipStream_t stream)
 {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(div_scalar_kernel, dim3(grid_for(n)), dim3(256), 0, stream, Z, W, lambda, n);
+    if (n % 4 == 0 && reinterpret_cast<uintptr_t>(Z) % 16 == 0 && reinterpret_cast<uintptr_t>(W) % 16 == 0)
+        hipLaunchKernelGGL(div_scalar_kernel<4>, dim3(grid_for(n / 4)), dim3(256), 0, stream, Z, W, lambda, n);
+    else
+        hipLaunchKernelGGL(div_scalar_kernel<1>, dim3(grid_for(n)), dim3(256), 0, stream, Z, W, lambda, n);
     return hipGetLastError();
 }
 
@@ -813,7 +1019,20 @@ hipError_t launch_sdca_mlr(const float* Zl, const float* X, float* P, float* dU,
     if (B <= 0 || J <= 0) return hipSuccess;
     if (B > 0x7fffffffLL) return hipErrorInvalidValue;
     const float inv_lambda_n = (float)(1.0 / ((double)lambda * (double)n_total));
-    hipLaunchKernelGGL(sdca_mlr_kernel, dim3((unsigned)B), dim3(256), 0, stream, Zl, X, P, dU, J, D, inv_lambda_n, beta);
+    auto go = [&](auto nt, auto per) {
+        constexpr int NT = decltype(nt)::value, PER = decltype(per)::value;
+        hipLaunchKernelGGL((sdca_mlr_kernel<NT, PER>), dim3((unsigned)B), dim3(NT), 0, stream, Zl, X, P, dU, J, D, inv_lambda_n, beta);
+    };
+    if (J <= 256)
+        go(std::integral_constant<int, 256>{}, std::integral_constant<int, 1>{});
+    else if (J <= 512)
+        go(std::integral_constant<int, 512>{}, std::integral_constant<int, 1>{});
+    else if (J <= 1024)
+        go(std::integral_constant<int, 512>{}, std::integral_constant<int, 2>{});
+    else if (J <= 4096)
+        go(std::integral_constant<int, 1024>{}, std::integral_constant<int, 4>{});
+    else
+        go(std::integral_constant<int, 256>{}, std::integral_constant<int, 0>{});
     return hipGetLastError();
 }
 
@@ -829,14 +1048,25 @@ hipError_t launch_dml_scale(const float* Q, const int8_t* sim, float* U, int32_t
                             int64_t K, hipStream_t stream)
 {
     if (B <= 0) return hipSuccess;
-    hipLaunchKernelGGL(dml_scale_kernel, dim3((unsigned)B), dim3(256), 0, stream, Q, sim, U, n_active, margin, K);
+    if (K <= 1024)
+        hipLaunchKernelGGL(dml_scale_kernel<4>, dim3((unsigned)B), dim3(256), 0, stream, Q, sim, U, n_active, margin, K);
+    else
+        hipLaunchKernelGGL(dml_scale_kernel<0>, dim3((unsigned)B), dim3(256), 0, stream, Q, sim, U, n_active, margin, K);
     return hipGetLastError();
 }
 
 hipError_t launch_prox_rows(float* W, int64_t J, int64_t D, int mode, hipStream_t stream)
 {
     if (J <= 0 || D <= 0) return hipSuccess;
-    hipLaunchKernelGGL(prox_rows_kernel, dim3((unsigned)J), dim3(256), 0, stream, W, D, mode);
+    if (D <= 1024) {
+        const dim3 grid((unsigned)((J + 3) / 4));
+        if (D % 4 == 0 && reinterpret_cast<uintptr_t>(W) % 16 == 0)
+            hipLaunchKernelGGL(prox_rows_wave_kernel<true>, grid, dim3(256), 0, stream, W, J, D, mode);
+        else
+            hipLaunchKernelGGL(prox_rows_wave_kernel<false>, grid, dim3(256), 0, stream, W, J, D, mode);
+    } else {
+        hipLaunchKernelGGL(prox_rows_kernel, dim3((unsigned)J), dim3(256), 0, stream, W, D, mode);
+    }
     return hipGetLastError();
 }
 
@@ -854,8 +1084,8 @@ int64_t power_chunks(int64_t J)
     return ch < 1 ? 1 : ch;
 }
 
-hipError_t launch_power_iteration(const float* W, int64_t J, int64_t D, int iters, float* scratch, float* L_out,
-                                  hipStream_t stream)
+hipError_t launch_power_iteration(const float* W, int64_t J, int64_t D, int iters, float* scratch, float* spare, int64_t spare_floats,
+                                  float* L_out, hipStream_t stream)
 {
     const int rows = power_rows(J);
     if (rows > POWER_MAX_ROWS) return hipErrorInvalidValue;
@@ -866,18 +1096,33 @@ hipError_t launch_power_iteration(const float* W, int64_t J, int64_t D, int iter
     const float b0 = 1.0f / sqrtf((float)D);
     hipError_t e = launch_fill_u32(b, __builtin_bit_cast(uint32_t, b0), D, stream);
     if (e != hipSuccess) return e;
-    const bool in_registers = rows == 16 && D <= 1024 && D % 4 == 0 && reinterpret_cast<uintptr_t>(W) % 16 == 0 &&
-                              reinterpret_cast<uintptr_t>(scratch) % 16 == 0 && J % 4 == 0;
+    const bool in_registers = rows == 16 && D <= 1024;
+    auto aligned = [](const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; };
+    const bool vec = in_registers && D % 4 == 0 && J % 4 == 0 && aligned(W) && aligned(scratch) && aligned(spare);
+    // One launch per iteration where a workgroup adds up the partials faster than a launch of its own (3 us) does: up to
+    // 128 KB of them, and with a second array for them to alternate with.
+    const bool one_launch = in_registers && chunks > 1 && chunks * D <= 32768 && spare_floats >= chunks * D;
+    const float* from = b;
+    int from_chunks = 1;
     for (int it = 0; it < iters; ++it) {
-        if (in_registers)
-            hipLaunchKernelGGL(power_step16_kernel, dim3((unsigned)chunks), dim3(256), 0, stream, W, it == 0 ? b : g, part, J, D);
+        float* const to = one_launch && (it & 1) ? spare : part;
+        if (vec)
+            hipLaunchKernelGGL(power_step16_kernel<true>, dim3((unsigned)chunks), dim3(256), 0, stream, W, from, from_chunks, to, J, D);
+        else if (in_registers)
+            hipLaunchKernelGGL(power_step16_kernel<false>, dim3((unsigned)chunks), dim3(256), 0, stream, W, from, from_chunks, to, J, D);
         else
-            hipLaunchKernelGGL(power_step_kernel, dim3((unsigned)chunks), dim3(256), 0, stream, W, it == 0 ? b : g, part, J, D, rows);
-        hipLaunchKernelGGL(power_reduce_kernel, dim3((unsigned)((D + 15) / 16)), dim3(256), 0, stream, part, g, D, chunks);
+            hipLaunchKernelGGL(power_step_kernel, dim3((unsigned)chunks), dim3(256), 0, stream, W, from, to, J, D, rows);
+        if (one_launch) {
+            from = to;
+            from_chunks = (int)chunks;
+        } else {
+            hipLaunchKernelGGL(power_reduce_kernel, dim3((unsigned)((D + 15) / 16)), dim3(256), 0, stream, to, g, D, chunks);
+            from = g;
+        }
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(vec_norm_kernel, dim3(1), dim3(1024), 0, stream, g, L_out, D);
+    hipLaunchKernelGGL(vec_norm_kernel, dim3(1), dim3(1024), 0, stream, from, from_chunks, L_out, D);
     return hipGetLastError();
 }
 

@@ -504,7 +504,7 @@ int sfb_compute_sf(sfb_ctx* ctx, int32_t model, const float* W, int64_t J, int64
     float* A = static_cast<float*>(U);
     float* R = static_cast<float*>(V);
     const float* X = static_cast<const float*>(batch->X);
-    SFB_RUN(KID_POWER_ITERATION, sfb::launch_power_iteration(W, J, D, batch->power_iters, scratch, Lp, st));
+    SFB_RUN(KID_POWER_ITERATION, sfb::launch_power_iteration(W, J, D, batch->power_iters, scratch, A, B * J, Lp, st));
     SFB_RUN(KID_FILL, sfb::launch_fill_u32(A, 0u, B * J, st));
     for (int it = 0; it <= batch->ista_iters; ++it) {
         if (it == 0) {
