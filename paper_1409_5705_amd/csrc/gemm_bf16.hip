@@ -595,20 +595,226 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1))) void
     wait_all_vmem();   // no direct load may be in flight when the workgroup's LDS is released
 }
 
+// The apply with few factor pairs, where the pass over W is all that counts: 128 x 128 tiles (four wavefronts of 32 x 128),
+// two workgroups per CU.  What bounds it is the stream of W (a copy of 4 GiB runs at 4.8 TB/s): 8192 x 4096 with 256 pairs
+// 69 -> 44 us, 325000 x 10000 on the planes with 100 pairs 3.62 -> 3.37 ms (5.8 TB/s).  A workgroup requests its first two k-slices and then its whole tile of W, so that the stream of
+// W never waits for a k-loop or an epilogue: the other workgroup's loads are in flight meanwhile.  (The 256 x 256 kernel
+// above, one workgroup per CU, stands still on W between its k-loops.)
+constexpr int SM = 128, SN = 128;
+constexpr uint32_t SSTAGE = 0x8000u, SB_OFF = SM * 128;      // one k-slice: [A tile 16 KiB][B tile 16 KiB]
+
+// Whether any of the LANES neighbouring lanes that write one 128-byte line of the bf16 copy (high plane) has something to
+// write there: a line is stored whole or not at all, since one written in part costs the memory a read as well.  Measured:
+// apply of 40000 x 10000 with 100 pairs, 2 to 3 % of the values changing, 0.97 -> 0.83 ms with the copy, 0.69 -> 0.57 on
+// the planes.  (In the 256 x 256 kernel, with its many pairs, it gains nothing.)
+template <int LANES>
+__device__ __forceinline__ bool any_in_line(bool mine, int lane)
+{
+    const uint64_t b = __builtin_amdgcn_ballot_w64(mine);
+    return ((b >> (lane & ~(LANES - 1))) & ((1ull << LANES) - 1)) != 0;
+}
+
+template <int MODE>
+__global__ __launch_bounds__(NT, 2) void apply_small_kernel(Params p)
+{
+    static_assert(MODE == MODE_APPLY || MODE == MODE_SPLIT, "apply");
+    constexpr int UM = 2, UN = 8;
+    constexpr bool SPLIT8 = MODE != MODE_SPLIT;      // a lane's eight columns: two groups of four 64 apart, or eight in a row
+    __shared__ u32x4 small_smem[2 * SSTAGE / 16];
+    const char* const lds_bytes = reinterpret_cast<const char*>(small_smem);
+    const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)small_smem;
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, quad = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    // each XCD a contiguous range of a raster of groups of group_m row-tiles, row-tile index fastest
+    int64_t m0, n0;
+    {
+        const uint32_t tiles = gridDim.x, xcds = (uint32_t)p.num_xcd, tiles_n = (uint32_t)p.tiles_n, tiles_m = (uint32_t)p.tiles_m;
+        const uint32_t x = blockIdx.x % xcds, wi = blockIdx.x / xcds, q = tiles / xcds, r = tiles % xcds;
+        const uint32_t t = x * q + (x < r ? x : r) + wi;
+        const uint32_t per_group = (uint32_t)p.group_m * tiles_n;
+        const uint32_t grp = t / per_group, rr = t % per_group, first = grp * (uint32_t)p.group_m;
+        const uint32_t gm = tiles_m - first < (uint32_t)p.group_m ? tiles_m - first : (uint32_t)p.group_m;
+        m0 = (int64_t)(first + rr % gm) * SM;
+        n0 = (int64_t)(rr / gm) * SN;
+    }
+    const int nk = (int)(p.K / BK);
+    const int last_m = (int)(p.M - m0 < SM ? p.M - m0 : SM) - 1, last_n = (int)(p.N - n0 < SN ? p.N - n0 : SN) - 1;
+
+    // ---- operands: LDS row r of the A tile is row r of the tile, of the B tile column col_of(r) (a lane then owns eight
+    // columns of C that 16-byte accesses cover); rows past the end are clamped
+    auto col_of = [](int r) {
+        return SPLIT8 ? ((r & 15) << 2) | ((r >> 4) & 3) | (((r >> 6) & 1) << 6) : ((r & 15) << 3) | ((r >> 4) & 7);
+    };
+    uint32_t offA[4], offB[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = 8 * (4 * wave + i) + (lane >> 3), c = col_of(r);
+        const uint32_t c16 = (uint32_t)(((lane & 7) ^ swz(r)) << 4);
+        offA[i] = (uint32_t)(r < last_m ? r : last_m) * 128u + c16;
+        offB[i] = (uint32_t)(c < last_n ? c : last_n) * 128u + c16;
+    }
+    const uint64_t gA = uniform64(reinterpret_cast<uint64_t>(p.A) + (uint64_t)(m0 / BM) * (uint64_t)nk * 32768u + (uint64_t)(m0 % BM) * 128u);
+    const uint64_t gB = uniform64(reinterpret_cast<uint64_t>(p.B) + (uint64_t)(n0 / BN) * (uint64_t)nk * 32768u + (uint64_t)(n0 % BN) * 128u);
+    auto issue = [&](int s) {
+        const uint32_t dst = lds_base + (uint32_t)(s & 1) * SSTAGE + (uint32_t)(4 * wave) * 1024u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) load_to_lds_16<false>(dst + i * 1024u, gA + (uint64_t)s * 32768u, offA[i]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) load_to_lds_16<false>(dst + SB_OFF + i * 1024u, gB + (uint64_t)s * 32768u, offB[i]);
+    };
+    issue(0);
+    if (nk > 1) issue(1);
+
+    // ---- the tile of W (unconditional loads at clamped places: the waits below count them)
+    auto make_rsrc = [&](const void* base) {
+        return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(uniform64(reinterpret_cast<uint64_t>(base))), 0, 0xffffffff, 0x00020000);
+    };
+    const bool has_shadow = p.shadow != nullptr;
+    const auto crs = make_rsrc(MODE == MODE_SPLIT ? p.C : p.C + m0 * p.ldc + n0);
+    const auto srs = make_rsrc(has_shadow ? p.shadow + ((m0 / BM) * (p.ld_shadow / BK) + n0 / BK) * (int64_t)(BM * BK) + (m0 % BM) * BK : p.shadow);
+    const auto lrs = make_rsrc(MODE == MODE_SPLIT ? p.lo + ((m0 / BM) * ((p.N + BN - 1) / BN) + n0 / BN) * (int64_t)(BM * BN) + (m0 % BM) * BN + n0 % BN : p.lo);
+    const uint32_t row_c = (uint32_t)p.ldc * 4u;
+    // first column of a lane's first and second group of four (SPLIT: of its eight)
+    const int c0 = (SPLIT8 ? 4 : 8) * l16, c1 = 64 + 4 * l16;
+    const bool ok0 = c0 <= last_n, ok1 = c1 <= last_n;              // N % 8 == 0: a whole group or none
+    const uint32_t at0 = (uint32_t)(ok0 ? c0 : 0), at1 = (uint32_t)(ok1 ? c1 : 0);
+    auto row_of = [&](int ta, int e) { return 32 * wave + 16 * ta + 4 * quad + e; };
+    auto row_in = [&](int ta, int e) { const int r = row_of(ta, e); return (uint32_t)(r < last_m ? r : last_m); };
+    // byte offset of column c of tile row r in the blocked bf16 copy / high plane
+    auto shadow_at = [](uint32_t r, uint32_t c) { return (c / BK) * (uint32_t)(BM * BK * 2) + r * (uint32_t)(BK * 2) + (c % BK) * 2u; };
+    u32x4 w[UM][4][2];
+#pragma unroll
+    for (int ta = 0; ta < UM; ++ta)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t r = row_in(ta, e);
+            if (MODE == MODE_SPLIT) {
+                w[ta][e][0] = __builtin_amdgcn_raw_buffer_load_b128(srs, shadow_at(r, at0), 0, C_POLICY);
+                w[ta][e][1] = __builtin_amdgcn_raw_buffer_load_b128(lrs, r * (uint32_t)(BN * 2) + at0 * 2u, 0, C_POLICY);
+            } else {
+                w[ta][e][0] = __builtin_amdgcn_raw_buffer_load_b128(crs, r * row_c + at0 * 4u, 0, C_POLICY);
+                w[ta][e][1] = __builtin_amdgcn_raw_buffer_load_b128(crs, r * row_c + at1 * 4u, 0, C_POLICY);
+            }
+        }
+    constexpr int WL = UM * 4 * 2;
+    __builtin_amdgcn_sched_barrier(0);
+
+    floatx4 acc[UM][UN];
+#pragma unroll
+    for (int ta = 0; ta < UM; ++ta)
+#pragma unroll
+        for (int tb = 0; tb < UN; ++tb) acc[ta][tb] = floatx4{0.f, 0.f, 0.f, 0.f};
+    uint32_t ra[UM], rb[4];
+#pragma unroll
+    for (int t = 0; t < UM; ++t) ra[t] = lds_byte(32 * wave + 16 * t + l16, quad);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) rb[t] = lds_byte(16 * t + l16, quad) + SB_OFF;
+    for (int s = 0; s < nk; ++s) {
+        // slices 0 and 1 were requested in front of W, later ones behind it
+        if (s == 0) {
+            if (nk > 1)
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(8 + WL) : "memory");
+            else
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(WL) : "memory");
+        } else if (s == 1) {
+            if (nk > 2)
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(8 + WL) : "memory");
+            else
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(WL) : "memory");
+        } else if (s + 1 < nk) {
+            asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        } else {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        }
+        __syncthreads();
+        const char* const stage = lds_bytes + (s & 1) * SSTAGE;
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            bf16x8 a[UM], b[UN];
+#pragma unroll
+            for (int t = 0; t < UM; ++t) a[t] = *reinterpret_cast<const bf16x8*>(stage + (ra[t] ^ (64u * ks)));
+#pragma unroll
+            for (int t = 0; t < UN; ++t) b[t] = *reinterpret_cast<const bf16x8*>(stage + (rb[t & 3] ^ (64u * ks)) + (t >> 2) * 64 * 128);
+#pragma unroll
+            for (int tb = 0; tb < UN; ++tb)
+#pragma unroll
+                for (int ta = 0; ta < UM; ++ta) acc[ta][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ta], b[tb], acc[ta][tb], 0, 0, 0);
+        }
+        if (s + 2 < nk) {
+            __syncthreads();                 // every wavefront has read the stage
+            issue(s + 2);
+        }
+    }
+
+    // ---- W - eta * acc.  Register e of lane (quad, l16) of MFMA tile (ta, tb): row 16 ta + 4 quad + e, column tb of the lane's
+#pragma unroll
+    for (int ta = 0; ta < UM; ++ta)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int r = row_of(ta, e);
+            if (r > last_m) continue;
+            if (MODE == MODE_SPLIT) {
+                if (!ok0) continue;
+                uint32_t oh[4], ol[4];
+                bool changed = false;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const uint32_t hk = w[ta][e][0][k], lk = w[ta][e][1][k];
+                    const uint32_t w0 = split_word(split_value(join_pair0(hk, lk)) - p.eta * acc[ta][2 * k][e]);
+                    const uint32_t w1 = split_word(split_value(join_pair1(hk, lk)) - p.eta * acc[ta][2 * k + 1][e]);
+                    oh[k] = pack_hi(w0, w1);
+                    ol[k] = pack_lo(w0, w1);
+                    changed = changed || oh[k] != hk;
+                }
+                if (any_in_line<8>(changed, lane))
+                    __builtin_amdgcn_raw_buffer_store_b128(u32x4{oh[0], oh[1], oh[2], oh[3]}, srs, shadow_at((uint32_t)r, at0), 0, C_POLICY);
+                __builtin_amdgcn_raw_buffer_store_b128(u32x4{ol[0], ol[1], ol[2], ol[3]}, lrs, (uint32_t)r * (uint32_t)(BN * 2) + at0 * 2u, 0, C_POLICY);
+            } else {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {       // the two groups of four columns
+                    if (!(h ? ok1 : ok0)) continue;
+                    const uint32_t at = h ? at1 : at0;
+                    float nf[4];
+                    uint32_t sh[2];
+                    bool changed = false;
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        const uint32_t oa = w[ta][e][h][2 * k], ob = w[ta][e][h][2 * k + 1];
+                        nf[2 * k] = __uint_as_float(oa) - p.eta * acc[ta][4 * h + 2 * k][e];
+                        nf[2 * k + 1] = __uint_as_float(ob) - p.eta * acc[ta][4 * h + 2 * k + 1][e];
+                        sh[k] = pack_bf16(nf[2 * k], nf[2 * k + 1]);
+                        changed = changed || sh[k] != pack_bf16(__uint_as_float(oa), __uint_as_float(ob));
+                    }
+                    const u32x4 out = {__float_as_uint(nf[0]), __float_as_uint(nf[1]), __float_as_uint(nf[2]), __float_as_uint(nf[3])};
+                    __builtin_amdgcn_raw_buffer_store_b128(out, crs, (uint32_t)r * row_c + at * 4u, 0, C_POLICY);
+                    if (has_shadow && any_in_line<16>(changed, lane))
+                        __builtin_amdgcn_raw_buffer_store_b64(u32x2{sh[0], sh[1]}, srs, shadow_at((uint32_t)r, at), 0, C_POLICY);
+                }
+            }
+        }
+}
+
 // src[rows_src][cols] (bf16, row-major) -> dst = its transpose [cols][pitch] in the blocked operand layout of
 // sf_gemm_kernel; source rows rows_src..pitch-1 are taken as zero.  cols % 8 == 0, pitch % 64 == 0.
 // 64x64 tiles through LDS, 256 threads, 16-byte global accesses on both sides
 // (8 lanes cover one 128-byte row segment).
 // coef (nullable): source row k is scaled by coef[k] (product in fp32, rounded to
 // bf16 to nearest even).
-__global__ __launch_bounds__(256) void transpose_bf16_kernel(const uint16_t* __restrict__ src,
-                                                             uint16_t* __restrict__ dst, int64_t rows_src,
-                                                             int64_t cols, int64_t pitch,
-                                                             const float* __restrict__ coef)
+// Two matrices by one launch: workgroups blockIdx.x < blocks0 take the first, the others the second (with coef).
+__global__ __launch_bounds__(256) void transpose_bf16_kernel(const uint16_t* __restrict__ src0, uint16_t* __restrict__ dst0, int64_t cols0,
+                                                             unsigned blocks0, const uint16_t* __restrict__ src1,
+                                                             uint16_t* __restrict__ dst1, int64_t cols1,
+                                                             const float* __restrict__ coef1, int64_t rows_src, int64_t pitch)
 {
+    const bool second = blockIdx.x >= blocks0;
+    const uint16_t* const src = second ? src1 : src0;
+    uint16_t* const dst = second ? dst1 : dst0;
+    const int64_t cols = second ? cols1 : cols0;
+    const float* const coef = second ? coef1 : nullptr;
     constexpr int LP = 72;   // LDS row pitch in elements: 144 bytes, rows stay 16-byte aligned
     __shared__ __attribute__((aligned(16))) uint16_t tile[64 * LP];
-    const int64_t c0 = (int64_t)blockIdx.x * 64, k0 = (int64_t)blockIdx.y * 64;
+    const int64_t c0 = (int64_t)(second ? blockIdx.x - blocks0 : blockIdx.x) * 64, k0 = (int64_t)blockIdx.y * 64;
 #pragma unroll
     for (int it = 0; it < 2; ++it) {
         const int id = threadIdx.x + 256 * it, r = id >> 3, cc = (id & 7) * 8;
@@ -754,6 +960,24 @@ hipError_t launch(Params p, DeviceInfo& dev, hipStream_t stream)
     return hipGetLastError();
 }
 
+// (the checks of `launch` hold here too: same operands, same C)
+template <int MODE>
+hipError_t launch_small(Params p, DeviceInfo& dev, hipStream_t stream)
+{
+    if (dev.cus <= 0 || dev.xcds <= 0) return hipErrorInvalidDevice;
+    const int64_t tm = (p.M + SM - 1) / SM, tn = (p.N + SN - 1) / SN;
+    if (tm * tn > 0x7fffffffLL || p.ldc * 4 * SM >= (1LL << 31) || p.N % 8 != 0 || p.K <= 0 || p.K % BK != 0) return hipErrorInvalidValue;
+    if (MODE != MODE_SPLIT && (reinterpret_cast<uintptr_t>(p.C) % 16 != 0 || p.ldc % 4 != 0)) return hipErrorInvalidValue;
+    if (p.shadow && (reinterpret_cast<uintptr_t>(p.shadow) % 16 != 0 || p.ld_shadow % BK != 0 || p.ld_shadow < p.N)) return hipErrorInvalidValue;
+    if (MODE == MODE_SPLIT && (!p.shadow || !p.lo || reinterpret_cast<uintptr_t>(p.lo) % 16 != 0)) return hipErrorInvalidValue;
+    p.tiles_m = (int)tm;
+    p.tiles_n = (int)tn;
+    p.num_xcd = dev.xcds;
+    if (p.group_m <= 0 || p.group_m > tm) p.group_m = (int)tm;
+    hipLaunchKernelGGL((apply_small_kernel<MODE>), dim3((unsigned)(tm * tn)), dim3(NT), 0, stream, p);
+    return hipGetLastError();
+}
+
 unsigned grid_for(int64_t n)
 {
     int64_t g = (n + 255) / 256;
@@ -819,11 +1043,9 @@ hipError_t launch_apply_bf16_transpose(const uint16_t* U, const uint16_t* V, con
     const int64_t Np = bf16_pitch(N);
     uint16_t* Ut = static_cast<uint16_t*>(workspace);
     uint16_t* Vt = apply_bf16_vt(workspace, N, J);
-    hipLaunchKernelGGL(transpose_bf16_kernel, dim3((unsigned)((J + 63) / 64), (unsigned)(Np / 64)), dim3(256), 0,
-                       stream, U, Ut, N, J, Np, static_cast<const float*>(nullptr));
-    if (V)     // null: the caller writes V^T itself (apply_bf16_vt)
-        hipLaunchKernelGGL(transpose_bf16_kernel, dim3((unsigned)((D + 63) / 64), (unsigned)(Np / 64)), dim3(256), 0,
-                           stream, V, Vt, N, D, Np, coef);
+    const unsigned blocks_u = (unsigned)((J + 63) / 64), blocks_v = V ? (unsigned)((D + 63) / 64) : 0;   // V null: the caller writes V^T (apply_bf16_vt)
+    hipLaunchKernelGGL(transpose_bf16_kernel, dim3(blocks_u + blocks_v, (unsigned)(Np / 64)), dim3(256), 0, stream, U, Ut, J, blocks_u, V, Vt, D,
+                       coef, N, Np);
     return hipGetLastError();
 }
 
@@ -843,6 +1065,19 @@ hipError_t launch_w_from_split(const uint16_t* hi, const uint16_t* lo, float* W,
     return hipGetLastError();
 }
 
+// Which kernel applies Np / 64 k-slices to a J x D matrix.  The 128 x 128 tiles of apply_small_kernel stream W without
+// pauses but take 1.4 times as long per k-slice with the chip full (0.52 against 0.38 us per 128 x 128), and less where the
+// 256 x 256 tiles do not fill the chip.  Measured, whole call, us, 256 / 128 tiles (N pairs; f: fp32 array, p: planes):
+//   1000 x 512     f, N 100 19.5 / 13.4, 512 26 / 16, 2048 56 / 38        3000 x 1000  f, 100 25 / 13, 1024 48 / 30, 2048 65 / 45
+//   8192 x 4096    f, 100 86 / 57, 256 93 / 64, 512 103 / 87, 1024 125 / 118, 2048 172 / 182;   p, 100 68 / 60, 512 89 / 77, 1024 111 / 111
+//   20000 x 3000   f, 256 143 / 132, 512 159 / 150, 1024 202 / 210        (the V^T panels of 512 pairs fit an L2: 3 MB)
+//   40000 x 10000  f, 100 703 / 673, 256 715 / 696, 512 755 / 780;  p, 100 597 / 574, 256 606 / 602   (they do not: 10 MB)
+static bool apply_is_small(int64_t J, int64_t D, int64_t Np, int cus)
+{
+    const int64_t tiles = ((J + BM - 1) / BM) * ((D + BN - 1) / BN);
+    return Np <= 256 || tiles <= cus / 2 || (Np <= 512 && D * Np * 2 <= (4 << 20));
+}
+
 hipError_t launch_apply_bf16(float* W, uint16_t* W_shadow, uint16_t* W_lo, int64_t N, int64_t J, int64_t D, float eta,
                              const void* workspace, DeviceInfo& dev, hipStream_t stream)
 {
@@ -858,10 +1093,13 @@ hipError_t launch_apply_bf16(float* W, uint16_t* W_shadow, uint16_t* W_lo, int64
     p.K = Np;
     p.eta = eta;
     p.group_m = 8;               // 8 row-tiles x 4 column tiles under one L2 at a time (measured best of 1..32)
+    const bool small = apply_is_small(J, D, Np, dev.cus);
+    if (small) p.group_m = Np <= 256 ? 2 : 4;      // (measured with 1, 2, 4, 8: 2 up to 4 k-slices, 4 and 8 beyond)
     if (W_lo) {
         p.lo = W_lo;
-        return launch<MODE_SPLIT>(p, dev, stream);
+        return small ? launch_small<MODE_SPLIT>(p, dev, stream) : launch<MODE_SPLIT>(p, dev, stream);
     }
+    if (small) return launch_small<MODE_APPLY>(p, dev, stream);
     return launch<MODE_APPLY>(p, dev, stream);
 }
 
