@@ -395,6 +395,7 @@ __global__ __launch_bounds__(GF_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
             fetch(t0 + TB, nxt);
 #pragma unroll
             for (int s = 0; s < GF_SPT; ++s) {
+                if (t0 >= len[s]) continue;          // (uniform: no entry of this slice left in the chunk; 3.03 -> 2.89 ms at 325000 x 10000, 0.5 %)
 #pragma unroll
                 for (int u = 0; u < TB; ++u) {
                     const uint32_t at = BF16 ? (cur[s][u][0] & 0xffffu) : cur[s][u][0];
