@@ -293,7 +293,7 @@ hipError_t launch_fwd(FwdParams p, int split, DeviceInfo& dev, int slot, hipStre
 // 3000: f 57 [72 + 55], h 31 [55]; 1000, 4000 x 2000: f 34, h 27 [10 + 43]; 256, 40000 x 2048: f 114 [98 + 42],
 // h 74 [42].  Per tile and slice the kernel takes 0.5 to 0.9 us, bound by what a CU pulls from the L2 (48 KB in f)
 // and by its LDS; W as fp32 arrives at 4.6 TB/s.
-MlrForwardPlan mlr_forward_plan(int64_t B, int64_t J, int64_t D, bool have_copy)
+MlrForwardPlan mlr_forward_plan(int64_t B, int64_t J, int64_t D, bool have_copy, bool may_split)
 {
     const int64_t nk = (D + KS - 1) / KS;
     const double cus = 256.0, w = (double)J * (double)D;
@@ -311,7 +311,7 @@ MlrForwardPlan mlr_forward_plan(int64_t B, int64_t J, int64_t D, bool have_copy)
     for (int i = 0; i < 3; ++i) {
         const Shape& sh = have_copy ? copy_shapes[i] : fp32_shapes[i];
         const int64_t tm = (B + 64 * sh.mt - 1) / (64 * sh.mt), tn = (J + 32 * sh.ntl - 1) / (32 * sh.ntl);
-        for (int s = 1; s <= 16; ++s) {
+        for (int s = 1; s <= (may_split ? 16 : 1); ++s) {
             const int64_t per = (nk + s - 1) / s;
             if (s > 1 && (J > MLR_SOFTMAX_ROW_MAX || per < 4 || (nk + per - 1) / per != s)) continue;
             const double rounds = std::ceil((double)(tm * tn * s) / cus);

@@ -73,7 +73,7 @@ hipError_t launch_shadow_from_w(const float* W, uint16_t* shadow, int64_t J, int
 struct MlrForwardPlan {
     int mt = 0, ntl = 0, split = 1;
 };
-MlrForwardPlan mlr_forward_plan(int64_t B, int64_t J, int64_t D, bool have_copy);
+MlrForwardPlan mlr_forward_plan(int64_t B, int64_t J, int64_t D, bool have_copy, bool may_split);
 hipError_t launch_mlr_forward_bf16(const MlrForwardPlan& plan, const uint16_t* X, const float* W, const uint16_t* W_shadow, float* Z,
                                    uint16_t* X_aligned, int64_t B, int64_t J, int64_t D, DeviceInfo& dev, hipStream_t stream);
 hipError_t launch_fwd_stream(const MlrForwardPlan& plan, const uint16_t* X_aligned, const float* W, const uint16_t* W_shadow, float* Z,

@@ -144,21 +144,29 @@ int64_t sc_partial_bytes(int64_t B, int64_t J, int64_t D)
 }
 
 // Front of the workspace on the bf16 multiclass-logistic path: the tile-blocked logits (as many planes of partial sums
-// as the forward may leave, with or without a bf16 copy of W), then the words the workgroups of the one-read softmax
-// exchange.
-int64_t bf16_logits_bytes(int64_t B, int64_t J, int64_t D)
+// as the forward may leave, with or without a bf16 copy of W; one where it may not split k), then the words the
+// workgroups of the one-read softmax exchange.
+int64_t bf16_logits_bytes(int64_t B, int64_t J, int64_t D, bool may_split = true)
 {
     int planes = 1;
     for (bool copy : {false, true}) {
-        const int s = sfb::mlr_forward_plan(B, J, D, copy).split;
+        const int s = sfb::mlr_forward_plan(B, J, D, copy, may_split).split;
         if (s > planes) planes = s;
     }
     return round_up(planes * sfb::mlr_logits_floats(B, J) * 4) + round_up(sfb::mlr_softmax_scratch_bytes(B, J));
 }
-void* bf16_softmax_scratch(sfb_ctx* ctx, int64_t B, int64_t J, int64_t D)
+void* bf16_softmax_scratch(sfb_ctx* ctx, int64_t B, int64_t J, int64_t D, bool may_split)
 {
     const int64_t bytes = round_up(sfb::mlr_softmax_scratch_bytes(B, J));
-    return bytes ? ctx->ws + bf16_logits_bytes(B, J, D) - bytes : nullptr;
+    return bytes ? ctx->ws + bf16_logits_bytes(B, J, D, may_split) - bytes : nullptr;
+}
+// A workspace without room for several planes (the size that was asked for before the forward split k) still does: one plane
+// and no split.  `need` becomes what that takes.
+bool bf16_may_split(const sfb_ctx* ctx, int64_t B, int64_t J, int64_t D, int64_t* need)
+{
+    if (ctx->ws_bytes >= *need) return true;
+    *need -= bf16_logits_bytes(B, J, D) - bf16_logits_bytes(B, J, D, false);
+    return false;
 }
 
 // True if W is currently kept as two planes by this context: its fp32 array is stale.
@@ -426,7 +434,11 @@ int sfb_compute_sf(sfb_ctx* ctx, int32_t model, const float* W, int64_t J, int64
     const bool has_shadow = ctx->shadow_buf && ctx->shadow_W == W && ctx->shadow_J == J && ctx->shadow_D == D;
     if (is_split(ctx, W) && !has_shadow) return SFB_EINVAL;   // attached as planes of another shape: the fp32 array is stale
     int64_t need = sfb_workspace_bytes(model, J, D, batch);
-    if (model == SFB_MLR && batch->in_dtype == SFB_BF16 && has_shadow) need -= sfb_shadow_bytes(J, D);
+    bool may_split = true;
+    if (model == SFB_MLR && batch->in_dtype == SFB_BF16) {
+        if (has_shadow) need -= sfb_shadow_bytes(J, D);
+        may_split = bf16_may_split(ctx, B, J, D, &need);
+    }
     if (need > 0 && (!ctx->ws || ctx->ws_bytes < need)) return SFB_ENOWS;
     SFB_TRY(hipSetDevice(ctx->device));
     hipStream_t st = ctx->stream;
@@ -456,9 +468,9 @@ int sfb_compute_sf(sfb_ctx* ctx, int32_t model, const float* W, int64_t J, int64
             if (sfb::gemm_f32_partial_bytes(B, J, D) > 0) g.partial = reinterpret_cast<float*>(ctx->ws + round_up(B * J * 4));
             SFB_RUN(KID_GEMM_F32_STORE, sfb::launch_gemm_f32(g, st));
         } else {
-            uint16_t* Xa = reinterpret_cast<uint16_t*>(ctx->ws + bf16_logits_bytes(B, J, D));
+            uint16_t* Xa = reinterpret_cast<uint16_t*>(ctx->ws + bf16_logits_bytes(B, J, D, may_split));
             const uint16_t* Wb = has_shadow ? ctx->shadow_buf : nullptr;
-            const sfb::MlrForwardPlan plan = sfb::mlr_forward_plan(B, J, D, has_shadow);
+            const sfb::MlrForwardPlan plan = sfb::mlr_forward_plan(B, J, D, has_shadow, may_split);
             if (!has_shadow && plan.mt == 0) {   // no working copy attached: make one for this call
                 uint16_t* tmp = Xa + round_up(sfb::bf16_operand_bytes(B, D)) / 2;
                 SFB_RUN(KID_SHADOW, sfb::launch_shadow_from_w(W, tmp, J, D, st));
@@ -469,7 +481,7 @@ int sfb_compute_sf(sfb_ctx* ctx, int32_t model, const float* W, int64_t J, int64
             sm.out_bf16 = sm.blocked = true;
             sm.planes = plan.split;
             sm.plane_floats = sfb::mlr_logits_floats(B, J);
-            sm.scratch = bf16_softmax_scratch(ctx, B, J, D);
+            sm.scratch = bf16_softmax_scratch(ctx, B, J, D, may_split);
         }
         SFB_RUN(KID_SOFTMAX, sfb::launch_mlr_softmax(sm, st));
         return SFB_OK;
@@ -727,6 +739,7 @@ int sfb_mlr_sf_csr(sfb_ctx* ctx, const float* W, int64_t J, int64_t D, const sfb
     int64_t need = sfb_mlr_sf_csr_workspace_bytes(J, D, B, X->dtype);
     if (need < 0) return (int)need;
     if (bf16 && has_shadow) need -= sfb_shadow_bytes(J, D);
+    const bool may_split = bf16 && bf16_may_split(ctx, B, J, D, &need);
     if (!ctx->ws || ctx->ws_bytes < need) return SFB_ENOWS;
     SFB_TRY(hipSetDevice(ctx->device));
     hipStream_t st = ctx->stream;
@@ -761,9 +774,9 @@ int sfb_mlr_sf_csr(sfb_ctx* ctx, const float* W, int64_t J, int64_t D, const sfb
         return SFB_OK;
     }
     const int64_t pitch = sfb::bf16_pitch(D);
-    char* region = ctx->ws + bf16_logits_bytes(B, J, D);
+    char* region = ctx->ws + bf16_logits_bytes(B, J, D, may_split);
     const uint16_t* Wb = has_shadow ? ctx->shadow_buf : nullptr;
-    const sfb::MlrForwardPlan plan = sfb::mlr_forward_plan(B, J, D, has_shadow);
+    const sfb::MlrForwardPlan plan = sfb::mlr_forward_plan(B, J, D, has_shadow, may_split);
     if (!has_shadow && (gather || plan.mt == 0)) {
         uint16_t* tmp = reinterpret_cast<uint16_t*>(region + csr_operand_bytes(J, D, B, true));
         SFB_RUN(KID_SHADOW, sfb::launch_shadow_from_w(W, tmp, J, D, st));
@@ -781,7 +794,7 @@ int sfb_mlr_sf_csr(sfb_ctx* ctx, const float* W, int64_t J, int64_t D, const sfb
     }
     sm.out_bf16 = sm.blocked = true;
     sm.plane_floats = sfb::mlr_logits_floats(B, J);
-    sm.scratch = bf16_softmax_scratch(ctx, B, J, D);
+    sm.scratch = bf16_softmax_scratch(ctx, B, J, D, may_split);
     SFB_RUN(KID_SOFTMAX, sfb::launch_mlr_softmax(sm, st));
     return SFB_OK;
 }

@@ -54,3 +54,43 @@ def test_stream_forward(sfb, oracle, J, D, B, layout):
     Uo, _ = oracle.mlr_sf(W0, X, y)
     mlr_u_check(U.float().cpu().numpy(), Uo, y, TOL_BF16)
     ctx.close()
+
+
+def test_workspace_without_room_for_a_split(sfb, oracle):
+    """A workspace with one plane of logits is enough: the same call then does not split k."""
+    J, D, B = 1504, 3000, 200
+    ru = lambda x, a=256: (x + a - 1) // a * a
+    planes1 = ru(ru(B, 256) * ru(J, 256) * 4) + ru(ru(B, 256) * ru(D, 64) * 2)
+    W0 = S.normal_matrix(J, D, 0.05, seed=35)
+    X, y = S.mlr_batch(J, D, B, seed=35, zero_frac=0.5, bf16=True)
+    Uo, _ = oracle.mlr_sf(W0, X, y)
+    for layout in ("plain", "planes"):
+        ctx = sfb.Context(0)
+        W = dev(W0)
+        if layout == "planes":
+            ctx.sfb_split_attach(W)
+        U = torch.empty((B, J), dtype=torch.bfloat16, device="cuda:0")
+        args = (sfb.SFB_MLR, W, dev_bf16(X))
+        ctx.sfb_compute_sf(*args, Y=dev(y), U=U)
+        size = planes1 + (sfb.lib().sfb_shadow_bytes(J, D) if layout == "plain" else 0)
+        assert size < sfb.lib().sfb_workspace_bytes(sfb.SFB_MLR, J, D, _batch(sfb, B))
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda:0")
+        assert ws.data_ptr() % 256 == 0
+        ctx._ensure_workspace = lambda *a, **k: None
+        assert sfb.lib().sfb_set_workspace(ctx._h, ws.data_ptr(), size) == 0
+        U2 = torch.empty_like(U)
+        ctx.sfb_compute_sf(*args, Y=dev(y), U=U2)
+        torch.cuda.synchronize()
+        mlr_u_check(U2.float().cpu().numpy(), Uo, y, TOL_BF16)
+        assert sfb.lib().sfb_set_workspace(ctx._h, ws.data_ptr(), size - 256) == 0
+        with pytest.raises(sfb.SfbError) as e:
+            ctx.sfb_compute_sf(*args, Y=dev(y), U=U2)
+        assert e.value.code == sfb.SFB_ENOWS
+        ctx.close()
+
+
+def _batch(sfb, B):
+    import ctypes
+    b = sfb.binding.sfb_batch()
+    b.B, b.in_dtype, b.sf_dtype = B, sfb.SFB_BF16, sfb.SFB_BF16
+    return ctypes.byref(b)
