@@ -41,11 +41,20 @@ __device__ __forceinline__ float wave_max(float v)
     v = fmaxf(v, dpp<DPP_MIRROR>(v));
     return fmaxf(fmaxf(lane_value(v, 0), lane_value(v, 16)), fmaxf(lane_value(v, 32), lane_value(v, 48)));
 }
+// The sum as a butterfly over distances 32, 16, .. 1.  The multiclass-logistic softmax keeps this order: where a sample is
+// classified with near certainty its factor is 1 / s - 1 with s close to 1, and which way the last bit of s falls is a
+// few per cent of that factor (either order is as far from the exact sum).
+__device__ __forceinline__ float wave_sum_butterfly(float v)
+{
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
 // Block reductions; `sm` has NT/64 floats.  Every thread gets the result.
-template <int NT>
+template <int NT, bool BUTTERFLY = false>
 __device__ __forceinline__ float block_sum(float v, float* sm)
 {
-    v = wave_sum(v);
+    v = BUTTERFLY ? wave_sum_butterfly(v) : wave_sum(v);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
     __syncthreads();
@@ -131,7 +140,7 @@ __global__ __launch_bounds__(NT) void mlr_softmax_kernel(const float* __restrict
     }
     // (a thread that saw no element has m = -inf, s = 0: its term is 0 * exp(-inf) = 0)
     const float M = block_max<NT>(m, sm);
-    s = block_sum<NT>(s * expf(m - M), sm);
+    s = block_sum<NT, true>(s * expf(m - M), sm);
     const float inv = 1.0f / s;
 
     const int64_t lab = y[row];
@@ -237,7 +246,7 @@ __global__ __launch_bounds__(256) void mlr_softmax_row_kernel(const float* __res
         for (int e = 0; e < E; ++e) v[i][e] = expf(v[i][e] - M);
         s += VEC ? (v[i][0] + v[i][E > 1 ? 1 : 0]) + (v[i][E > 2 ? 2 : 0] + v[i][E > 3 ? 3 : 0]) : v[i][0];
     }
-    s = block_sum<NT>(s, sm);
+    s = block_sum<NT, true>(s, sm);
     const float inv = 1.0f / s;
     const int64_t lab = y[row];
 #pragma unroll
@@ -364,7 +373,7 @@ __global__ __launch_bounds__(1024) void mlr_softmax_cluster_kernel(const float* 
                 s += v[i][e];
             }
         }
-        float s_own = block_sum<NT>(s, sm);
+        float s_own = block_sum<NT, true>(s, sm);
         if (m_own == -INFINITY) s_own = 1.0f;       // no class at all in this part: counts as 1 * exp(-inf) = 0
         if (tid == 0) {
             const unsigned long long word = ((unsigned long long)__float_as_uint(s_own) << 32) | __float_as_uint(m_own);
@@ -408,7 +417,7 @@ __global__ __launch_bounds__(1024) void mlr_softmax_cluster_kernel(const float* 
                     online_update(mk, sk, *reinterpret_cast<const floatx4*>(base + tile * tiles_m * 65536 + (c & 63) * 4));
             }
             const float Mk = block_max<NT>(mk, sm);
-            float Sk = block_sum<NT>(mk == -INFINITY ? 0.f : sk * expf(mk - Mk), sm);
+            float Sk = block_sum<NT, true>(mk == -INFINITY ? 0.f : sk * expf(mk - Mk), sm);
             if (Mk == -INFINITY) Sk = 1.0f;
             if (tid == 0) {
                 part_m[k] = Mk;
