@@ -437,7 +437,7 @@ __global__ __launch_bounds__(NT, 2) void gemm_f32_kernel(Params p)
     auto unit_row = [&](int unit, int e) { return m0 + wm0 + TA * (4 * quad + (unit % (4 / EU)) * EU + e) + unit / (4 / EU); };
     auto load_old = [&]() {
         if (direct) return;
-        const float* src = EPI == EPI_RMW ? p.C : p.aux;
+        const float* src = EPI == EPI_RMW ? p.C : p.aux;      // (EPI_SHRINK, null: zeros)
 #pragma unroll
         for (int i = 0; i < PO; ++i) {
             const int unit = kw * PER + i;
@@ -446,7 +446,7 @@ __global__ __launch_bounds__(NT, 2) void gemm_f32_kernel(Params p)
                 const int64_t row = unit_row(unit, e);
 #pragma unroll
                 for (int b = 0; b < TB; ++b) old[i][e][b] = 0.f;
-                if (unit < UNITS && row < p.M) {
+                if (unit < UNITS && row < p.M && (EPI != EPI_SHRINK || src)) {
                     const float* s = src + row * p.ldc + col;
                     if (col + TB <= p.N) {
                         const VecC v = *reinterpret_cast<const VecC*>(s);
@@ -627,7 +627,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(Params p)
         float sum = p.partial[i];
         for (int z = 1; z < p.split_k; ++z) sum += p.partial[z * total + i];
         const int64_t idx = i / p.N * p.ldc + i % p.N;
-        const float old = EPI == EPI_RMW ? p.C[idx] : (EPI == EPI_STORE ? 0.f : p.aux[idx]);
+        const float old = EPI == EPI_RMW ? p.C[idx] : (EPI == EPI_STORE || (EPI == EPI_SHRINK && !p.aux) ? 0.f : p.aux[idx]);
         p.C[idx] = combine<EPI>(old, sum, p.eta, invL, th);
     }
 }

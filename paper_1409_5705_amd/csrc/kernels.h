@@ -41,7 +41,7 @@ struct GemmF32Args {
     int64_t M, N, K;
     int epilogue;
     float eta;           // EPI_RMW
-    const float* aux;    // EPI_RESID / EPI_SHRINK, same leading dimension as C; may alias C
+    const float* aux;    // EPI_RESID / EPI_SHRINK, same leading dimension as C; may alias C; EPI_SHRINK: null counts as zeros
     const float* L_ptr;  // EPI_SHRINK: device scalar
     float lambda;        // EPI_SHRINK
     float* partial;      // scratch of gemm_f32_partial_bytes(M, N, K) for the k-split, or null (no split)

@@ -517,12 +517,13 @@ int sfb_compute_sf(sfb_ctx* ctx, int32_t model, const float* W, int64_t J, int64
     float* R = static_cast<float*>(V);
     const float* X = static_cast<const float*>(batch->X);
     SFB_RUN(KID_POWER_ITERATION, sfb::launch_power_iteration(W, J, D, batch->power_iters, scratch, A, B * J, Lp, st));
-    SFB_RUN(KID_FILL, sfb::launch_fill_u32(A, 0u, B * J, st));
+    // a = 0  =>  r = x: the first iteration takes X for the residual and zeros for the codes
+    if (batch->ista_iters == 0) {
+        SFB_RUN(KID_FILL, sfb::launch_fill_u32(A, 0u, B * J, st));
+        SFB_RUN(KID_COPY, hipMemcpyAsync(R, X, (size_t)(B * D * 4), hipMemcpyDeviceToDevice, st));
+    }
     for (int it = 0; it <= batch->ista_iters; ++it) {
-        if (it == 0) {
-            // a = 0  =>  r = x
-            SFB_RUN(KID_COPY, hipMemcpyAsync(R, X, (size_t)(B * D * 4), hipMemcpyDeviceToDevice, st));
-        } else {
+        if (it > 0) {
             sfb::GemmF32Args g = {};  // R = X - A W   (contraction over the basis index j)
             g.dev = &ctx->dev;
             g.A = A; g.lda = J; g.a_kstrided = false;
@@ -537,12 +538,12 @@ int sfb_compute_sf(sfb_ctx* ctx, int32_t model, const float* W, int64_t J, int64
         if (it == batch->ista_iters) break;
         sfb::GemmF32Args g = {};  // A = soft(A + (R W^T)/L, lambda/L)
         g.dev = &ctx->dev;
-        g.A = R; g.lda = D; g.a_kstrided = false;
+        g.A = it > 0 ? R : X; g.lda = D; g.a_kstrided = false;
         g.B = W; g.ldb = D; g.b_kstrided = false;
         g.C = A; g.ldc = J;
         g.M = B; g.N = J; g.K = D;
         g.epilogue = sfb::EPI_SHRINK;
-        g.aux = A;
+        g.aux = it > 0 ? A : nullptr;
         g.L_ptr = Lp;
         g.lambda = batch->lambda;
         g.partial = ksplit;
