@@ -173,15 +173,21 @@ def version() -> str:
     return lib().sfb_version().decode()
 
 
+_DTYPE_CODES = {torch.float32: SFB_F32, torch.bfloat16: SFB_BF16}
+
+
 def _dtype_code(t: torch.Tensor) -> int:
-    if t.dtype == torch.float32:
-        return SFB_F32
-    if t.dtype == torch.bfloat16:
-        return SFB_BF16
-    raise TypeError("unsupported dtype %s" % t.dtype)
+    code = _DTYPE_CODES.get(t.dtype)
+    if code is None:
+        raise TypeError("unsupported dtype %s" % t.dtype)
+    return code
 
 
 def _ptr(t, name, dtype=None, shape=None):
+    # a plain tensor that passes every check below: nothing converted, one comparison each (a small step is bound by these)
+    if (type(t) is torch.Tensor and t.is_cuda and t.is_contiguous() and (dtype is None or t.dtype is dtype)
+            and (shape is None or t.shape == shape)):
+        return t.data_ptr()
     if t is None:
         return None
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
@@ -354,9 +360,10 @@ class Context:
         N = U.shape[0]
         if U.dtype != V.dtype:
             raise TypeError("U and V must share a dtype")
-        self._grow_workspace(self.sfb_apply_workspace_bytes(J, D, N, _dtype_code(U)))
+        code = _dtype_code(U)
+        self._grow_workspace(self.sfb_apply_workspace_bytes(J, D, N, code))
         rc = lib().sfb_apply(self._h, _ptr(W, "W", dtype=torch.float32), J, D, _ptr(U, "U", shape=(N, J)),
-                             _ptr(V, "V", shape=(N, D)), N, _dtype_code(U), float(eta))
+                             _ptr(V, "V", shape=(N, D)), N, code, float(eta))
         self._check(rc, "sfb_apply")
 
     def sfb_apply_static(self, W, U, V, eta):
