@@ -596,10 +596,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1))) void
 }
 
 // The apply with few factor pairs, where the pass over W is all that counts: 128 x 128 tiles (four wavefronts of 32 x 128),
-// two workgroups per CU.  What bounds it is the stream of W (a copy of 4 GiB runs at 4.8 TB/s): 8192 x 4096 with 256 pairs
-// 69 -> 44 us, 325000 x 10000 on the planes with 100 pairs 3.62 -> 3.37 ms (5.8 TB/s).  A workgroup requests its first two k-slices and then its whole tile of W, so that the stream of
+// two workgroups per CU.  A workgroup requests its first two k-slices and then its whole tile of W, so that the stream of
 // W never waits for a k-loop or an epilogue: the other workgroup's loads are in flight meanwhile.  (The 256 x 256 kernel
-// above, one workgroup per CU, stands still on W between its k-loops.)
+// above, one workgroup per CU, stands still on W between its k-loops.)  What bounds it is that stream (a copy of 4 GiB
+// runs at 4.8 TB/s): 8192 x 4096 with 256 pairs 69 -> 44 us (6.1 TB/s, part of W in the caches), 325000 x 10000 on the
+// planes with 100 pairs 3.62 -> 3.37 ms (5.8 TB/s).
 constexpr int SM = 128, SN = 128;
 constexpr uint32_t SSTAGE = 0x8000u, SB_OFF = SM * 128;      // one k-slice: [A tile 16 KiB][B tile 16 KiB]
 
