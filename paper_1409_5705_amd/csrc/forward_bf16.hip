@@ -9,6 +9,7 @@
 // wavefronts share them; where W has no bf16 copy they are read as fp32 and rounded
 // on the way, which saves the pass that makes the copy.  The samples are small and
 // come from the L2: each wavefront loads its own fragments straight into registers.
+#include "forward_index.h"
 #include "kernels.h"
 
 #include <cmath>
@@ -195,7 +196,7 @@ __global__ __launch_bounds__(NT, 2) void fwd_stream_kernel(FwdParams p)
             int64_t j = n0 + row;
             if (j >= p.J) j = p.J - 1;
             if (FP32)
-                wsrc[i] = reinterpret_cast<uint64_t>(p.W) + (uint64_t)(j * p.D + 4 * part) * 4;
+                wsrc[i] = reinterpret_cast<uint64_t>(p.W) + (uint64_t)(j * p.D) * 4;
             else
                 wsrc[i] = reinterpret_cast<uint64_t>(p.W) + (uint64_t)((j / 256) * (p.P / 64) * 16384 + (j % 256) * 64 + part * 8) * 2;
             // class c of a wavefront's block sits in LDS row 16 (c % NTL) + c / NTL: a lane's NTL columns are neighbours
@@ -206,9 +207,9 @@ __global__ __launch_bounds__(NT, 2) void fwd_stream_kernel(FwdParams p)
         u32x4 wreg[DW][PIECES];
         // (No branch around a load: where paths with and without it meet, the compiler can only wait for everything.
         // Past the last slice the loads repeat it and W counts as zero, as do fp32 columns past D.)
-        auto live = [&](int s) { return s < nk && (!FP32 || at(s) * KS + 4 * part < p.D); };
+        auto live = [&](int s) { return s < nk && (!FP32 || (int64_t)at(s) * KS + 4 * part < p.D); };
         auto fetch = [&](int s, u32x4 (&dst)[PIECES]) {
-            const uint64_t off = FP32 ? (uint64_t)(at(s) * KS + 4 * part < p.D ? at(s) * KS : 0) * 4 : (uint64_t)at(s) * 32768;
+            const uint64_t off = FP32 ? (uint64_t)fwd_w_column((int64_t)at(s) * KS, part, p.D) * 4 : (uint64_t)at(s) * 32768;
 #pragma unroll
             for (int i = 0; i < PIECES; ++i) dst[i] = *reinterpret_cast<const __attribute__((address_space(1))) u32x4*>(wsrc[i] + off);
         };

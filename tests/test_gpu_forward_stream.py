@@ -29,6 +29,7 @@ def dev_bf16(a):
 
 @pytest.mark.parametrize("J,D,B", [
     (8, 8, 1), (72, 136, 17), (264, 72, 64),     # one slice, partial slices; up to 64 samples
+    (264, 56, 300), (4096, 32, 40), (40, 24, 5),   # rows narrower than a slice
     (1000, 2056, 65), (1504, 520, 128),          # up to 128 samples
     (1504, 3000, 200), (2040, 1032, 256),        # up to 256, k-split
     (520, 1000, 300), (1000, 4104, 520),         # several tiles of samples, the last one ragged
