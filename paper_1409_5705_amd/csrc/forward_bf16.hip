@@ -297,6 +297,7 @@ hipError_t launch_fwd(FwdParams p, int split, DeviceInfo& dev, int slot, hipStre
 MlrForwardPlan mlr_forward_plan(int64_t B, int64_t J, int64_t D, bool have_copy, bool may_split)
 {
     const int64_t nk = (D + KS - 1) / KS;
+    // The CU count of an MI355X, not the context's: the workspace is sized from the plan, and that query has no device.
     const double cus = 256.0, w = (double)J * (double)D;
     MlrForwardPlan best = {};
     best.split = 1;
@@ -314,7 +315,8 @@ MlrForwardPlan mlr_forward_plan(int64_t B, int64_t J, int64_t D, bool have_copy,
         const int64_t tm = (B + 64 * sh.mt - 1) / (64 * sh.mt), tn = (J + 32 * sh.ntl - 1) / (32 * sh.ntl);
         for (int s = 1; s <= (may_split ? 16 : 1); ++s) {
             const int64_t per = (nk + s - 1) / s;
-            if (s > 1 && (J > MLR_SOFTMAX_ROW_MAX || per < 4 || (nk + per - 1) / per != s)) continue;
+            if (s > 1 && (J > MLR_SOFTMAX_ROW_MAX || per < 4)) break;      // (so for every larger s)
+            if (s > 1 && (nk + per - 1) / per != s) continue;
             const double rounds = std::ceil((double)(tm * tn * s) / cus);
             double t = 3.0 + rounds * ((double)per * sh.us + 4.5) + (s > 1 ? (double)s * (double)B * (double)J * 8.0 / 4e6 : 0.0);
             const double stream_us = w * (have_copy ? 2.0 : 4.0) * (double)tm / 4.6e6 + 5.0;

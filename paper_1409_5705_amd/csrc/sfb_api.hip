@@ -143,30 +143,48 @@ int64_t sc_partial_bytes(int64_t B, int64_t J, int64_t D)
     return round_up(a > b ? a : b);
 }
 
-// Front of the workspace on the bf16 multiclass-logistic path: the tile-blocked logits (as many planes of partial sums
-// as the forward may leave, with or without a bf16 copy of W; one where it may not split k), then the words the
-// workgroups of the one-read softmax exchange.
-int64_t bf16_logits_bytes(int64_t B, int64_t J, int64_t D, bool may_split = true)
+// Front of the workspace on the bf16 multiclass-logistic path: the tile-blocked logits (one array, or as many as the
+// forward leaves partial sums), then the words the workgroups of the one-read softmax exchange.
+int64_t bf16_logits_bytes(int64_t B, int64_t J, int planes)
 {
-    int planes = 1;
-    for (bool copy : {false, true}) {
-        const int s = sfb::mlr_forward_plan(B, J, D, copy, may_split).split;
-        if (s > planes) planes = s;
-    }
     return round_up(planes * sfb::mlr_logits_floats(B, J) * 4) + round_up(sfb::mlr_softmax_scratch_bytes(B, J));
 }
-void* bf16_softmax_scratch(sfb_ctx* ctx, int64_t B, int64_t J, int64_t D, bool may_split)
+// The forward of a call with ([1]) and without ([0]) a bf16 copy of W; the size that is asked for has room for either.
+struct Bf16Plans {
+    sfb::MlrForwardPlan plan[2];
+    int planes;
+};
+Bf16Plans bf16_plans(int64_t B, int64_t J, int64_t D)
 {
-    const int64_t bytes = round_up(sfb::mlr_softmax_scratch_bytes(B, J));
-    return bytes ? ctx->ws + bf16_logits_bytes(B, J, D, may_split) - bytes : nullptr;
+    Bf16Plans p;
+    p.plan[0] = sfb::mlr_forward_plan(B, J, D, false, true);
+    p.plan[1] = sfb::mlr_forward_plan(B, J, D, true, true);
+    p.planes = p.plan[0].split > p.plan[1].split ? p.plan[0].split : p.plan[1].split;
+    return p;
 }
-// A workspace without room for several planes (the size that was asked for before the forward split k) still does: one plane
-// and no split.  `need` becomes what that takes.
-bool bf16_may_split(const sfb_ctx* ctx, int64_t B, int64_t J, int64_t D, int64_t* need)
+
+// What one call does with the workspace it has: the forward's plan, where its logits end.
+struct Bf16Call {
+    sfb::MlrForwardPlan plan;
+    int64_t logits_bytes;
+    void* softmax_scratch;
+};
+// operand_bytes: the region between the logits and the copy of W.  A workspace without room for several arrays of
+// partial sums (the size that was asked for before the forward split k) still does: no split then.
+int bf16_call(const sfb_ctx* ctx, int64_t B, int64_t J, int64_t D, int64_t operand_bytes, bool has_copy, Bf16Call* call)
 {
-    if (ctx->ws_bytes >= *need) return true;
-    *need -= bf16_logits_bytes(B, J, D) - bf16_logits_bytes(B, J, D, false);
-    return false;
+    Bf16Plans plans = bf16_plans(B, J, D);
+    const int64_t rest = operand_bytes + (has_copy ? 0 : sfb_shadow_bytes(J, D));
+    call->plan = plans.plan[has_copy ? 1 : 0];
+    if (plans.planes > 1 && ctx->ws_bytes < bf16_logits_bytes(B, J, plans.planes) + rest) {
+        plans.planes = 1;
+        call->plan = sfb::mlr_forward_plan(B, J, D, has_copy, false);
+    }
+    call->logits_bytes = bf16_logits_bytes(B, J, plans.planes);
+    if (!ctx->ws || ctx->ws_bytes < call->logits_bytes + rest) return SFB_ENOWS;
+    const int64_t words = round_up(sfb::mlr_softmax_scratch_bytes(B, J));
+    call->softmax_scratch = words ? ctx->ws + call->logits_bytes - words : nullptr;
+    return SFB_OK;
 }
 
 // True if W is currently kept as two planes by this context: its fp32 array is stale.
@@ -316,7 +334,7 @@ int64_t sfb_workspace_bytes(int32_t model, int64_t J, int64_t D, const sfb_batch
     switch (model) {
         case SFB_MLR:
             if (batch->in_dtype == SFB_BF16)   // logits (tile-blocked), aligned copy of X, bf16 copy of W
-                return bf16_logits_bytes(B, J, D) + round_up(sfb::bf16_operand_bytes(B, D)) + sfb_shadow_bytes(J, D);
+                return bf16_logits_bytes(B, J, bf16_plans(B, J, D).planes) + round_up(sfb::bf16_operand_bytes(B, D)) + sfb_shadow_bytes(J, D);
             return round_up(B * J * 4) + round_up(sfb::gemm_f32_partial_bytes(B, J, D));   // logits, k-split scratch
         case SFB_DML:
             return round_up(B * J * 4) + round_up(sfb::gemm_f32_partial_bytes(B, J, D));   // projections Q[B][K], k-split scratch
@@ -433,13 +451,14 @@ int sfb_compute_sf(sfb_ctx* ctx, int32_t model, const float* W, int64_t J, int64
     if (!batch->X || !U || !aligned16(batch->X) || !aligned16(U) || (V && !aligned16(V))) return SFB_EINVAL;
     const bool has_shadow = ctx->shadow_buf && ctx->shadow_W == W && ctx->shadow_J == J && ctx->shadow_D == D;
     if (is_split(ctx, W) && !has_shadow) return SFB_EINVAL;   // attached as planes of another shape: the fp32 array is stale
-    int64_t need = sfb_workspace_bytes(model, J, D, batch);
-    bool may_split = true;
-    if (model == SFB_MLR && batch->in_dtype == SFB_BF16) {
-        if (has_shadow) need -= sfb_shadow_bytes(J, D);
-        may_split = bf16_may_split(ctx, B, J, D, &need);
+    Bf16Call call = {};
+    if (batch->in_dtype == SFB_BF16) {      // (check_batch: MLR)
+        rc = bf16_call(ctx, B, J, D, round_up(sfb::bf16_operand_bytes(B, D)), has_shadow, &call);
+        if (rc != SFB_OK) return rc;
+    } else {
+        const int64_t need = sfb_workspace_bytes(model, J, D, batch);
+        if (need > 0 && (!ctx->ws || ctx->ws_bytes < need)) return SFB_ENOWS;
     }
-    if (need > 0 && (!ctx->ws || ctx->ws_bytes < need)) return SFB_ENOWS;
     SFB_TRY(hipSetDevice(ctx->device));
     hipStream_t st = ctx->stream;
 
@@ -468,20 +487,19 @@ int sfb_compute_sf(sfb_ctx* ctx, int32_t model, const float* W, int64_t J, int64
             if (sfb::gemm_f32_partial_bytes(B, J, D) > 0) g.partial = reinterpret_cast<float*>(ctx->ws + round_up(B * J * 4));
             SFB_RUN(KID_GEMM_F32_STORE, sfb::launch_gemm_f32(g, st));
         } else {
-            uint16_t* Xa = reinterpret_cast<uint16_t*>(ctx->ws + bf16_logits_bytes(B, J, D, may_split));
+            uint16_t* Xa = reinterpret_cast<uint16_t*>(ctx->ws + call.logits_bytes);
             const uint16_t* Wb = has_shadow ? ctx->shadow_buf : nullptr;
-            const sfb::MlrForwardPlan plan = sfb::mlr_forward_plan(B, J, D, has_shadow, may_split);
-            if (!has_shadow && plan.mt == 0) {   // no working copy attached: make one for this call
+            if (!has_shadow && call.plan.mt == 0) {   // no working copy attached: make one for this call
                 uint16_t* tmp = Xa + round_up(sfb::bf16_operand_bytes(B, D)) / 2;
                 SFB_RUN(KID_SHADOW, sfb::launch_shadow_from_w(W, tmp, J, D, st));
                 Wb = tmp;
             }
-            SFB_RUN(KID_FORWARD_BF16, sfb::launch_mlr_forward_bf16(plan, static_cast<const uint16_t*>(batch->X), W, Wb, Z, Xa, B, J, D,
+            SFB_RUN(KID_FORWARD_BF16, sfb::launch_mlr_forward_bf16(call.plan, static_cast<const uint16_t*>(batch->X), W, Wb, Z, Xa, B, J, D,
                                                                    ctx->dev, st));
             sm.out_bf16 = sm.blocked = true;
-            sm.planes = plan.split;
+            sm.planes = call.plan.split;
             sm.plane_floats = sfb::mlr_logits_floats(B, J);
-            sm.scratch = bf16_softmax_scratch(ctx, B, J, D, may_split);
+            sm.scratch = call.softmax_scratch;
         }
         SFB_RUN(KID_SOFTMAX, sfb::launch_mlr_softmax(sm, st));
         return SFB_OK;
@@ -737,11 +755,16 @@ int sfb_mlr_sf_csr(sfb_ctx* ctx, const float* W, int64_t J, int64_t D, const sfb
     if (!y || !U || !aligned16(U)) return SFB_EINVAL;
     const bool has_shadow = ctx->shadow_buf && ctx->shadow_W == W && ctx->shadow_J == J && ctx->shadow_D == D;
     if (is_split(ctx, W) && (!bf16 || !has_shadow)) return SFB_EINVAL;
-    int64_t need = sfb_mlr_sf_csr_workspace_bytes(J, D, B, X->dtype);
-    if (need < 0) return (int)need;
-    if (bf16 && has_shadow) need -= sfb_shadow_bytes(J, D);
-    const bool may_split = bf16 && bf16_may_split(ctx, B, J, D, &need);
-    if (!ctx->ws || ctx->ws_bytes < need) return SFB_ENOWS;
+    const int64_t operand = csr_operand_bytes(J, D, B, bf16);
+    Bf16Call call = {};
+    if (bf16) {
+        rc = bf16_call(ctx, B, J, D, operand, has_shadow, &call);
+        if (rc != SFB_OK) return rc;
+    } else {
+        const int64_t need = sfb_mlr_sf_csr_workspace_bytes(J, D, B, X->dtype);
+        if (need < 0) return (int)need;
+        if (!ctx->ws || ctx->ws_bytes < need) return SFB_ENOWS;
+    }
     SFB_TRY(hipSetDevice(ctx->device));
     hipStream_t st = ctx->stream;
     float* Z = reinterpret_cast<float*>(ctx->ws);
@@ -775,11 +798,10 @@ int sfb_mlr_sf_csr(sfb_ctx* ctx, const float* W, int64_t J, int64_t D, const sfb
         return SFB_OK;
     }
     const int64_t pitch = sfb::bf16_pitch(D);
-    char* region = ctx->ws + bf16_logits_bytes(B, J, D, may_split);
+    char* region = ctx->ws + call.logits_bytes;
     const uint16_t* Wb = has_shadow ? ctx->shadow_buf : nullptr;
-    const sfb::MlrForwardPlan plan = sfb::mlr_forward_plan(B, J, D, has_shadow, may_split);
-    if (!has_shadow && (gather || plan.mt == 0)) {
-        uint16_t* tmp = reinterpret_cast<uint16_t*>(region + csr_operand_bytes(J, D, B, true));
+    if (!has_shadow && (gather || call.plan.mt == 0)) {
+        uint16_t* tmp = reinterpret_cast<uint16_t*>(region + operand);
         SFB_RUN(KID_SHADOW, sfb::launch_shadow_from_w(W, tmp, J, D, st));
         Wb = tmp;
     }
@@ -790,12 +812,12 @@ int sfb_mlr_sf_csr(sfb_ctx* ctx, const float* W, int64_t J, int64_t D, const sfb
         uint16_t* Xa = reinterpret_cast<uint16_t*>(region);
         SFB_RUN(KID_FILL, sfb::launch_fill_u32(Xa, 0u, sfb::bf16_operand_bytes(B, D) / 4, st));
         SFB_RUN(KID_CSR, sfb::launch_csr_scatter(X->indptr, X->indices, X->values, true, nullptr, Xa, B, D, X->nnz, -pitch, 1, st));
-        SFB_RUN(KID_FORWARD_BF16, sfb::launch_mlr_forward_bf16(plan, nullptr, W, Wb, Z, Xa, B, J, D, ctx->dev, st));
-        sm.planes = plan.split;
+        SFB_RUN(KID_FORWARD_BF16, sfb::launch_mlr_forward_bf16(call.plan, nullptr, W, Wb, Z, Xa, B, J, D, ctx->dev, st));
+        sm.planes = call.plan.split;
     }
     sm.out_bf16 = sm.blocked = true;
     sm.plane_floats = sfb::mlr_logits_floats(B, J);
-    sm.scratch = bf16_softmax_scratch(ctx, B, J, D, may_split);
+    sm.scratch = call.softmax_scratch;
     SFB_RUN(KID_SOFTMAX, sfb::launch_mlr_softmax(sm, st));
     return SFB_OK;
 }

@@ -2,6 +2,8 @@
 against the CPU oracle's loops over the stored non-zeros, and bit-equality with
 the dense entry points on the same data.
 """
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -258,3 +260,50 @@ def test_gather_route_edge_cases(ctx, sfb, oracle, bf16):
         assert rel_err(host(U2), want) <= (TOL_BF16 if bf16 else TOL_F32)
     finally:
         ctx.sfb_set_csr_route(0)
+
+
+@pytest.mark.parametrize("layout", ["plain", "planes"])
+@pytest.mark.parametrize("route", [1, 2])
+def test_mlr_sf_csr_workspace_sizes(sfb, oracle, layout, route):
+    """A shape whose bf16 forward may split k: any workspace of at least the queried size gives the same bits, one with
+    room for one array of logits is accepted as well (no split), a smaller one is refused."""
+    J, D, B = 1504, 3000, 200
+    print("mlr_sf_csr workspace", layout, "route", route, flush=True)
+    ru = lambda x, a=256: (x + a - 1) // a * a
+    L = sfb.lib()
+    shadow, logits = L.sfb_shadow_bytes(J, D), ru(B, 256) * ru(J, 256) * 4
+    full = L.sfb_mlr_sf_csr_workspace_bytes(J, D, B, 1)
+    b = sfb.sfb_batch()
+    b.B, b.in_dtype, b.sf_dtype = B, 1, 1
+    dense = L.sfb_workspace_bytes(sfb.SFB_MLR, J, D, ctypes.byref(b))
+    planes = (dense - shadow - ru(ru(B, 256) * ru(D, 64) * 2)) // logits
+    assert planes > 1
+    if layout == "planes":
+        full -= shadow
+    one = full - (planes - 1) * logits
+    W0 = S.normal_matrix(J, D, 0.05, seed=37)
+    X, y = S.mlr_batch(J, D, B, seed=37, zero_frac=0.95, bf16=True)
+    (indptr, indices, values), (ip, ix, vals) = csr_dev(X, True)
+    Uo = oracle.mlr_sf_csr(W0, indptr, indices, values, y)
+    ctx, W, yd = sfb.Context(0), dev(W0), dev(y)
+    if layout == "planes":
+        ctx.sfb_split_attach(W)
+    ctx.sfb_set_csr_route(route)
+    ctx._grow_workspace = lambda need: None
+    ws = torch.empty(full + (1 << 20), dtype=torch.uint8, device="cuda:0")
+    assert ws.data_ptr() % 256 == 0
+
+    def call(size):
+        U = torch.empty((B, J), dtype=torch.bfloat16, device="cuda:0")
+        assert L.sfb_set_workspace(ctx._h, ws.data_ptr(), size) == 0
+        ctx.sfb_mlr_sf_csr(W, ip, ix, vals, yd, U)
+        return host(U)
+
+    u = call(full)
+    mlr_u_check(u, Uo, y, TOL_BF16)
+    assert np.array_equal(u, call(full + (1 << 20)))
+    mlr_u_check(call(one), Uo, y, TOL_BF16)
+    with pytest.raises(sfb.SfbError) as e:
+        call(one - 256)
+    assert e.value.code == sfb.SFB_ENOWS
+    ctx.close()
