@@ -643,6 +643,7 @@ constexpr int NTILES = 6;
 
 struct Plan {
     int cfg, split;
+    double us;       // estimated duration
 };
 
 // Estimated duration (us) of a contraction as `rounds` of one workgroup per CU, each walking its k-slices.  Per tile
@@ -668,17 +669,13 @@ Plan plan_gemm(int64_t M, int64_t N, int64_t K, int cus, int max_split, bool dir
     static const double us[2][NTILES][2] = {{{2.10, 6.5}, {1.22, 5.0}, {1.25, 4.7}, {0.69, 3.5}, {0.80, 3.0}, {0.40, 1.2}},
                                             {{1.82, 6.5}, {1.01, 5.0}, {1.03, 4.7}, {0.55, 3.5}, {0.55, 3.0}, {0.38, 1.2}}};
     const double(*u)[2] = us[direct ? 1 : 0];
-    Plan best = {0, 1};
-    double best_t = 1e30;
+    Plan best = {0, 1, 1e30};
     for (int s = 1; s <= max_split; ++s) {
         const double t[NTILES] = {plan_time<T0>(M, N, K, cus, s, u[0][0], u[0][1], 0.05), plan_time<T1>(M, N, K, cus, s, u[1][0], u[1][1], 0.05),
                                   plan_time<T2>(M, N, K, cus, s, u[2][0], u[2][1], 0.1), plan_time<T3>(M, N, K, cus, s, u[3][0], u[3][1], 0.2),
                                   plan_time<T4>(M, N, K, cus, s, u[4][0], u[4][1], 0.0), plan_time<T5>(M, N, K, cus, s, u[5][0], u[5][1], 1.0)};
         for (int c = 0; c < NTILES; ++c)
-            if (t[c] < best_t) {
-                best_t = t[c];
-                best = Plan{c, s};
-            }
+            if (t[c] < best.us) best = Plan{c, s, t[c]};
     }
     return best;
 }
@@ -732,14 +729,19 @@ hipError_t launch_vec(Params p, DeviceInfo& dev, int combo, int max_split, hipSt
     }
 }
 
-template <bool A_KS, bool B_KS, int EPI>
-hipError_t launch_any(const Params& p, DeviceInfo& dev, int combo, int max_split, hipStream_t stream)
+// Direct loads: every operand row 16-byte aligned, 32-bit byte offsets between the rows of a load.
+bool direct_loads(const GemmF32Args& a)
 {
-    // 16-byte loads: every operand row 16-byte aligned, 32-bit byte offsets between the rows of a load
     auto rows16 = [](const float* P, int64_t ld, bool ks, int64_t rows) {
         return ld % 4 == 0 && reinterpret_cast<uintptr_t>(P) % 16 == 0 && (!ks || rows % 4 == 0) && ld < (1LL << 25);
     };
-    if (rows16(p.A, p.lda, A_KS, p.M) && rows16(p.B, p.ldb, B_KS, p.N)) return launch_vec<A_KS, B_KS, EPI, true>(p, dev, combo, max_split, stream);
+    return rows16(a.A, a.lda, a.a_kstrided, a.M) && rows16(a.B, a.ldb, a.b_kstrided, a.N);
+}
+
+template <bool A_KS, bool B_KS, int EPI>
+hipError_t launch_any(const Params& p, DeviceInfo& dev, int combo, int max_split, bool direct, hipStream_t stream)
+{
+    if (direct) return launch_vec<A_KS, B_KS, EPI, true>(p, dev, combo, max_split, stream);
     return launch_vec<A_KS, B_KS, EPI, false>(p, dev, combo, max_split, stream);
 }
 
@@ -763,6 +765,12 @@ int64_t gemm_f32_partial_bytes(int64_t M, int64_t N, int64_t K)
     return s > 1 ? (int64_t)s * M * N * 4 : 0;
 }
 
+double gemm_f32_estimate_us(const GemmF32Args& a)
+{
+    const int max_split = a.partial ? gemm_f32_max_split(a.M, a.N, a.K) : 1;
+    return plan_gemm(a.M, a.N, a.K, a.dev->cus > 0 ? a.dev->cus : 256, max_split, direct_loads(a)).us;
+}
+
 hipError_t launch_gemm_f32(const GemmF32Args& a, hipStream_t stream)
 {
     if (a.M <= 0 || a.N <= 0) return hipSuccess;
@@ -774,11 +782,11 @@ hipError_t launch_gemm_f32(const GemmF32Args& a, hipStream_t stream)
     p.eta = a.eta; p.lambda = a.lambda;
     p.partial = a.partial;
     const int max_split = a.partial ? gemm_f32_max_split(a.M, a.N, a.K) : 1;
-    const bool aks = a.a_kstrided, bks = a.b_kstrided;
-    if (!aks && !bks && a.epilogue == EPI_STORE) return launch_any<false, false, EPI_STORE>(p, *a.dev, 0, max_split, stream);
-    if (!aks && !bks && a.epilogue == EPI_SHRINK) return launch_any<false, false, EPI_SHRINK>(p, *a.dev, 1, max_split, stream);
-    if (!aks && bks && a.epilogue == EPI_RESID) return launch_any<false, true, EPI_RESID>(p, *a.dev, 2, max_split, stream);
-    if (aks && bks && a.epilogue == EPI_RMW) return launch_any<true, true, EPI_RMW>(p, *a.dev, 3, max_split, stream);
+    const bool aks = a.a_kstrided, bks = a.b_kstrided, direct = direct_loads(a);
+    if (!aks && !bks && a.epilogue == EPI_STORE) return launch_any<false, false, EPI_STORE>(p, *a.dev, 0, max_split, direct, stream);
+    if (!aks && !bks && a.epilogue == EPI_SHRINK) return launch_any<false, false, EPI_SHRINK>(p, *a.dev, 1, max_split, direct, stream);
+    if (!aks && bks && a.epilogue == EPI_RESID) return launch_any<false, true, EPI_RESID>(p, *a.dev, 2, max_split, direct, stream);
+    if (aks && bks && a.epilogue == EPI_RMW) return launch_any<true, true, EPI_RMW>(p, *a.dev, 3, max_split, direct, stream);
     return hipErrorInvalidValue;
 }
 

@@ -48,6 +48,7 @@ struct GemmF32Args {
     DeviceInfo* dev;     // the context's device facts
 };
 hipError_t launch_gemm_f32(const GemmF32Args& a, hipStream_t stream);
+double gemm_f32_estimate_us(const GemmF32Args& a);      // of that launch; a.dev is needed
 // Scratch a contraction of this shape can use to split its k range over several
 // workgroups (0: it would not be split).  16-byte aligned.
 int64_t gemm_f32_partial_bytes(int64_t M, int64_t N, int64_t K);
@@ -121,6 +122,8 @@ int64_t csr_gather_workspace_bytes(int64_t B, int64_t D, bool bf16);
 hipError_t launch_csr_forward_gather(const int64_t* indptr, const int32_t* indices, const void* values, bool bf16,
                                      const void* W, float* Z, int64_t B, int64_t J, int64_t D, int64_t nnz,
                                      void* workspace, hipStream_t stream);
+// Estimated duration (us) of that call for fp32 values, every sample with nnz / B entries.
+double csr_gather_f32_estimate_us(int64_t B, int64_t J, int64_t D, int64_t nnz, int cus);
 // Adds the number of format violations to *bad (device, zeroed by the caller).
 hipError_t launch_csr_check(const int64_t* indptr, const int32_t* indices, int64_t rows, int64_t cols, int64_t nnz,
                             unsigned int* bad, hipStream_t stream);

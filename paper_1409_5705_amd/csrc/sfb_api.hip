@@ -717,22 +717,33 @@ int64_t sfb_mlr_sf_csr_workspace_bytes(int64_t J, int64_t D, int64_t B, int32_t 
     return base + csr_operand_bytes(J, D, B, false);     // fp32: logits, k-split scratch, operand region
 }
 
-// Whether the logits of these CSR samples are computed over the stored entries only.  Measured on MI355X
-// (J = 325000, D = 10000, bf16): the gather kernel takes, per group of up to 1024 samples, one pass over W
-// (1.6 ms: 5e-13 s per element) plus 8.4e-11 s per class and stored entry of an average sample (a lane walks one
-// sample, so the time follows the entries per sample, not their total); the dense MFMA product runs at about
-// 1.45 PFLOP/s on ceil(B / 256) * 256 rows.  That puts the crossover near 1 % of non-zeros at B = 1024 and leaves
-// batches of 256 and fewer to the dense product at any density.  fp32: both routes are slower (twice the bytes of W,
-// twice the LDS reads per entry; the fp32 MFMA product runs at about 60 TFLOP/s), the gather route wins up to some 10 %.
-static bool csr_use_gather(const sfb_ctx* ctx, int64_t B, int64_t J, int64_t D, int64_t nnz, bool bf16)
+// Whether the logits of these CSR samples are computed over the stored entries only.
+// fp32 (`dense`: the contraction of the other route): the faster by the estimates of both.  Measured, us of the whole
+// call, stored entries / dense product, at 0.2, 1, 3 and 10 % of non-zeros:
+//   1000 x 2000,    256 samples   49 / 25,    78 / 26,    129 / 26,    304 / 27      1024   69 / 55,    112 / 54,    208 / 56,    514 / 58
+//   4000 x 5000,    256           88 / 98,    162 / 98,   327 / 101,   859 / 104     1024   131 / 327,  245 / 325,   486 / 323,   1294 / 328
+//   100000 x 10000, 100           926 / 2107, 1348 / 2100, 2280 / 2107, 5236 / 2108  1024   1605 / 14933, 2735 / 14956, 5195 / 14970, 13012 / 14995
+// bf16: the gather kernel takes, per group of up to 1024 samples, one pass over W (5e-13 s per element) plus 8.4e-11 s per
+// class and stored entry of an average sample (a lane walks one sample, so the time follows the entries per sample, not
+// their total); the dense product runs at up to 1.45 PFLOP/s on ceil(B / 256) * 256 rows.  That puts the crossover near
+// 1 % of non-zeros at 1024 samples and leaves batches of 256 and fewer to the dense product at any density.  Measured
+// with a copy of W, the same figures at 0.2, 0.5, 1 and 2 %:
+//   325000 x 10000, 512           1714 / 2274, 2101 / 2287, 2833 / 2299, 4140 / 2320
+//                   1024          2393 / 4330, 3096 / 4375, 4214 / 4454, 6223 / 4499
+// It holds for large W.  It does not see that the streaming dense forward finishes a small W (tens of us a call) first at
+// 0.2 % already (1000 x 2000, 1024 samples, 1 %: 76 / 28), nor that without a copy of W the gather route always has to
+// make one, the dense one not always (8192 x 4096, 1024 samples, 1 %: 176 / 140).
+static bool csr_use_gather(const sfb_ctx* ctx, int64_t B, int64_t J, int64_t D, int64_t nnz, const sfb::GemmF32Args* dense)
 {
     if (!sfb::csr_gather_supported(B, J, D) || ctx->csr_route == 1) return false;
     if (ctx->csr_route == 2) return true;
+    if (dense) {
+        const double stream = (double)J * (double)D * 4.0 / 4.6e6, product = sfb::gemm_f32_estimate_us(*dense);
+        return sfb::csr_gather_f32_estimate_us(B, J, D, nnz, ctx->dev.cus) < 9.0 + 1.05 * (product > stream ? product : stream);
+    }
     const double groups = (double)((B + 1023) / 1024), per_sample = (double)nnz / (double)B;
-    const double gather = groups * ((bf16 ? 5e-13 : 1e-12) * (double)J * (double)D + (bf16 ? 8.4e-11 : 1.7e-10) * (double)J * per_sample);
     const double rows = (double)((B + 255) / 256 * 256);
-    const double dense = 2.0 * rows * (double)J * (double)D / (bf16 ? 1.45e15 : 6e13);
-    return gather < dense;
+    return groups * (5e-13 * (double)J * (double)D + 8.4e-11 * (double)J * per_sample) < 2.0 * rows * (double)J * (double)D / 1.45e15;
 }
 
 int sfb_set_csr_route(sfb_ctx* ctx, int route)
@@ -768,7 +779,6 @@ int sfb_mlr_sf_csr(sfb_ctx* ctx, const float* W, int64_t J, int64_t D, const sfb
     SFB_TRY(hipSetDevice(ctx->device));
     hipStream_t st = ctx->stream;
     float* Z = reinterpret_cast<float*>(ctx->ws);
-    const bool gather = csr_use_gather(ctx, B, J, D, X->nnz, bf16);
     sfb::MlrSoftmaxArgs sm = {};
     sm.Z = Z; sm.y = y; sm.U = U;
     sm.B = B; sm.J = J;
@@ -777,21 +787,21 @@ int sfb_mlr_sf_csr(sfb_ctx* ctx, const float* W, int64_t J, int64_t D, const sfb
     if (!bf16) {
         const int64_t part = round_up(sfb::gemm_f32_partial_bytes(B, J, D));
         char* region = ctx->ws + round_up(B * J * 4) + part;
-        if (gather) {
+        float* Xd = reinterpret_cast<float*>(region);      // the dense route's operand
+        sfb::GemmF32Args g = {};
+        g.dev = &ctx->dev;
+        g.A = Xd; g.lda = D; g.a_kstrided = false;
+        g.B = W; g.ldb = D; g.b_kstrided = false;
+        g.C = Z; g.ldc = J;
+        g.M = B; g.N = J; g.K = D;
+        g.epilogue = sfb::EPI_STORE;
+        if (part > 0) g.partial = reinterpret_cast<float*>(ctx->ws + round_up(B * J * 4));
+        if (csr_use_gather(ctx, B, J, D, X->nnz, &g)) {
             SFB_RUN(KID_CSR_GATHER, sfb::launch_csr_forward_gather(X->indptr, X->indices, X->values, false, W, Z, B, J, D,
                                                                    X->nnz, region, st));
         } else {
-            float* Xd = reinterpret_cast<float*>(region);
             SFB_RUN(KID_FILL, sfb::launch_fill_u32(Xd, 0u, B * D, st));
             SFB_RUN(KID_CSR, sfb::launch_csr_scatter(X->indptr, X->indices, X->values, false, nullptr, Xd, B, D, X->nnz, D, 1, st));
-            sfb::GemmF32Args g = {};
-            g.dev = &ctx->dev;
-            g.A = Xd; g.lda = D; g.a_kstrided = false;
-            g.B = W; g.ldb = D; g.b_kstrided = false;
-            g.C = Z; g.ldc = J;
-            g.M = B; g.N = J; g.K = D;
-            g.epilogue = sfb::EPI_STORE;
-            if (part > 0) g.partial = reinterpret_cast<float*>(ctx->ws + round_up(B * J * 4));
             SFB_RUN(KID_GEMM_F32_STORE, sfb::launch_gemm_f32(g, st));
         }
         SFB_RUN(KID_SOFTMAX, sfb::launch_mlr_softmax(sm, st));
@@ -799,6 +809,7 @@ int sfb_mlr_sf_csr(sfb_ctx* ctx, const float* W, int64_t J, int64_t D, const sfb
     }
     const int64_t pitch = sfb::bf16_pitch(D);
     char* region = ctx->ws + call.logits_bytes;
+    const bool gather = csr_use_gather(ctx, B, J, D, X->nnz, nullptr);
     const uint16_t* Wb = has_shadow ? ctx->shadow_buf : nullptr;
     if (!has_shadow && (gather || call.plan.mt == 0)) {
         uint16_t* tmp = reinterpret_cast<uint16_t*>(region + operand);

@@ -117,6 +117,26 @@ def test_mlr_sf_csr_picks_its_route(ctx, sfb):
         assert ("csr_forward_gather" in ran) == want, (zero_frac, ran)
 
 
+@pytest.mark.parametrize("J,D,B,nonzero,want", [
+    (1000, 2000, 256, 0.01, False), (1000, 2000, 1024, 0.1, False),     # (us, stored entries / dense) 78 / 26, 514 / 58
+    (4000, 5000, 256, 0.03, False), (4000, 5000, 1024, 0.1, False),     # 327 / 101, 1294 / 328
+    (4000, 5000, 1024, 0.002, True), (4000, 5000, 2048, 0.01, True),    # 131 / 327, 251 / 628
+])
+def test_mlr_sf_csr_fp32_picks_the_faster_route(ctx, sfb, J, D, B, nonzero, want):
+    """fp32, at shapes where one route takes at least 2.4 times as long as the other."""
+    print("fp32 route", J, D, B, nonzero, flush=True)
+    W = dev(S.normal_matrix(J, D, 0.02, seed=9))
+    U = torch.empty((B, J), dtype=torch.float32, device="cuda:0")
+    X, y = S.mlr_batch(J, D, B, seed=9, zero_frac=1.0 - nonzero)
+    _, (ip, ix, vals) = csr_dev(X, False)
+    ctx.sfb_profile_enable(True)
+    ctx.sfb_profile_collect()
+    ctx.sfb_mlr_sf_csr(W, ip, ix, vals, dev(y), U)
+    ran = ctx.sfb_profile_collect()
+    ctx.sfb_profile_enable(False)
+    assert ("csr_forward_gather" in ran) == want, ran
+
+
 @pytest.mark.parametrize("N,J,D,bf16,zero_frac,signed", [
     (32, 64, 128, False, 0.9, False),
     (2048, 1000, 2048, False, 0.9, False),
