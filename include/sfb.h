@@ -48,7 +48,7 @@ typedef enum { SFB_PROX_PROJECT = 0, SFB_PROX_NORMALIZE = 1 } sfb_prox_mode;
 typedef enum {
     SFB_OK = 0,
     SFB_EINVAL = -1, /* null pointer, bad shape, bad enum, misaligned pointer, unsupported dtype mix */
-    SFB_ENOWS = -2,  /* workspace missing or smaller than sfb_workspace_bytes() */
+    SFB_ENOWS = -2,  /* workspace missing or too small for the call (its query gives a size that always does) */
     SFB_EHIP = -3,   /* a HIP call failed; sfb_last_hip_error() has the code */
     SFB_ETOOBIG = -4 /* sfb_apply_static: the scratch this shape needs exceeds SFB_STATIC_SCRATCH_BYTES */
 } sfb_status;
@@ -73,7 +73,12 @@ int sfb_create(sfb_ctx** out, int device_id, void* hip_stream);
 int sfb_destroy(sfb_ctx* ctx);
 
 /* Bytes of device scratch sfb_compute_sf needs for this model/shape/batch
- * (0 is possible; negative sfb_status on bad arguments). */
+ * (0 is possible; negative sfb_status on bad arguments).  With a workspace of
+ * this size or any larger one a call gives the same bits.  The bf16
+ * multiclass-logistic calls (this one and sfb_mlr_sf_csr) may add up the logits
+ * from several partial sums, whose arrays the size includes; they also take a
+ * workspace with room for a single array and then sum in one piece, so the
+ * factors agree with the others to rounding only. */
 int64_t sfb_workspace_bytes(int32_t model, int64_t J, int64_t D, const sfb_batch* batch);
 /* Bytes of device scratch sfb_apply needs (0 for fp32 factors; bf16 factors
  * are transposed into it).  sfb_prox_rows needs none.  One workspace of the
@@ -91,12 +96,15 @@ int64_t sfb_apply_workspace_bytes(int64_t J, int64_t D, int64_t N, int32_t sf_dt
  *   - sfb_compute_sf(SFB_MLR, bf16) on that W reads the copy and needs
  *     sfb_shadow_bytes less workspace;
  *   - sfb_apply and sfb_prox_rows on that W keep the copy current (sfb_apply
- *     relies on it being current on entry: it rewrites only the entries whose
- *     bf16 value changes);
+ *     relies on it being current on entry: it need not rewrite entries whose
+ *     bf16 value stays the same);
  *   - any other modification of W by the caller must be followed by another
  *     sfb_shadow_attach (a refresh), otherwise the copy is stale.
- * Without an attached copy the bf16 path converts W into the workspace on every
- * sfb_compute_sf call: same results, one more pass over W.
+ * Without an attached copy the bf16 path rounds the same values on every
+ * sfb_compute_sf call, into the workspace or on their way into the contraction,
+ * whichever it expects to be faster (the workspace is sized for the former).
+ * Which kernel sums the logits, and in what order, depends on the shape and on
+ * whether there is a copy: with and without one the factors agree to rounding.
  */
 int64_t sfb_shadow_bytes(int64_t J, int64_t D);
 int sfb_shadow_attach(sfb_ctx* ctx, const float* W, int64_t J, int64_t D, void* dev_ptr, int64_t bytes);
@@ -113,9 +121,9 @@ int sfb_shadow_detach(sfb_ctx* ctx);
  * blocks of 256 rows x 64 columns, lo in tiles of 256 x 256, each block one
  * contiguous piece); the layout is the library's business, the caller only provides
  * sfb_split_bytes bytes.  The forward contraction reads the hi plane as its bf16
- * operand; sfb_apply reads both planes and writes the lo plane, and the hi plane
- * only where the update moves a value across a bf16 rounding boundary (6 to 8 bytes
- * per element against 8 to 10 for the fp32 array plus working copy), with the same
+ * operand; sfb_apply reads both planes and writes the lo plane, and of the hi plane
+ * only pieces in which the update moves a value across a bf16 rounding boundary (6 to 8
+ * bytes per element against 8 to 10 for the fp32 array plus working copy), with the same
  * fp32 arithmetic and the same resulting bits.
  * sfb_split_attach converts W into the caller-allocated buffer (sfb_split_bytes,
  * 256-byte aligned; never freed by the library) and remembers (W, J, D).  While
