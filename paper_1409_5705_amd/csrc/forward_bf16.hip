@@ -3,12 +3,14 @@
 //
 //   Z[b][j] = sum_d X[b][d] * bf16(W[j][d]),   fp32 accumulate.
 //
-// A workgroup takes a few dozen classes and up to 256 samples over the whole of d.
-// The rows of W are the long stream (every one is read once per 256 samples): they
-// travel through registers, several k-slices ahead, into LDS, where the eight
-// wavefronts share them; where W has no bf16 copy they are read as fp32 and rounded
-// on the way, which saves the pass that makes the copy.  The samples are small and
-// come from the L2: each wavefront loads its own fragments straight into registers.
+// A workgroup takes 64 or 128 classes and up to 256 samples, over the whole of d or,
+// where that leaves CUs idle, over a part of it (the partial sums go to planes of
+// their own, which the softmax adds up).  The rows of W are the long stream (every
+// one is read once per 256 samples): four of the eight wavefronts carry them through
+// registers, several k-slices ahead, into LDS; where W has no bf16 copy they are read
+// as fp32 and rounded on the way, which saves the pass that makes the copy.  The
+// samples are small and come from the L2: the other four wavefronts bring them
+// straight into three LDS stages.  All eight multiply what LDS holds.
 #include "forward_index.h"
 #include "kernels.h"
 
@@ -98,7 +100,7 @@ __global__ __launch_bounds__(NT, 2) void fwd_stream_kernel(FwdParams p)
     const int nk_all = (int)((p.D + KS - 1) / KS), first = (int)blockIdx.y * p.per_split;
     const int nk = nk_all - first < p.per_split ? nk_all - first : p.per_split;       // (>= 1: no empty split)
     // the workgroups start at different k: all at the same one would ask the same memory channels for it (rows of W are
-    // often a multiple of 4 KB apart)
+    // often a multiple of 4 KB apart).  The order in which a logit is summed so depends on its tile.
     const int turn = (int)((blockIdx.x * 5u) % (uint32_t)nk);
     auto at = [&](int s) {
         s = s < nk ? s : nk - 1;

@@ -904,8 +904,8 @@ __global__ __launch_bounds__(256) void split_from_w_kernel(const float* __restri
     }
 }
 
-// One workgroup per 64 rows of a 256 x 256 tile (both planes in whole pieces, 1 KB of a row of W), 16 rows of a thread's
-// loads in flight.  325000 x 10000 (26 GB): 5.41 -> 5.07 ms, with both planes read in pieces of 32 KB instead of line by line.
+// One workgroup per 64 rows of a 256 x 256 tile (both planes in whole pieces, 1 KB of a row of W), the 16 loads of a
+// thread's eight rows in flight together.  325000 x 10000 (26 GB): 5.41 -> 5.07 ms, with both planes read in pieces of 32 KB instead of line by line.
 __global__ __launch_bounds__(256) void w_from_split_kernel(const uint16_t* __restrict__ hi, const uint16_t* __restrict__ lo,
                                                            float* __restrict__ W, int64_t rows, int64_t cols,
                                                            int64_t pitch, uint32_t tiles_n)

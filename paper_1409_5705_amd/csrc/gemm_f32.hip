@@ -29,8 +29,8 @@
 //   100 x 1003 x 2047 (nothing aligned)      20 -> 14
 // 16x16x4 MFMAs rather than 32x32x2: in a kernel of 60 us a loop of nothing but MFMAs on
 // random operands runs at 2.40 GHz with the former and 2.23 with the latter.  Two
-// wavefronts per SIMD hide each other's LDS latency, barriers and load issue: without any
-// loads or reads the loop of T1 below takes 68 instead of 74 us.
+// wavefronts per SIMD hide each other's LDS latency, barriers and load issue: a launch of
+// the first of these without any loads or reads in its loop takes 68 instead of 74 us.
 #include "kernels.h"
 
 #include <cmath>

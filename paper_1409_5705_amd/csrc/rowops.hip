@@ -1,8 +1,8 @@
 // Row-wise and elementwise kernels around the GEMMs: the softmax/label step of
 // multiclass logistic regression, the pair difference and hinge coefficient of
 // distance metric learning, the power iteration and the row projection of
-// sparse coding.  All are HBM-bound streaming kernels with wavefront (64-lane)
-// shuffle reductions.
+// sparse coding.  Rows stay in registers where they fit; sums over the 64 lanes go
+// through DPP, those of the softmax through shuffles.
 #include "kernels.h"
 
 #include <type_traits>
@@ -177,8 +177,8 @@ __global__ __launch_bounds__(NT) void mlr_softmax_kernel(const float* __restrict
 }
 
 // Rows of at most PER floats per thread: the row stays in registers between the maximum, the exponentials and the
-// output, every logit is read once and exponentiated once (the elements of a thread and the order of the sums are those
-// of the kernel above).  PLANES: the logits are the sum of several partial arrays.  Workgroups past the B rows copy
+// output, every logit is read once and exponentiated once (the exponentials of a thread are added in groups of four, as in
+// the kernel above).  PLANES: the logits are the sum of several partial arrays.  Workgroups past the B rows copy
 // copy_bytes from copy_src to copy_dst (the samples that become the second factors): one launch less.
 template <int PER, bool OUT_BF16, bool VEC, bool PLANES>
 __global__ __launch_bounds__(256) void mlr_softmax_row_kernel(const float* __restrict__ Z, const int32_t* __restrict__ y,
