@@ -61,14 +61,14 @@ struct Params {
     int group_m;          // raster: groups of group_m row-tiles, row-tile index fastest inside a group
 };
 
-// A workgroup tile of BM x BN, WM x WN wavefronts over it and KW over k: each wavefront multiplies a block of
-// 16 TA x 16 TB over its 16 of the KB = 16 KW values of k of a slice.
+// A workgroup tile of BM x BN, WM x WN wavefronts over it and KW (at least two) over k: each wavefront multiplies a block
+// of 16 TA x 16 TB over its 16 of the KB = 16 KW values of k of a slice.
 template <int BM_, int BN_, int WM_, int WN_, int KW_, int MAX_NS = 5>
 struct Tile {
     static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, KW = KW_, KB = 16 * KW;
     static constexpr int TA = BM / WM / 16, TB = BN / WN / 16;  // 16 x 16 MFMA tiles of a wavefront
     static constexpr int A_BYTES = BM * KB * 4, B_BYTES = BN * KB * 4, STAGE = A_BYTES + B_BYTES;
-    static constexpr int MEET = KW > 1 ? NWAVES * TA * TB * 1024 : 0;      // LDS of the partial sums
+    static constexpr int MEET = NWAVES * TA * TB * 1024;                   // LDS of the partial sums
     static constexpr int NS = LDS_MAX / STAGE < MAX_NS ? LDS_MAX / STAGE : MAX_NS;   // LDS stages
     static constexpr int NSR = NS > 5 ? NS : 3;                            // the same where slices wait in registers first
     static constexpr int lds(bool direct) { return (direct ? NS : NSR) * STAGE > MEET ? (direct ? NS : NSR) * STAGE : MEET; }
@@ -558,37 +558,30 @@ __global__ __launch_bounds__(NT, 2) void gemm_f32_kernel(Params p)
     // partial sums: EU floats a lane per (tile, unit of it), added in the order of kw
     typedef float VecE __attribute__((ext_vector_type(EU)));
     VecE* const meet = reinterpret_cast<VecE*>(gemm_smem);
-    if (KW > 1) {
-        __syncthreads();
+    __syncthreads();
 #pragma unroll
-        for (int t = 0; t < TA * TB; ++t)
+    for (int t = 0; t < TA * TB; ++t)
 #pragma unroll
-            for (int q = 0; q < 4 / EU; ++q) {
-                VecE v;
+        for (int q = 0; q < 4 / EU; ++q) {
+            VecE v;
 #pragma unroll
-                for (int e = 0; e < EU; ++e) v[e] = acc[t / TB][t % TB][q * EU + e];
-                meet[((wave * TA * TB + t) * (4 / EU) + q) * 64 + lane] = v;
-            }
-        __syncthreads();
-    }
+            for (int e = 0; e < EU; ++e) v[e] = acc[t / TB][t % TB][q * EU + e];
+            meet[((wave * TA * TB + t) * (4 / EU) + q) * 64 + lane] = v;
+        }
+    __syncthreads();
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-        const int unit = KW > 1 ? kw * PER + i : i;
+        const int unit = kw * PER + i;
         if (unit >= UNITS) break;
         float v[TB][EU];
 #pragma unroll
         for (int b = 0; b < TB; ++b) {
-            if (KW > 1) {
-                const int w0 = wave % (WM * WN), t = unit / (4 / EU) * TB + b, q = unit % (4 / EU);
-                VecE sum = meet[((w0 * TA * TB + t) * (4 / EU) + q) * 64 + lane];
+            const int w0 = wave % (WM * WN), t = unit / (4 / EU) * TB + b, q = unit % (4 / EU);
+            VecE sum = meet[((w0 * TA * TB + t) * (4 / EU) + q) * 64 + lane];
 #pragma unroll
-                for (int k = 1; k < KW; ++k) sum += meet[(((w0 + k * WM * WN) * TA * TB + t) * (4 / EU) + q) * 64 + lane];
+            for (int k = 1; k < KW; ++k) sum += meet[(((w0 + k * WM * WN) * TA * TB + t) * (4 / EU) + q) * 64 + lane];
 #pragma unroll
-                for (int e = 0; e < EU; ++e) v[b][e] = sum[e];
-            } else {
-#pragma unroll
-                for (int e = 0; e < EU; ++e) v[b][e] = acc[i / (4 / EU)][b][(i % (4 / EU)) * EU + e];
-            }
+            for (int e = 0; e < EU; ++e) v[b][e] = sum[e];
         }
 #pragma unroll
         for (int e = 0; e < EU; ++e) {

@@ -99,10 +99,11 @@ __device__ __forceinline__ void online_update(float& m, float& s, const floatx4 
 
 // tiles_m > 0: Z is not row-major but an array of 256 x 256 tiles, tile (row / 256, j / 256) at index
 // (j / 256) * tiles_m + row / 256 (the layout the bf16 forward contraction writes: one piece per workgroup).
-template <int NT, bool OUT_BF16>
-__global__ __launch_bounds__(NT) void mlr_softmax_kernel(const float* __restrict__ Z, const int32_t* __restrict__ y,
+template <bool OUT_BF16>
+__global__ __launch_bounds__(1024) void mlr_softmax_kernel(const float* __restrict__ Z, const int32_t* __restrict__ y,
                                                          void* __restrict__ Uv, int64_t J, int vec, int64_t tiles_m)
 {
+    constexpr int NT = 1024;
     __shared__ float sm[NT / 64];
     const int64_t row = blockIdx.x;
     const bool blocked = tiles_m > 0;
@@ -988,9 +989,9 @@ hipError_t launch_mlr_softmax(const MlrSoftmaxArgs& a, hipStream_t stream)
     const dim3 grid((unsigned)a.B);
     const int64_t tiles_m = a.blocked ? (a.B + 255) / 256 : 0;
     if (a.out_bf16)
-        hipLaunchKernelGGL((mlr_softmax_kernel<1024, true>), grid, dim3(1024), 0, stream, a.Z, a.y, a.U, a.J, (int)vec, tiles_m);
+        hipLaunchKernelGGL((mlr_softmax_kernel<true>), grid, dim3(1024), 0, stream, a.Z, a.y, a.U, a.J, (int)vec, tiles_m);
     else
-        hipLaunchKernelGGL((mlr_softmax_kernel<1024, false>), grid, dim3(1024), 0, stream, a.Z, a.y, a.U, a.J, (int)vec, tiles_m);
+        hipLaunchKernelGGL((mlr_softmax_kernel<false>), grid, dim3(1024), 0, stream, a.Z, a.y, a.U, a.J, (int)vec, tiles_m);
     return hipGetLastError();
 }
 
