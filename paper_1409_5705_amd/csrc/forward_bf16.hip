@@ -11,18 +11,16 @@
 // as fp32 and rounded on the way, which saves the pass that makes the copy.  The
 // samples are small and come from the L2: the other four wavefronts bring them
 // straight into three LDS stages.  All eight multiply what LDS holds.
+#include "device.h"
 #include "forward_index.h"
 #include "kernels.h"
 
 #include <cmath>
-#include <type_traits>
 
 namespace sfb {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -30,33 +28,6 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 constexpr int NT = 512;
 constexpr int KS = 64;       // k-slice
 constexpr int NX = 3;        // LDS stages of the samples
-
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b)
-{
-    floatx2 f = {a, b};
-    bf16x2 h = __builtin_convertvector(f, bf16x2);  // round to nearest even
-    return __builtin_bit_cast(uint32_t, h);
-}
-__device__ __forceinline__ int swz(int r) { return (r ^ (r >> 3)) & 7; }
-__device__ __forceinline__ void load_to_lds_16(uint32_t lds_addr, uint64_t gbase, uint32_t voff)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(voff), "s"(gbase) : "memory");
-}
-__device__ __forceinline__ uint64_t uniform64(uint64_t a)
-{
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
-    return ((uint64_t)hi << 32) | (uint64_t)lo;
-}
-
-template <int B, int E, typename F>
-__device__ __forceinline__ void static_for(F&& f)
-{
-    if constexpr (B < E) {
-        f(std::integral_constant<int, B>{});
-        static_for<B + 1, E>(f);
-    }
-}
 
 struct FwdParams {
     const uint16_t* X;       // samples in the operand layout (blocks of 256 x 64, pitch P)

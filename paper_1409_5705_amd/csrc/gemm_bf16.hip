@@ -50,6 +50,7 @@
 //     XCDs (one L2 each; 8 of 32 CUs on MI355X, both read from the device): the
 //     workgroups of an XCD walk consecutive tiles of a raster in which tiles
 //     sharing operand panels are neighbours.
+#include "device.h"
 #include "kernels.h"
 
 #include <type_traits>
@@ -58,8 +59,6 @@ namespace sfb {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -122,13 +121,6 @@ struct Params {
     int num_xcd;        // XCDs of the device: consecutive workgroup ids go to consecutive XCDs
 };
 
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b)
-{
-    floatx2 f = {a, b};
-    bf16x2 h = __builtin_convertvector(f, bf16x2);  // round to nearest even
-    return __builtin_bit_cast(uint32_t, h);
-}
-
 // A parameter matrix kept as two 16-bit planes: the halves of word = bits + 0x8000 (modulo 2^32).  hi = word >> 16
 // is the value rounded to bf16 (to nearest, ties away from zero), lo = word & 0xffff; bits = ((hi << 16) | lo) -
 // 0x8000, exactly.  Two elements a dword in both planes: split_pair / join_pair move between the packed halves and
@@ -148,28 +140,9 @@ __device__ __forceinline__ int64_t operand_index(int64_t r, int64_t c, int64_t p
 {
     return ((r / BM) * (pitch / BK) + c / BK) * (int64_t)(BM * BK) + (r % BM) * BK + c % BK;
 }
-// Chunk-slot swizzle of tile row r: chunk c of the row sits in slot c ^ swz(r).
-// Chosen by measurement: an MFMA operand read (runs of 16 consecutive rows at one
-// chunk, 16 bytes a lane: rows of either parity meet the eight slots once each)
-// costs 26.9 cycles with this function, as little as with padded rows, against
-// 32.2 with r & 7 or (r >> 1) ^ (r >> 3) and 128 without a swizzle.
-// swz(r + 16) = swz(r) ^ 2, swz(r + 32) = swz(r) ^ 4 and swz(r + 64) = swz(r).
-__device__ __forceinline__ int swz(int r) { return (r ^ (r >> 3)) & 7; }
 // LDS byte offset of chunk c (0..7) of tile row r (128-byte rows).  Chunk
 // (4 ks + q), q < 4, of row r sits at lds_byte(r, q) ^ (64 ks).
 __device__ __forceinline__ uint32_t lds_byte(int r, int c) { return (uint32_t)(r * 128 + ((c ^ swz(r)) << 4)); }
-
-// f(integral_constant<int, B>), ..., f(integral_constant<int, E - 1>): a loop that is unrolled by construction (the
-// 64-MFMA steps of the slice are beyond what the unroller accepts under a pragma, and an index that is not a
-// constant would put the accumulators in scratch memory).
-template <int B, int E, typename F>
-__device__ __forceinline__ void static_for(F&& f)
-{
-    if constexpr (B < E) {
-        f(std::integral_constant<int, B>{});
-        static_for<B + 1, E>(f);
-    }
-}
 
 // The i-th of n loads goes after MFMA (2 i + 1) m / (2 n) of the m MFMAs of a window; -1: no load after MFMA j.
 constexpr int slot(int j, int n, int m)
@@ -179,35 +152,6 @@ constexpr int slot(int j, int n, int m)
     return -1;
 }
 
-// A wave-uniform 64-bit value as the compiler can see it (scalar registers).
-__device__ __forceinline__ uint64_t uniform64(uint64_t a)
-{
-    // (the builtin returns a signed int: narrow to 32 unsigned bits before widening)
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
-    return ((uint64_t)hi << 32) | (uint64_t)lo;
-}
-
-// 16 bytes per lane from global memory straight into LDS: lane l's bytes land at
-// LDS address lds_addr + 16 l (lds_addr wave-uniform, in M0); the global address
-// is gbase (uniform) + voff (per lane).  Issued as inline assembly so that the
-// compiler's wait-count insertion does not tie every later LDS read to it; the
-// caller waits (vmcnt) before the barrier that publishes the data.
-// NT: non-temporal, for an operand whose lines are used by a few CUs at about the
-// same time and never again (the class panel of the forward contraction: 6.5 GB
-// streaming past a 4 MiB L2 in which the sample panels should stay; forward
-// 4.78 -> 4.72 ms).  On an operand that IS reused it is ruinous (sample panel of
-// the forward +20 %, either operand of the apply +25 %).
-template <bool NT>
-__device__ __forceinline__ void load_to_lds_16(uint32_t lds_addr, uint64_t gbase, uint32_t voff)
-{
-    if (NT)
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds_addr), "v"(voff), "s"(gbase)
-                     : "memory");
-    else
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(voff), "s"(gbase)
-                     : "memory");
-}
 // One accumulator element out of the accumulation registers.  Written as
 // assembly because the compiler otherwise copies whole 16-register tiles (64
 // registers per block of the epilogue) to ordinary registers up front.  The
@@ -312,8 +256,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1))) void
     auto issue_one = [&](int j) {
         const uint32_t dst = lds_base + iss_stage + (uint32_t)(8 * wave) * 1024u;
         if (j < 8)
-            load_to_lds_16<false>(dst + j * 1024u, gA, offA[j & 7]);
+            load_to_lds_16(dst + j * 1024u, gA, offA[j & 7]);
         else
+            // (the class panel of the forward, 6.5 GB streaming past a 4 MiB L2 in which the sample panels should stay, is
+            // loaded non-temporally: forward 4.78 -> 4.72 ms.  On an operand that is reused it is ruinous: sample panel
+            // of the forward +20 %, either operand of the apply +25 %)
             load_to_lds_16<MODE == MODE_FWD>(dst + B_OFF + (j - 8) * 1024u, gB, offB[j & 7]);
     };
     auto issue_done = [&]() {   // advance the load cursor by one slice
@@ -660,9 +607,9 @@ __global__ __launch_bounds__(NT, 2) void apply_small_kernel(Params p)
     auto issue = [&](int s) {
         const uint32_t dst = lds_base + (uint32_t)(s & 1) * SSTAGE + (uint32_t)(4 * wave) * 1024u;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) load_to_lds_16<false>(dst + i * 1024u, gA + (uint64_t)s * 32768u, offA[i]);
+        for (int i = 0; i < 4; ++i) load_to_lds_16(dst + i * 1024u, gA + (uint64_t)s * 32768u, offA[i]);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) load_to_lds_16<false>(dst + SB_OFF + i * 1024u, gB + (uint64_t)s * 32768u, offB[i]);
+        for (int i = 0; i < 4; ++i) load_to_lds_16(dst + SB_OFF + i * 1024u, gB + (uint64_t)s * 32768u, offB[i]);
     };
     issue(0);
     if (nk > 1) issue(1);

@@ -31,6 +31,7 @@
 // random operands runs at 2.40 GHz with the former and 2.23 with the latter.  Two
 // wavefronts per SIMD hide each other's LDS latency, barriers and load issue: a launch of
 // the first of these without any loads or reads in its loop takes 68 instead of 74 us.
+#include "device.h"
 #include "kernels.h"
 
 #include <cmath>
@@ -75,21 +76,6 @@ struct Tile {
     static_assert(WM * WN * KW == NWAVES && KW % 2 == 0 && NS >= 3 && MEET <= LDS_MAX, "tile");
 };
 
-__device__ __forceinline__ void load_to_lds_16(uint32_t lds_addr, uint64_t gbase, uint32_t voff)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(voff), "s"(gbase) : "memory");
-}
-__device__ __forceinline__ void load_to_lds_4(uint32_t lds_addr, uint64_t vaddr)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_addr), "v"(vaddr) : "memory");
-}
-__device__ __forceinline__ uint64_t uniform64(uint64_t a)
-{
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
-    return ((uint64_t)hi << 32) | (uint64_t)lo;
-}
-
 // LDS image of one operand's slice (ROWS x KB floats):
 //   k-contiguous: per 32 of k, ROWS rows of 32 floats (128 bytes), the eight 16-byte chunks of row r XOR-swizzled by
 //     (r ^ r / 8) & 7, so that the 16-byte fragment reads of 16 consecutive rows meet every bank once;
@@ -97,7 +83,6 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t a)
 // MFMA tile x, lane l of a wavefront's block of 16 T rows is row T l + x of the block in both images (LDS row 16 x + l
 // of a k-contiguous block holds it): a lane's T columns of C are neighbours and its fragments of a k-strided operand
 // one read.  Rows past the end of the matrix are clamped (they feed accumulators that are not stored).
-__device__ __forceinline__ int swz(int r) { return (r ^ (r >> 3)) & 7; }
 template <int T>
 __device__ __forceinline__ int tile_row(int r) { return (r / (16 * T)) * (16 * T) + T * (r % 16) + (r % (16 * T)) / 16; }
 

@@ -3,16 +3,13 @@
 // distance metric learning, the power iteration and the row projection of
 // sparse coding.  Rows stay in registers where they fit; sums over the 64 lanes go
 // through DPP, those of the softmax through shuffles.
+#include "device.h"
 #include "kernels.h"
-
-#include <type_traits>
 
 namespace sfb {
 namespace {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
@@ -74,13 +71,6 @@ __device__ __forceinline__ float block_max(float v, float* sm)
 #pragma unroll
     for (int w = 1; w < NT / 64; ++w) r = fmaxf(r, sm[w]);
     return r;
-}
-
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b)
-{
-    floatx2 f = {a, b};
-    bf16x2 h = __builtin_convertvector(f, bf16x2);
-    return __builtin_bit_cast(uint32_t, h);
 }
 
 // ---------------------------------------------------------------------------
