@@ -619,11 +619,6 @@ typedef Tile<32, 32, 1, 1, 8> T4;
 typedef Tile<16, 16, 1, 1, 8, 9> T5;
 constexpr int NTILES = 6;
 
-struct Plan {
-    int cfg, split;
-    double us;       // estimated duration
-};
-
 // Estimated duration (us) of a contraction as `rounds` of one workgroup per CU, each walking its k-slices.  Per tile
 // shape: us per slice with every CU busy, and us per tile beside the slices (first loads, partial sums, epilogue).
 // Measured (direct, us of one launch, 2.5 of them between dependent launches): 1000 x 2048 x 2048 73 with T1, 78 T2,
@@ -642,18 +637,18 @@ double plan_time(int64_t M, int64_t N, int64_t K, int cus, int s, double slice_u
     return t;
 }
 
-Plan plan_gemm(int64_t M, int64_t N, int64_t K, int cus, int max_split, bool direct)
+GemmF32Plan plan_gemm(int64_t M, int64_t N, int64_t K, int cus, int max_split, bool direct)
 {
     static const double us[2][NTILES][2] = {{{2.10, 6.5}, {1.22, 5.0}, {1.25, 4.7}, {0.69, 3.5}, {0.80, 3.0}, {0.40, 1.2}},
                                             {{1.82, 6.5}, {1.01, 5.0}, {1.03, 4.7}, {0.55, 3.5}, {0.55, 3.0}, {0.38, 1.2}}};
     const double(*u)[2] = us[direct ? 1 : 0];
-    Plan best = {0, 1, 1e30};
+    GemmF32Plan best = {0, 1, direct, 1e30};
     for (int s = 1; s <= max_split; ++s) {
         const double t[NTILES] = {plan_time<T0>(M, N, K, cus, s, u[0][0], u[0][1], 0.05), plan_time<T1>(M, N, K, cus, s, u[1][0], u[1][1], 0.05),
                                   plan_time<T2>(M, N, K, cus, s, u[2][0], u[2][1], 0.1), plan_time<T3>(M, N, K, cus, s, u[3][0], u[3][1], 0.2),
                                   plan_time<T4>(M, N, K, cus, s, u[4][0], u[4][1], 0.0), plan_time<T5>(M, N, K, cus, s, u[5][0], u[5][1], 1.0)};
         for (int c = 0; c < NTILES; ++c)
-            if (t[c] < best.us) best = Plan{c, s, t[c]};
+            if (t[c] < best.us) best = GemmF32Plan{c, s, direct, t[c]};
     }
     return best;
 }
@@ -693,11 +688,10 @@ hipError_t launch_tile(Params p, DeviceInfo& dev, int slot, int split, hipStream
 }
 
 template <bool A_KS, bool B_KS, int EPI, bool DIRECT>
-hipError_t launch_vec(Params p, DeviceInfo& dev, int combo, int max_split, hipStream_t stream)
+hipError_t launch_vec(const Params& p, DeviceInfo& dev, int combo, const GemmF32Plan& plan, hipStream_t stream)
 {
-    const Plan plan = plan_gemm(p.M, p.N, p.K, dev.cus > 0 ? dev.cus : 256, max_split, DIRECT);
-    const int slot = (combo * 2 + (DIRECT ? 1 : 0)) * NTILES + plan.cfg;
-    switch (plan.cfg) {
+    const int slot = (combo * 2 + (DIRECT ? 1 : 0)) * NTILES + plan.tile;
+    switch (plan.tile) {
         case 0: return launch_tile<T0, A_KS, B_KS, EPI, DIRECT>(p, dev, slot, plan.split, stream);
         case 1: return launch_tile<T1, A_KS, B_KS, EPI, DIRECT>(p, dev, slot, plan.split, stream);
         case 2: return launch_tile<T2, A_KS, B_KS, EPI, DIRECT>(p, dev, slot, plan.split, stream);
@@ -717,10 +711,10 @@ bool direct_loads(const GemmF32Args& a)
 }
 
 template <bool A_KS, bool B_KS, int EPI>
-hipError_t launch_any(const Params& p, DeviceInfo& dev, int combo, int max_split, bool direct, hipStream_t stream)
+hipError_t launch_any(const Params& p, DeviceInfo& dev, int combo, const GemmF32Plan& plan, hipStream_t stream)
 {
-    if (direct) return launch_vec<A_KS, B_KS, EPI, true>(p, dev, combo, max_split, stream);
-    return launch_vec<A_KS, B_KS, EPI, false>(p, dev, combo, max_split, stream);
+    if (plan.direct) return launch_vec<A_KS, B_KS, EPI, true>(p, dev, combo, plan, stream);
+    return launch_vec<A_KS, B_KS, EPI, false>(p, dev, combo, plan, stream);
 }
 
 // How many ways a contraction may be split along k at most: only when there are few output tiles and every
@@ -743,10 +737,10 @@ int64_t gemm_f32_partial_bytes(int64_t M, int64_t N, int64_t K)
     return s > 1 ? (int64_t)s * M * N * 4 : 0;
 }
 
-double gemm_f32_estimate_us(const GemmF32Args& a)
+GemmF32Plan gemm_f32_plan(const GemmF32Args& a)
 {
     const int max_split = a.partial ? gemm_f32_max_split(a.M, a.N, a.K) : 1;
-    return plan_gemm(a.M, a.N, a.K, a.dev->cus > 0 ? a.dev->cus : 256, max_split, direct_loads(a)).us;
+    return plan_gemm(a.M, a.N, a.K, a.dev->cus > 0 ? a.dev->cus : 256, max_split, direct_loads(a));
 }
 
 hipError_t launch_gemm_f32(const GemmF32Args& a, hipStream_t stream)
@@ -759,12 +753,12 @@ hipError_t launch_gemm_f32(const GemmF32Args& a, hipStream_t stream)
     p.M = a.M; p.N = a.N; p.K = a.K;
     p.eta = a.eta; p.lambda = a.lambda;
     p.partial = a.partial;
-    const int max_split = a.partial ? gemm_f32_max_split(a.M, a.N, a.K) : 1;
-    const bool aks = a.a_kstrided, bks = a.b_kstrided, direct = direct_loads(a);
-    if (!aks && !bks && a.epilogue == EPI_STORE) return launch_any<false, false, EPI_STORE>(p, *a.dev, 0, max_split, direct, stream);
-    if (!aks && !bks && a.epilogue == EPI_SHRINK) return launch_any<false, false, EPI_SHRINK>(p, *a.dev, 1, max_split, direct, stream);
-    if (!aks && bks && a.epilogue == EPI_RESID) return launch_any<false, true, EPI_RESID>(p, *a.dev, 2, max_split, direct, stream);
-    if (aks && bks && a.epilogue == EPI_RMW) return launch_any<true, true, EPI_RMW>(p, *a.dev, 3, max_split, direct, stream);
+    const GemmF32Plan plan = gemm_f32_plan(a);
+    const bool aks = a.a_kstrided, bks = a.b_kstrided;
+    if (!aks && !bks && a.epilogue == EPI_STORE) return launch_any<false, false, EPI_STORE>(p, *a.dev, 0, plan, stream);
+    if (!aks && !bks && a.epilogue == EPI_SHRINK) return launch_any<false, false, EPI_SHRINK>(p, *a.dev, 1, plan, stream);
+    if (!aks && bks && a.epilogue == EPI_RESID) return launch_any<false, true, EPI_RESID>(p, *a.dev, 2, plan, stream);
+    if (aks && bks && a.epilogue == EPI_RMW) return launch_any<true, true, EPI_RMW>(p, *a.dev, 3, plan, stream);
     return hipErrorInvalidValue;
 }
 

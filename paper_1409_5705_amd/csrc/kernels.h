@@ -48,7 +48,14 @@ struct GemmF32Args {
     DeviceInfo* dev;     // the context's device facts
 };
 hipError_t launch_gemm_f32(const GemmF32Args& a, hipStream_t stream);
-double gemm_f32_estimate_us(const GemmF32Args& a);      // of that launch; a.dev is needed
+// How that launch does it (a.dev is needed): the tile shape by its index in gemm_f32.hip, the ways k is divided over
+// workgroups, direct-to-LDS loads or loads through registers, and the estimated duration.
+struct GemmF32Plan {
+    int tile, split;
+    bool direct;
+    double us;
+};
+GemmF32Plan gemm_f32_plan(const GemmF32Args& a);
 // Scratch a contraction of this shape can use to split its k range over several
 // workgroups (0: it would not be split).  16-byte aligned.
 int64_t gemm_f32_partial_bytes(int64_t M, int64_t N, int64_t K);

@@ -27,14 +27,21 @@ def dev_bf16(a):
     return dev(S.bf16_bits(a)).view(torch.bfloat16)
 
 
-@pytest.mark.parametrize("J,D,B", [
+# test_kernel_plans.py asserts that these reach every instantiation, with and without the k-split
+SHAPES = [
     (8, 8, 1), (72, 136, 17), (264, 72, 64),     # one slice, partial slices; up to 64 samples
     (264, 56, 300), (4096, 32, 40), (40, 24, 5),   # rows narrower than a slice
     (1000, 2056, 65), (1504, 520, 128),          # up to 128 samples
     (1504, 3000, 200), (2040, 1032, 256),        # up to 256, k-split
     (520, 1000, 300), (1000, 4104, 520),         # several tiles of samples, the last one ragged
     (8192, 264, 100), (16400, 72, 40),           # rows at and past the longest that one workgroup keeps in registers
-])
+    (8816, 136, 65), (8352, 480, 67),            # samples in tiles of 128: 64 and 128 classes, without and with a k-split
+    (8296, 136, 129), (5416, 152, 705),          # in tiles of 256
+    (3232, 1840, 142),                           # and with a k-split
+]
+
+
+@pytest.mark.parametrize("J,D,B", SHAPES)
 @pytest.mark.parametrize("layout", ["plain", "copy", "planes"])
 def test_stream_forward(sfb, oracle, J, D, B, layout):
     print("stream forward", J, D, B, layout, flush=True)

@@ -40,14 +40,18 @@ def host(t):
     return t.cpu().numpy()
 
 
-@pytest.mark.parametrize("J,D,N", [
+APPLY_SHAPES = [
     (2048, 4096, 96), (2001, 4001, 130),       # 128 x 128 tiles
     (1000, 2048, 300), (1003, 2047, 200),      # 128 x 64
     (700, 800, 300), (701, 803, 300),          # 64 x 64
     (400, 600, 200), (401, 603, 77),           # 32 x 32
+    (600, 800, 200), (501, 603, 100),          # 64 x 32
     (33, 70, 96), (16, 16, 128), (17, 48, 1),  # 16 x 16
     (3, 2052, 65), (2052, 3, 200), (2, 37, 130), (1, 1, 5), (4, 6, 32),   # rows of fewer floats than a load takes
-])
+]
+
+
+@pytest.mark.parametrize("J,D,N", APPLY_SHAPES)
 def test_apply_tiles(ctx, oracle, J, D, N):
     print("apply", J, D, N, flush=True)
     g = np.random.default_rng([21, J, D, N])
@@ -92,3 +96,44 @@ def test_sparse_code_tiles(ctx, sfb, oracle, J, D, B):
     Uo, Vo, _ = oracle.sc_sf(W0, X, lam=0.1, ista_iters=3, power_iters=10)
     assert rel_err(host(U), Uo) <= TOL_F32
     assert rel_err(host(V), Vo) <= TOL_F32
+
+
+# test_kernel_plans.py asserts that these reach every tile shape, with direct loads and through registers
+SC_SHAPES = [
+    (104, 264, 602), (135, 134, 914),           # both contractions on 32 x 32 tiles
+    (284, 264, 910), (261, 261, 908),           # 64 x 32
+    (324, 2144, 233), (102, 1282, 603),         # 64 x 32 and 32 x 32 with a k-split, residual 64 x 64
+    (4280, 108, 74), (1377, 145, 437),          # shrink 64 x 64; residual 32 x 32 with a k-split
+    (2140, 100, 703), (4164, 103, 195),         # shrink 128 x 64
+    (104, 4296, 203), (161, 2531, 678),         # residual 128 x 64; shrink 64 x 64 with a k-split
+    (4108, 100, 481), (2058, 101, 963),         # shrink 128 x 128
+    (100, 4236, 453), (100, 2954, 662),         # residual 128 x 128
+    (2204, 2214, 119),                          # both 128 x 64 with a k-split
+]
+
+
+@pytest.mark.parametrize("J,D,B", SC_SHAPES)
+def test_sparse_code_and_projection_shapes(ctx, sfb, J, D, B):
+    """The shrink, residual and plain-store epilogues against 64-bit torch: two ISTA iterations, and U = 2 X W^T."""
+    print("sparse codes, projection", J, D, B, flush=True)
+    W0, X0 = S.sc_dictionary(J, D, seed=24), S.sc_batch(D, B, seed=24)
+    W, X = dev(W0), dev(X0)
+    U = torch.empty((B, J), dtype=torch.float32, device="cuda:0")
+    V = torch.empty((B, D), dtype=torch.float32, device="cuda:0")
+    lam, iters = 0.1, 2
+    ctx.sfb_compute_sf(sfb.SFB_SC, W, X, U=U, V=V, lam=lam, ista_iters=iters, power_iters=10)
+    W64, X64 = W.double(), X.double()
+    b = torch.full((D,), D ** -0.5, dtype=torch.float64, device="cuda:0")
+    for _ in range(10):
+        b = W64.t() @ (W64 @ (b / b.norm()))
+    L = b.norm()
+    a, r = torch.zeros((B, J), dtype=torch.float64, device="cuda:0"), X64
+    for _ in range(iters):
+        t = a + r @ W64.t() / L
+        a = torch.sign(t) * torch.clamp(t.abs() - lam / L, min=0.0)
+        r = X64 - a @ W64
+    assert rel_err(host(U), host(a)) <= TOL_F32
+    assert rel_err(host(V), host(r)) <= TOL_F32
+    ctx.sfb_compute_sf(sfb.SFB_DML, W, X, Y=torch.zeros_like(X), sim=torch.ones(B, dtype=torch.int8, device="cuda:0"), U=U, V=V)
+    size = 2.0 * (X64.abs() @ W64.abs().t())
+    assert bool(torch.all((U.double() - 2.0 * (X64 @ W64.t())).abs() <= (D + 2) * EPS * size + 1e-30))

@@ -1,0 +1,36 @@
+"""The shapes of the GPU tests reach the kernel instantiations that those tests are there for (the planners run on the host)."""
+import os
+
+import pytest
+
+import kernel_plans as K
+import test_gpu_forward_stream as fwd
+import test_gpu_gemm_f32_tiles as f32
+
+
+@pytest.fixture(scope="module")
+def lib():
+    import paper_1409_5705_amd as m
+    if not os.path.exists(m.binding.LIB_PATH):
+        from paper_1409_5705_amd.build import build_library
+        build_library()
+    return m.lib()
+
+
+@pytest.mark.parametrize("copy,shapes", [(False, [(4, 2), (2, 2), (1, 2)]), (True, [(4, 2), (2, 4), (1, 2)])])
+def test_stream_forward_shapes(lib, copy, shapes):
+    got = {K.forward(lib, B, J, D, copy) for J, D, B in fwd.SHAPES}
+    reached = {(mt, ntl, split > 1) for mt, ntl, split in got if mt}
+    assert reached == {(mt, ntl, split) for mt, ntl in shapes for split in (False, True)}
+
+
+def test_apply_shapes(lib):
+    reached = {K.gemm_f32(lib, "apply", N, J, D)[::2] for J, D, N in f32.APPLY_SHAPES}
+    assert reached == {(t, direct) for t in K.TILES for direct in (False, True)}
+
+
+@pytest.mark.parametrize("kind", ["logits", "residual"])
+def test_sparse_code_shapes(lib, kind):
+    plans = [K.gemm_f32(lib, kind, B, J, D) for J, D, B in f32.SC_SHAPES + [(1001, 301, 99), (64, 4, 3)]]
+    assert {(t, direct) for t, _, direct in plans} == {(t, direct) for t in K.TILES for direct in (False, True)}
+    assert len({t for t, split, _ in plans if split > 1}) >= 2
