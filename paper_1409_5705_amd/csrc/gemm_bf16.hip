@@ -851,11 +851,36 @@ __global__ __launch_bounds__(256) void split_from_w_kernel(const float* __restri
     }
 }
 
-// One workgroup per 64 rows of a 256 x 256 tile (both planes in whole pieces, 1 KB of a row of W), the 16 loads of a
-// thread's eight rows in flight together.  325000 x 10000 (26 GB): 5.41 -> 5.07 ms, with both planes read in pieces of 32 KB instead of line by line.
+// Eight values from their halves.
+__device__ __forceinline__ void join_eight(u32x4 h, u32x4 l, floatx4& a, floatx4& b)
+{
+    const uint32_t h0 = h[0], h1 = h[1], h2 = h[2], h3 = h[3], l0 = l[0], l1 = l[1], l2 = l[2], l3 = l[3];
+    a = floatx4{split_value(join_pair0(h0, l0)), split_value(join_pair1(h0, l0)), split_value(join_pair0(h1, l1)), split_value(join_pair1(h1, l1))};
+    b = floatx4{split_value(join_pair0(h2, l2)), split_value(join_pair1(h2, l2)), split_value(join_pair0(h3, l3)), split_value(join_pair1(h3, l3))};
+}
+
+// Both planes back into the fp32 array, eight columns a thread.
 __global__ __launch_bounds__(256) void w_from_split_kernel(const uint16_t* __restrict__ hi, const uint16_t* __restrict__ lo,
                                                            float* __restrict__ W, int64_t rows, int64_t cols,
-                                                           int64_t pitch, uint32_t tiles_n)
+                                                           int64_t pitch, int64_t tiles_n)
+{
+    const int64_t chunks = cols / 8, total = rows * chunks;
+    for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (int64_t)gridDim.x * 256) {
+        const int64_t r = idx / chunks, c = (idx % chunks) * 8;
+        const u32x4 h = *reinterpret_cast<const u32x4*>(hi + operand_index(r, c, pitch));
+        const u32x4 l = *reinterpret_cast<const u32x4*>(lo + split_lo_index(r, c, tiles_n));
+        floatx4 a, b;
+        join_eight(h, l, a, b);
+        *reinterpret_cast<floatx4*>(W + r * cols + c) = a;
+        *reinterpret_cast<floatx4*>(W + r * cols + c + 4) = b;
+    }
+}
+
+// The same for a matrix far larger than the memory-side cache: one workgroup per 64 rows of a 256 x 256 tile (both planes in
+// whole pieces, 1 KB of a row of W), the 16 loads of a thread's eight rows in flight together, nothing kept in the caches.
+__global__ __launch_bounds__(256) void w_from_split_tiles_kernel(const uint16_t* __restrict__ hi, const uint16_t* __restrict__ lo,
+                                                                 float* __restrict__ W, int64_t rows, int64_t cols,
+                                                                 int64_t pitch, uint32_t tiles_n)
 {
     const int64_t tile_m = (blockIdx.x / 4) / tiles_n, tile_n = (blockIdx.x / 4) % tiles_n;
     const int64_t c = tile_n * BN + (threadIdx.x & 31) * 8, r0 = tile_m * BM + (blockIdx.x % 4) * 64 + (threadIdx.x >> 5);
@@ -873,11 +898,8 @@ __global__ __launch_bounds__(256) void w_from_split_kernel(const uint16_t* __res
 #pragma unroll
     for (int i = 0; i < N; ++i) {
         if (r0 + STEP * i >= rows) return;
-        const uint32_t h0 = h[i][0], h1 = h[i][1], h2 = h[i][2], h3 = h[i][3], l0 = l[i][0], l1 = l[i][1], l2 = l[i][2], l3 = l[i][3];
-        const floatx4 a = {split_value(join_pair0(h0, l0)), split_value(join_pair1(h0, l0)),
-                           split_value(join_pair0(h1, l1)), split_value(join_pair1(h1, l1))};
-        const floatx4 b = {split_value(join_pair0(h2, l2)), split_value(join_pair1(h2, l2)),
-                           split_value(join_pair0(h3, l3)), split_value(join_pair1(h3, l3))};
+        floatx4 a, b;
+        join_eight(h[i], l[i], a, b);
         floatx4* const to = reinterpret_cast<floatx4*>(W + (r0 + STEP * i) * cols + c);
         __builtin_nontemporal_store(a, to);
         __builtin_nontemporal_store(b, to + 1);
@@ -1022,9 +1044,17 @@ hipError_t launch_split_from_w(const float* W, uint16_t* hi, uint16_t* lo, int64
 hipError_t launch_w_from_split(const uint16_t* hi, const uint16_t* lo, float* W, int64_t J, int64_t D, hipStream_t stream)
 {
     if (J <= 0 || D <= 0) return hipSuccess;
+    // After training steps much of a smaller matrix's planes is still in the 256 MB memory-side cache, and its fp32 array stays
+    // there for whoever reads it next.  Measured, us of an export that follows an apply, line by line / in tiles without
+    // the caches: 8192 x 4096 (134 MB) 45 / 55, 20000 x 3000 93 / 112, 40000 x 2048 (328 MB) 129 / 141, 20000 x 10000
+    // (800 MB) 318 / 308, 325000 x 10000 5398 / 5036; 1000 x 512 6.3 / 7.3 (too few workgroups).
     const int64_t tiles_n = (D + BN - 1) / BN, blocks = (J + BM - 1) / BM * tiles_n * 4;
+    if (J * D * 4 < (1LL << 29)) {
+        hipLaunchKernelGGL(w_from_split_kernel, dim3(grid_for(J * (D / 8))), dim3(256), 0, stream, hi, lo, W, J, D, bf16_pitch(D), tiles_n);
+        return hipGetLastError();
+    }
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(w_from_split_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, hi, lo, W, J, D, bf16_pitch(D), (uint32_t)tiles_n);
+    hipLaunchKernelGGL(w_from_split_tiles_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, hi, lo, W, J, D, bf16_pitch(D), (uint32_t)tiles_n);
     return hipGetLastError();
 }
 

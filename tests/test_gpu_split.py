@@ -55,6 +55,21 @@ def test_split_round_trip_is_exact(sfb):
     c.close()
 
 
+@pytest.mark.parametrize("J,D", [(131072, 1024), (131080, 1032), (16392, 8200), (131072, 1016)])   # 512 MB and more; below
+def test_split_round_trip_of_a_large_matrix(sfb, J, D):
+    print("split round trip", J, D, flush=True)
+    g = torch.Generator(device="cuda:0").manual_seed(J + D)
+    W = torch.randint(-2 ** 31, 2 ** 31, (J, D), generator=g, device="cuda:0", dtype=torch.int64).to(torch.int32).view(torch.float32)
+    before = W.view(torch.int32).clone()
+    c = sfb.Context(0)
+    c.sfb_split_attach(W)
+    W.zero_()
+    c.sfb_split_export(W)
+    torch.cuda.synchronize()
+    assert torch.equal(W.view(torch.int32), before)
+    c.close()
+
+
 @pytest.mark.parametrize("N,J,D,kind", [
     (1024, 520, 328, "plain"),
     (100, 4104, 4104, "plain"),      # 289 tiles, ragged both ways
