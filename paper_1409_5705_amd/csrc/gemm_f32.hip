@@ -43,7 +43,7 @@ namespace {
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int NWAVES = 8, NT = 64 * NWAVES;
-constexpr int LDS_MAX = 152 * 1024;      // of the 160 KB of a CU
+constexpr int LDS_CU = 160 * 1024, LDS_MAX = 152 * 1024;      // of a CU; of one workgroup
 
 struct Params {
     const float* A;
@@ -72,7 +72,13 @@ struct Tile {
     static constexpr int MEET = NWAVES * TA * TB * 1024;                   // LDS of the partial sums
     static constexpr int NS = LDS_MAX / STAGE < MAX_NS ? LDS_MAX / STAGE : MAX_NS;   // LDS stages
     static constexpr int NSR = NS > 5 ? NS : 3;                            // the same where slices wait in registers first
-    static constexpr int lds(bool direct) { return (direct ? NS : NSR) * STAGE > MEET ? (direct ? NS : NSR) * STAGE : MEET; }
+    // LDS of a workgroup that walks n slices: a short walk does not use all stages
+    static constexpr int stages(bool direct) { return direct ? NS : NSR; }
+    static constexpr int lds(bool direct, int64_t n)
+    {
+        const int used = (n < stages(direct) ? (int)n : stages(direct)) * STAGE;
+        return used > MEET ? used : MEET;
+    }
     static_assert(WM * WN * KW == NWAVES && KW % 2 == 0 && NS >= 3 && MEET <= LDS_MAX, "tile");
 };
 
@@ -625,30 +631,45 @@ constexpr int NTILES = 6;
 // 89 T3, 100 T4; 256 x 1000 x 2048 12.0 T4, 20.5 T3, 20.7 T5, 16 T3 split in two; 100 x 300 x 1000 5.7 T5, 9.4 T4,
 // 13 T3; 4096 x 4096 x 1024 260 T0, 283 T1.  The smallest tile waits for memory rather than for the matrix pipes, and
 // waits less where it leaves CUs idle.
+// A contraction of few slices needs less LDS, and several workgroups share a CU where registers allow it: each takes
+// longer (`share` of its time per neighbour), the round of all of them less.  Measured (us of sfb_apply, one workgroup
+// per CU / several, with the same tile): 16 x 100000 with 100 pairs 55 / 22 T5, 32 x 200000 with 256 103 / 66 T4,
+// 100000 x 16 with 100 34 / 20 T3, 5000 x 3000 with 10 49 / 35 T1.
+struct TileCost {
+    double slice_us, tile_us, idle_gain, share;
+    int wgs;       // workgroups a CU has registers for
+};
 template <class TL>
-double plan_time(int64_t M, int64_t N, int64_t K, int cus, int s, double slice_us, double tile_us, double idle_gain)
+double plan_time(int64_t M, int64_t N, int64_t K, int cus, int s, bool direct, const TileCost& c)
 {
-    const int64_t tiles = ((M + TL::BM - 1) / TL::BM) * ((N + TL::BN - 1) / TL::BN), nk = (K + TL::KB - 1) / TL::KB;
-    const double rounds = (double)((tiles * s + cus - 1) / cus), slices = (double)((nk + s - 1) / s);
-    const double busy = (double)(tiles * s) / (double)cus;
-    if (busy < 1.0) slice_us *= 1.0 - idle_gain * (1.0 - busy);
-    double t = 2.5 + rounds * (slices * slice_us + tile_us);
+    const int64_t tiles = ((M + TL::BM - 1) / TL::BM) * ((N + TL::BN - 1) / TL::BN) * s, nk = (K + TL::KB - 1) / TL::KB;
+    const int64_t slices = (nk + s - 1) / s, per_cu = (tiles + cus - 1) / cus;
+    int64_t wgs = 1;
+    if (TL::lds(direct, slices) < TL::lds(direct, TL::stages(direct))) {
+        wgs = LDS_CU / TL::lds(direct, slices);
+        if (wgs > c.wgs) wgs = c.wgs;
+        if (wgs > per_cu) wgs = per_cu;
+    }
+    const double rounds = (double)((tiles + cus * wgs - 1) / (cus * wgs)), busy = (double)tiles / (double)cus;
+    const double slice_us = busy < 1.0 ? c.slice_us * (1.0 - c.idle_gain * (1.0 - busy)) : c.slice_us;
+    double t = 2.5 + rounds * ((double)slices * slice_us + c.tile_us) * (1.0 + c.share * (double)(wgs - 1));
     if (s > 1) t += 4.5 + (double)(s + 1) * (double)M * (double)N * 4.0 / 3e6;      // the second pass
     return t;
 }
 
 GemmF32Plan plan_gemm(int64_t M, int64_t N, int64_t K, int cus, int max_split, bool direct)
 {
-    static const double us[2][NTILES][2] = {{{2.10, 6.5}, {1.22, 5.0}, {1.25, 4.7}, {0.69, 3.5}, {0.80, 3.0}, {0.40, 1.2}},
-                                            {{1.82, 6.5}, {1.01, 5.0}, {1.03, 4.7}, {0.55, 3.5}, {0.55, 3.0}, {0.38, 1.2}}};
-    const double(*u)[2] = us[direct ? 1 : 0];
+    static const TileCost costs[2][NTILES] = {
+        {{2.10, 6.5, 0.05, 0.0, 1}, {1.22, 5.0, 0.05, 0.5, 1}, {1.25, 4.7, 0.1, 0.3, 1}, {0.69, 3.5, 0.2, 0.2, 2}, {0.80, 3.0, 0.0, 0.3, 2}, {0.40, 1.2, 1.0, 0.35, 2}},
+        {{1.82, 6.5, 0.05, 0.0, 1}, {1.01, 5.0, 0.05, 0.5, 2}, {1.03, 4.7, 0.1, 0.3, 2}, {0.55, 3.5, 0.2, 0.2, 3}, {0.55, 3.0, 0.0, 0.3, 3}, {0.38, 1.2, 1.0, 0.35, 4}}};
+    const TileCost* const c = costs[direct ? 1 : 0];
     GemmF32Plan best = {0, 1, direct, 1e30};
     for (int s = 1; s <= max_split; ++s) {
-        const double t[NTILES] = {plan_time<T0>(M, N, K, cus, s, u[0][0], u[0][1], 0.05), plan_time<T1>(M, N, K, cus, s, u[1][0], u[1][1], 0.05),
-                                  plan_time<T2>(M, N, K, cus, s, u[2][0], u[2][1], 0.1), plan_time<T3>(M, N, K, cus, s, u[3][0], u[3][1], 0.2),
-                                  plan_time<T4>(M, N, K, cus, s, u[4][0], u[4][1], 0.0), plan_time<T5>(M, N, K, cus, s, u[5][0], u[5][1], 1.0)};
-        for (int c = 0; c < NTILES; ++c)
-            if (t[c] < best.us) best = GemmF32Plan{c, s, direct, t[c]};
+        const double t[NTILES] = {plan_time<T0>(M, N, K, cus, s, direct, c[0]), plan_time<T1>(M, N, K, cus, s, direct, c[1]),
+                                  plan_time<T2>(M, N, K, cus, s, direct, c[2]), plan_time<T3>(M, N, K, cus, s, direct, c[3]),
+                                  plan_time<T4>(M, N, K, cus, s, direct, c[4]), plan_time<T5>(M, N, K, cus, s, direct, c[5])};
+        for (int i = 0; i < NTILES; ++i)
+            if (t[i] < best.us) best = GemmF32Plan{i, s, direct, t[i]};
     }
     return best;
 }
@@ -660,7 +681,7 @@ hipError_t launch_tile(Params p, DeviceInfo& dev, int slot, int split, hipStream
     if (tm * tn > 0x7fffffffLL) return hipErrorInvalidValue;
     if (!dev.gemm_f32_lds_set[slot]) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_f32_kernel<TL, A_KS, B_KS, EPI, DIRECT>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, TL::lds(DIRECT));
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, TL::lds(DIRECT, TL::stages(DIRECT)));
         if (e != hipSuccess) return e;
         dev.gemm_f32_lds_set[slot] = true;
     }
@@ -677,8 +698,8 @@ hipError_t launch_tile(Params p, DeviceInfo& dev, int slot, int split, hipStream
         if (gm > tm) gm = (int)tm;
         p.group_m = gm;
     }
-    hipLaunchKernelGGL((gemm_f32_kernel<TL, A_KS, B_KS, EPI, DIRECT>), dim3((unsigned)(tm * tn), (unsigned)p.split_k), dim3(NT), TL::lds(DIRECT),
-                       stream, p);
+    hipLaunchKernelGGL((gemm_f32_kernel<TL, A_KS, B_KS, EPI, DIRECT>), dim3((unsigned)(tm * tn), (unsigned)p.split_k), dim3(NT),
+                       TL::lds(DIRECT, p.per_split), stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.split_k <= 1) return e;
     int64_t g = (p.M * p.N + 255) / 256;

@@ -44,8 +44,9 @@ APPLY_SHAPES = [
     (2048, 4096, 96), (2001, 4001, 130),       # 128 x 128 tiles
     (1000, 2048, 300), (1003, 2047, 200),      # 128 x 64
     (700, 800, 300), (701, 803, 300),          # 64 x 64
-    (400, 600, 200), (401, 603, 77),           # 32 x 32
-    (600, 800, 200), (501, 603, 100),          # 64 x 32
+    (600, 800, 200), (401, 603, 77),           # 32 x 32
+    (500, 1000, 260), (501, 603, 100),         # 64 x 32
+    (400, 600, 200), (16, 10000, 30), (30, 9001, 100), (9000, 20, 64), (64, 4100, 33),   # few slices, several workgroups a CU
     (33, 70, 96), (16, 16, 128), (17, 48, 1),  # 16 x 16
     (3, 2052, 65), (2052, 3, 200), (2, 37, 130), (1, 1, 5), (4, 6, 32),   # rows of fewer floats than a load takes
 ]
@@ -100,14 +101,16 @@ def test_sparse_code_tiles(ctx, sfb, oracle, J, D, B):
 
 # test_kernel_plans.py asserts that these reach every tile shape, with direct loads and through registers
 SC_SHAPES = [
-    (104, 264, 602), (135, 134, 914),           # both contractions on 32 x 32 tiles
-    (284, 264, 910), (261, 261, 908),           # 64 x 32
-    (324, 2144, 233), (102, 1282, 603),         # 64 x 32 and 32 x 32 with a k-split, residual 64 x 64
-    (4280, 108, 74), (1377, 145, 437),          # shrink 64 x 64; residual 32 x 32 with a k-split
-    (2140, 100, 703), (4164, 103, 195),         # shrink 128 x 64
-    (104, 4296, 203), (161, 2531, 678),         # residual 128 x 64; shrink 64 x 64 with a k-split
-    (4108, 100, 481), (2058, 101, 963),         # shrink 128 x 128
-    (100, 4236, 453), (100, 2954, 662),         # residual 128 x 128
+    (100, 112, 16), (106, 105, 16),             # both contractions on 16 x 16 tiles
+    (132, 664, 452), (648, 116, 536),           # 32 x 32 and 64 x 32
+    (135, 134, 914), (273, 274, 942),           # both 32 x 32; both 64 x 32
+    (1416, 1471, 36), (2128, 2196, 17),         # both 64 x 32, both 32 x 32, with a k-split
+    (2184, 204, 395), (324, 2144, 233),         # 64 x 64 shrink; residual
+    (4212, 133, 100), (139, 4143, 98),
+    (3296, 136, 259), (136, 4280, 197),         # 128 x 64
+    (4164, 103, 195), (161, 2531, 678),
+    (4408, 164, 705), (132, 3780, 515),         # 128 x 128
+    (2058, 101, 963), (103, 3662, 533),
     (2204, 2214, 119),                          # both 128 x 64 with a k-split
 ]
 
