@@ -876,8 +876,10 @@ __global__ __launch_bounds__(256) void w_from_split_kernel(const uint16_t* __res
     }
 }
 
-// The same for a matrix far larger than the memory-side cache: one workgroup per 64 rows of a 256 x 256 tile (both planes in
-// whole pieces, 1 KB of a row of W), the 16 loads of a thread's eight rows in flight together, nothing kept in the caches.
+// The same in tiles: one workgroup per 64 rows of a 256 x 256 tile (both planes in whole
+// pieces, 1 KB of a row of W), the 16 loads of a thread's eight rows in flight together and past the caches.  STREAM: the
+// stores as well.
+template <bool STREAM>
 __global__ __launch_bounds__(256) void w_from_split_tiles_kernel(const uint16_t* __restrict__ hi, const uint16_t* __restrict__ lo,
                                                                  float* __restrict__ W, int64_t rows, int64_t cols,
                                                                  int64_t pitch, uint32_t tiles_n)
@@ -901,8 +903,13 @@ __global__ __launch_bounds__(256) void w_from_split_tiles_kernel(const uint16_t*
         floatx4 a, b;
         join_eight(h[i], l[i], a, b);
         floatx4* const to = reinterpret_cast<floatx4*>(W + (r0 + STEP * i) * cols + c);
-        __builtin_nontemporal_store(a, to);
-        __builtin_nontemporal_store(b, to + 1);
+        if (STREAM) {
+            __builtin_nontemporal_store(a, to);
+            __builtin_nontemporal_store(b, to + 1);
+        } else {
+            to[0] = a;
+            to[1] = b;
+        }
     }
 }
 
@@ -1044,17 +1051,29 @@ hipError_t launch_split_from_w(const float* W, uint16_t* hi, uint16_t* lo, int64
 hipError_t launch_w_from_split(const uint16_t* hi, const uint16_t* lo, float* W, int64_t J, int64_t D, hipStream_t stream)
 {
     if (J <= 0 || D <= 0) return hipSuccess;
-    // After training steps much of a smaller matrix's planes is still in the 256 MB memory-side cache, and its fp32 array stays
-    // there for whoever reads it next.  Measured, us of an export that follows an apply, line by line / in tiles without
-    // the caches: 8192 x 4096 (134 MB) 45 / 55, 20000 x 3000 93 / 112, 40000 x 2048 (328 MB) 129 / 141, 20000 x 10000
-    // (800 MB) 318 / 308, 325000 x 10000 5398 / 5036; 1000 x 512 6.3 / 7.3 (too few workgroups).
-    const int64_t tiles_n = (D + BN - 1) / BN, blocks = (J + BM - 1) / BM * tiles_n * 4;
-    if (J * D * 4 < (1LL << 29)) {
+    // What is in the 256 MB memory-side cache decides.  Up to some 16 MB the tiles are too few workgroups.  Then planes and fp32
+    // array fit that cache or nearly so, and tiles whose stores leave the array there are fastest; above, up to some 512 MB,
+    // line by line, and for far larger matrices nothing is to be kept.  Measured, us, line by line / tiles / tiles with
+    // streamed stores: five applies of 100 pairs and the export, everything else evicted before; the same and a sum over
+    // W; a step and its export again and again:
+    //   1000 x 512             54 / 56 / 56          68 / 68 / 69          14.6 / 14.1 / 14.2
+    //   22256 x 1000  (89 MB)  285 / 273 / 278       307 / 296 / 318       68 / 81 / 91
+    //   8192 x 4096  (134 MB)  390 / 366 / 368       421 / 399 / 423       96 / 111 / 113
+    //   20000 x 3000 (240 MB)  617 / 600 / 613       688 / 657 / 709       178 / 180 / 211
+    //   20000 x 5000 (400 MB)  967 / 954 / 974       1087 / 1103 / 1108    294 / 334 / 338
+    //   40000 x 10000          3502 / 3518 / 3504    3924 / 3951 / 3928    1198 / 1225 / 1195
+    // 98144 x 680 (267 MB), five CSR steps and the export, among passes over other matrices: 757 / 782 / 766.  325000 x 10000,
+    // the export alone: 5398 / 5450 / 5036.
+    const int64_t tiles_n = (D + BN - 1) / BN, blocks = (J + BM - 1) / BM * tiles_n * 4, mb = J * D * 4 >> 20;
+    if (mb < 16 || (mb >= 192 && mb < 512)) {
         hipLaunchKernelGGL(w_from_split_kernel, dim3(grid_for(J * (D / 8))), dim3(256), 0, stream, hi, lo, W, J, D, bf16_pitch(D), tiles_n);
         return hipGetLastError();
     }
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(w_from_split_tiles_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, hi, lo, W, J, D, bf16_pitch(D), (uint32_t)tiles_n);
+    if (mb < 512)
+        hipLaunchKernelGGL(w_from_split_tiles_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, stream, hi, lo, W, J, D, bf16_pitch(D), (uint32_t)tiles_n);
+    else
+        hipLaunchKernelGGL(w_from_split_tiles_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, stream, hi, lo, W, J, D, bf16_pitch(D), (uint32_t)tiles_n);
     return hipGetLastError();
 }
 

@@ -55,7 +55,8 @@ def test_split_round_trip_is_exact(sfb):
     c.close()
 
 
-@pytest.mark.parametrize("J,D", [(131072, 1024), (131080, 1032), (16392, 8200), (131072, 1016)])   # 512 MB and more; below
+@pytest.mark.parametrize("J,D", [(131072, 1024), (131080, 1032), (16392, 8200), (131072, 1016),    # 512 MB and more; below
+                                  (16384, 256), (16392, 264), (1032, 4072), (4096, 1016)])            # 16 MB and more; below
 def test_split_round_trip_of_a_large_matrix(sfb, J, D):
     print("split round trip", J, D, flush=True)
     g = torch.Generator(device="cuda:0").manual_seed(J + D)
