@@ -38,6 +38,7 @@ SHAPES = [
     (8816, 136, 65), (8352, 480, 67),            # samples in tiles of 128: 64 and 128 classes, without and with a k-split
     (8296, 136, 129), (5416, 152, 705),          # in tiles of 256
     (3232, 1840, 142),                           # and with a k-split
+    (4208, 400, 67),                             # a k-split of rows of 4097 to 8192 classes
 ]
 
 

@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 import sfb_synth as S
-from parity import TOL_F32, rel_err
+from parity import TOL_F32, mlr_u_check, rel_err
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -33,6 +33,20 @@ def dev(a):
 def host(t):
     torch.cuda.synchronize()
     return t.cpu().numpy()
+
+
+@pytest.mark.parametrize("J", [1, 255, 256, 257, 260, 1023, 1024, 1025, 1028, 4095, 4096, 4097, 4100, 8191, 8192, 8193, 8196, 16384, 16385])
+def test_softmax_row_lengths(ctx, sfb, oracle, J):
+    print("softmax", J, flush=True)
+    D, B = 20, 9
+    W0 = S.normal_matrix(J, D, 0.3, seed=36)
+    X, y = S.mlr_batch(J, D, B, seed=36)
+    U, V = torch.empty((B, J), device="cuda:0"), torch.empty((B, D), device="cuda:0")
+    ctx.sfb_compute_sf(sfb.SFB_MLR, dev(W0), dev(X), Y=dev(y), U=U, V=V)
+    Uo, Vo = oracle.mlr_sf(W0, X, y)
+    assert np.array_equal(host(V), X)
+    if J > 1:                                    # (one class: its probability is 1 whatever the sample, the factor 0)
+        mlr_u_check(host(U), Uo, y, TOL_F32)
 
 
 @pytest.mark.parametrize("J", [1, 256, 257, 512, 513, 1024, 1025, 4096, 4097])
