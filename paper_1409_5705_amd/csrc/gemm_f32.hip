@@ -643,16 +643,22 @@ template <class TL>
 double plan_time(int64_t M, int64_t N, int64_t K, int cus, int s, bool direct, const TileCost& c)
 {
     const int64_t tiles = ((M + TL::BM - 1) / TL::BM) * ((N + TL::BN - 1) / TL::BN) * s, nk = (K + TL::KB - 1) / TL::KB;
-    const int64_t slices = (nk + s - 1) / s, per_cu = (tiles + cus - 1) / cus;
-    int64_t wgs = 1;
-    if (TL::lds(direct, slices) < TL::lds(direct, TL::stages(direct))) {
-        wgs = LDS_CU / TL::lds(direct, slices);
-        if (wgs > c.wgs) wgs = c.wgs;
-        if (wgs > per_cu) wgs = per_cu;
+    const int64_t slices = s > 1 ? (nk + s - 1) / s : nk;
+    double slice_us = c.slice_us, rounds = 1.0, together = 1.0;
+    if (tiles < cus) {
+        slice_us *= 1.0 - c.idle_gain * (1.0 - (double)tiles / (double)cus);
+    } else {
+        int64_t wgs = 1;
+        const int used = TL::lds(direct, slices);
+        if (used < TL::lds(direct, TL::stages(direct))) {
+            const int64_t per_cu = (tiles + cus - 1) / cus;
+            wgs = LDS_CU / used < c.wgs ? LDS_CU / used : c.wgs;
+            if (wgs > per_cu) wgs = per_cu;
+        }
+        rounds = (double)((tiles + cus * wgs - 1) / (cus * wgs));
+        together += c.share * (double)(wgs - 1);
     }
-    const double rounds = (double)((tiles + cus * wgs - 1) / (cus * wgs)), busy = (double)tiles / (double)cus;
-    const double slice_us = busy < 1.0 ? c.slice_us * (1.0 - c.idle_gain * (1.0 - busy)) : c.slice_us;
-    double t = 2.5 + rounds * ((double)slices * slice_us + c.tile_us) * (1.0 + c.share * (double)(wgs - 1));
+    double t = 2.5 + rounds * ((double)slices * slice_us + c.tile_us) * together;
     if (s > 1) t += 4.5 + (double)(s + 1) * (double)M * (double)N * 4.0 / 3e6;      // the second pass
     return t;
 }
