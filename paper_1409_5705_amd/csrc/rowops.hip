@@ -518,7 +518,7 @@ __device__ __forceinline__ float lambert_w_exp(float L)
 //
 // Rows of at most PER classes a thread: logits and dual point stay in registers for all the passes (seven on average),
 // every pass takes one barrier (two sums reduced together, alternating LDS slots); what bounds it is the chain of
-// exponentials and logarithms of a Newton step, hence two to four classes a thread rather than more (256 samples of 1000
+// exponentials and logarithms of a Newton step, hence few classes a thread while there are few samples (256 samples of 1000
 // classes: 27.7 us re-reading the rows with four barriers a step, 16.0 now).  PER == 0: rows of any length, re-read
 // from the cache.
 template <int NT, int PER>
@@ -1021,7 +1021,7 @@ hipError_t launch_div_scalar(const float* Z, float* W, float lambda, int64_t n, 
 }
 
 hipError_t launch_sdca_mlr(const float* Zl, const float* X, float* P, float* dU, int64_t B, int64_t J, int64_t D,
-                           float lambda, int64_t n_total, float beta, hipStream_t stream)
+                           float lambda, int64_t n_total, float beta, int cus, hipStream_t stream)
 {
     if (B <= 0 || J <= 0) return hipSuccess;
     if (B > 0x7fffffffLL) return hipErrorInvalidValue;
@@ -1030,16 +1030,26 @@ hipError_t launch_sdca_mlr(const float* Zl, const float* X, float* P, float* dU,
         constexpr int NT = decltype(nt)::value, PER = decltype(per)::value;
         hipLaunchKernelGGL((sdca_mlr_kernel<NT, PER>), dim3((unsigned)B), dim3(NT), 0, stream, Zl, X, P, dU, J, D, inv_lambda_n, beta);
     };
+    // Up to two samples a CU: few classes a thread, for the chain of exponentials of each.  More: workgroups of 256, of which
+    // more share a CU (us, 512 or 1024 threads / 256, 16 features: 300 classes, 256 samples 11.4 / 12.2, 1024 17.4 / 15.2, 4096
+    // 47.7 / 36.0; 1025 classes, 256 samples 14.8 / 17.2, 512 21.8 / 20.5, 4096 117 / 86; 4096 classes, 512 samples 44 / 48,
+    // 4096 239 / 227).
+    using std::integral_constant;
+    const bool few = B <= 2 * (int64_t)cus;
     if (J <= 256)
-        go(std::integral_constant<int, 256>{}, std::integral_constant<int, 1>{});
+        go(integral_constant<int, 256>{}, integral_constant<int, 1>{});
     else if (J <= 512)
-        go(std::integral_constant<int, 512>{}, std::integral_constant<int, 1>{});
+        few ? go(integral_constant<int, 512>{}, integral_constant<int, 1>{}) : go(integral_constant<int, 256>{}, integral_constant<int, 2>{});
     else if (J <= 1024)
-        go(std::integral_constant<int, 512>{}, std::integral_constant<int, 2>{});
+        few ? go(integral_constant<int, 512>{}, integral_constant<int, 2>{}) : go(integral_constant<int, 256>{}, integral_constant<int, 4>{});
+    else if (J <= 4096 && few)
+        go(integral_constant<int, 1024>{}, integral_constant<int, 4>{});
+    else if (J <= 2048)
+        go(integral_constant<int, 256>{}, integral_constant<int, 8>{});
     else if (J <= 4096)
-        go(std::integral_constant<int, 1024>{}, std::integral_constant<int, 4>{});
+        go(integral_constant<int, 256>{}, integral_constant<int, 16>{});
     else
-        go(std::integral_constant<int, 256>{}, std::integral_constant<int, 0>{});
+        go(integral_constant<int, 256>{}, integral_constant<int, 0>{});
     return hipGetLastError();
 }
 

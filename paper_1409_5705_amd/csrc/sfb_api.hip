@@ -914,7 +914,7 @@ int sfb_sdca_mlr_sf(sfb_ctx* ctx, const float* W, int64_t J, int64_t D, const fl
     g.epilogue = sfb::EPI_STORE;
     if (sfb::gemm_f32_partial_bytes(B, J, D) > 0) g.partial = reinterpret_cast<float*>(ctx->ws + round_up(B * J * 4));
     SFB_RUN(KID_GEMM_F32_STORE, sfb::launch_gemm_f32(g, ctx->stream));
-    SFB_RUN(KID_SDCA, sfb::launch_sdca_mlr(Zl, X, P, dU, B, J, D, lambda, N, beta, ctx->stream));
+    SFB_RUN(KID_SDCA, sfb::launch_sdca_mlr(Zl, X, P, dU, B, J, D, lambda, N, beta, ctx->dev.cus, ctx->stream));
     return SFB_OK;
 }
 
