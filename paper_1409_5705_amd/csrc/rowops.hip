@@ -1113,12 +1113,16 @@ hipError_t launch_power_iteration(const float* W, int64_t J, int64_t D, int iter
     const float b0 = 1.0f / sqrtf((float)D);
     hipError_t e = launch_fill_u32(b, __builtin_bit_cast(uint32_t, b0), D, stream);
     if (e != hipSuccess) return e;
-    const bool in_registers = rows == 16 && D <= 1024;
     auto aligned = [](const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; };
-    const bool vec = in_registers && D % 4 == 0 && J % 4 == 0 && aligned(W) && aligned(scratch) && aligned(spare);
-    // One launch per iteration where a workgroup adds up the partials faster than a launch of its own (3 us) does: up to
-    // 128 KB of them, and with a second array for them to alternate with.
-    const bool one_launch = in_registers && chunks > 1 && chunks * D <= 32768 && spare_floats >= chunks * D;
+    const bool vec = rows == 16 && D <= 1024 && D % 4 == 0 && J % 4 == 0 && aligned(W) && aligned(scratch) && aligned(spare);
+    // Unaligned rows of up to a float a thread: power_step_kernel waits for nothing longer (ten iterations, us, it / the rows in
+    // registers: 1000 x 61 82 / 98, 1000 x 255 97 / 104, 1000 x 301 112 / 106, 1000 x 1023 209 / 109).
+    const bool in_registers = vec || (rows == 16 && D <= 1024 && D > 256);
+    // One launch per iteration where a workgroup adds up the partials faster than a launch of its own (3 us) does, and with a
+    // second array for them to alternate with: up to 128 KB of them in 16-byte loads, of rows that are not so short that the
+    // adders of a column meet in a long chain (152 x 8 117 / 70 in two launches, 152 x 64 69 / 73); up to 20 KB otherwise
+    // (152 x 301 91 / 97, 1000 x 301 155 / 106).
+    const bool one_launch = in_registers && chunks > 1 && spare_floats >= chunks * D && (vec ? D >= 32 && chunks * D <= 32768 : chunks * D <= 5120);
     const float* from = b;
     int from_chunks = 1;
     for (int it = 0; it < iters; ++it) {
