@@ -9,11 +9,12 @@
 // against the SF index), so "U^T V" needs no transposed copy: a k-strided tile
 // is kept in LDS as it sits in memory.
 //
-// One workgroup of eight wavefronts (two per SIMD) owns one output tile.  Operands
-// go from global memory straight into LDS, several k-slices ahead; the wavefronts
-// divide the tile between them, and the k of every slice as well where the tile is
-// too small for eight (their partial sums meet in LDS at the end), so that a
-// contraction with few outputs and a long k fills the chip in one launch.
+// One workgroup of eight wavefronts (two per SIMD) owns one output tile; where its
+// walk over k is short, several workgroups share a CU.  Operands go from global memory
+// straight into LDS, several k-slices ahead; the wavefronts divide the tile between
+// them, and the k of every slice two, four or eight ways (their partial sums meet in
+// LDS at the end), so that a contraction with few outputs and a long k fills the chip
+// in one launch.
 //
 // What bounds it (MI355X, us of one launch in a row of dependent ones; in front of the
 // arrow the kernel this one replaced: four wavefronts of 32x32x2 MFMAs, a k-split over
@@ -23,7 +24,7 @@
 //   512 x 4096 x 1024  (both k-contiguous)   45 -> 40   32 in the loop, 27.9 at 2.4 GHz
 //   512 x 1024 x 4096  (k-contiguous x strided) 47 -> 43   k divided inside the workgroup, no second launch
 //   256 x 1000 x 2048                        21 -> 12
-//   100 x 1000 x 300                         14 -> 6.6  launch, first loads, epilogue: 5 us
+//   100 x 1000 x 300                         14 -> 4.9  launch, first loads, epilogue; two workgroups share a CU
 //   100 x 300 x 1000                         14 -> 5.7
 //   1003 x 2047 x 800 (nothing aligned)      60 -> 41
 //   100 x 1003 x 2047 (nothing aligned)      20 -> 14
