@@ -32,8 +32,7 @@
 // random operands runs at 2.40 GHz with the former and 2.23 with the latter.  Two
 // wavefronts per SIMD hide each other's LDS latency, barriers and load issue: a launch of
 // the first of these without any loads or reads in its loop takes 68 instead of 74 us.
-#include "device.h"
-#include "kernels.h"
+#include "gemm_f32.h"
 
 #include <cmath>
 #include <type_traits>
@@ -46,22 +45,7 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 constexpr int NWAVES = 8, NT = 64 * NWAVES;
 constexpr int LDS_CU = 160 * 1024, LDS_MAX = 152 * 1024;      // of a CU; of one workgroup
 
-struct Params {
-    const float* A;
-    const float* B;
-    float* C;
-    const float* aux;
-    const float* L_ptr;
-    int64_t lda, ldb, ldc;
-    int64_t M, N, K;
-    float eta, lambda;
-    int tiles_m, tiles_n;
-    int split_k;          // > 1: workgroup z of a tile covers k-slices [z * per_split, (z + 1) * per_split) and writes partial[z]
-    int64_t per_split;    // k-slices per split
-    float* partial;       // [split_k][M][N]
-    int num_xcd;
-    int group_m;          // raster: groups of group_m row-tiles, row-tile index fastest inside a group
-};
+typedef GemmF32Params Params;
 
 // A workgroup tile of BM x BN, WM x WN wavefronts over it and KW (at least two) over k: each wavefront multiplies a block
 // of 16 TA x 16 TB over its 16 of the KB = 16 KW values of k of a slice.
@@ -234,18 +218,6 @@ struct TailPart {
     }
 };
 
-template <int EPI>
-__device__ __forceinline__ float combine(float old, float acc, float eta, float invL, float th)
-{
-    if (EPI == EPI_RMW) return old - eta * acc;
-    if (EPI == EPI_RESID) return old - acc;
-    if (EPI == EPI_SHRINK) {
-        const float t = old + acc * invL;
-        return t > th ? t - th : (t < -th ? t + th : 0.f);
-    }
-    return acc;
-}
-
 template <class TL, bool A_KS, bool B_KS, int EPI, bool DIRECT>
 __global__ __launch_bounds__(NT, 2) void gemm_f32_kernel(Params p)
 {
@@ -259,20 +231,9 @@ __global__ __launch_bounds__(NT, 2) void gemm_f32_kernel(Params p)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kw = wave / (WM * WN), wm0 = ((wave / WN) % WM) * (16 * TA), wn0 = (wave % WN) * (16 * TB);
 
-    // tiles: each XCD (one L2) takes a contiguous range of a raster in which consecutive tiles form compact blocks
-    // (group_m row-tiles x as many column-tiles): the workgroups of an XCD walk k together, so a line of an operand
-    // panel is fetched into that L2 once and found there by the other tiles that share the panel
-    int64_t m0, n0;
-    {   // (32-bit: a 64-bit division is some hundred instructions in front of the first load)
-        const uint32_t tiles = gridDim.x, xcds = (uint32_t)p.num_xcd, tiles_n = (uint32_t)p.tiles_n, tiles_m = (uint32_t)p.tiles_m;
-        const uint32_t x = blockIdx.x % xcds, wi = blockIdx.x / xcds, q = tiles / xcds, r = tiles % xcds;
-        const uint32_t t = x * q + (x < r ? x : r) + wi;
-        const uint32_t per_group = (uint32_t)p.group_m * tiles_n;      // (<= tiles)
-        const uint32_t grp = t / per_group, rr = t % per_group, first = grp * (uint32_t)p.group_m;
-        const uint32_t gm = tiles_m - first < (uint32_t)p.group_m ? tiles_m - first : (uint32_t)p.group_m;
-        m0 = (int64_t)(first + rr % gm) * BM;
-        n0 = (int64_t)(rr / gm) * BN;
-    }
+    uint32_t tile_m, tile_n;
+    gemm_tile_of(p, tile_m, tile_n);
+    const int64_t m0 = (int64_t)tile_m * BM, n0 = (int64_t)tile_n * BN;
     const int64_t z = blockIdx.y;
     // slices of this workgroup: the whole ones [k_first, k_end) and, for the last split, the partial one, which comes
     // first (stage 0, through registers, under the latency of the direct loads of the others)
@@ -582,7 +543,7 @@ __global__ __launch_bounds__(NT, 2) void gemm_f32_kernel(Params p)
             float r[TB];
 #pragma unroll
             for (int b = 0; b < TB; ++b)
-                r[b] = direct ? v[b][e] : combine<EPI>(old[EPI == EPI_STORE ? 0 : i][e][b], v[b][e], p.eta, invL, th);
+                r[b] = direct ? v[b][e] : gemm_combine<EPI>(old[EPI == EPI_STORE ? 0 : i][e][b], v[b][e], p.eta, invL, th);
             float* dst = out + row * ldo + col;
             if (col + TB <= p.N) {
                 VecC w;
@@ -598,22 +559,40 @@ __global__ __launch_bounds__(NT, 2) void gemm_f32_kernel(Params p)
     }
 }
 
-// Sum of the k-splits in index order, then the epilogue.
+// Sum of the k-splits in index order, then the epilogue; four columns of a row a thread.
 template <int EPI>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(Params p)
 {
+    typedef typename Vec<4>::type V;
     float invL = 0.f, th = 0.f;
     if (EPI == EPI_SHRINK) {
         invL = 1.0f / p.L_ptr[0];
         th = p.lambda * invL;
     }
-    const int64_t total = p.M * p.N, stride = (int64_t)gridDim.x * 256;
+    const int64_t groups = (p.N + 3) / 4, total = p.M * groups, plane = p.M * p.N, stride = (int64_t)gridDim.x * 256;
+    const float* aux = EPI == EPI_RMW ? p.C : p.aux;      // (EPI_SHRINK, null: zeros)
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += stride) {
-        float sum = p.partial[i];
-        for (int z = 1; z < p.split_k; ++z) sum += p.partial[z * total + i];
-        const int64_t idx = i / p.N * p.ldc + i % p.N;
-        const float old = EPI == EPI_RMW ? p.C[idx] : (EPI == EPI_STORE || (EPI == EPI_SHRINK && !p.aux) ? 0.f : p.aux[idx]);
-        p.C[idx] = combine<EPI>(old, sum, p.eta, invL, th);
+        // (a 32-bit division where that is enough)
+        const int64_t row = total <= 0xffffffffLL ? (int64_t)((uint32_t)i / (uint32_t)groups) : i / groups, col = 4 * (i - row * groups);
+        const float* src = p.partial + row * p.N + col;
+        float* dst = p.C + row * p.ldc + col;
+        if (col + 4 <= p.N) {
+            V old = {0.f, 0.f, 0.f, 0.f};
+            if (EPI != EPI_STORE && (EPI != EPI_SHRINK || aux)) old = *reinterpret_cast<const V*>(aux + row * p.ldc + col);
+            V sum = *reinterpret_cast<const V*>(src);
+#pragma unroll 4
+            for (int z = 1; z < p.split_k; ++z) sum += *reinterpret_cast<const V*>(src + z * plane);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) sum[c] = gemm_combine<EPI>(old[c], sum[c], p.eta, invL, th);
+            *reinterpret_cast<V*>(dst) = sum;
+        } else {
+            for (int c = 0; col + c < p.N; ++c) {
+                float sum = src[c];
+                for (int z = 1; z < p.split_k; ++z) sum += src[z * plane + c];
+                const float old = EPI == EPI_STORE || (EPI == EPI_SHRINK && !aux) ? 0.f : aux[row * p.ldc + col + c];
+                dst[c] = gemm_combine<EPI>(old, sum, p.eta, invL, th);
+            }
+        }
     }
 }
 
@@ -695,24 +674,12 @@ hipError_t launch_tile(Params p, DeviceInfo& dev, int slot, int split, hipStream
     const int64_t nk = (p.K + TL::KB - 1) / TL::KB;
     p.per_split = split > 1 ? (nk + split - 1) / split : nk;
     p.split_k = split > 1 ? (int)((nk + p.per_split - 1) / p.per_split) : 1;      // (no empty split)
-    p.tiles_m = (int)tm;
-    p.tiles_n = (int)tn;
-    p.num_xcd = dev.xcds > 0 ? dev.xcds : 1;
-    {   // block of tiles per XCD with the fewest operand rows: group_m ~ sqrt(tiles per XCD * BN / BM)
-        const double per_xcd = (double)(tm * tn) / p.num_xcd;
-        int gm = (int)(sqrt(per_xcd * TL::BN / TL::BM) + 0.5);
-        if (gm < 1) gm = 1;
-        if (gm > tm) gm = (int)tm;
-        p.group_m = gm;
-    }
+    gemm_f32_raster(p, tm, tn, TL::BM, TL::BN, dev);
     hipLaunchKernelGGL((gemm_f32_kernel<TL, A_KS, B_KS, EPI, DIRECT>), dim3((unsigned)(tm * tn), (unsigned)p.split_k), dim3(NT),
                        TL::lds(DIRECT, p.per_split), stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.split_k <= 1) return e;
-    int64_t g = (p.M * p.N + 255) / 256;
-    if (g > 4096) g = 4096;
-    hipLaunchKernelGGL((splitk_reduce_kernel<EPI>), dim3((unsigned)g), dim3(256), 0, stream, p);
-    return hipGetLastError();
+    return launch_splitk_reduce(p, EPI, stream);
 }
 
 template <bool A_KS, bool B_KS, int EPI, bool DIRECT>
@@ -759,6 +726,33 @@ int gemm_f32_max_split(int64_t M, int64_t N, int64_t K)
 
 }  // namespace
 
+void gemm_f32_raster(Params& p, int64_t tiles_m, int64_t tiles_n, int BM, int BN, const DeviceInfo& dev)
+{
+    p.tiles_m = (int)tiles_m;
+    p.tiles_n = (int)tiles_n;
+    p.num_xcd = dev.xcds > 0 ? dev.xcds : 1;
+    // block of tiles per XCD with the fewest operand rows: group_m ~ sqrt(tiles per XCD * BN / BM)
+    const double per_xcd = (double)(tiles_m * tiles_n) / p.num_xcd;
+    int gm = (int)(sqrt(per_xcd * BN / BM) + 0.5);
+    if (gm < 1) gm = 1;
+    if (gm > tiles_m) gm = (int)tiles_m;
+    p.group_m = gm;
+}
+
+hipError_t launch_splitk_reduce(const Params& p, int epilogue, hipStream_t stream)
+{
+    int64_t g = (p.M * ((p.N + 3) / 4) + 255) / 256;
+    if (g > 4096) g = 4096;
+    const dim3 grid((unsigned)g), block(256);
+    switch (epilogue) {
+        case EPI_STORE: hipLaunchKernelGGL(splitk_reduce_kernel<EPI_STORE>, grid, block, 0, stream, p); break;
+        case EPI_RMW: hipLaunchKernelGGL(splitk_reduce_kernel<EPI_RMW>, grid, block, 0, stream, p); break;
+        case EPI_RESID: hipLaunchKernelGGL(splitk_reduce_kernel<EPI_RESID>, grid, block, 0, stream, p); break;
+        default: hipLaunchKernelGGL(splitk_reduce_kernel<EPI_SHRINK>, grid, block, 0, stream, p); break;
+    }
+    return hipGetLastError();
+}
+
 int64_t gemm_f32_partial_bytes(int64_t M, int64_t N, int64_t K)
 {
     const int s = gemm_f32_max_split(M, N, K);
@@ -782,6 +776,8 @@ hipError_t launch_gemm_f32(const GemmF32Args& a, hipStream_t stream)
     p.eta = a.eta; p.lambda = a.lambda;
     p.partial = a.partial;
     const GemmF32Plan plan = gemm_f32_plan(a);
+    const GemmF32x3Plan plan3 = gemm_f32x3_plan(a, a.partial ? gemm_f32_max_split(a.M, a.N, a.K) : 1);
+    if (plan3.tile >= 0 && plan3.us < plan.us) return launch_gemm_f32x3(a, p, plan3, stream);
     const bool aks = a.a_kstrided, bks = a.b_kstrided;
     if (!aks && !bks && a.epilogue == EPI_STORE) return launch_any<false, false, EPI_STORE>(p, *a.dev, 0, plan, stream);
     if (!aks && !bks && a.epilogue == EPI_SHRINK) return launch_any<false, false, EPI_SHRINK>(p, *a.dev, 1, plan, stream);

@@ -12,6 +12,7 @@ struct DeviceInfo {
     int xcds = 0;                                  // accelerator dies, one L2 each (workgroup ids go round-robin over them)
     bool gemm_bf16_lds_set[3] = {false, false, false};   // dynamic-LDS attribute of sf_gemm_kernel<mode> set on this device
     bool gemm_f32_lds_set[48] = {};                      // the same for the fp32 kernels (operand combination x load width x tile shape)
+    bool gemm_f32x3_lds_set[2] = {};                     // of the kernel on three bf16 terms, per tile shape
     bool fwd_stream_lds_set[6] = {};                     // and of the streaming bf16 forward
     int softmax_wait_polls = 1000;                 // bound of the one-read softmax's wait for a partner's word
 };

@@ -49,3 +49,24 @@ def gemm_f32(lib, kind, B, J, D):
         a.M, a.N, a.K, a.lda, a.ldb, a.ldc, a.a_kstrided, a.b_kstrided = J, D, B, J, D, D, True, True
     p = f(ctypes.byref(a))
     return TILES[p.tile], p.split, p.direct
+
+
+class _X3Plan(ctypes.Structure):         # GemmF32x3Plan of csrc/gemm_f32.h
+    _fields_ = [("tile", ctypes.c_int), ("split", ctypes.c_int), ("us", ctypes.c_double)]
+
+
+X3_TILES = ["128x64", "128x128"]
+
+
+def gemm_f32x3(lib, kind, B, J, D, max_split=8):
+    """(tile, k split) where the kernel on three bf16 terms takes that contraction, else None."""
+    f = lib._ZN3sfb15gemm_f32x3_planERKNS_11GemmF32ArgsEi
+    f.restype, f.argtypes = _X3Plan, [ctypes.c_void_p, ctypes.c_int]
+    g = lib._ZN3sfb13gemm_f32_planERKNS_11GemmF32ArgsE
+    g.restype, g.argtypes = _GemmPlan, [ctypes.c_void_p]
+    dev = (ctypes.c_int * 64)(CUS, 8)
+    a = _GemmArgs(A=4096, B=4096, partial=4096, dev=ctypes.addressof(dev))
+    if kind == "apply":
+        a.M, a.N, a.K, a.lda, a.ldb, a.ldc, a.a_kstrided, a.b_kstrided, a.epilogue = J, D, B, J, D, D, True, True, 1
+    p = f(ctypes.byref(a), max_split)
+    return (X3_TILES[p.tile], p.split) if p.tile >= 0 and p.us < g(ctypes.byref(a)).us else None

@@ -34,3 +34,12 @@ def test_sparse_code_shapes(lib, kind):
     plans = [K.gemm_f32(lib, kind, B, J, D) for J, D, B in f32.SC_SHAPES + [(1001, 301, 99), (64, 4, 3)]]
     assert {(t, direct) for t, _, direct in plans} == {(t, direct) for t in K.TILES for direct in (False, True)}
     assert len({t for t, split, _ in plans if split > 1}) >= 2
+
+
+def test_three_term_shapes(lib):
+    import test_gpu_gemm_f32x3 as x3
+    plans = [K.gemm_f32x3(lib, "apply", N, J, D) for J, D, N in x3.APPLY_SHAPES]
+    assert all(plans) and all(K.gemm_f32x3(lib, "apply", N, J, D) for J, D, N in [(1003, 2047, 300), (1001, 2049, 333)]), list(zip(x3.APPLY_SHAPES, plans))
+    assert {(t, split > 1) for t, split in plans} == {(t, s) for t in K.X3_TILES for s in (False, True)}
+    assert {K.gemm_f32(lib, "apply", N, J, D)[::2] for J, D, N in x3.FP32_SHAPES} == {("128x64", True), ("128x64", False)}
+    assert not any(K.gemm_f32x3(lib, "apply", N, J, D) for J, D, N in x3.FP32_SHAPES)
