@@ -765,6 +765,23 @@ GemmF32Plan gemm_f32_plan(const GemmF32Args& a)
     return plan_gemm(a.M, a.N, a.K, a.dev->cus > 0 ? a.dev->cus : 256, max_split, direct_loads(a));
 }
 
+namespace {
+// The kernel on three bf16 terms where its estimate is the lower one (tile >= 0).
+GemmF32x3Plan x3_plan(const GemmF32Args& a, const GemmF32Plan& plan)
+{
+    GemmF32x3Plan x3 = gemm_f32x3_plan(a, a.partial ? gemm_f32_max_split(a.M, a.N, a.K) : 1);
+    if (x3.us >= plan.us) x3.tile = -1;
+    return x3;
+}
+}  // namespace
+
+double gemm_f32_estimate_us(const GemmF32Args& a)
+{
+    const GemmF32Plan plan = gemm_f32_plan(a);
+    const GemmF32x3Plan x3 = x3_plan(a, plan);
+    return x3.tile >= 0 ? x3.us : plan.us;
+}
+
 hipError_t launch_gemm_f32(const GemmF32Args& a, hipStream_t stream)
 {
     if (a.M <= 0 || a.N <= 0) return hipSuccess;
@@ -776,8 +793,8 @@ hipError_t launch_gemm_f32(const GemmF32Args& a, hipStream_t stream)
     p.eta = a.eta; p.lambda = a.lambda;
     p.partial = a.partial;
     const GemmF32Plan plan = gemm_f32_plan(a);
-    const GemmF32x3Plan plan3 = gemm_f32x3_plan(a, a.partial ? gemm_f32_max_split(a.M, a.N, a.K) : 1);
-    if (plan3.tile >= 0 && plan3.us < plan.us) return launch_gemm_f32x3(a, p, plan3, stream);
+    const GemmF32x3Plan x3 = x3_plan(a, plan);
+    if (x3.tile >= 0) return launch_gemm_f32x3(a, p, x3, stream);
     const bool aks = a.a_kstrided, bks = a.b_kstrided;
     if (!aks && !bks && a.epilogue == EPI_STORE) return launch_any<false, false, EPI_STORE>(p, *a.dev, 0, plan, stream);
     if (!aks && !bks && a.epilogue == EPI_SHRINK) return launch_any<false, false, EPI_SHRINK>(p, *a.dev, 1, plan, stream);

@@ -11,9 +11,10 @@
 //
 // One workgroup of four wavefronts, one per SIMD, owns an output tile; each wavefront multiplies 128 x 64 of it over its
 // own blocks of 32 of k (KW wavefronts take turns), and the partial sums meet in LDS at the end.  No wavefront shares
-// operand data with another, so the loop has no LDS and no barrier: a lane loads what it multiplies (16 bytes a lane
-// along the rows of a k-strided operand, 512 contiguous bytes per 32 lanes), two steps of 16 ahead, cuts it into its terms between the
-// MFMAs (11 instructions per pair; 5.5 of them per MFMA of 32 cycles, which hides that many) and multiplies.
+// operand data with another, so the loop has no barrier.  Two k-strided operands: a lane loads what it multiplies (16
+// bytes a lane along the rows, 512 contiguous bytes per 32 lanes), two steps of 16 ahead.  Otherwise a wavefront brings a
+// block of its operands into LDS of its own while it multiplies the one before.  It cuts the values into their terms
+// between the MFMAs (11 instructions per pair; 5.5 of them per MFMA of 32 cycles, which hides that many).
 //
 // 32x32x16 rather than 16x16x32 MFMAs: the latter hide two vector instructions each, and the loop has three times as many.
 //
@@ -42,8 +43,8 @@ constexpr int NT = 256;
 template <int WN_, int KW_>
 struct Tile {
     static constexpr int WN = WN_, KW = KW_, BM = 32 * TA, BN = 32 * TB * WN;
-    static constexpr int LDS = KW * BM * BN * 4;      // the partial sums
-    static_assert(WN * KW * 64 == NT, "four wavefronts");
+    static constexpr int LDS = KW * BM * BN * 4;      // the partial sums (or, before, 24 KB a wavefront)
+    static_assert(WN * KW * 64 == NT && LDS >= 4 * 4096 * (TA + TB), "four wavefronts");
 };
 
 // The three terms of eight values of k of a row, packed as MFMA operands.
@@ -67,44 +68,12 @@ __device__ __forceinline__ void cut_pair(float x0, float x1, Terms& s, int i)
     s.t[2][i] = pack_bf16(s0, s1);
 }
 
-// One operand of a wavefront ([k][rows]): 32 T rows.  Lane (l32, half) holds of MFMA tile x the row T l32 + x and the k
-// 8 half .. + 7 of a step of 16; a block is two steps.  Loads go through a buffer descriptor that ends with the matrix:
-// what lies behind its end reads as zero, and rows past the last one reach only elements of C that are not stored.
+// What both kinds of operands have of a wavefront's 32 T rows: lane (l32, half) holds of MFMA tile x the row T l32 + x and
+// the k 8 half .. + 7 of a step of 16; a block is two steps.
 template <int T>
-struct Operand {
+struct Raw {
     float raw[2][T][8];      // two steps
-    uint32_t voff, ld4;
-    uint64_t base, end;      // uniform
 
-    __device__ __forceinline__ void init(const float* P, int64_t ld, int64_t row0, int64_t rows, int64_t K, int l32, int half)
-    {
-        ld4 = (uint32_t)ld * 4u;
-        base = uniform64(reinterpret_cast<uint64_t>(P) + (uint64_t)row0 * 4);
-        end = uniform64(reinterpret_cast<uint64_t>(P) + (uint64_t)((K - 1) * ld + rows) * 4);
-        voff = 8u * half * ld4 + 4u * T * l32;
-    }
-    __device__ __forceinline__ Rsrc at(int block) const
-    {
-        const uint64_t b = uniform64(base + (uint64_t)block * 32 * ld4);
-        const uint64_t left = b < end ? end - b : 0;
-        return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(b), 0, left > 0xffffffffu ? 0xffffffffu : (uint32_t)left, 0x00020000);
-    }
-    // step j of the block at r
-    __device__ __forceinline__ void load(Rsrc r, int j, int slot)
-    {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            if (T == 4) {
-                const uintx4 v = __builtin_amdgcn_raw_buffer_load_b128(r, voff, (16u * j + i) * ld4, 0);
-#pragma unroll
-                for (int x = 0; x < T; ++x) raw[slot][x][i] = __uint_as_float(v[x & 3]);
-            } else {
-                const uintx2 v = __builtin_amdgcn_raw_buffer_load_b64(r, voff, (16u * j + i) * ld4, 0);
-#pragma unroll
-                for (int x = 0; x < T; ++x) raw[slot][x][i] = __uint_as_float(v[x & 1]);
-            }
-        }
-    }
     // pair i (values 2 i, 2 i + 1) of the terms of tile x; MASKED: zeros from value `left` of the step on
     template <bool MASKED>
     __device__ __forceinline__ void cut(Terms& s, int x, int slot, int i, int left, int half) const
@@ -117,7 +86,127 @@ struct Operand {
     }
 };
 
-template <class TL, int EPI>
+// Loads go through a buffer descriptor that ends with the matrix: what lies behind its end is not read (and masked), and
+// rows past the last one reach only elements of C that are not stored.
+template <bool KS>
+struct Extent {
+    uint64_t base, end;      // uniform
+    uint32_t ld4;
+    __device__ __forceinline__ void init(const float* P, int64_t ld, int64_t row0, int64_t rows, int64_t K)
+    {
+        ld4 = (uint32_t)ld * 4u;
+        base = uniform64(reinterpret_cast<uint64_t>(P) + (uint64_t)(KS ? row0 : row0 * ld) * 4);
+        end = uniform64(reinterpret_cast<uint64_t>(P) + (uint64_t)(KS ? (K - 1) * ld + rows : (rows - 1) * ld + K) * 4);
+    }
+    __device__ __forceinline__ uint64_t start(int block) const { return uniform64(base + (uint64_t)block * (KS ? 32 * (uint64_t)ld4 : 128)); }
+    __device__ __forceinline__ uint32_t bytes(uint64_t b) const
+    {
+        const uint64_t left = b < end ? end - b : 0;
+        return left > 0xffffffffu ? 0xffffffffu : (uint32_t)left;
+    }
+};
+
+// An operand that is strided along k ([k][rows]): a lane loads what it multiplies, at any alignment.
+template <int T>
+struct StridedOperand : Raw<T> {
+    Extent<true> ext;
+    uint32_t voff;
+
+    __device__ __forceinline__ void init(const float* P, int64_t ld, int64_t row0, int64_t rows, int64_t K, int lane)
+    {
+        ext.init(P, ld, row0, rows, K);
+        voff = 8u * (lane >> 5) * ext.ld4 + 4u * T * (lane & 31);
+    }
+    __device__ __forceinline__ Rsrc at(int block) const
+    {
+        const uint64_t b = ext.start(block);
+        return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(b), 0, ext.bytes(b), 0x00020000);
+    }
+    // step j of the block at r
+    __device__ __forceinline__ void load(Rsrc r, int j, int slot)
+    {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            if (T == 4) {
+                const uintx4 v = __builtin_amdgcn_raw_buffer_load_b128(r, voff, (16u * j + i) * ext.ld4, 0);
+#pragma unroll
+                for (int x = 0; x < T; ++x) this->raw[slot][x][i] = __uint_as_float(v[x & 3]);
+            } else {
+                const uintx2 v = __builtin_amdgcn_raw_buffer_load_b64(r, voff, (16u * j + i) * ext.ld4, 0);
+#pragma unroll
+                for (int x = 0; x < T; ++x) this->raw[slot][x][i] = __uint_as_float(v[x & 1]);
+            }
+        }
+    }
+};
+
+// An operand whose rows are 16-byte aligned, by way of the wavefront's own LDS (4 KB for 32 rows and a block, no other
+// wavefront reads it).  Loading k-contiguous rows lane by lane as they are multiplied costs the address unit 72 cycles
+// per kilobyte (32 rows at the same offset), direct loads of eight lanes a row 16.
+//   k-contiguous: a unit is a tile, 32 rows of 128 bytes, the 16-byte chunks of row r swizzled by swz(r);
+//   k-strided (T = 2): a unit is a step, 16 rows of 64 columns as in memory.
+template <int T, bool KS>
+struct LdsOperand : Raw<T> {
+    Extent<KS> ext;
+    uint32_t voff[KS ? 1 : 4];       // of the direct loads
+    uint32_t from[KS ? 1 : 4];       // of the LDS reads
+    uint32_t lds;                    // of the first unit (uniform)
+
+    __device__ __forceinline__ void init(const float* P, int64_t ld, int64_t row0, int64_t rows, int64_t K, int lane, uint32_t lds_at)
+    {
+        ext.init(P, ld, row0, rows, K);
+        lds = lds_at;
+        const int l32 = lane & 31, half = lane >> 5;
+        if (KS) {
+            voff[0] = (lane >> 4) * ext.ld4 + 16u * (lane & 15);
+            from[0] = 8u * half * 256 + 8u * l32;
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                voff[KS ? 0 : i] = T * (lane >> 3) * ext.ld4 + 16u * ((lane & 7) ^ swz(8 * i + (lane >> 3)));
+                from[KS ? 0 : i] = l32 * 128u + (((4 * (i >> 1) + 2 * half + (i & 1)) ^ swz(l32)) << 4);
+            }
+        }
+    }
+    __device__ __forceinline__ uintx4 at(int block) const
+    {
+        const uint64_t b = ext.start(block);
+        return uintx4{(uint32_t)b, (uint32_t)(b >> 32) & 0xffffu, (uint32_t)__builtin_amdgcn_readfirstlane((int)ext.bytes(b)), 0x00020000u};
+    }
+    // request q of the 4 T of a block
+    __device__ __forceinline__ void request(uintx4 r, int q)
+    {
+        const uint32_t dst = lds + 1024u * q, v = voff[KS ? 0 : q % 4];
+        const uint32_t soff = KS ? 4u * q * ext.ld4 : (T * 8u * (q % 4) + q / 4) * ext.ld4;
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(dst), "v"(v), "s"(r), "s"(soff) : "memory");
+    }
+    // both steps of tiles x0 .. x1 - 1 (k-strided: of both tiles)
+    __device__ __forceinline__ void read(int x0, int x1)
+    {
+        typedef __attribute__((address_space(3))) const char* LdsPtr;
+        if (KS) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const floatx2 v = *reinterpret_cast<__attribute__((address_space(3))) const floatx2*>((LdsPtr)(uintptr_t)(lds + from[0] + 4096u * j + 256u * i));
+#pragma unroll
+                    for (int x = 0; x < T; ++x) this->raw[j][x][i] = v[x & 1];
+                }
+        } else {
+#pragma unroll
+            for (int x = x0; x < x1; ++x)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const floatx4 v = *reinterpret_cast<__attribute__((address_space(3))) const floatx4*>((LdsPtr)(uintptr_t)(lds + from[KS ? 0 : q] + 4096u * x));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) this->raw[q >> 1][x][4 * (q & 1) + e] = v[e];
+                }
+        }
+    }
+};
+
+template <class TL, bool A_KS, bool B_KS, int EPI>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_f32x3_kernel(GemmF32Params p)
 {
     constexpr int WN = TL::WN, KW = TL::KW, BM = TL::BM, BN = TL::BN;
@@ -145,13 +234,38 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1))) void
             for (int e = 0; e < 16; ++e) acc[a][b][e] = cor[a][b][e] = 0.f;
 
     if (n > 0) {
-        Operand<TA> A;
-        Operand<TB> B;
-        A.init(p.A, p.lda, m0, p.M, p.K, l32, half);
-        B.init(p.B, p.ldb, n0 + wn0, p.N, p.K, l32, half);
+        constexpr bool LDS = !A_KS;      // (rows are 16-byte aligned then)
+        typename std::conditional<LDS, LdsOperand<TA, A_KS>, StridedOperand<TA>>::type A;
+        typename std::conditional<LDS, LdsOperand<TB, B_KS>, StridedOperand<TB>>::type B;
         const int first = tail ? all - 1 : b0 + kw, lim = tail ? left : 32;
         const int second = n < 2 ? first : (tail ? b0 + kw : b0 + kw + KW);      // (no further block: the last one again)
-        {
+        // (LDS) the 24 requests of a block, B and A tile 0 first, in four parts
+        [[maybe_unused]] auto request = [&](auto ra, auto rb, auto part_) {
+            if constexpr (LDS) {
+                constexpr int part = decltype(part_)::value;
+#pragma unroll
+                for (int q = 6 * part; q < 6 * part + 6; ++q) {
+                    if (q < 4 * TB)
+                        B.request(rb, q);
+                    else
+                        A.request(ra, q - 4 * TB);
+                }
+            }
+        };
+        if constexpr (LDS) {
+            const uint32_t at0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)x3_smem + (uint32_t)wave * (4096u * (TA + TB));
+            A.init(p.A, p.lda, m0, p.M, p.K, lane, at0 + 4096u * TB);
+            B.init(p.B, p.ldb, n0 + wn0, p.N, p.K, lane, at0);
+            const uintx4 ra = A.at(first), rb = B.at(first);
+            static_for<0, 4>([&](auto part) { request(ra, rb, part); });
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            B.read(0, TB);
+            A.read(0, TA);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            request(A.at(second), B.at(second), std::integral_constant<int, 0>{});
+        } else {
+            A.init(p.A, p.lda, m0, p.M, p.K, lane);
+            B.init(p.B, p.ldb, n0 + wn0, p.N, p.K, lane);
             const Rsrc ra = A.at(first), rb = B.at(first);
             B.load(rb, 0, 0);
             A.load(ra, 0, 0);
@@ -166,7 +280,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1))) void
             for (int b = 0; b < TB; ++b) B.template cut<true>(bt[0][b], b, 0, i, lim, half);
             A.template cut<true>(at[0], 0, 0, i, lim, half);
         }
-        B.load(B.at(second), 0, 0);
+        if constexpr (!LDS) B.load(B.at(second), 0, 0);
         auto products = [&](const Terms& ta, const Terms& tb, floatx16& ac, floatx16& co) {
             constexpr int PA[6] = {2, 0, 0, 1, 1, 0}, PB[6] = {0, 2, 0, 1, 0, 1};
 #pragma unroll
@@ -181,9 +295,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1))) void
             __builtin_amdgcn_sched_barrier(0);
         };
         // One block: eight phases a step, the six products of one MFMA tile each.  Beside them 24 pairs are cut, three a
-        // phase: of A tiles 1, 2, 3 and, for the next step, of B tiles 0, 1 and A tile 0.  A step's raw values are
-        // requested again (for the step behind the next; B for the one behind that) as soon as all of them are cut.
-        auto block = [&](auto first_tag, Rsrc a_next, Rsrc b_next, Rsrc b_after) {
+        // phase: of A tiles 1, 2, 3 and, for the next step, of B tiles 0, 1 and A tile 0.  Raw values follow as soon as
+        // those of both steps (by way of LDS) or of a step are cut: the block behind this one is read from LDS, where it
+        // has been on its way for a step, and the one behind that requested; or a step's values are loaded for the step
+        // behind the next (B: for the one behind that).
+        auto block = [&](auto first_tag, auto a_next, auto b_next, auto a_after, auto b_after) {
             constexpr bool FIRST = decltype(first_tag)::value;
             static_for<0, 2>([&](auto j_) {
                 constexpr int j = decltype(j_)::value;
@@ -201,21 +317,37 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1))) void
                 static_for<0, 8>([&](auto ph_) {
                     constexpr int ph = decltype(ph_)::value, a = ph / 2, b = (a & 1) ? 1 - ph % 2 : ph % 2;
                     static_for<3 * ph, 3 * ph + 3>(cut);
-                    if constexpr (ph == 4) A.load(a_next, j, j);
-                    if constexpr (ph == 7) B.load(j ? b_after : b_next, j ^ 1, j ^ 1);
+                    if constexpr (!LDS) {
+                        if constexpr (ph == 4) A.load(a_next, j, j);
+                        if constexpr (ph == 7) B.load(j ? b_after : b_next, j ^ 1, j ^ 1);
+                    } else if constexpr (j == 0) {
+                        if constexpr (ph < 3) request(a_next, b_next, std::integral_constant<int, ph + 1>{});
+                    } else if constexpr (ph == 0) {
+                        asm volatile("s_waitcnt vmcnt(12)" ::: "memory");      // (all but A tiles 1 to 3)
+                        B.read(0, TB);
+                        A.read(0, 1);
+                    } else if constexpr (ph == 4) {
+                        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                        A.read(1, TA);
+                    } else if constexpr (ph == 7) {
+                        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // (read out: the LDS is free again)
+                        request(a_after, b_after, std::integral_constant<int, 0>{});
+                    }
                     products(at[(j + a) % 3], bt[j][b], acc[a][b], cor[a][b]);
                 });
             });
             at[0] = at[2];
         };
         int next = n < 3 ? second : second + KW;
-        block(std::true_type{}, A.at(second), B.at(second), B.at(next));
+        block(std::true_type{}, A.at(second), B.at(second), A.at(next), B.at(next));
         for (int i = 1; i < n; ++i) {
             const int after = i + 2 < n ? next + KW : next;
-            block(std::false_type{}, A.at(next), B.at(next), B.at(after));
+            block(std::false_type{}, A.at(next), B.at(next), A.at(after), B.at(after));
             next = after;
         }
+        if (LDS) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // (requested once too often: the sums go there)
     }
+    if (!A_KS) __syncthreads();
 
     // ---- the partial sums meet in LDS as [kw][row][column]; a thread takes four neighbouring columns of a row
     float* const meet = reinterpret_cast<float*>(x3_smem);
@@ -289,12 +421,12 @@ typedef Tile<1, 4> X0;      // 128 x 64
 typedef Tile<2, 2> X1;      // 128 x 128
 constexpr int NTILES = 2;
 
-template <class TL, int EPI>
-hipError_t launch_tile(GemmF32Params& p, DeviceInfo& dev, int slot, int split, hipStream_t stream)
+template <class TL, bool A_KS, bool B_KS, int EPI>
+hipError_t launch_tile(GemmF32Params p, DeviceInfo& dev, int slot, int split, hipStream_t stream)
 {
     const int64_t tm = (p.M + TL::BM - 1) / TL::BM, tn = (p.N + TL::BN - 1) / TL::BN;
     if (!dev.gemm_f32x3_lds_set[slot]) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_f32x3_kernel<TL, EPI>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_f32x3_kernel<TL, A_KS, B_KS, EPI>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, TL::LDS);
         if (e != hipSuccess) return e;
         dev.gemm_f32x3_lds_set[slot] = true;
@@ -303,10 +435,17 @@ hipError_t launch_tile(GemmF32Params& p, DeviceInfo& dev, int slot, int split, h
     p.per_split = split > 1 ? (blocks + split - 1) / split : blocks;
     p.split_k = split > 1 ? (int)((blocks + p.per_split - 1) / p.per_split) : 1;      // (no empty split)
     gemm_f32_raster(p, tm, tn, TL::BM, TL::BN, dev);
-    hipLaunchKernelGGL((gemm_f32x3_kernel<TL, EPI>), dim3((unsigned)(tm * tn), (unsigned)p.split_k), dim3(NT), TL::LDS, stream, p);
+    hipLaunchKernelGGL((gemm_f32x3_kernel<TL, A_KS, B_KS, EPI>), dim3((unsigned)(tm * tn), (unsigned)p.split_k), dim3(NT), TL::LDS, stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.split_k <= 1) return e;
     return launch_splitk_reduce(p, EPI, stream);
+}
+
+template <bool A_KS, bool B_KS, int EPI>
+hipError_t launch_any(const GemmF32Params& p, DeviceInfo& dev, int combo, const GemmF32x3Plan& plan, hipStream_t stream)
+{
+    if (plan.tile == 0) return launch_tile<X0, A_KS, B_KS, EPI>(p, dev, combo * NTILES, plan.split, stream);
+    return launch_tile<X1, A_KS, B_KS, EPI>(p, dev, combo * NTILES + 1, plan.split, stream);
 }
 
 }  // namespace
@@ -318,13 +457,16 @@ hipError_t launch_tile(GemmF32Params& p, DeviceInfo& dev, int slot, int split, h
 // two was 13.1 % faster in the mean than that kernel alone, the better one each time 13.2 %.  fp32 kernel / this one (us):
 //   1000 x 2048, 2048 pairs 77 / 50    4096 x 4096, 2048 483 / 339    1003 x 2047, 800 43 / 29    1024 x 4096, 512 41 / 30
 //   616 x 2488, 327 19 / 17            1720 x 208, 1531 19.2 / 19.0   284 x 850, 1340 14.8 / 16.3  1561 x 5818, 37 34 / 39
-// What is within 3 % stays with the fp32 kernel.
+// What is within 3 % stays with the fp32 kernel.  The same constants hold for operands that come by way of LDS (58 shapes,
+// rms 7 %): 512 x 4096 over 1024 42 / 30, 512 x 1024 over 4096 42 / 33 and (k-strided B) 44 / 34 with a k-split of four,
+// 454 x 2559 over 476 21 / 16, 256 x 1000 over 2048 13.0 / 18.2 (loading them lane by lane: 35, 39 and 36 of the first three).
 GemmF32x3Plan gemm_f32x3_plan(const GemmF32Args& a, int max_split)
 {
     GemmF32x3Plan best = {-1, 1, 1e30};
-    if (!a.a_kstrided || !a.b_kstrided || a.epilogue != EPI_RMW) return best;
-    // a handful of blocks of k for a wavefront (with 128 pairs it was never faster); 32-bit offsets inside a block
-    if (a.K < 160 || a.K > (1LL << 30) || a.lda >= (1LL << 24) || a.ldb >= (1LL << 24)) return best;
+    // a handful of blocks of k for a wavefront (with 128 pairs it was never faster); 32-bit offsets inside a block and tile
+    if (a.K < 160 || a.K > (1LL << 30) || a.lda >= (1LL << 22) || a.ldb >= (1LL << 22)) return best;
+    auto aligned = [](const float* P, int64_t ld) { return ld % 4 == 0 && reinterpret_cast<uintptr_t>(P) % 16 == 0; };
+    if (!a.a_kstrided && !(aligned(a.A, a.lda) && aligned(a.B, a.ldb))) return best;      // (direct loads)
     static const double own[NTILES] = {5.1, 10.1}, step[NTILES] = {2.07, 2.02};
     const int cus = a.dev->cus > 0 ? a.dev->cus : 256;
     const int64_t blocks = (a.K + 31) / 32;
@@ -345,8 +487,12 @@ GemmF32x3Plan gemm_f32x3_plan(const GemmF32Args& a, int max_split)
 
 hipError_t launch_gemm_f32x3(const GemmF32Args& a, GemmF32Params p, const GemmF32x3Plan& plan, hipStream_t stream)
 {
-    if (plan.tile == 0) return launch_tile<X0, EPI_RMW>(p, *a.dev, 0, plan.split, stream);
-    return launch_tile<X1, EPI_RMW>(p, *a.dev, 1, plan.split, stream);
+    const bool aks = a.a_kstrided, bks = a.b_kstrided;
+    if (!aks && !bks && a.epilogue == EPI_STORE) return launch_any<false, false, EPI_STORE>(p, *a.dev, 0, plan, stream);
+    if (!aks && !bks && a.epilogue == EPI_SHRINK) return launch_any<false, false, EPI_SHRINK>(p, *a.dev, 1, plan, stream);
+    if (!aks && bks && a.epilogue == EPI_RESID) return launch_any<false, true, EPI_RESID>(p, *a.dev, 2, plan, stream);
+    if (aks && bks && a.epilogue == EPI_RMW) return launch_any<true, true, EPI_RMW>(p, *a.dev, 3, plan, stream);
+    return hipErrorInvalidValue;
 }
 
 }  // namespace sfb

@@ -12,7 +12,7 @@ struct DeviceInfo {
     int xcds = 0;                                  // accelerator dies, one L2 each (workgroup ids go round-robin over them)
     bool gemm_bf16_lds_set[3] = {false, false, false};   // dynamic-LDS attribute of sf_gemm_kernel<mode> set on this device
     bool gemm_f32_lds_set[48] = {};                      // the same for the fp32 kernels (operand combination x load width x tile shape)
-    bool gemm_f32x3_lds_set[2] = {};                     // of the kernel on three bf16 terms, per tile shape
+    bool gemm_f32x3_lds_set[8] = {};                     // of the kernel on three bf16 terms (operand combination x tile shape)
     bool fwd_stream_lds_set[6] = {};                     // and of the streaming bf16 forward
     int softmax_wait_polls = 1000;                 // bound of the one-read softmax's wait for a partner's word
 };
@@ -49,8 +49,11 @@ struct GemmF32Args {
     DeviceInfo* dev;     // the context's device facts
 };
 hipError_t launch_gemm_f32(const GemmF32Args& a, hipStream_t stream);
-// How that launch does it (a.dev is needed): the tile shape by its index in gemm_f32.hip, the ways k is divided over
-// workgroups, direct-to-LDS loads or loads through registers, and the estimated duration.
+// Estimated duration (us) of that launch (a.dev is needed).
+double gemm_f32_estimate_us(const GemmF32Args& a);
+// How the fp32 matrix pipes do it: the tile shape by its index in gemm_f32.hip, the ways k is divided over
+// workgroups, direct-to-LDS loads or loads through registers, and the estimated duration.  (Where the bf16 pipes on three
+// terms per value are estimated faster, launch_gemm_f32 takes those: gemm_f32x3.hip.)
 struct GemmF32Plan {
     int tile, split;
     bool direct;

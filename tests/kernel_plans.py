@@ -66,7 +66,11 @@ def gemm_f32x3(lib, kind, B, J, D, max_split=8):
     g.restype, g.argtypes = _GemmPlan, [ctypes.c_void_p]
     dev = (ctypes.c_int * 64)(CUS, 8)
     a = _GemmArgs(A=4096, B=4096, partial=4096, dev=ctypes.addressof(dev))
-    if kind == "apply":
+    if kind == "logits":
+        a.M, a.N, a.K, a.lda, a.ldb, a.ldc = B, J, D, D, D, J
+    elif kind == "residual":
+        a.M, a.N, a.K, a.lda, a.ldb, a.ldc, a.b_kstrided, a.epilogue = B, D, J, J, D, D, True, 2
+    else:
         a.M, a.N, a.K, a.lda, a.ldb, a.ldc, a.a_kstrided, a.b_kstrided, a.epilogue = J, D, B, J, D, D, True, True, 1
     p = f(ctypes.byref(a), max_split)
     return (X3_TILES[p.tile], p.split) if p.tile >= 0 and p.us < g(ctypes.byref(a)).us else None

@@ -89,6 +89,50 @@ def test_rows_of_a_larger_matrix_and_alignment(ctx):
     assert bool(torch.all((W.double() - ref).abs() <= (N + 4) * EPS * size + 2 * EPS * ref.abs() + 1e-30))
 
 
+# (J, D, B): logits of B samples and projections are J columns over D of k, residuals D columns over J; test_kernel_plans.py
+# asserts that these reach both tile shapes, whole and with a k-split
+LOGITS_SHAPES = [(3476, 236, 295), (4096, 1024, 512), (1028, 4004, 517), (2548, 304, 770), (2732, 4148, 177)]
+SC_SHAPES = [(4096, 1024, 512), (2196, 2140, 98), (244, 3620, 275), (292, 2752, 714), (4120, 1824, 264), (3476, 236, 295)]
+
+
+@pytest.mark.parametrize("J,D,B", LOGITS_SHAPES)
+def test_projection(ctx, J, D, B):
+    """U = 2 (X - Y) W^T of similar pairs: two k-contiguous operands, stored as they come."""
+    import paper_1409_5705_amd as sfb
+    print("projection", J, D, B, flush=True)
+    W, X = 0.1 * normal(13, J, D), normal(14, B, D)
+    U, V = torch.empty(B, J, device="cuda:0"), torch.empty(B, D, device="cuda:0")
+    ctx.sfb_compute_sf(sfb.SFB_DML, W, X, Y=torch.zeros_like(X), sim=torch.ones(B, dtype=torch.int8, device="cuda:0"), U=U, V=V)
+    ref = 2.0 * (X.double() @ W.double().t())
+    size = 2.0 * (X.abs().double() @ W.abs().double().t())
+    assert bool(torch.all((U.double() - ref).abs() <= (D + 2) * EPS * size + 1e-30))
+
+
+@pytest.mark.parametrize("J,D,B", SC_SHAPES)
+def test_sparse_codes(ctx, J, D, B):
+    """The residual (k-contiguous x k-strided) and shrink epilogues: three ISTA iterations against 64-bit torch."""
+    import paper_1409_5705_amd as sfb
+    print("sparse codes", J, D, B, flush=True)
+    W, X = normal(15, J, D), normal(16, B, D)
+    W /= W.norm(dim=1, keepdim=True)
+    U, V = torch.empty(B, J, device="cuda:0"), torch.empty(B, D, device="cuda:0")
+    lam, iters = 0.1, 3
+    ctx.sfb_compute_sf(sfb.SFB_SC, W, X, U=U, V=V, lam=lam, ista_iters=iters, power_iters=10)
+    W64, X64 = W.double(), X.double()
+    b = torch.full((D,), D ** -0.5, dtype=torch.float64, device="cuda:0")
+    for _ in range(10):
+        b = W64.t() @ (W64 @ (b / b.norm()))
+    L = b.norm()
+    a, r = torch.zeros((B, J), dtype=torch.float64, device="cuda:0"), X64
+    for _ in range(iters):
+        t = a + r @ W64.t() / L
+        a = torch.sign(t) * torch.clamp(t.abs() - lam / L, min=0.0)
+        r = X64 - a @ W64
+    for got, want in ((U, a), (V, r)):
+        err = (got.double() - want).abs() / (want.abs() + want.square().mean().sqrt())
+        assert float(err.max()) <= 1e-4
+
+
 # few pairs: the 128 x 64 tiles of the fp32 kernel keep these (test_kernel_plans.py)
 FP32_SHAPES = [(1104, 1580, 31), (1107, 1583, 30)]
 

@@ -43,3 +43,10 @@ def test_three_term_shapes(lib):
     assert {(t, split > 1) for t, split in plans} == {(t, s) for t in K.X3_TILES for s in (False, True)}
     assert {K.gemm_f32(lib, "apply", N, J, D)[::2] for J, D, N in x3.FP32_SHAPES} == {("128x64", True), ("128x64", False)}
     assert not any(K.gemm_f32x3(lib, "apply", N, J, D) for J, D, N in x3.FP32_SHAPES)
+
+
+@pytest.mark.parametrize("kind", ["logits", "residual"])
+def test_three_term_shapes_of_contiguous_operands(lib, kind):
+    import test_gpu_gemm_f32x3 as x3
+    plans = [K.gemm_f32x3(lib, kind, B, J, D) for J, D, B in (x3.LOGITS_SHAPES if kind == "logits" else x3.SC_SHAPES)]
+    assert {(p[0], p[1] > 1) for p in plans if p} == {(t, s) for t in K.X3_TILES for s in (False, True)}
