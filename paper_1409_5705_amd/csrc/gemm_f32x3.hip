@@ -19,7 +19,10 @@
 // 32x32x16 rather than 16x16x32 MFMAs: the latter hide two vector instructions each, and the loop has three times as many.
 //
 // What bounds it: power.  The launch of 1000 x 2048 over 2048 takes 79000 cycles of which the matrix pipes are busy for
-// 49000; on zeros the clock is 2.37 GHz and the launch takes 36 us, on N(0,1) values 1.65 to 1.8 GHz and 46 to 49.
+// 49000; on zeros the clock is 2.37 GHz and the launch takes 36 us, on N(0,1) values 1.65 to 1.8 GHz and 46 to 49.  Where k is
+// short the launch, first loads and epilogue (8 us in all) count as much.  The epilogue goes through buffer descriptors
+// because the branches of a bounds check per access made it wait for each old value in turn (24 instead of 29 us at
+// 1003 x 2047 over 800).
 #include "gemm_f32.h"
 
 #include <type_traits>
@@ -30,7 +33,6 @@ namespace {
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t uintx2 __attribute__((ext_vector_type(2)));
 typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -43,8 +45,8 @@ constexpr int NT = 256;
 template <int WN_, int KW_>
 struct Tile {
     static constexpr int WN = WN_, KW = KW_, BM = 32 * TA, BN = 32 * TB * WN;
-    static constexpr int LDS = KW * BM * BN * 4;      // the partial sums (or, before, 24 KB a wavefront)
-    static_assert(WN * KW * 64 == NT && LDS >= 4 * 4096 * (TA + TB), "four wavefronts");
+    static constexpr int SUMS = KW * BM * BN * 4, LDS = SUMS + 16;      // the partial sums (before: 24 KB a wavefront); a flag
+    static_assert(WN * KW * 64 == NT && SUMS >= 4 * 4096 * (TA + TB), "four wavefronts");
 };
 
 // The three terms of eight values of k of a row, packed as MFMA operands.
@@ -349,72 +351,102 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1))) void
     }
     if (!A_KS) __syncthreads();
 
-    // ---- the partial sums meet in LDS as [kw][row][column]; a thread takes four neighbouring columns of a row
-    float* const meet = reinterpret_cast<float*>(x3_smem);
+    // ---- the partial sums meet in LDS, four accumulators of a lane as one word; of the KW wavefronts with the same part of
+    // C each finishes TA / KW row tiles: rows TA (8 (e / 4) + 4 half + e % 4) + a, columns 2 l32 and 2 l32 + 1
+    floatx4* const meet = x3_smem;
     const bool direct = EPI == EPI_STORE || p.split_k > 1;
     float* const out = p.split_k > 1 ? p.partial + (int64_t)z * p.M * p.N : p.C;
     const int64_t ldo = p.split_k > 1 ? p.N : p.ldc;
-    constexpr int PER = BM * BN / 4 / NT, PO = EPI == EPI_STORE ? 1 : PER;
-    floatx4 old[PO];
+    constexpr int AT = TA / KW;
+    // C, aux and the partial sums through buffer descriptors that end with the matrix: rows past the last one are not
+    // accessed; a column past the last one is read from the next row and not stored
+    auto tile_rsrc = [&](const float* P, int64_t ld) {
+        const uint64_t at = uniform64(reinterpret_cast<uint64_t>(P) + (uint64_t)(m0 * ld + n0 + wn0) * 4);
+        const uint64_t end = uniform64(reinterpret_cast<uint64_t>(P) + (uint64_t)((p.M - 1) * ld + p.N) * 4), left = at < end ? end - at : 0;
+        return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(at), 0, left > 0xffffffffu ? 0xffffffffu : (uint32_t)left, 0x00020000);
+    };
+    auto row_of = [&](int t, int e) { return (uint32_t)(TA * (8 * (e / 4) + 4 * half + e % 4) + AT * kw + t); };
+    floatx2 old[EPI == EPI_STORE ? 1 : AT][16];
     float invL = 0.f, th = 0.f;
     if (EPI != EPI_STORE && !direct) {      // (on their way while the sums meet)
         if (EPI == EPI_SHRINK) {
             invL = 1.0f / p.L_ptr[0];
             th = p.lambda * invL;
         }
-        const float* src = EPI == EPI_RMW ? p.C : p.aux;      // (EPI_SHRINK, null: zeros)
+        const float* src = EPI == EPI_RMW ? p.C : p.aux;
+        const Rsrc rs = EPI != EPI_SHRINK || src ? tile_rsrc(src, p.ldc) : __builtin_amdgcn_make_buffer_rsrc(p.C, 0, 0, 0x00020000);   // (null: zeros)
 #pragma unroll
-        for (int i = 0; i < PO; ++i) {
-            const int u = tid + NT * i;
-            const int64_t row = m0 + u / (BN / 4), col = n0 + 4 * (u % (BN / 4));
-            old[i] = floatx4{0.f, 0.f, 0.f, 0.f};
-            if (row < p.M && (EPI != EPI_SHRINK || src)) {
-                const float* s = src + row * p.ldc + col;
-                if (col + 4 <= p.N) {
-                    const floatx4u v = *reinterpret_cast<const floatx4u*>(s);
-                    old[i] = floatx4{v[0], v[1], v[2], v[3]};
-                } else {
+        for (int t = 0; t < AT; ++t)
 #pragma unroll
-                    for (int c = 0; c < 4; ++c)
-                        if (col + c < p.N) old[i][c] = s[c];
-                }
+            for (int e = 0; e < 16; ++e) {
+                const uintx2 v = __builtin_amdgcn_raw_buffer_load_b64(rs, row_of(t, e) * ((uint32_t)p.ldc * 4u) + 4u * TB * l32, 0, 0);
+                old[EPI == EPI_STORE ? 0 : t][e] = floatx2{__uint_as_float(v[0]), __uint_as_float(v[1])};
             }
-        }
     }
+    auto put = [&](auto leading_tag) {
 #pragma unroll
-    for (int a = 0; a < TA; ++a)
+        for (int a = 0; a < TA; ++a)
+#pragma unroll
+            for (int b = 0; b < TB; ++b)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    floatx4 v;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = acc[a][b][4 * q + e] + (decltype(leading_tag)::value ? 0.f : cor[a][b][4 * q + e]);
+                    meet[(((kw * WN + wave % WN) * TA + a) * TB + b) * 256 + q * 64 + lane] = v;
+                }
+    };
+    float sum[AT][16][TB];
+    auto get = [&](auto&& take) {
+#pragma unroll
+        for (int t = 0; t < AT; ++t)
+#pragma unroll
+            for (int b = 0; b < TB; ++b)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    floatx4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int k = 0; k < KW; ++k) {
+                        const floatx4 w = meet[(((k * WN + wave % WN) * TA + AT * kw + t) * TB + b) * 256 + q * 64 + lane];
+                        v = k ? v + w : w;
+                    }
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) take(sum[t][4 * q + e][b], v[e]);
+                }
+    };
+    int* const flag = reinterpret_cast<int*>(x3_smem) + TL::SUMS / 4;
+    if (tid == 0) *flag = 0;
+    put(std::false_type{});
+    __syncthreads();
+    bool finite = true;
+    get([&](float& s, float v) {
+        s = v;
+        finite &= __builtin_fabsf(v) < __builtin_inff();
+    });
+    if (!finite) *flag = 1;
+    __syncthreads();
+    if (*flag) {      // such a sum is the one of the leading products (the others hold Inf - Inf)
+        put(std::true_type{});
+        __syncthreads();
+        get([&](float& s, float v) { s = __builtin_fabsf(s) < __builtin_inff() ? s : v; });
+    }
+    const Rsrc ro = tile_rsrc(out, ldo);
+    const int64_t cols = p.N - (n0 + wn0) - TB * l32;      // (left in the row from this lane's first one)
+#pragma unroll
+    for (int t = 0; t < AT; ++t)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-            floatx2 v;
+            uint32_t r[TB];
 #pragma unroll
-            for (int b = 0; b < TB; ++b) {      // (a sum of leading products that is not finite is the result)
-                const float x = acc[a][b][e], y = x + cor[a][b][e];
-                v[b] = __builtin_fabsf(x) < __builtin_inff() ? y : x;
-            }
-            *reinterpret_cast<floatx2*>(meet + (kw * BM + TA * (8 * (e / 4) + 4 * half + e % 4) + a) * BN + wn0 + TB * l32) = v;
+            for (int b = 0; b < TB; ++b)
+                r[b] = __float_as_uint(direct ? sum[t][e][b]
+                                              : gemm_combine<EPI>(old[EPI == EPI_STORE ? 0 : t][e][b], sum[t][e][b], p.eta, invL, th));
+            const uint32_t at = row_of(t, e) * ((uint32_t)ldo * 4u) + 4u * TB * l32;
+            if (cols >= TB)
+                __builtin_amdgcn_raw_buffer_store_b64(uintx2{r[0], r[1]}, ro, at, 0, 0);
+            else if (cols > 0)
+                __builtin_amdgcn_raw_buffer_store_b32(r[0], ro, at, 0, 0);
         }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        const int u = tid + NT * i;
-        const int64_t row = m0 + u / (BN / 4), col = n0 + 4 * (u % (BN / 4));
-        floatx4 sum = *reinterpret_cast<const floatx4*>(meet + 4 * u);
-#pragma unroll
-        for (int k = 1; k < KW; ++k) sum += *reinterpret_cast<const floatx4*>(meet + k * BM * BN + 4 * u);
-        if (row >= p.M) continue;
-        if (!direct) {
-#pragma unroll
-            for (int c = 0; c < 4; ++c) sum[c] = gemm_combine<EPI>(old[EPI == EPI_STORE ? 0 : i][c], sum[c], p.eta, invL, th);
-        }
-        float* dst = out + row * ldo + col;
-        if (col + 4 <= p.N) {
-            *reinterpret_cast<floatx4u*>(dst) = floatx4u{sum[0], sum[1], sum[2], sum[3]};
-        } else {
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-                if (col + c < p.N) dst[c] = sum[c];
-        }
-    }
 }
 
 typedef Tile<1, 4> X0;      // 128 x 64
@@ -452,22 +484,24 @@ hipError_t launch_any(const GemmF32Params& p, DeviceInfo& dev, int combo, const 
 
 // Estimated duration (us): the launch (more with the chip full), and rounds of one workgroup per CU, each `own` for its
 // first loads, meeting and epilogue and `step` for every block of 32 of k of a wavefront (less where CUs are idle); a
-// k-split pays a second launch and the traffic of the partial sums.  Fitted to 60 shapes of sfb_apply, 100 x 100 with 32
-// pairs to 4100 x 8200 with 4000 (rms of the logarithm 8 %); with the estimates of the fp32 kernel the choice between the
-// two was 13.1 % faster in the mean than that kernel alone, the better one each time 13.2 %.  fp32 kernel / this one (us):
-//   1000 x 2048, 2048 pairs 77 / 50    4096 x 4096, 2048 483 / 339    1003 x 2047, 800 43 / 29    1024 x 4096, 512 41 / 30
-//   616 x 2488, 327 19 / 17            1720 x 208, 1531 19.2 / 19.0   284 x 850, 1340 14.8 / 16.3  1561 x 5818, 37 34 / 39
-// What is within 3 % stays with the fp32 kernel.  The same constants hold for operands that come by way of LDS (58 shapes,
-// rms 7 %): 512 x 4096 over 1024 42 / 30, 512 x 1024 over 4096 42 / 33 and (k-strided B) 44 / 34 with a k-split of four,
-// 454 x 2559 over 476 21 / 16, 256 x 1000 over 2048 13.0 / 18.2 (loading them lane by lane: 35, 39 and 36 of the first three).
+// k-split pays a second launch and the traffic of the partial sums.  Fitted to 118 shapes, 60 of sfb_apply (100 x 100 with
+// 32 pairs to 4100 x 8200 with 4000), 58 of logits and residuals (64 samples to 700; rms of the logarithm 4 %); with the
+// estimates of the fp32 kernel the choice between the two was 13.5 % faster in the mean than that kernel alone, the better
+// one each time 14.0 %.  fp32 kernel / this one (us):
+//   1000 x 2048, 2048 pairs 77 / 48    4096 x 4096, 2048 483 / 321    1003 x 2047, 800 43 / 24    1024 x 4096, 512 41 / 28
+//   616 x 2488, 327 19 / 13            2090 x 831, 148 15.9 / 11.3    1561 x 5818, 37 34 / 30     284 x 850, 1340 14.8 / 16
+//   by way of LDS: 512 x 4096 over 1024 41 / 27, 512 x 1024 over 4096 41 / 33 and (k-strided B) 43 / 34 with a k-split of
+//   four, 454 x 2559 over 476 21 / 16, 678 x 1365 over 712 17.9 / 18.1, 256 x 1000 over 2048 13.0 / 18.2
+//   (loading those lane by lane: 33, 39 and 36 of the first three).
+// What is within 5 % stays with the fp32 kernel.
 GemmF32x3Plan gemm_f32x3_plan(const GemmF32Args& a, int max_split)
 {
     GemmF32x3Plan best = {-1, 1, 1e30};
-    // a handful of blocks of k for a wavefront (with 128 pairs it was never faster); 32-bit offsets inside a block and tile
-    if (a.K < 160 || a.K > (1LL << 30) || a.lda >= (1LL << 22) || a.ldb >= (1LL << 22)) return best;
+    // a whole block of k; 32-bit offsets inside a block and tile
+    if (a.K < 32 || a.K > (1LL << 30) || a.lda >= (1LL << 22) || a.ldb >= (1LL << 22) || a.ldc >= (1LL << 22) || a.N >= (1LL << 22)) return best;
     auto aligned = [](const float* P, int64_t ld) { return ld % 4 == 0 && reinterpret_cast<uintptr_t>(P) % 16 == 0; };
     if (!a.a_kstrided && !(aligned(a.A, a.lda) && aligned(a.B, a.ldb))) return best;      // (direct loads)
-    static const double own[NTILES] = {5.1, 10.1}, step[NTILES] = {2.07, 2.02};
+    static const double own[NTILES] = {4.9, 6.3}, step[NTILES] = {2.16, 2.05};
     const int cus = a.dev->cus > 0 ? a.dev->cus : 256;
     const int64_t blocks = (a.K + 31) / 32;
     for (int t = 0; t < NTILES; ++t) {
@@ -476,12 +510,12 @@ GemmF32x3Plan gemm_f32x3_plan(const GemmF32Args& a, int max_split)
         for (int s = 1; s <= max_split; ++s) {
             const int64_t steps = ((blocks + s - 1) / s + kw - 1) / kw, wgs = tiles * s;
             const double idle = wgs < cus ? 1.0 - (double)wgs / cus : 0.0;
-            double us = 4.5 + 1.8 * (1.0 - idle) + (double)((wgs + cus - 1) / cus) * (own[t] + (double)steps * step[t] * (1.0 - 0.18 * idle));
+            double us = 1.5 + 0.8 * (1.0 - idle) + (double)((wgs + cus - 1) / cus) * (own[t] + (double)steps * step[t] * (1.0 - 0.2 * idle));
             if (s > 1) us += 4.0 + (double)(s + 1) * (double)a.M * (double)a.N * 4.0 / 6e6;
             if (us < best.us) best = GemmF32x3Plan{t, s, us};
         }
     }
-    best.us /= 0.97;
+    best.us /= 0.95;
     return best;
 }
 

@@ -28,6 +28,7 @@ def normal(seed, *shape):
 
 # test_kernel_plans.py asserts that these reach both tile shapes, whole and with a k-split
 APPLY_SHAPES = [
+    (1619, 4136, 35), (2766, 377, 185),                                # fewer blocks of k than wavefronts; one each
     (785, 4669, 164), (449, 2195, 193), (1003, 2047, 200),             # 128 x 64, one or two blocks of k a wavefront
     (1000, 2048, 801), (641, 2050, 1024),
     (364, 1707, 1148), (262, 899, 1921), (256, 3056, 2848),            # with a k-split
