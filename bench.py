@@ -423,7 +423,8 @@ def main():
         kt["mlr_forward_bf16"] += kt["shadow_convert"]
     gather_ms = kt.get("csr_forward_gather")                 # CSR samples sparse enough for the route over stored entries
     fwd_ms = kt.get("mlr_forward_bf16", gather_ms if gather_ms is not None else float("nan"))
-    app_ms = kt.get("apply_bf16", float("nan"))
+    sparse_app_ms = kt.get("apply_gather")                   # and for the apply over the stored entries
+    app_ms = kt.get("apply_bf16", sparse_app_ms if sparse_app_ms is not None else float("nan"))
     tr_ms = kt.get("apply_bf16_transpose", float("nan"))
     smx_ms = kt.get("mlr_softmax", float("nan"))
     gemm_flops = 2.0 * B * J * D                             # per GEMM stage
@@ -458,6 +459,9 @@ def main():
     }
     if gather_ms is not None:
         stages["forward_gemm"] = {"ms": 0.0, "note": "the dense product did not run: see forward_gather"}
+    if sparse_app_ms is not None:      # (U is read as it is)
+        stages["apply_gather"] = {"ms": app_ms, "hbm_gbs": app_bytes / app_ms / 1e6, "hbm_frac": app_bytes / app_ms / 1e6 / PEAK_HBM_GBS}
+        stages["apply_gemm"] = stages["apply_transposes"] = {"ms": 0.0, "note": "the dense product did not run: see apply_gather"}
     # Roofline of the dominant kernel.  At this shape the forward contraction is
     # MFMA-bound (845 flop/B); the apply is bound by whichever roof its flops per
     # algorithmic byte put it under (ridge: 312 flop/B; 250 with the fp32 array,
@@ -466,7 +470,10 @@ def main():
     # passes (FETCH_SIZE, WRITE_SIZE, scaled by the copy-kernel calibration) that
     # the committed summary under profiles/ records; null if it has no such line.
     traffic, traffic_current = profile_traffic_bytes()
-    if fwd_ms >= app_ms:
+    if sparse_app_ms is not None:
+        roof = {"kernel": "apply_gather_kernel", "bound": "hbm", "achieved": stages["apply_gather"]["hbm_gbs"], "peak": PEAK_HBM_GBS,
+                "unit": "GB/s", "frac": stages["apply_gather"]["hbm_frac"], "traffic": None, "algorithmic_bytes": app_bytes}
+    elif fwd_ms >= app_ms:
         roof = {"kernel": "sf_gemm_kernel<0> (forward)", "bound": "mfma", "achieved": stages["forward_gemm"]["tflops"],
                 "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": stages["forward_gemm"]["mfma_frac"],
                 "traffic": traffic.get("sf_gemm_kernel<0>")}
@@ -504,8 +511,9 @@ def main():
                                   if split else "an fp32 array plus a bf16 working copy"),
                    "J": J, "D": D, "B": B, "rank1_terms_per_step": B},
         "ms_per_step_events": {"median": per_step[len(per_step) // 2], "min": per_step[0], "max": per_step[-1]},
-        "tflops_gemm_stages": 2 * gemm_flops / (ms_per_step * 1e-3) / 1e12,
-        "mfma_frac_gemm_stages": (2 * gemm_flops / ((fwd_ms + app_ms) * 1e-3) / 1e12 / PEAK_BF16_TFLOPS if gather_ms is None
+        "tflops_gemm_stages": 2 * gemm_flops / (ms_per_step * 1e-3) / 1e12 if sparse_app_ms is None else None,
+        "mfma_frac_gemm_stages": (None if sparse_app_ms is not None else
+                                  2 * gemm_flops / ((fwd_ms + app_ms) * 1e-3) / 1e12 / PEAK_BF16_TFLOPS if gather_ms is None
                                   else gemm_flops / (app_ms * 1e-3) / 1e12 / PEAK_BF16_TFLOPS),
         "stages": stages,
         "roofline": roof,

@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsfb.so")
 PEAKS = os.path.join(HERE, "sfb_peaks")
-SOURCES = ["sfb_api.hip", "gemm_f32.hip", "gemm_f32x3.hip", "gemm_bf16.hip", "forward_bf16.hip", "rowops.hip", "sparse.hip", "ssp.cpp"]
+SOURCES = ["sfb_api.hip", "gemm_f32.hip", "gemm_f32x3.hip", "gemm_bf16.hip", "apply_gather.hip", "forward_bf16.hip", "rowops.hip", "sparse.hip", "ssp.cpp"]
 FLAGS = [
     "-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC",
     # packed-fp32 VALU forms are not trusted on the test machines

@@ -50,8 +50,7 @@
 //     XCDs (one L2 each; 8 of 32 CUs on MI355X, both read from the device): the
 //     workgroups of an XCD walk consecutive tiles of a raster in which tiles
 //     sharing operand panels are neighbours.
-#include "device.h"
-#include "kernels.h"
+#include "planes.h"
 
 #include <type_traits>
 
@@ -60,20 +59,13 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int BK = 64;                   // k-slice: one 128-byte LDS row of bf16
-constexpr int BM = 256, BN = 256;        // workgroup tile
+// (BK: a k-slice, one 128-byte LDS row of bf16; BM x BN: the workgroup tile)
 constexpr int TM = 8, TN = 8;            // 16 x 16 MFMA tiles per wavefront: 128 x 128 (2 x 2 wavefronts)
 constexpr int NT = 256;
 constexpr uint32_t STAGE = 0x10000u;     // bytes of one LDS stage: [A tile 32 KiB][B tile 32 KiB]
 constexpr uint32_t B_OFF = BM * 128;
 constexpr int LDS_BYTES = 2 * STAGE;
-// Cache policy of the accesses of C and of its bf16 copy: non-temporal (each
-// line is touched once per launch; left at the default policy they sweep the
-// operand panels, which ARE reused, out of the 4 MiB L2 of the XCD).
-constexpr int C_POLICY = 2;
 // Load schedule: of the 16 direct loads a wavefront issues per k-slice, N2B go out
 // in the third quarter of the slice two before the one they fetch (as soon as its
 // LDS stage is free), N3 in its last quarter, N0 in the first quarter of the next
@@ -121,18 +113,6 @@ struct Params {
     int num_xcd;        // XCDs of the device: consecutive workgroup ids go to consecutive XCDs
 };
 
-// A parameter matrix kept as two 16-bit planes: the halves of word = bits + 0x8000 (modulo 2^32).  hi = word >> 16
-// is the value rounded to bf16 (to nearest, ties away from zero), lo = word & 0xffff; bits = ((hi << 16) | lo) -
-// 0x8000, exactly.  Two elements a dword in both planes: split_pair / join_pair move between the packed halves and
-// the two words with one byte permute each.
-__device__ __forceinline__ uint32_t split_word(float v) { return __float_as_uint(v) + 0x8000u; }
-__device__ __forceinline__ float split_value(uint32_t word) { return __uint_as_float(word - 0x8000u); }
-// words of elements 0 and 1 from their packed high halves h = [h1 : h0] and low halves l = [l1 : l0]
-__device__ __forceinline__ uint32_t join_pair0(uint32_t h, uint32_t l) { return __builtin_amdgcn_perm(h, l, 0x05040100u); }
-__device__ __forceinline__ uint32_t join_pair1(uint32_t h, uint32_t l) { return __builtin_amdgcn_perm(h, l, 0x07060302u); }
-// packed high halves [w1 >> 16 : w0 >> 16] and low halves [w1 & 0xffff : w0 & 0xffff] of two words
-__device__ __forceinline__ uint32_t pack_hi(uint32_t w0, uint32_t w1) { return __builtin_amdgcn_perm(w1, w0, 0x07060302u); }
-__device__ __forceinline__ uint32_t pack_lo(uint32_t w0, uint32_t w1) { return __builtin_amdgcn_perm(w1, w0, 0x05040100u); }
 
 // Element (r, c) of a bf16 operand of sf_gemm_kernel (and of the high plane): blocks of BM rows x BK columns
 // (one k-slice of a row tile, 32 KB in one piece), block (r / BM, c / BK) at index (r / BM) * (pitch / BK) + c / BK.
@@ -550,17 +530,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1))) void
 // planes with 100 pairs 3.62 -> 3.37 ms (5.8 TB/s).
 constexpr int SM = 128, SN = 128;
 constexpr uint32_t SSTAGE = 0x8000u, SB_OFF = SM * 128;      // one k-slice: [A tile 16 KiB][B tile 16 KiB]
-
-// Whether any of the LANES neighbouring lanes that write one 128-byte line of the bf16 copy (high plane) has something to
-// write there: a line is stored whole or not at all, since one written in part costs the memory a read as well.  Measured:
-// apply of 40000 x 10000 with 100 pairs, 2 to 3 % of the values changing, 0.97 -> 0.83 ms with the copy, 0.69 -> 0.57 on
-// the planes.  (In the 256 x 256 kernel, with its many pairs, it gains nothing.)
-template <int LANES>
-__device__ __forceinline__ bool any_in_line(bool mine, int lane)
-{
-    const uint64_t b = __builtin_amdgcn_ballot_w64(mine);
-    return ((b >> (lane & ~(LANES - 1))) & ((1ull << LANES) - 1)) != 0;
-}
 
 template <int MODE>
 __global__ __launch_bounds__(NT, 2) void apply_small_kernel(Params p)

@@ -13,6 +13,7 @@ struct DeviceInfo {
     bool gemm_bf16_lds_set[3] = {false, false, false};   // dynamic-LDS attribute of sf_gemm_kernel<mode> set on this device
     bool gemm_f32_lds_set[48] = {};                      // the same for the fp32 kernels (operand combination x load width x tile shape)
     bool gemm_f32x3_lds_set[8] = {};                     // of the kernel on three bf16 terms (operand combination x tile shape)
+    bool apply_gather_lds_set[2] = {};                   // of the apply of sparse factors (fp32 array, planes)
     bool fwd_stream_lds_set[6] = {};                     // and of the streaming bf16 forward
     int softmax_wait_polls = 1000;                 // bound of the one-read softmax's wait for a partner's word
 };
@@ -106,6 +107,13 @@ hipError_t launch_apply_bf16_transpose(const uint16_t* U, const uint16_t* V, con
 // to bf16) and W_lo the low one; both are updated and the fp32 array W is not touched.
 hipError_t launch_apply_bf16(float* W, uint16_t* W_shadow, uint16_t* W_lo, int64_t N, int64_t J, int64_t D, float eta,
                              const void* workspace, DeviceInfo& dev, hipStream_t stream);
+// The same for a V^T (bf16 operand D x N, columns N.. zero) that holds few entries, with U as it is; contractions over the
+// rows of V with entries only (another order of summation).  workspace: apply_gather_workspace_bytes(N, D), 256-byte
+// aligned.
+bool apply_gather_supported(int64_t N, int64_t J, int64_t D);
+int64_t apply_gather_workspace_bytes(int64_t N, int64_t D);
+hipError_t launch_apply_gather(float* W, uint16_t* W_shadow, uint16_t* W_lo, const uint16_t* U, const uint16_t* Vt, int64_t N, int64_t J,
+                               int64_t D, float eta, void* workspace, DeviceInfo& dev, hipStream_t stream);
 // fp32 W[J][D] <-> planes hi (a J x D bf16 operand, bf16_operand_bytes(J, D)) and lo (split_lo_bytes(J, D)
 // bytes: 256 x 256 tiles in row-major tile order, one piece per workgroup of the apply):
 // the halves of bits + 0x8000; bits = ((hi << 16) | lo) - 0x8000.

@@ -31,12 +31,13 @@ enum KernelId : int {
     KID_CSR_GATHER,
     KID_SDCA,
     KID_DUAL_TO_PRIMAL,
+    KID_APPLY_GATHER,
     KID_COUNT
 };
 static const char* const kKernelNames[KID_COUNT] = {
     "mlr_forward_bf16", "apply_bf16", "apply_bf16_transpose", "mlr_softmax", "gemm_f32_store", "gemm_f32_rmw(apply)", "gemm_f32_resid",
     "gemm_f32_shrink", "diff", "dml_scale", "fill", "prox_rows", "power_iteration", "copy", "shadow_convert", "scale_rows",
-    "csr_to_operand", "csr_forward_gather", "sdca_mlr", "dual_to_primal"};
+    "csr_to_operand", "csr_forward_gather", "sdca_mlr", "dual_to_primal", "apply_gather"};
 
 struct ProfSpan {
     hipEvent_t t0, t1;
@@ -63,7 +64,7 @@ struct sfb_ctx {
     uint16_t* split_lo;
     // CU / XCD counts of the device, per-device launch state, wait bound of the one-read softmax
     sfb::DeviceInfo dev;
-    // route of sfb_mlr_sf_csr: 0 chosen from the number of stored entries, 1 dense contraction, 2 over the non-zeros
+    // route of sfb_mlr_sf_csr and sfb_apply_csr: 0 chosen from the number of stored entries, 1 dense contraction, 2 over the non-zeros
     int csr_route;
     // this device's copy of the library's static scratch array (sfb_apply_static), resolved by sfb_create
     char* static_scratch;
@@ -840,6 +841,32 @@ int64_t sfb_apply_csr_workspace_bytes(int64_t J, int64_t D, int64_t N, int32_t s
     return base + round_up(N * D * 4);                   // fp32: dense V
 }
 
+// Whether a bf16 apply of CSR rows goes over the stored entries.  Nanoseconds per element of W, fitted to 58 shapes (1000 x
+// 512 to 325000 x 10000, 100 to 1276 pairs, 0.2 to 3 % stored): the dense contraction a constant (the stream of W) plus
+// 1.18e-3 a pair, the other one a constant plus 0.1 (fp32 array 0.08) for every 32 rows of V that have entries in sixteen
+// columns, as many as random positions give.  Dense / over the entries (ms): 325000 x 10000 on the planes, 1024 pairs
+// 0.2 % 6.4 / 4.4, 0.5 % 6.6 / 4.6, 1 % 6.7 / 5.3, 2 % 6.9 / 6.7, 5 % 7.1 / 9.8; 512 pairs 0.5 % 4.6 / 4.4, 256 4.09 /
+// 4.14; fp32 array 1024 pairs 0.5 % 7.2 / 6.0, with the copy 7.8 / 6.8; 51344 x 696, 1191 pairs 0.4 % 0.19 / 0.13.
+// Matrices that the caches hold, or too few panels of 64 classes for the chip, stay dense (2120 x 1216: 28 / 43 us).
+static bool apply_csr_use_gather(const sfb_ctx* ctx, int64_t N, int64_t J, int64_t D, int64_t nnz, bool planes, bool copy)
+{
+    // the lists must fit where U^T would be, in front of V^T
+    const int64_t room = reinterpret_cast<const char*>(sfb::apply_bf16_vt(ctx->ws, N, J)) - ctx->ws;
+    if (ctx->csr_route == 1 || !sfb::apply_gather_supported(N, J, D) || sfb::apply_gather_workspace_bytes(N, D) > room) return false;
+    if (ctx->csr_route == 2) return true;
+    const double panels = (double)((J + 63) / 64), cus = (double)ctx->dev.cus;
+    if (panels < 0.75 * cus || (double)J * (double)D < 33e6) return false;
+    const double rounds = (double)(((J + 63) / 64 + ctx->dev.cus - 1) / ctx->dev.cus);
+    const double last_round = panels > cus ? 1.0 + 0.5 * (rounds * cus / panels - 1.0) : 1.0;
+    double none = 1.0 - (double)nnz / ((double)N * (double)D);      // share of zeros; of rows without an entry in 16 columns
+    if (none < 0.0) none = 0.0;
+    for (int i = 0; i < 4; ++i) none *= none;
+    const double steps = (double)N * (1.0 - none) / 32.0 + 0.3;
+    const double dense = (planes ? 0.83 : copy ? 1.2 : 1.0) + 1.18e-3 * (double)N;
+    const double gather = (planes ? 1.12 + 0.1 * steps : (copy ? 1.85 : 1.6) + 0.08 * steps) * last_round;
+    return gather < 0.95 * dense;
+}
+
 int sfb_apply_csr(sfb_ctx* ctx, float* W, int64_t J, int64_t D, const void* U, const sfb_csr* V, const float* coef,
                   float eta)
 {
@@ -880,6 +907,11 @@ int sfb_apply_csr(sfb_ctx* ctx, float* W, int64_t J, int64_t D, const void* U, c
     uint16_t* Vt = sfb::apply_bf16_vt(ctx->ws, N, J);
     SFB_RUN(KID_FILL, sfb::launch_fill_u32(Vt, 0u, sfb::bf16_operand_bytes(D, N) / 4, st));
     SFB_RUN(KID_CSR, sfb::launch_csr_scatter(V->indptr, V->indices, V->values, true, coef, Vt, N, D, V->nnz, 1, -Np, st));
+    if (apply_csr_use_gather(ctx, N, J, D, V->nnz, is_split(ctx, W), has_shadow)) {      // (its lists take the place of U^T)
+        SFB_RUN(KID_APPLY_GATHER, sfb::launch_apply_gather(W, has_shadow ? ctx->shadow_buf : nullptr, is_split(ctx, W) ? ctx->split_lo : nullptr,
+                                                         static_cast<const uint16_t*>(U), Vt, N, J, D, eta, ctx->ws, ctx->dev, st));
+        return SFB_OK;
+    }
     SFB_RUN(KID_APPLY_TRANSPOSE, sfb::launch_apply_bf16_transpose(static_cast<const uint16_t*>(U), nullptr, nullptr, N, J,
                                                                   D, ctx->ws, st));
     SFB_RUN(KID_APPLY_BF16, sfb::launch_apply_bf16(W, has_shadow ? ctx->shadow_buf : nullptr,
