@@ -19,6 +19,7 @@ struct GemmF32Params {
     int split_k;          // > 1: workgroup z of a tile covers k-slices [z * per_split, (z + 1) * per_split) and writes partial[z]
     int64_t per_split;    // k-slices per split
     float* partial;       // [split_k][M][N]
+    int* parts;           // (host) GemmF32Args::parts
     int num_xcd;
     int group_m;          // raster: groups of group_m row-tiles, row-tile index fastest inside a group
 };

@@ -678,7 +678,8 @@ hipError_t launch_tile(Params p, DeviceInfo& dev, int slot, int split, hipStream
     hipLaunchKernelGGL((gemm_f32_kernel<TL, A_KS, B_KS, EPI, DIRECT>), dim3((unsigned)(tm * tn), (unsigned)p.split_k), dim3(NT),
                        TL::lds(DIRECT, p.per_split), stream, p);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || p.split_k <= 1) return e;
+    if (p.parts) *p.parts = p.split_k;
+    if (e != hipSuccess || p.split_k <= 1 || p.parts) return e;
     return launch_splitk_reduce(p, EPI, stream);
 }
 
@@ -792,6 +793,7 @@ hipError_t launch_gemm_f32(const GemmF32Args& a, hipStream_t stream)
     p.M = a.M; p.N = a.N; p.K = a.K;
     p.eta = a.eta; p.lambda = a.lambda;
     p.partial = a.partial;
+    p.parts = a.epilogue == EPI_STORE ? a.parts : nullptr;
     const GemmF32Plan plan = gemm_f32_plan(a);
     const GemmF32x3Plan x3 = x3_plan(a, plan);
     if (x3.tile >= 0) return launch_gemm_f32x3(a, p, x3, stream);

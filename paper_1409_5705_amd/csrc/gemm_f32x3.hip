@@ -469,7 +469,8 @@ hipError_t launch_tile(GemmF32Params p, DeviceInfo& dev, int slot, int split, hi
     gemm_f32_raster(p, tm, tn, TL::BM, TL::BN, dev);
     hipLaunchKernelGGL((gemm_f32x3_kernel<TL, A_KS, B_KS, EPI>), dim3((unsigned)(tm * tn), (unsigned)p.split_k), dim3(NT), TL::LDS, stream, p);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || p.split_k <= 1) return e;
+    if (p.parts) *p.parts = p.split_k;
+    if (e != hipSuccess || p.split_k <= 1 || p.parts) return e;
     return launch_splitk_reduce(p, EPI, stream);
 }
 

@@ -48,6 +48,8 @@ struct GemmF32Args {
     float lambda;        // EPI_SHRINK
     float* partial;      // scratch of gemm_f32_partial_bytes(M, N, K) for the k-split, or null (no split)
     DeviceInfo* dev;     // the context's device facts
+    int* parts;          // EPI_STORE, nullable: the caller adds up the k-splits itself.  *parts of them are [M][N] arrays in
+                         // `partial`, to be added in their order, and C is not written; 1: C is the result
 };
 hipError_t launch_gemm_f32(const GemmF32Args& a, hipStream_t stream);
 // Estimated duration (us) of that launch (a.dev is needed).
@@ -172,6 +174,8 @@ struct MlrSoftmaxArgs {
     int64_t copy_bytes;
 };
 int64_t mlr_softmax_scratch_bytes(int64_t B, int64_t J);
+// Whether the row kernel adds up the k-splits of fp32 logits [B][J] faster than a launch of its own in front does.
+bool mlr_softmax_adds(int64_t B, int64_t J, int cus);
 hipError_t launch_mlr_softmax(const MlrSoftmaxArgs& a, hipStream_t stream);
 // Partner pairs that workgroups of the one-read softmax computed themselves instead of receiving them, on the
 // current device since the library was loaded (copies a device counter: the caller synchronises first).
@@ -180,8 +184,10 @@ hipError_t softmax_fallbacks(unsigned long long* count);
 // V = X - Y over n floats; *counter (nullable, device) is set to 0 by the same launch.
 hipError_t launch_diff(const float* X, const float* Y, float* V, int64_t n, int32_t* counter, hipStream_t stream);
 // DML coefficient: d = ||Q_i||^2; c = +2 (sim>0), -2 (sim<=0 and d<margin), else 0; U_i = c Q_i.
-// n_active (nullable) must have been zeroed; it is incremented once per active row.
-hipError_t launch_dml_scale(const float* Q, const int8_t* sim, float* U, int32_t* n_active,
+// n_active (nullable) must have been zeroed; it is incremented once per active row.  Q is the sum of `parts` arrays of B K
+// floats, one behind the other (more than 1: dml_scale_adds(K)).
+inline bool dml_scale_adds(int64_t K) { return K <= 1024; }
+hipError_t launch_dml_scale(const float* Q, int parts, const int8_t* sim, float* U, int32_t* n_active,
                             float margin, int64_t B, int64_t K, hipStream_t stream);
 // Vs[i][d] = coef[i] * V[i][d] (N rows of D).
 hipError_t launch_scale_rows(const float* V, const float* coef, float* Vs, int64_t N, int64_t D, hipStream_t stream);

@@ -209,22 +209,28 @@ __global__ __launch_bounds__(256) void mlr_softmax_row_kernel(const float* __res
         for (int e = 0; e < E; ++e) v[i][e] = -INFINITY;
         if (j < J) load(z + (blocked ? (j >> 8) * (tiles_m * 65536) + (j & 255) : j), v[i]);
     }
-    if (PLANES)
-        for (int k = 1; k < planes; ++k) {
-            const float* zk = z + k * plane_floats;
-            float t[CH][E];
+    if (PLANES) {
+        constexpr int AHEAD = PER <= 4 ? 7 : (PER <= 16 ? 2 : 1);      // arrays in flight
+        for (int k0 = 1; k0 < planes; k0 += AHEAD) {
+            float t[AHEAD][CH][E];
 #pragma unroll
-            for (int i = 0; i < CH; ++i) {
-                const int64_t j = (int64_t)(tid + NT * i) * E;
-                if (j < J) load(zk + (blocked ? (j >> 8) * (tiles_m * 65536) + (j & 255) : j), t[i]);
-            }
+            for (int a = 0; a < AHEAD; ++a)
 #pragma unroll
-            for (int i = 0; i < CH; ++i)
-                if ((int64_t)(tid + NT * i) * E < J) {
-#pragma unroll
-                    for (int e = 0; e < E; ++e) v[i][e] += t[i][e];
+                for (int i = 0; i < CH; ++i) {
+                    const int64_t j = (int64_t)(tid + NT * i) * E;
+                    if (k0 + a < planes && j < J)
+                        load(z + (k0 + a) * plane_floats + (blocked ? (j >> 8) * (tiles_m * 65536) + (j & 255) : j), t[a][i]);
                 }
+#pragma unroll
+            for (int a = 0; a < AHEAD; ++a)
+#pragma unroll
+                for (int i = 0; i < CH; ++i)
+                    if (k0 + a < planes && (int64_t)(tid + NT * i) * E < J) {
+#pragma unroll
+                        for (int e = 0; e < E; ++e) v[i][e] += t[a][i][e];
+                    }
         }
+    }
 #pragma unroll
     for (int i = 0; i < CH; ++i)
 #pragma unroll
@@ -635,12 +641,17 @@ __global__ __launch_bounds__(NT) void sdca_mlr_kernel(const float* __restrict__ 
 }
 
 // DML: one workgroup per pair; PER > 0: rows of at most 256 PER floats, in registers between the norm and the product.
+// Q is the sum of `parts` arrays, `part` floats apart (PER > 0), all of them in flight together.  With the sum as a launch of
+// its own / here (us of the whole factor computation, pairs x rows of the metric x features): 100 x 601 x 5000 21.5 / 18.9,
+// 1000 x 600 x 1000 26.8 / 25.0, 500 x 1001 x 5000 48.0 / 45.5; adding one array at a time 100 x 1000 x 21504 57.2 / 60.4
+// (now 54.6).
 template <int PER>
-__global__ __launch_bounds__(256) void dml_scale_kernel(const float* __restrict__ Q, const int8_t* __restrict__ sim,
+__global__ __launch_bounds__(256) void dml_scale_kernel(const float* __restrict__ Q, int parts, int64_t part, const int8_t* __restrict__ sim,
                                                         float* __restrict__ U, int32_t* __restrict__ n_active,
                                                         float margin, int64_t K)
 {
     __shared__ float sm[4];
+    constexpr int AHEAD = 7;      // arrays in flight beside the first
     const int64_t row = blockIdx.x;
     const float* q = Q + row * K;
     float* const u = U + row * K;
@@ -649,6 +660,18 @@ __global__ __launch_bounds__(256) void dml_scale_kernel(const float* __restrict_
     if (PER > 0) {
 #pragma unroll
         for (int i = 0; i < PER; ++i) v[i] = threadIdx.x + 256 * i < K ? q[threadIdx.x + 256 * i] : 0.f;
+        for (int z0 = 1; z0 < parts; z0 += AHEAD) {
+            float t[AHEAD][PER > 0 ? PER : 1];
+#pragma unroll
+            for (int z = 0; z < AHEAD; ++z)
+#pragma unroll
+                for (int i = 0; i < PER; ++i)
+                    t[z][i] = z0 + z < parts && threadIdx.x + 256 * i < K ? q[(z0 + z) * part + threadIdx.x + 256 * i] : 0.f;
+#pragma unroll
+            for (int z = 0; z < AHEAD; ++z)
+#pragma unroll
+                for (int i = 0; i < PER; ++i) v[i] = z0 + z < parts ? v[i] + t[z][i] : v[i];
+        }
 #pragma unroll
         for (int i = 0; i < PER; ++i) d += v[i] * v[i];
     } else {
@@ -925,6 +948,14 @@ hipError_t softmax_fallbacks(unsigned long long* count)
 
 int64_t mlr_softmax_scratch_bytes(int64_t B, int64_t J) { return softmax_cluster(J) ? B * softmax_cluster(J) * 8 : 0; }
 
+constexpr int64_t SOFTMAX_ADDS_MAX = 4096;
+// The launch of its own (4.3 us and more) has as many workgroups as there are logits, the row kernel one a sample: it adds
+// them up where a thread has at most four logits, so that all their parts are in flight together, or where the samples fill
+// the chip.  Measured (us of the whole factor computation, with the launch / without; samples x classes x features):
+// 100 x 191 x 20000 22.8 / 18.2, 100 x 1000 x 4000 19.0 / 16.8, 600 x 1001 x 1000 24.1 / 21.3, 256 x 2000 x 4000 36.3 / 34.9,
+// 256 x 2001 x 2000 27.9 / 25.4; but 100 x 1300 x 4000 23.3 / 24.3, 100 x 2000 x 4000 26.2 / 27.0.
+bool mlr_softmax_adds(int64_t B, int64_t J, int cus) { return J <= 1024 || (J <= SOFTMAX_ADDS_MAX && B >= cus); }
+
 template <int PER, bool VEC>
 static hipError_t launch_softmax_row(const MlrSoftmaxArgs& a, hipStream_t stream)
 {
@@ -943,7 +974,10 @@ static hipError_t launch_softmax_row(const MlrSoftmaxArgs& a, hipStream_t stream
     typedef std::false_type N;
     if constexpr (VEC)
         if (a.planes > 1 && a.out_bf16) return go(Y{}, Y{});
-    if (a.planes > 1) return hipErrorInvalidValue;      // (only the bf16 path leaves several)
+    if (a.planes > 1 && a.out_bf16) return hipErrorInvalidValue;      // (its logits are tile-blocked)
+    if constexpr (PER <= SOFTMAX_ADDS_MAX / 256)
+        if (a.planes > 1) return go(N{}, Y{});
+    if (a.planes > 1) return hipErrorInvalidValue;
     return a.out_bf16 ? go(Y{}, N{}) : go(N{}, N{});
 }
 
@@ -1061,14 +1095,15 @@ hipError_t launch_fill_u32(void* p, uint32_t value, int64_t n, hipStream_t strea
     return hipGetLastError();
 }
 
-hipError_t launch_dml_scale(const float* Q, const int8_t* sim, float* U, int32_t* n_active, float margin, int64_t B,
+hipError_t launch_dml_scale(const float* Q, int parts, const int8_t* sim, float* U, int32_t* n_active, float margin, int64_t B,
                             int64_t K, hipStream_t stream)
 {
     if (B <= 0) return hipSuccess;
+    if (parts > 1 && !dml_scale_adds(K)) return hipErrorInvalidValue;
     if (K <= 1024)
-        hipLaunchKernelGGL(dml_scale_kernel<4>, dim3((unsigned)B), dim3(256), 0, stream, Q, sim, U, n_active, margin, K);
+        hipLaunchKernelGGL(dml_scale_kernel<4>, dim3((unsigned)B), dim3(256), 0, stream, Q, parts, B * K, sim, U, n_active, margin, K);
     else
-        hipLaunchKernelGGL(dml_scale_kernel<0>, dim3((unsigned)B), dim3(256), 0, stream, Q, sim, U, n_active, margin, K);
+        hipLaunchKernelGGL(dml_scale_kernel<0>, dim3((unsigned)B), dim3(256), 0, stream, Q, 1, B * K, sim, U, n_active, margin, K);
     return hipGetLastError();
 }
 

@@ -439,6 +439,13 @@ int sfb_set_workspace(sfb_ctx* ctx, void* dev_ptr, int64_t bytes)
     return SFB_OK;
 }
 
+// The softmax reads the k-splits that a contraction has left ([parts][B][J]).
+static void sum_of_parts(sfb::MlrSoftmaxArgs& sm, const sfb::GemmF32Args& g)
+{
+    sm.Z = g.partial;
+    sm.plane_floats = g.M * g.N;
+}
+
 int sfb_compute_sf(sfb_ctx* ctx, int32_t model, const float* W, int64_t J, int64_t D, const sfb_batch* batch,
                    void* U, void* V, int32_t* n_active)
 {
@@ -486,7 +493,9 @@ int sfb_compute_sf(sfb_ctx* ctx, int32_t model, const float* W, int64_t J, int64
             g.M = B; g.N = J; g.K = D;
             g.epilogue = sfb::EPI_STORE;
             if (sfb::gemm_f32_partial_bytes(B, J, D) > 0) g.partial = reinterpret_cast<float*>(ctx->ws + round_up(B * J * 4));
+            if (sfb::mlr_softmax_adds(B, J, ctx->dev.cus)) g.parts = &sm.planes;
             SFB_RUN(KID_GEMM_F32_STORE, sfb::launch_gemm_f32(g, st));
+            if (sm.planes > 1) sum_of_parts(sm, g);
         } else {
             uint16_t* Xa = reinterpret_cast<uint16_t*>(ctx->ws + call.logits_bytes);
             const uint16_t* Wb = has_shadow ? ctx->shadow_buf : nullptr;
@@ -521,8 +530,10 @@ int sfb_compute_sf(sfb_ctx* ctx, int32_t model, const float* W, int64_t J, int64
         g.M = B; g.N = J; g.K = D;
         g.epilogue = sfb::EPI_STORE;
         if (sfb::gemm_f32_partial_bytes(B, J, D) > 0) g.partial = reinterpret_cast<float*>(ctx->ws + round_up(B * J * 4));
+        int parts = 1;
+        if (sfb::dml_scale_adds(J)) g.parts = &parts;
         SFB_RUN(KID_GEMM_F32_STORE, sfb::launch_gemm_f32(g, st));
-        SFB_RUN(KID_DML_SCALE, sfb::launch_dml_scale(Q, batch->sim, static_cast<float*>(U), n_active, batch->margin, B, J, st));
+        SFB_RUN(KID_DML_SCALE, sfb::launch_dml_scale(parts > 1 ? g.partial : Q, parts, batch->sim, static_cast<float*>(U), n_active, batch->margin, B, J, st));
         return SFB_OK;
     }
 
@@ -803,7 +814,9 @@ int sfb_mlr_sf_csr(sfb_ctx* ctx, const float* W, int64_t J, int64_t D, const sfb
         } else {
             SFB_RUN(KID_FILL, sfb::launch_fill_u32(Xd, 0u, B * D, st));
             SFB_RUN(KID_CSR, sfb::launch_csr_scatter(X->indptr, X->indices, X->values, false, nullptr, Xd, B, D, X->nnz, D, 1, st));
+            if (sfb::mlr_softmax_adds(B, J, ctx->dev.cus)) g.parts = &sm.planes;
             SFB_RUN(KID_GEMM_F32_STORE, sfb::launch_gemm_f32(g, st));
+            if (sm.planes > 1) sum_of_parts(sm, g);
         }
         SFB_RUN(KID_SOFTMAX, sfb::launch_mlr_softmax(sm, st));
         return SFB_OK;

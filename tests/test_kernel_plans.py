@@ -50,3 +50,14 @@ def test_three_term_shapes_of_contiguous_operands(lib, kind):
     import test_gpu_gemm_f32x3 as x3
     plans = [K.gemm_f32x3(lib, kind, B, J, D) for J, D, B in (x3.LOGITS_SHAPES if kind == "logits" else x3.SC_SHAPES)]
     assert {(p[0], p[1] > 1) for p in plans if p} == {(t, s) for t in K.X3_TILES for s in (False, True)}
+
+
+def test_shapes_whose_row_kernels_add_up_the_splits(lib):
+    import test_gpu_split_sums as s
+
+    def split(B, J, D):
+        x3 = K.gemm_f32x3(lib, "logits", B, J, D)
+        return (x3[1] if x3 else K.gemm_f32(lib, "logits", B, J, D)[1]) > 1
+
+    assert all(split(*shape) for shape in s.MLR_SHAPES[:-1] + s.DML_SHAPES[:-1])
+    assert not split(*s.MLR_SHAPES[-1]) and not split(*s.DML_SHAPES[-1])
