@@ -1,6 +1,10 @@
 // fp32 MFMA GEMM family for gfx950 (v_mfma_f32_16x16x4_f32), used by every
 // fp32 workload: MLR logits, DML projections, the two ISTA contractions of
-// sparse coding, and the reconstruction + application of the SF sum.
+// sparse coding, and the reconstruction + application of the SF sum.  It keeps the
+// contractions of less than some 10 us and the ones with a k below 32; the larger ones go
+// to the bf16 matrix instructions on three terms per value (gemm_f32x3.hip) wherever the
+// two cost models find that faster, so the first, second, third and seventh line below
+// are the ones it no longer has (now 48, 29, 33 and 26 us).
 //
 //   acc[m][n] = sum_k A(m,k) * B(n,k)
 //
