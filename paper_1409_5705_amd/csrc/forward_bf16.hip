@@ -31,6 +31,7 @@ constexpr int NX = 3;        // LDS stages of the samples
 
 struct FwdParams {
     const uint16_t* X;       // samples in the operand layout (blocks of 256 x 64, pitch P)
+    int64_t x_pitch;         // or, where this is not 0, as rows of x_pitch elements, a multiple of 64
     const void* W;           // fp32 [J][D], or bf16 in the operand layout
     float* Z;                // per k-split: 256 x 256 tiles, tile (b / 256, j / 256) at index (j / 256) * tiles_b + b / 256
     int64_t plane;           // floats from one split's logits to the next
@@ -128,15 +129,18 @@ __global__ __launch_bounds__(NT, 2) void fwd_stream_kernel(FwdParams p)
             const int r = 8 * (LX * wave + i) + (lane >> 3);
             int64_t b = m0 + r;
             if (b >= p.B) b = p.B - 1;
-            voff[i] = (uint32_t)(((b / 256 - m0 / 256) * (p.P / 64) * 16384 + (b % 256) * 64) * 2) + (uint32_t)(((lane & 7) ^ swz(r)) << 4);
+            const int64_t row = p.x_pitch ? (b - m0) * p.x_pitch : (b / 256 - m0 / 256) * (p.P / 64) * 16384 + (b % 256) * 64;
+            voff[i] = (uint32_t)(row * 2) + (uint32_t)(((lane & 7) ^ swz(r)) << 4);
         }
-        const uint64_t base = uniform64(reinterpret_cast<uint64_t>(p.X) + (uint64_t)(m0 / 256) * (uint64_t)(p.P / 64) * 32768);
+        const uint64_t base = uniform64(reinterpret_cast<uint64_t>(p.X) +
+                                        (p.x_pitch ? (uint64_t)(m0 * p.x_pitch) * 2 : (uint64_t)(m0 / 256) * (uint64_t)(p.P / 64) * 32768));
+        const uint64_t x_slice = p.x_pitch ? 128 : 32768;
         auto issue_one = [&](int i, int stage, uint64_t from) {
             load_to_lds_16(lds_base + (uint32_t)(stage * XS + (LX * wave + i) * 1024), from, voff[i]);
         };
         auto issue = [&](int s, int stage) {
 #pragma unroll
-            for (int i = 0; i < LX; ++i) issue_one(i, stage, base + (uint64_t)at(s) * 32768);
+            for (int i = 0; i < LX; ++i) issue_one(i, stage, base + (uint64_t)at(s) * x_slice);
         };
         static_for<0, NX>([&](auto S) { issue(decltype(S)::value, decltype(S)::value); });
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NX - 1) * LX) : "memory");
@@ -150,7 +154,7 @@ __global__ __launch_bounds__(NT, 2) void fwd_stream_kernel(FwdParams p)
                 step(f0, f1, xs, u & 1, 1, [](auto) {});
                 asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NX - 2) * LX) : "memory");
                 __syncthreads();
-                const uint64_t from = base + (uint64_t)at(s0 + u + NX) * 32768;
+                const uint64_t from = base + (uint64_t)at(s0 + u + NX) * x_slice;
                 step(f1, f0, xn, (u + 1) & 1, 0, [&](auto J) {
                     constexpr int j = decltype(J)::value, M = MT * NTL;
                     static_for<j * LX / M, (j + 1) * LX / M>([&](auto Q) { issue_one(decltype(Q)::value, xs, from); });
@@ -303,11 +307,20 @@ MlrForwardPlan mlr_forward_plan(int64_t B, int64_t J, int64_t D, bool have_copy,
     return best;
 }
 
-hipError_t launch_fwd_stream(const MlrForwardPlan& plan, const uint16_t* Xa, const float* W, const uint16_t* W_shadow, float* Z, int64_t B,
+// Whole k-slices need no padding with zeros, and a piece of a sample in one is a line of 128 bytes in either layout: the
+// samples are then read as they come (32-bit offsets inside a tile of 256).  Rows that end inside a slice would bring the
+// next sample's features, which zeros of W do not cancel where they are infinite.  Copy in front / none (us of the whole
+// factor computation, samples x classes x features, W as fp32; from its copy): 16 x 1000 x 1024 15.0 / 9.7; 15.0 / 10.2,
+// 256 x 1504 x 8960 38.8 / 32.8; 33.5 / 27.5, 256 x 8192 x 4096 48.6 / 46.1; 41.0 / 37.7, 1000 x 4000 x 2048 46.2 / 42.4;
+// 39.9 / 35.7, 256 x 40000 x 2048 130.7 / 127.5; 78.0 / 76.8, 64 x 325000 x 10048 2548 / 2556 (fp32).
+bool fwd_stream_takes_rows(const MlrForwardPlan& plan, int64_t D) { return plan.mt > 0 && D % KS == 0 && D < (1LL << 22); }
+
+hipError_t launch_fwd_stream(const MlrForwardPlan& plan, const uint16_t* X, bool rows, const float* W, const uint16_t* W_shadow, float* Z, int64_t B,
                              int64_t J, int64_t D, DeviceInfo& dev, hipStream_t stream)
 {
     FwdParams p = {};
-    p.X = Xa;
+    p.X = X;
+    p.x_pitch = rows ? D : 0;
     p.W = W_shadow ? static_cast<const void*>(W_shadow) : static_cast<const void*>(W);
     p.Z = Z;
     p.plane = mlr_logits_floats(B, J);

@@ -963,13 +963,14 @@ hipError_t launch_mlr_forward_bf16(const MlrForwardPlan& plan, const uint16_t* X
 {
     if (B <= 0 || J <= 0) return hipSuccess;
     const int64_t pitch = bf16_pitch(D);
+    if (X && fwd_stream_takes_rows(plan, D)) return launch_fwd_stream(plan, X, true, W, W_shadow, Z, B, J, D, dev, stream);
     if (X) {   // null: the caller has already written X_aligned (rows of `pitch` elements, zero padded)
         hipLaunchKernelGGL((pad_rows_bf16_kernel<uint16_t>), dim3(grid_for(B * (pitch / 8))), dim3(256), 0, stream, X,
                            X_aligned, B, D, pitch);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    if (plan.mt > 0) return launch_fwd_stream(plan, X_aligned, W, W_shadow, Z, B, J, D, dev, stream);
+    if (plan.mt > 0) return launch_fwd_stream(plan, X_aligned, false, W, W_shadow, Z, B, J, D, dev, stream);
     Params p = {};
     p.A = X_aligned; p.lda = pitch; p.M = B;
     p.B = W_shadow; p.ldb = pitch; p.N = J;

@@ -91,7 +91,9 @@ struct MlrForwardPlan {
 MlrForwardPlan mlr_forward_plan(int64_t B, int64_t J, int64_t D, bool have_copy, bool may_split);
 hipError_t launch_mlr_forward_bf16(const MlrForwardPlan& plan, const uint16_t* X, const float* W, const uint16_t* W_shadow, float* Z,
                                    uint16_t* X_aligned, int64_t B, int64_t J, int64_t D, DeviceInfo& dev, hipStream_t stream);
-hipError_t launch_fwd_stream(const MlrForwardPlan& plan, const uint16_t* X_aligned, const float* W, const uint16_t* W_shadow, float* Z,
+// (X, 16-byte aligned: rows of D elements where `rows`, which fwd_stream_takes_rows allows, otherwise in the operand layout)
+bool fwd_stream_takes_rows(const MlrForwardPlan& plan, int64_t D);
+hipError_t launch_fwd_stream(const MlrForwardPlan& plan, const uint16_t* X, bool rows, const float* W, const uint16_t* W_shadow, float* Z,
                              int64_t B, int64_t J, int64_t D, DeviceInfo& dev, hipStream_t stream);
 // W[j][d] -= eta * sum_i U[i][j] * V[i][d];  U bf16 [N][J], V bf16 [N][D], W fp32 [J][D].
 // Two steps: launch_apply_bf16_transpose writes U^T and V^T into `workspace`

@@ -61,3 +61,10 @@ def test_shapes_whose_row_kernels_add_up_the_splits(lib):
 
     assert all(split(*shape) for shape in s.MLR_SHAPES[:-1] + s.DML_SHAPES[:-1])
     assert not split(*s.MLR_SHAPES[-1]) and not split(*s.DML_SHAPES[-1])
+
+
+def test_shapes_of_the_forward_on_rows(lib):
+    from test_gpu_forward_rows import SHAPES
+    plans = [K.forward(lib, *s, copy) for s in SHAPES for copy in (False, True)]
+    assert all(mt > 0 for mt, _, _ in plans), list(zip([s for s in SHAPES for _ in "ab"], plans))
+    assert {mt for mt, _, _ in plans} == {1, 2, 4} and {split > 1 for _, _, split in plans} == {False, True}
