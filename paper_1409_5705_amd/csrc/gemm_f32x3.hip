@@ -6,8 +6,10 @@
 // which leave out less than 2^-24 of it; every one of them is exact in fp32, and v_mfma_f32_32x32x16_bf16 adds sixteen of
 // them with two roundings.  The leading products have accumulators of their own, so that the running sum is rounded as
 // rarely as possible: the 2-norm of the error of a product of 1000 x 2048 over 2048 pairs, N(0,1), is 1.5e-7 (5.7e-7 with
-// fp32 MFMAs), of 512 x 4096 over 1024 0.9e-7, over 64 0.5e-7 (1.4e-7).  Infinities and NaN: where the sum of the leading
-// products is not finite it is the result (the others then hold Inf - Inf).
+// fp32 MFMAs), of 512 x 4096 over 1024 0.9e-7, over 64 0.5e-7 (1.4e-7).  Infinities and NaN: h and the terms behind it do not
+// hold them apart (Inf - Inf, a NaN cut off to Inf, a sum just above the largest value whose leading products stay below
+// it), so a workgroup with a sum that is not finite multiplies its part again with fp32 MFMAs and takes those results
+// there.
 //
 // One workgroup of four wavefronts, one per SIMD, owns an output tile; each wavefront multiplies 128 x 64 of it over its
 // own blocks of 32 of k (KW wavefronts take turns), and the partial sums meet in LDS at the end.  No wavefront shares
@@ -383,7 +385,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1))) void
                 old[EPI == EPI_STORE ? 0 : t][e] = floatx2{__uint_as_float(v[0]), __uint_as_float(v[1])};
             }
     }
-    auto put = [&](auto leading_tag) {
+    auto put = [&](auto single_tag) {
 #pragma unroll
         for (int a = 0; a < TA; ++a)
 #pragma unroll
@@ -392,7 +394,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1))) void
                 for (int q = 0; q < 4; ++q) {
                     floatx4 v;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] = acc[a][b][4 * q + e] + (decltype(leading_tag)::value ? 0.f : cor[a][b][4 * q + e]);
+                    for (int e = 0; e < 4; ++e) v[e] = acc[a][b][4 * q + e] + (decltype(single_tag)::value ? 0.f : cor[a][b][4 * q + e]);
                     meet[(((kw * WN + wave % WN) * TA + a) * TB + b) * 256 + q * 64 + lane] = v;
                 }
     };
@@ -425,7 +427,43 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1))) void
     });
     if (!finite) *flag = 1;
     __syncthreads();
-    if (*flag) {      // such a sum is the one of the leading products (the others hold Inf - Inf)
+    if (*flag) {      // such sums are those of fp32 products
+        static_for<0, TA>([&](auto a) { static_for<0, TB>([&](auto b) { acc[a][b] = floatx16{}; }); });
+        // (the arguments and the lane read again: kept since the start they would take registers from the loop)
+        uint64_t args = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+        int l = threadIdx.x & 63;
+        asm volatile("" : "+s"(args), "+v"(l));
+        const auto* q = (const __attribute__((address_space(4))) GemmF32Params*)args;
+        const int64_t M = q->M, N = q->N, K = q->K, ka = A_KS ? q->lda : 1, kb = B_KS ? q->ldb : 1;
+        const float *pa[TA], *pb[TB];
+#pragma unroll
+        for (int a = 0; a < TA; ++a) {
+            const int64_t r = m0 + TA * (l & 31) + a, row = r < M ? r : M - 1;
+            pa[a] = q->A + (A_KS ? row : row * q->lda);
+        }
+#pragma unroll
+        for (int b = 0; b < TB; ++b) {
+            const int64_t c = n0 + wn0 + TB * (l & 31) + b, col = c < N ? c : N - 1;
+            pb[b] = q->B + (B_KS ? col : col * q->ldb);
+        }
+        for (int i = 0; i < n; ++i) {
+            const int64_t k0 = 32 * (int64_t)(b0 + kw + KW * i);
+#pragma unroll 4
+            for (int j = 0; j < 32; j += 2) {
+                const bool in = k0 + j + (l >> 5) < K;
+                const int64_t k = in ? k0 + j + (l >> 5) : K - 1;
+                float av[TA], bv[TB];
+#pragma unroll
+                for (int a = 0; a < TA; ++a) av[a] = pa[a][k * ka];
+#pragma unroll
+                for (int b = 0; b < TB; ++b) bv[b] = pb[b][k * kb];
+#pragma unroll
+                for (int a = 0; a < TA; ++a)
+#pragma unroll
+                    for (int b = 0; b < TB; ++b)
+                        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(in ? av[a] : 0.f, in ? bv[b] : 0.f, acc[a][b], 0, 0, 0);
+            }
+        }
         put(std::true_type{});
         __syncthreads();
         get([&](float& s, float v) { s = __builtin_fabsf(s) < __builtin_inff() ? s : v; });

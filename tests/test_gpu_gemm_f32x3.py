@@ -78,6 +78,80 @@ def test_not_finite(ctx):
     assert W[500, 99].item() == float(np.finfo(np.float32).max)
 
 
+# two factors, and whether their product is infinite in fp32: just above the largest value with leading bf16 terms that stay
+# below it, the largest value itself, and below
+OVERFLOWS = [
+    (3.4028234663852886e38, 1.0078124, True), (3e38, 1.137, True), (2e38, 1.7109, True),
+    ((1 + 2.0 ** -7 - 2.0 ** -23) * 2.0 ** 64, 1.9921875 * 2.0 ** 63, True),
+    (3.4028234663852886e38, 1.0, False), (1e38, 3.4, False), (1.9999 * 2.0 ** 70, 1.00004 * 2.0 ** 57, False),
+]
+NANS = [0x7f800001, -0x7fffff, 0x7fc00000, 0x7f80ffff]      # (payloads in the low 16 bits only; -0x7fffff: 0xff800001)
+
+
+def from_bits(bits):
+    return torch.tensor([bits], dtype=torch.int32, device="cuda:0").view(torch.float32)[0]
+
+
+def extremes(K, M, N):
+    """a [K][M], b [K][N] whose contraction has one or two products at the elements that the tests look at."""
+    a, b = torch.zeros(K, M, device="cuda:0"), torch.zeros(K, N, device="cuda:0")
+    for i, (x, y, _) in enumerate(OVERFLOWS):
+        a[101 * i + 3, i], b[101 * i + 3, i] = x, y
+        a[101 * i + 4, 64 + i], b[101 * i + 4, 64 + i] = -x, y
+    for i, bits in enumerate(NANS):
+        a[7 * i, 32 + i], b[7 * i, 32 + i] = from_bits(bits), 1.0
+        a[7 * i + 1, 40 + i], b[7 * i + 1, 40 + i] = 1.0, from_bits(bits)
+    a[500:502, 50], b[500:502, 50] = 2.0 ** 126 * 1.0039, 2.0             # a sum above the largest value, of products below it
+    return a, b
+
+
+def test_overflow_and_nan_strided(ctx):
+    a, b = extremes(1024, 512, 4096)
+    C = torch.zeros(512, 4096, device="cuda:0")
+    ctx.sfb_apply(C, a, b, -1.0)
+    for i, (x, y, overflow) in enumerate(OVERFLOWS):
+        for at, sign in ((i, 1.0), (64 + i, -1.0)):
+            got, exact = C[at, at].item(), sign * float(np.float32(x)) * float(np.float32(y))
+            assert got == sign * float("inf") if overflow else abs(got - exact) <= 5 * EPS * abs(exact), (i, got, exact)
+    for i in range(len(NANS)):
+        assert torch.isnan(C[32 + i, 32 + i]) and torch.isnan(C[40 + i, 40 + i]), (i, C[32 + i, 32 + i].item(), C[40 + i, 40 + i].item())
+    assert torch.isposinf(C[50, 50])
+
+
+def test_overflow_and_nan_contiguous(ctx):
+    """Logits: the softmax of a row with an infinite one or NaN is NaN, with a finite one, however large, it is not."""
+    import paper_1409_5705_amd as sfb
+    a, b = extremes(1024, 512, 4096)
+    b[:, 40:40 + len(NANS)] = 0.0                       # (NaN in every row otherwise)
+    X, W = a.t().contiguous(), b.t().contiguous()
+    U = torch.empty(512, 4096, device="cuda:0")
+    ctx.sfb_compute_sf(sfb.SFB_MLR, W, X, Y=torch.zeros(512, dtype=torch.int32, device="cuda:0"), U=U)
+    nan = torch.isnan(U).any(dim=1)
+    want = torch.zeros(512, dtype=torch.bool)
+    for i, (_, _, overflow) in enumerate(OVERFLOWS):
+        want[i] = overflow
+    want[32:32 + len(NANS)], want[50] = True, True
+    assert torch.equal(nan.cpu(), want), (nan.cpu() != want).nonzero()
+
+
+def test_not_finite_residual(ctx):
+    """The shrink step of samples with infinities and NaN and the residual X - U W (k-contiguous x k-strided) of their codes."""
+    import paper_1409_5705_amd as sfb
+    J, D, B = 1024, 4096, 512
+    W = torch.zeros(J, D, device="cuda:0")
+    W[torch.arange(J), torch.arange(J)] = 1.0                # L is 1
+    X = torch.zeros(B, D, device="cuda:0")
+    X[3, 5], X[4, 6], X[5, 7], X[6, 8] = float("inf"), float("nan"), 3e38, from_bits(0x7f800001)
+    U, V = torch.empty(B, J, device="cuda:0"), torch.empty(B, D, device="cuda:0")
+    ctx.sfb_compute_sf(sfb.SFB_SC, W, X, U=U, V=V, lam=0.0, ista_iters=1, power_iters=10)
+    t = X.double() @ W.double().t()
+    codes = torch.where(t > 0, t, torch.where(t < 0, t, torch.zeros_like(t)))       # (NaN: no code)
+    for got, want in ((U, codes), (V, X.double() - codes @ W.double())):
+        for test in (torch.isnan, torch.isposinf, torch.isneginf):
+            assert torch.equal(test(got), test(want)), (test, (test(got) != test(want)).nonzero()[:4])
+    assert abs(U[5, 7].item() / 3e38 - 1) <= 1e-5
+
+
 def test_rows_of_a_larger_matrix_and_alignment(ctx):
     """Factors whose first row starts 4 bytes off 16 (leading dimensions of no particular size)."""
     J, D, N = 1001, 2049, 333
