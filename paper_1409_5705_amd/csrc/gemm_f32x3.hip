@@ -1,7 +1,8 @@
 // The fp32 contractions of gemm_f32.hip where they are large, on the bf16 matrix pipes.
 //
-// A value of 24 bits is the sum of three bf16 values of 8 bits each, x = h + m + l (h and m rounded to nearest, l what is left:
-// exact for |x| >= 2^-110, below that to 2^-134).  A product of two values is taken as the six products
+// A value of 24 bits is the sum of three bf16 values of 8 bits each, x = h + m + l (h and m rounded to nearest, l what is
+// left).  bf16 ends at 2^-133, so the values are multiplied by 2^16 first and the sums by 2^-32 at the end: exact down to the
+// smallest denormal (without that only from 2^-110 on, and values below 2^-134 were lost).  A product is taken as the six
 //   h h' + (h m' + m h') + (h l' + m m' + l h')
 // Every one of them is exact in fp32, and v_mfma_f32_32x32x16_bf16 adds sixteen of them with two roundings.  The rest,
 // m l' + l m' + l l', is at most 2 * 2^-8 * 2^-17 of the product and a little: (1 + 2^-9) 2^-24, typically 2^-26 (h cut off
@@ -9,15 +10,16 @@
 // rounded as rarely as possible.  rms error over the sum of the products' sizes in units of 2^-24, here / with fp32 MFMAs,
 // by the number of products that are not zero: one 0.44 / 0.42, two 0.48 / 0.47, three 0.49 / 0.48, five 0.44 / 0.46, twelve
 // 0.33 / 0.40, fifty 0.19 / 0.35.  2-norm of the error of a product of 1003 x 2047 over 300 pairs, N(0,1): 0.7e-7 (2.2e-7).
-// Infinities and NaN: the terms do not hold them apart (Inf - Inf; the largest values are rounded to Inf), so a workgroup
-// with a sum that is not finite multiplies its part again with fp32 MFMAs and takes those results there.
+// Infinities and NaN: the terms do not hold them apart (Inf - Inf), and values from 2^112 and sums from 2^96 on become infinite
+// here, so a workgroup with a sum that is not finite multiplies its part again with fp32 MFMAs and takes those results.
 //
 // One workgroup of four wavefronts, one per SIMD, owns an output tile; each wavefront multiplies 128 x 64 of it over its
 // own blocks of 32 of k (KW wavefronts take turns), and the partial sums meet in LDS at the end.  No wavefront shares
 // operand data with another, so the loop has no barrier.  Two k-strided operands: a lane loads what it multiplies (16
 // bytes a lane along the rows, 512 contiguous bytes per 32 lanes), two steps of 16 ahead.  Otherwise a wavefront brings a
 // block of its operands into LDS of its own while it multiplies the one before.  It cuts the values into their terms
-// between the MFMAs (11 instructions per pair; 5.5 of them per MFMA of 32 cycles, which hides that many).
+// between the MFMAs (13 instructions per pair, 6.5 of them per MFMA of 32 cycles; without the multiplications by 2^16 five and
+// a half, and 1000 x 2048 over 2048 takes 47.5 instead of 48.9 us, 4096 x 4096 over 2048 335 instead of 347).
 //
 // 32x32x16 rather than 16x16x32 MFMAs: the latter hide two vector instructions each, and the loop has three times as many.
 //
@@ -43,6 +45,7 @@ typedef __amdgpu_buffer_rsrc_t Rsrc;
 
 constexpr int TA = 4, TB = 2;      // a wavefront's 32 x 32 MFMA tiles along the rows and columns of C
 constexpr int NT = 256;
+constexpr float SCALE = 0x1p16f, UNSCALE = 0x1p-32f;      // of the values before they are cut; of a sum
 
 // WN wavefronts side by side along n, KW over k.
 template <int WN_, int KW_>
@@ -61,9 +64,11 @@ __device__ __forceinline__ bf16x8 fragment(const uint32_t* t)
     const uintx4 v = {t[0], t[1], t[2], t[3]};
     return __builtin_bit_cast(bf16x8, v);
 }
-// (rounding may make the largest values infinite: their sums are then not finite and multiplied again)
+// (the largest values become infinite: their sums are then not finite and multiplied again)
 __device__ __forceinline__ void cut_pair(float x0, float x1, Terms& s, int i)
 {
+    x0 *= SCALE;
+    x1 *= SCALE;
     const uint32_t h = pack_bf16(x0, x1);
     const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xffff0000u);
     const uint32_t m = pack_bf16(r0, r1);
@@ -423,7 +428,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1))) void
     __syncthreads();
     bool finite = true;
     get([&](float& s, float v) {
-        s = v;
+        s = v * UNSCALE;
         finite &= __builtin_fabsf(v) < __builtin_inff();
     });
     if (!finite) *flag = 1;

@@ -78,6 +78,26 @@ def test_few_products(ctx, n):
     assert sum(ours) <= 1.05 * sum(theirs), (sum(ours) / 12 / EPS, sum(theirs) / 12 / EPS)
 
 
+@pytest.mark.parametrize("u,v", [(1, 1), (-116, 0), (-125, 0), (-120, 100), (-132, 100), (-140, 100), (100, -140), (62, 55), (110, -120)])
+def test_scales(ctx, u, v):
+    """Factors of 2^u and 2^v: as exact as those around 1, also below 2^-110 and where they are denormal (2-norm: 7e-8 measured,
+    a value rounded to the 2^-149 of the denormals is known to 2^-10 at 2^-140, in the reference too)."""
+    J, D, N = 1003, 2047, 300
+    U, V = normal(60, N, J) * 2.0 ** (u / 2) * 2.0 ** (u / 2), normal(61, N, D) * 2.0 ** (v / 2) * 2.0 ** (v / 2)
+    W = torch.zeros(J, D, device="cuda:0")
+    ctx.sfb_apply(W, U, V, -1.0)
+    ref = U.double().t() @ V.double()
+    assert float((W.double() - ref).norm() / ref.norm()) <= 4e-7
+    # and by way of LDS
+    import paper_1409_5705_amd as sfb
+    J, D, B = 1028, 4004, 517
+    W, X = normal(62, J, D) * 2.0 ** (u / 2) * 2.0 ** (u / 2), normal(63, B, D) * 2.0 ** (v / 2) * 2.0 ** (v / 2)
+    P, V = torch.empty(B, J, device="cuda:0"), torch.empty(B, D, device="cuda:0")
+    ctx.sfb_compute_sf(sfb.SFB_DML, W, X, Y=torch.zeros_like(X), sim=torch.ones(B, dtype=torch.int8, device="cuda:0"), U=P, V=V)
+    ref = 2.0 * (X.double() @ W.double().t())
+    assert float((P.double() - ref).norm() / ref.norm()) <= 4e-7
+
+
 def test_wide_range(ctx):
     """Values over 40 orders of magnitude: every product is as exact as fp32 ones, whatever its neighbours."""
     J, D, N = 1003, 2047, 300
