@@ -258,6 +258,83 @@ def test_sparse_codes(ctx, J, D, B):
         assert float(err.max()) <= 1e-4
 
 
+# One product per sum, at every k in turn, of factors with 24 significant bits: each of the six bf16 products that are taken is
+# worth 2^-18 of it or more, so one that is lost, or a value of k that is, shows (test_few_products: the bound).
+ONE = 2.08 * EPS
+
+
+def one_per_row(seed, rows, columns, count):
+    """[rows][columns] with N(0,1) at `count` places, no two of them in one row or column; and these."""
+    g = torch.Generator().manual_seed(seed)
+    r, c = torch.randperm(rows, generator=g)[:count].to("cuda:0"), torch.randperm(columns, generator=g)[:count].to("cuda:0")
+    m = torch.zeros(rows, columns, device="cuda:0")
+    m[r, c] = normal(seed, count)
+    return m, r, c
+
+
+@pytest.mark.parametrize("J,D,N", APPLY_SHAPES)
+@pytest.mark.parametrize("single", ["U", "V"])
+def test_apply_of_single_products(ctx, J, D, N, single):
+    print("apply, single", J, D, N, single, flush=True)
+    n = J if single == "U" else D
+    k = (torch.arange(n, device="cuda:0") * 7 + torch.arange(n, device="cuda:0") // N) % N
+    U, V, W = normal(70, N, J), normal(71, N, D), torch.zeros(J, D, device="cuda:0")
+    if single == "U":
+        u, v = U[k, torch.arange(J)], V[k]
+        U = torch.zeros_like(U)
+        U[k, torch.arange(J)] = u
+        ref = u.double()[:, None] * v.double()
+    else:
+        u, v = U[k], V[k, torch.arange(D)]
+        V = torch.zeros_like(V)
+        V[k, torch.arange(D)] = v
+        ref = (u.double() * v.double()[:, None]).t()
+    ctx.sfb_apply(W, U, V, -1.0)
+    assert bool(torch.all((W.double() - ref).abs() <= ONE * ref.abs()))
+
+
+@pytest.mark.parametrize("J,D,B", LOGITS_SHAPES)
+@pytest.mark.parametrize("single", ["W", "X"])
+def test_projection_of_single_products(ctx, J, D, B, single):
+    import paper_1409_5705_amd as sfb
+    print("projection, single", J, D, B, single, flush=True)
+    n = J if single == "W" else B
+    k = (torch.arange(n, device="cuda:0") * 7 + torch.arange(n, device="cuda:0") // D) % D
+    W, X = normal(72, J, D), normal(73, B, D)
+    full = W if single == "W" else X
+    kept = full[torch.arange(n), k]
+    full.zero_()
+    full[torch.arange(n), k] = kept
+    ref = 2.0 * (X[:, k].double() * kept.double() if single == "W" else kept.double()[:, None] * W[:, k].t().double())
+    U, V = torch.empty(B, J, device="cuda:0"), torch.empty(B, D, device="cuda:0")
+    ctx.sfb_compute_sf(sfb.SFB_DML, W, X, Y=torch.zeros_like(X), sim=torch.ones(B, dtype=torch.int8, device="cuda:0"), U=U, V=V)
+    assert bool(torch.all((U.double() - ref).abs() <= ONE * ref.abs()))
+
+
+@pytest.mark.parametrize("J,D,B", SC_SHAPES)
+def test_sparse_codes_of_single_products(ctx, J, D, B):
+    """A dictionary with one value per row and column, no shrinkage: a code is the sample's value there times the dictionary's
+    and 1 / L, which is the same for all codes, and the residual one product taken off the sample."""
+    import paper_1409_5705_amd as sfb
+    print("sparse codes, single", J, D, B, flush=True)
+    W, row, col = one_per_row(74, J, D, min(J, D))
+    X = normal(75, B, D)
+    U, V = torch.empty(B, J, device="cuda:0"), torch.empty(B, D, device="cuda:0")
+    ctx.sfb_compute_sf(sfb.SFB_SC, W, X, U=U, V=V, lam=0.0, ista_iters=1, power_iters=10)
+    w = W[row, col].double()
+    step = X[:, col].double() * w
+    big = step.abs() > 1e-3
+    ref = step * (U[:, row].double()[big] / step[big]).mean()                  # (1 / L, to much less than 2^-24)
+    assert bool(torch.all((U[:, row].double() - ref).abs() <= (ONE + EPS) * ref.abs()))
+    assert int((U != 0).sum()) == int((U[:, row] != 0).sum())
+    taken = U[:, row].double() * w
+    ref = X[:, col].double() - taken
+    assert bool(torch.all((V[:, col].double() - ref).abs() <= ONE * taken.abs() + EPS * ref.abs()))
+    rest = torch.ones(D, dtype=torch.bool, device="cuda:0")
+    rest[col] = False
+    assert torch.equal(V[:, rest], X[:, rest])
+
+
 # few pairs: the 128 x 64 tiles of the fp32 kernel keep these (test_kernel_plans.py)
 FP32_SHAPES = [(1104, 1580, 31), (1107, 1583, 30)]
 
