@@ -57,13 +57,10 @@ void gemm_f32_raster(GemmF32Params& p, int64_t tiles_m, int64_t tiles_n, int BM,
 // The sum of the k-splits in index order, then the epilogue.
 hipError_t launch_splitk_reduce(const GemmF32Params& p, int epilogue, hipStream_t stream);
 
-// The kernel on three bf16 terms: tile shape (its index in gemm_f32x3.hip, -1: it does not take the contraction) and
-// k-split, with the estimated duration; the combination of operand layouts and epilogue must be one of launch_gemm_f32.
-struct GemmF32x3Plan {
-    int tile, split;
-    double us;
-};
-GemmF32x3Plan gemm_f32x3_plan(const GemmF32Args& a, int max_split);
-hipError_t launch_gemm_f32x3(const GemmF32Args& a, GemmF32Params p, const GemmF32x3Plan& plan, hipStream_t stream);
+// The kernel on three bf16 terms where it takes the contraction (otherwise the duration is beyond all others); the combination
+// of operand layouts and epilogue must be one of launch_gemm_f32.
+GemmF32Plan gemm_f32x3_plan(const GemmF32Args& a, int max_split);
+double gemm_f32x3_least_us();      // that it estimates for any contraction
+hipError_t launch_gemm_f32x3(const GemmF32Args& a, GemmF32Params p, const GemmF32Plan& plan, hipStream_t stream);
 
 }  // namespace sfb

@@ -653,13 +653,13 @@ GemmF32Plan plan_gemm(int64_t M, int64_t N, int64_t K, int cus, int max_split, b
         {{2.10, 6.5, 0.05, 0.0, 1}, {1.22, 5.0, 0.05, 0.5, 1}, {1.25, 4.7, 0.1, 0.3, 1}, {0.69, 3.5, 0.2, 0.2, 2}, {0.80, 3.0, 0.0, 0.3, 2}, {0.40, 1.2, 1.0, 0.35, 2}},
         {{1.82, 6.5, 0.05, 0.0, 1}, {1.01, 5.0, 0.05, 0.5, 2}, {1.03, 4.7, 0.1, 0.3, 2}, {0.55, 3.5, 0.2, 0.2, 3}, {0.55, 3.0, 0.0, 0.3, 3}, {0.38, 1.2, 1.0, 0.35, 4}}};
     const TileCost* const c = costs[direct ? 1 : 0];
-    GemmF32Plan best = {0, 1, direct, 1e30};
+    GemmF32Plan best = {false, 0, 1, direct, 1e30};
     for (int s = 1; s <= max_split; ++s) {
         const double t[NTILES] = {plan_time<T0>(M, N, K, cus, s, direct, c[0]), plan_time<T1>(M, N, K, cus, s, direct, c[1]),
                                   plan_time<T2>(M, N, K, cus, s, direct, c[2]), plan_time<T3>(M, N, K, cus, s, direct, c[3]),
                                   plan_time<T4>(M, N, K, cus, s, direct, c[4]), plan_time<T5>(M, N, K, cus, s, direct, c[5])};
         for (int i = 0; i < NTILES; ++i)
-            if (t[i] < best.us) best = GemmF32Plan{i, s, direct, t[i]};
+            if (t[i] < best.us) best = GemmF32Plan{false, i, s, direct, t[i]};
     }
     return best;
 }
@@ -767,25 +767,10 @@ int64_t gemm_f32_partial_bytes(int64_t M, int64_t N, int64_t K)
 GemmF32Plan gemm_f32_plan(const GemmF32Args& a)
 {
     const int max_split = a.partial ? gemm_f32_max_split(a.M, a.N, a.K) : 1;
-    return plan_gemm(a.M, a.N, a.K, a.dev->cus > 0 ? a.dev->cus : 256, max_split, direct_loads(a));
-}
-
-namespace {
-// The kernel on three bf16 terms where its estimate is the lower one (tile >= 0).
-GemmF32x3Plan x3_plan(const GemmF32Args& a, const GemmF32Plan& plan)
-{
-    if (plan.us <= 6.5) return {-1, 1, 0.0};      // (its estimates begin at 6.7: a small call does without them, 0.1 us of the host)
-    GemmF32x3Plan x3 = gemm_f32x3_plan(a, a.partial ? gemm_f32_max_split(a.M, a.N, a.K) : 1);
-    if (x3.us >= plan.us) x3.tile = -1;
-    return x3;
-}
-}  // namespace
-
-double gemm_f32_estimate_us(const GemmF32Args& a)
-{
-    const GemmF32Plan plan = gemm_f32_plan(a);
-    const GemmF32x3Plan x3 = x3_plan(a, plan);
-    return x3.tile >= 0 ? x3.us : plan.us;
+    const GemmF32Plan plan = plan_gemm(a.M, a.N, a.K, a.dev->cus > 0 ? a.dev->cus : 256, max_split, direct_loads(a));
+    if (plan.us <= gemm_f32x3_least_us()) return plan;      // (a small call does without the other model, 0.1 us of the host)
+    const GemmF32Plan x3 = gemm_f32x3_plan(a, max_split);
+    return x3.us < plan.us ? x3 : plan;
 }
 
 hipError_t launch_gemm_f32(const GemmF32Args& a, hipStream_t stream)
@@ -800,8 +785,7 @@ hipError_t launch_gemm_f32(const GemmF32Args& a, hipStream_t stream)
     p.partial = a.partial;
     p.parts = a.epilogue == EPI_STORE ? a.parts : nullptr;
     const GemmF32Plan plan = gemm_f32_plan(a);
-    const GemmF32x3Plan x3 = x3_plan(a, plan);
-    if (x3.tile >= 0) return launch_gemm_f32x3(a, p, x3, stream);
+    if (plan.three_terms) return launch_gemm_f32x3(a, p, plan, stream);
     const bool aks = a.a_kstrided, bks = a.b_kstrided;
     if (!aks && !bks && a.epilogue == EPI_STORE) return launch_any<false, false, EPI_STORE>(p, *a.dev, 0, plan, stream);
     if (!aks && !bks && a.epilogue == EPI_SHRINK) return launch_any<false, false, EPI_SHRINK>(p, *a.dev, 1, plan, stream);

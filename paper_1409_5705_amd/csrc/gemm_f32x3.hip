@@ -519,7 +519,7 @@ hipError_t launch_tile(GemmF32Params p, DeviceInfo& dev, int slot, int split, hi
 }
 
 template <bool A_KS, bool B_KS, int EPI>
-hipError_t launch_any(const GemmF32Params& p, DeviceInfo& dev, int combo, const GemmF32x3Plan& plan, hipStream_t stream)
+hipError_t launch_any(const GemmF32Params& p, DeviceInfo& dev, int combo, const GemmF32Plan& plan, hipStream_t stream)
 {
     if (plan.tile == 0) return launch_tile<X0, A_KS, B_KS, EPI>(p, dev, combo * NTILES, plan.split, stream);
     return launch_tile<X1, A_KS, B_KS, EPI>(p, dev, combo * NTILES + 1, plan.split, stream);
@@ -539,14 +539,20 @@ hipError_t launch_any(const GemmF32Params& p, DeviceInfo& dev, int combo, const 
 //   four, 454 x 2559 over 476 21 / 16, 678 x 1365 over 712 17.9 / 18.1, 256 x 1000 over 2048 13.0 / 18.2
 //   (loading those lane by lane: 33, 39 and 36 of the first three).
 // What is within 5 % stays with the fp32 kernel.
-GemmF32x3Plan gemm_f32x3_plan(const GemmF32Args& a, int max_split)
+namespace {
+constexpr double LAUNCH_US = 1.5, OWN_US[NTILES] = {4.9, 6.3}, STEP_US[NTILES] = {2.16, 2.05}, IDLE_GAIN = 0.2, MARGIN = 0.95;
+}  // namespace
+
+// One workgroup on an idle chip, one block of k (8.56 us).
+double gemm_f32x3_least_us() { return (LAUNCH_US + OWN_US[0] + STEP_US[0] * (1.0 - IDLE_GAIN)) / MARGIN; }
+
+GemmF32Plan gemm_f32x3_plan(const GemmF32Args& a, int max_split)
 {
-    GemmF32x3Plan best = {-1, 1, 1e30};
+    GemmF32Plan best = {true, -1, 1, false, 1e30};
     // a whole block of k; 32-bit offsets inside a block and tile
     if (a.K < 32 || a.K > (1LL << 30) || a.lda >= (1LL << 22) || a.ldb >= (1LL << 22) || a.ldc >= (1LL << 22) || a.N >= (1LL << 22)) return best;
     auto aligned = [](const float* P, int64_t ld) { return ld % 4 == 0 && reinterpret_cast<uintptr_t>(P) % 16 == 0; };
     if (!a.a_kstrided && !(aligned(a.A, a.lda) && aligned(a.B, a.ldb))) return best;      // (direct loads)
-    static const double own[NTILES] = {4.9, 6.3}, step[NTILES] = {2.16, 2.05};
     const int cus = a.dev->cus > 0 ? a.dev->cus : 256;
     const int64_t blocks = (a.K + 31) / 32;
     for (int t = 0; t < NTILES; ++t) {
@@ -555,16 +561,16 @@ GemmF32x3Plan gemm_f32x3_plan(const GemmF32Args& a, int max_split)
         for (int s = 1; s <= max_split; ++s) {
             const int64_t steps = ((blocks + s - 1) / s + kw - 1) / kw, wgs = tiles * s;
             const double idle = wgs < cus ? 1.0 - (double)wgs / cus : 0.0;
-            double us = 1.5 + 0.8 * (1.0 - idle) + (double)((wgs + cus - 1) / cus) * (own[t] + (double)steps * step[t] * (1.0 - 0.2 * idle));
+            double us = LAUNCH_US + 0.8 * (1.0 - idle) + (double)((wgs + cus - 1) / cus) * (OWN_US[t] + (double)steps * STEP_US[t] * (1.0 - IDLE_GAIN * idle));
             if (s > 1) us += 4.0 + (double)(s + 1) * (double)a.M * (double)a.N * 4.0 / 6e6;
-            if (us < best.us) best = GemmF32x3Plan{t, s, us};
+            if (us < best.us) best = GemmF32Plan{true, t, s, false, us};
         }
     }
-    best.us /= 0.95;
+    best.us /= MARGIN;
     return best;
 }
 
-hipError_t launch_gemm_f32x3(const GemmF32Args& a, GemmF32Params p, const GemmF32x3Plan& plan, hipStream_t stream)
+hipError_t launch_gemm_f32x3(const GemmF32Args& a, GemmF32Params p, const GemmF32Plan& plan, hipStream_t stream)
 {
     const bool aks = a.a_kstrided, bks = a.b_kstrided;
     if (!aks && !bks && a.epilogue == EPI_STORE) return launch_any<false, false, EPI_STORE>(p, *a.dev, 0, plan, stream);

@@ -52,12 +52,11 @@ struct GemmF32Args {
                          // `partial`, to be added in their order, and C is not written; 1: C is the result
 };
 hipError_t launch_gemm_f32(const GemmF32Args& a, hipStream_t stream);
-// Estimated duration (us) of that launch (a.dev is needed).
-double gemm_f32_estimate_us(const GemmF32Args& a);
-// How the fp32 matrix pipes do it: the tile shape by its index in gemm_f32.hip, the ways k is divided over
-// workgroups, direct-to-LDS loads or loads through registers, and the estimated duration.  (Where the bf16 pipes on three
-// terms per value are estimated faster, launch_gemm_f32 takes those: gemm_f32x3.hip.)
+// How that launch does it (a.dev is needed): on the fp32 matrix pipes or, where that is estimated faster, on the bf16 pipes
+// with three terms per value (gemm_f32x3.hip); the tile shape by its index in that file; the ways k is divided over workgroups;
+// direct-to-LDS loads or loads through registers (fp32 pipes); and the estimated duration.
 struct GemmF32Plan {
+    bool three_terms;
     int tile, split;
     bool direct;
     double us;

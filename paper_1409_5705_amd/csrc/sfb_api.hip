@@ -750,7 +750,7 @@ static bool csr_use_gather(const sfb_ctx* ctx, int64_t B, int64_t J, int64_t D, 
     if (!sfb::csr_gather_supported(B, J, D) || ctx->csr_route == 1) return false;
     if (ctx->csr_route == 2) return true;
     if (dense) {
-        const double stream = (double)J * (double)D * 4.0 / 4.6e6, product = sfb::gemm_f32_estimate_us(*dense);
+        const double stream = (double)J * (double)D * 4.0 / 4.6e6, product = sfb::gemm_f32_plan(*dense).us;
         return sfb::csr_gather_f32_estimate_us(B, J, D, nnz, ctx->dev.cus) < 9.0 + 1.05 * (product > stream ? product : stream);
     }
     const double groups = (double)((B + 1023) / 1024), per_sample = (double)nnz / (double)B;

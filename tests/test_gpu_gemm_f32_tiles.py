@@ -46,6 +46,7 @@ APPLY_SHAPES = [
     (700, 800, 300), (701, 803, 300),          # 64 x 64
     (600, 800, 200), (401, 603, 77),           # 32 x 32
     (500, 1000, 260), (501, 603, 100),         # 64 x 32
+    (8324, 208, 8), (155, 8287, 4), (174, 5383, 140),      # the large tiles where the three bf16 terms do not take over (few pairs, narrow)
     (400, 600, 200), (16, 10000, 30), (30, 9001, 100), (9000, 20, 64), (64, 4100, 33),   # few slices, several workgroups a CU
     (33, 70, 96), (16, 16, 128), (17, 48, 1),  # 16 x 16
     (3, 2052, 65), (2052, 3, 200), (2, 37, 130), (1, 1, 5), (4, 6, 32),   # rows of fewer floats than a load takes
@@ -112,6 +113,8 @@ SC_SHAPES = [
     (4408, 164, 705), (132, 3780, 515),         # 128 x 128
     (2058, 101, 963), (103, 3662, 533),
     (2204, 2214, 119),                          # both 128 x 64 with a k-split
+    (8560, 4, 212), (5004, 4, 276),             # aligned and large, k below 32 (longer ones run on three bf16 terms): 128 x 128
+    (4, 8648, 200), (12, 5064, 264), (4, 8416, 130),   # and 128 x 64 shrink; 128 x 128, 128 x 64 and 64 x 64 residual
 ]
 
 

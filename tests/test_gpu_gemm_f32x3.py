@@ -214,10 +214,11 @@ def test_rows_of_a_larger_matrix_and_alignment(ctx):
     assert bool(torch.all((W.double() - ref).abs() <= (N + 4) * EPS * size + 2 * EPS * ref.abs() + 1e-30))
 
 
-# (J, D, B): logits of B samples and projections are J columns over D of k, residuals D columns over J; test_kernel_plans.py
-# asserts that these reach both tile shapes, whole and with a k-split
+# (J, D, B): logits of B samples, projections and shrink steps are J columns over D of k, residuals D columns over J;
+# test_kernel_plans.py asserts that each of these epilogues reaches both tile shapes, whole and with a k-split
 LOGITS_SHAPES = [(3476, 236, 295), (4096, 1024, 512), (1028, 4004, 517), (2548, 304, 770), (2732, 4148, 177)]
-SC_SHAPES = [(4096, 1024, 512), (2196, 2140, 98), (244, 3620, 275), (292, 2752, 714), (4120, 1824, 264), (3476, 236, 295)]
+SC_SHAPES = [(4096, 1024, 512), (2196, 2140, 98), (244, 3620, 275), (292, 2752, 714), (4120, 1824, 264), (3476, 236, 295),
+             (948, 1828, 648), (644, 44, 2956)]
 
 
 @pytest.mark.parametrize("J,D,B", LOGITS_SHAPES)

@@ -25,13 +25,14 @@ def test_stream_forward_shapes(lib, copy, shapes):
 
 
 def test_apply_shapes(lib):
-    reached = {K.gemm_f32(lib, "apply", N, J, D)[::2] for J, D, N in f32.APPLY_SHAPES}
-    assert reached == {(t, direct) for t in K.TILES for direct in (False, True)}
+    import test_gpu_gemm_f32x3 as x3
+    plans = [K.gemm_f32(lib, "apply", N, J, D) for J, D, N in f32.APPLY_SHAPES + x3.FP32_SHAPES]
+    assert {p[::2] for p in plans if p} == {(t, direct) for t in K.TILES for direct in (False, True)}
 
 
-@pytest.mark.parametrize("kind", ["logits", "residual"])
+@pytest.mark.parametrize("kind", ["logits", "shrink", "residual"])
 def test_sparse_code_shapes(lib, kind):
-    plans = [K.gemm_f32(lib, kind, B, J, D) for J, D, B in f32.SC_SHAPES + [(1001, 301, 99), (64, 4, 3)]]
+    plans = [p for p in (K.gemm_f32(lib, kind, B, J, D) for J, D, B in f32.SC_SHAPES + [(1001, 301, 99), (64, 4, 3)]) if p]
     assert {(t, direct) for t, _, direct in plans} == {(t, direct) for t in K.TILES for direct in (False, True)}
     assert len({t for t, split, _ in plans if split > 1}) >= 2
 
@@ -42,10 +43,9 @@ def test_three_term_shapes(lib):
     assert all(plans) and all(K.gemm_f32x3(lib, "apply", N, J, D) for J, D, N in [(1003, 2047, 300), (1001, 2049, 333)]), list(zip(x3.APPLY_SHAPES, plans))
     assert {(t, split > 1) for t, split in plans} == {(t, s) for t in K.X3_TILES for s in (False, True)}
     assert {K.gemm_f32(lib, "apply", N, J, D)[::2] for J, D, N in x3.FP32_SHAPES} == {("128x64", True), ("128x64", False)}
-    assert not any(K.gemm_f32x3(lib, "apply", N, J, D) for J, D, N in x3.FP32_SHAPES)
 
 
-@pytest.mark.parametrize("kind", ["logits", "residual"])
+@pytest.mark.parametrize("kind", ["logits", "shrink", "residual"])
 def test_three_term_shapes_of_contiguous_operands(lib, kind):
     import test_gpu_gemm_f32x3 as x3
     plans = [K.gemm_f32x3(lib, kind, B, J, D) for J, D, B in (x3.LOGITS_SHAPES if kind == "logits" else x3.SC_SHAPES)]
@@ -55,12 +55,8 @@ def test_three_term_shapes_of_contiguous_operands(lib, kind):
 def test_shapes_whose_row_kernels_add_up_the_splits(lib):
     import test_gpu_split_sums as s
 
-    def split(B, J, D):
-        x3 = K.gemm_f32x3(lib, "logits", B, J, D)
-        return (x3[1] if x3 else K.gemm_f32(lib, "logits", B, J, D)[1]) > 1
-
-    assert all(split(*shape) for shape in s.MLR_SHAPES[:-1] + s.DML_SHAPES[:-1])
-    assert not split(*s.MLR_SHAPES[-1]) and not split(*s.DML_SHAPES[-1])
+    assert all(K.split(lib, "logits", *shape) > 1 for shape in s.MLR_SHAPES[:-1] + s.DML_SHAPES[:-1])
+    assert K.split(lib, "logits", *s.MLR_SHAPES[-1]) == K.split(lib, "logits", *s.DML_SHAPES[-1]) == 1
 
 
 def test_shapes_of_the_forward_on_rows(lib):
