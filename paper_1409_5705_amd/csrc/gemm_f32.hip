@@ -619,12 +619,16 @@ constexpr int NTILES = 6;
 // longer (`share` of its time per neighbour), the round of all of them less.  Measured (us of sfb_apply, one workgroup
 // per CU / several, with the same tile): 16 x 100000 with 100 pairs 55 / 22 T5, 32 x 200000 with 256 103 / 66 T4,
 // 100000 x 16 with 100 34 / 20 T3, 5000 x 3000 with 10 49 / 35 T1.
+// The sum of a k-split is a launch of its own or, where the caller's row kernel adds the parts up (GemmF32Args::parts), the
+// traffic and a microsecond: 209 shapes of logits and 169 of projections (16 to 700 samples) are 1.4 and 1.2 % faster in the mean
+// than with the cost of the launch (22 x 20 over 6615 20.7 / 13.5, 64 x 624 over 5496 18.2 / 15.2; 104 x 520 over 4200
+// 13.5 / 14.9), those that the kernel on three bf16 terms takes among them.
 struct TileCost {
     double slice_us, tile_us, idle_gain, share;
     int wgs;       // workgroups a CU has registers for
 };
 template <class TL>
-double plan_time(int64_t M, int64_t N, int64_t K, int cus, int s, bool direct, const TileCost& c)
+double plan_time(int64_t M, int64_t N, int64_t K, int cus, int s, bool direct, bool parts, const TileCost& c)
 {
     const int64_t tiles = ((M + TL::BM - 1) / TL::BM) * ((N + TL::BN - 1) / TL::BN) * s, nk = (K + TL::KB - 1) / TL::KB;
     const int64_t slices = s > 1 ? (nk + s - 1) / s : nk;
@@ -643,11 +647,11 @@ double plan_time(int64_t M, int64_t N, int64_t K, int cus, int s, bool direct, c
         together += c.share * (double)(wgs - 1);
     }
     double t = 2.5 + rounds * ((double)slices * slice_us + c.tile_us) * together;
-    if (s > 1) t += 4.5 + (double)(s + 1) * (double)M * (double)N * 4.0 / 3e6;      // the second pass
+    if (s > 1) t += (parts ? 1.0 : 4.5) + (double)(s + 1) * (double)M * (double)N * 4.0 / 3e6;      // the second pass
     return t;
 }
 
-GemmF32Plan plan_gemm(int64_t M, int64_t N, int64_t K, int cus, int max_split, bool direct)
+GemmF32Plan plan_gemm(int64_t M, int64_t N, int64_t K, int cus, int max_split, bool direct, bool parts)
 {
     static const TileCost costs[2][NTILES] = {
         {{2.10, 6.5, 0.05, 0.0, 1}, {1.22, 5.0, 0.05, 0.5, 1}, {1.25, 4.7, 0.1, 0.3, 1}, {0.69, 3.5, 0.2, 0.2, 2}, {0.80, 3.0, 0.0, 0.3, 2}, {0.40, 1.2, 1.0, 0.35, 2}},
@@ -655,9 +659,9 @@ GemmF32Plan plan_gemm(int64_t M, int64_t N, int64_t K, int cus, int max_split, b
     const TileCost* const c = costs[direct ? 1 : 0];
     GemmF32Plan best = {false, 0, 1, direct, 1e30};
     for (int s = 1; s <= max_split; ++s) {
-        const double t[NTILES] = {plan_time<T0>(M, N, K, cus, s, direct, c[0]), plan_time<T1>(M, N, K, cus, s, direct, c[1]),
-                                  plan_time<T2>(M, N, K, cus, s, direct, c[2]), plan_time<T3>(M, N, K, cus, s, direct, c[3]),
-                                  plan_time<T4>(M, N, K, cus, s, direct, c[4]), plan_time<T5>(M, N, K, cus, s, direct, c[5])};
+        const double t[NTILES] = {plan_time<T0>(M, N, K, cus, s, direct, parts, c[0]), plan_time<T1>(M, N, K, cus, s, direct, parts, c[1]),
+                                  plan_time<T2>(M, N, K, cus, s, direct, parts, c[2]), plan_time<T3>(M, N, K, cus, s, direct, parts, c[3]),
+                                  plan_time<T4>(M, N, K, cus, s, direct, parts, c[4]), plan_time<T5>(M, N, K, cus, s, direct, parts, c[5])};
         for (int i = 0; i < NTILES; ++i)
             if (t[i] < best.us) best = GemmF32Plan{false, i, s, direct, t[i]};
     }
@@ -767,7 +771,7 @@ int64_t gemm_f32_partial_bytes(int64_t M, int64_t N, int64_t K)
 GemmF32Plan gemm_f32_plan(const GemmF32Args& a)
 {
     const int max_split = a.partial ? gemm_f32_max_split(a.M, a.N, a.K) : 1;
-    const GemmF32Plan plan = plan_gemm(a.M, a.N, a.K, a.dev->cus > 0 ? a.dev->cus : 256, max_split, direct_loads(a));
+    const GemmF32Plan plan = plan_gemm(a.M, a.N, a.K, a.dev->cus > 0 ? a.dev->cus : 256, max_split, direct_loads(a), a.parts != nullptr);
     if (plan.us <= gemm_f32x3_least_us()) return plan;      // (a small call does without the other model, 0.1 us of the host)
     const GemmF32Plan x3 = gemm_f32x3_plan(a, max_split);
     return x3.us < plan.us ? x3 : plan;
@@ -776,14 +780,14 @@ GemmF32Plan gemm_f32_plan(const GemmF32Args& a)
 hipError_t launch_gemm_f32(const GemmF32Args& a, hipStream_t stream)
 {
     if (a.M <= 0 || a.N <= 0) return hipSuccess;
-    if (!a.dev) return hipErrorInvalidValue;
+    if (!a.dev || (a.parts && a.epilogue != EPI_STORE)) return hipErrorInvalidValue;
     Params p = {};
     p.A = a.A; p.B = a.B; p.C = a.C; p.aux = a.aux; p.L_ptr = a.L_ptr;
     p.lda = a.lda; p.ldb = a.ldb; p.ldc = a.ldc;
     p.M = a.M; p.N = a.N; p.K = a.K;
     p.eta = a.eta; p.lambda = a.lambda;
     p.partial = a.partial;
-    p.parts = a.epilogue == EPI_STORE ? a.parts : nullptr;
+    p.parts = a.parts;
     const GemmF32Plan plan = gemm_f32_plan(a);
     if (plan.three_terms) return launch_gemm_f32x3(a, p, plan, stream);
     const bool aks = a.a_kstrided, bks = a.b_kstrided;

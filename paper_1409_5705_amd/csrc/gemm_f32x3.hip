@@ -527,23 +527,23 @@ hipError_t launch_any(const GemmF32Params& p, DeviceInfo& dev, int combo, const 
 
 }  // namespace
 
-// Estimated duration (us): the launch (more with the chip full), and rounds of one workgroup per CU, each `own` for its
-// first loads, meeting and epilogue and `step` for every block of 32 of k of a wavefront (less where CUs are idle); a
-// k-split pays a second launch and the traffic of the partial sums.  Fitted to 118 shapes, 60 of sfb_apply (100 x 100 with
-// 32 pairs to 4100 x 8200 with 4000), 58 of logits and residuals (64 samples to 700; rms of the logarithm 4 %); with the
-// estimates of the fp32 kernel the choice between the two was 13.5 % faster in the mean than that kernel alone, the better
-// one each time 14.0 %.  fp32 kernel / this one (us):
-//   1000 x 2048, 2048 pairs 77 / 48    4096 x 4096, 2048 483 / 321    1003 x 2047, 800 43 / 24    1024 x 4096, 512 41 / 28
-//   616 x 2488, 327 19 / 13            2090 x 831, 148 15.9 / 11.3    1561 x 5818, 37 34 / 30     284 x 850, 1340 14.8 / 16
-//   by way of LDS: 512 x 4096 over 1024 41 / 27, 512 x 1024 over 4096 41 / 33 and (k-strided B) 43 / 34 with a k-split of
+// Estimated duration (us): the launch (more with the chip full), and rounds of one workgroup per CU, each OWN_US for its
+// first loads, meeting and epilogue and STEP_US for every block of 32 of k of a wavefront (less where CUs are idle); a
+// k-split pays the traffic of the partial sums and, unless the caller's row kernel adds them up, a second launch.  Fitted to
+// 69 shapes of sfb_apply (100 x 100 with 16 pairs to 4096 x 8192 with 3000; rms of the logarithm 4 %); with the estimates of
+// the fp32 kernel the plan is within 1.2 % of the best one of all tiles, splits and both kernels in the mean, on 147 others
+// within 3 %.  fp32 kernel / this one (us):
+//   1000 x 2048, 2048 pairs 77 / 49    4096 x 4096, 2048 483 / 347    1003 x 2047, 800 43 / 25    1024 x 4096, 512 41 / 29.5
+//   616 x 2488, 327 19 / 13.8          2090 x 831, 148 15.9 / 11.3    1561 x 5818, 37 34 / 30     284 x 850, 1340 14.8 / 16
+//   by way of LDS: 512 x 4096 over 1024 41 / 27.5, 512 x 1024 over 4096 41 / 34 and (k-strided B) 43 / 35 with a k-split of
 //   four, 454 x 2559 over 476 21 / 16, 678 x 1365 over 712 17.9 / 18.1, 256 x 1000 over 2048 13.0 / 18.2
 //   (loading those lane by lane: 33, 39 and 36 of the first three).
 // What is within 5 % stays with the fp32 kernel.
 namespace {
-constexpr double LAUNCH_US = 1.5, OWN_US[NTILES] = {4.9, 6.3}, STEP_US[NTILES] = {2.16, 2.05}, IDLE_GAIN = 0.2, MARGIN = 0.95;
+constexpr double LAUNCH_US = 1.5, OWN_US[NTILES] = {5.2, 6.8}, STEP_US[NTILES] = {2.3, 2.12}, IDLE_GAIN = 0.2, MARGIN = 0.95;
 }  // namespace
 
-// One workgroup on an idle chip, one block of k (8.56 us).
+// One workgroup on an idle chip, one block of k (8.99 us).
 double gemm_f32x3_least_us() { return (LAUNCH_US + OWN_US[0] + STEP_US[0] * (1.0 - IDLE_GAIN)) / MARGIN; }
 
 GemmF32Plan gemm_f32x3_plan(const GemmF32Args& a, int max_split)
@@ -562,7 +562,7 @@ GemmF32Plan gemm_f32x3_plan(const GemmF32Args& a, int max_split)
             const int64_t steps = ((blocks + s - 1) / s + kw - 1) / kw, wgs = tiles * s;
             const double idle = wgs < cus ? 1.0 - (double)wgs / cus : 0.0;
             double us = LAUNCH_US + 0.8 * (1.0 - idle) + (double)((wgs + cus - 1) / cus) * (OWN_US[t] + (double)steps * STEP_US[t] * (1.0 - IDLE_GAIN * idle));
-            if (s > 1) us += 4.0 + (double)(s + 1) * (double)a.M * (double)a.N * 4.0 / 6e6;
+            if (s > 1) us += (a.parts ? 0.0 : 3.0) + (double)(s + 1) * (double)a.M * (double)a.N * 4.0 / 6e6;
             if (us < best.us) best = GemmF32Plan{true, t, s, false, us};
         }
     }

@@ -48,7 +48,7 @@ struct GemmF32Args {
     float lambda;        // EPI_SHRINK
     float* partial;      // scratch of gemm_f32_partial_bytes(M, N, K) for the k-split, or null (no split)
     DeviceInfo* dev;     // the context's device facts
-    int* parts;          // EPI_STORE, nullable: the caller adds up the k-splits itself.  *parts of them are [M][N] arrays in
+    int* parts;          // EPI_STORE only, nullable: the caller adds up the k-splits itself.  *parts of them are [M][N] arrays in
                          // `partial`, to be added in their order, and C is not written; 1: C is the result
 };
 hipError_t launch_gemm_f32(const GemmF32Args& a, hipStream_t stream);

@@ -808,13 +808,13 @@ int sfb_mlr_sf_csr(sfb_ctx* ctx, const float* W, int64_t J, int64_t D, const sfb
         g.M = B; g.N = J; g.K = D;
         g.epilogue = sfb::EPI_STORE;
         if (part > 0) g.partial = reinterpret_cast<float*>(ctx->ws + round_up(B * J * 4));
+        if (sfb::mlr_softmax_adds(B, J, ctx->dev.cus)) g.parts = &sm.planes;
         if (csr_use_gather(ctx, B, J, D, X->nnz, &g)) {
             SFB_RUN(KID_CSR_GATHER, sfb::launch_csr_forward_gather(X->indptr, X->indices, X->values, false, W, Z, B, J, D,
                                                                    X->nnz, region, st));
         } else {
             SFB_RUN(KID_FILL, sfb::launch_fill_u32(Xd, 0u, B * D, st));
             SFB_RUN(KID_CSR, sfb::launch_csr_scatter(X->indptr, X->indices, X->values, false, nullptr, Xd, B, D, X->nnz, D, 1, st));
-            if (sfb::mlr_softmax_adds(B, J, ctx->dev.cus)) g.parts = &sm.planes;
             SFB_RUN(KID_GEMM_F32_STORE, sfb::launch_gemm_f32(g, st));
             if (sm.planes > 1) sum_of_parts(sm, g);
         }

@@ -38,14 +38,16 @@ def forward(lib, B, J, D, have_copy):
 def _plan(lib, kind, B, J, D):
     """The plan that launch_gemm_f32 follows for a contraction of sfb_compute_sf or sfb_apply.
 
-    kind: "logits" (stored for a kernel that reads them: X W^T), "shrink" (the same operands), "residual" (codes times W) or
-    "apply" (U^T V over B pairs)."""
+    kind: "logits" and "projections" (X W^T, stored for a row kernel that may add up the k-splits), "shrink" (the same
+    operands), "residual" (codes times W) or "apply" (U^T V over B pairs)."""
     f = lib._ZN3sfb13gemm_f32_planERKNS_11GemmF32ArgsE
     f.restype, f.argtypes = _GemmPlan, [ctypes.c_void_p]
     dev = (ctypes.c_int * 64)(CUS, 8)           # DeviceInfo starts with the CU count
     a = _GemmArgs(A=4096, B=4096, partial=4096, dev=ctypes.addressof(dev))
-    if kind in ("logits", "shrink"):
-        a.M, a.N, a.K, a.lda, a.ldb, a.ldc, a.epilogue = B, J, D, D, D, J, EPI_STORE if kind == "logits" else EPI_SHRINK
+    if kind in ("logits", "projections", "shrink"):
+        a.M, a.N, a.K, a.lda, a.ldb, a.ldc, a.epilogue = B, J, D, D, D, J, EPI_SHRINK if kind == "shrink" else EPI_STORE
+        if kind == "projections" and J <= 1024 or kind == "logits" and (J <= 1024 or J <= 4096 and B >= CUS):
+            a.parts = 4096                      # (dml_scale_adds, mlr_softmax_adds)
     elif kind == "residual":
         a.M, a.N, a.K, a.lda, a.ldb, a.ldc, a.b_kstrided, a.epilogue = B, D, J, J, D, D, True, EPI_RESID
     else:
@@ -67,3 +69,7 @@ def gemm_f32x3(lib, kind, B, J, D):
 
 def split(lib, kind, B, J, D):
     return _plan(lib, kind, B, J, D).split
+
+
+def estimate(lib, kind, B, J, D):
+    return _plan(lib, kind, B, J, D).us

@@ -30,7 +30,7 @@ def test_apply_shapes(lib):
     assert {p[::2] for p in plans if p} == {(t, direct) for t in K.TILES for direct in (False, True)}
 
 
-@pytest.mark.parametrize("kind", ["logits", "shrink", "residual"])
+@pytest.mark.parametrize("kind", ["projections", "shrink", "residual"])
 def test_sparse_code_shapes(lib, kind):
     plans = [p for p in (K.gemm_f32(lib, kind, B, J, D) for J, D, B in f32.SC_SHAPES + [(1001, 301, 99), (64, 4, 3)]) if p]
     assert {(t, direct) for t, _, direct in plans} == {(t, direct) for t in K.TILES for direct in (False, True)}
@@ -45,18 +45,19 @@ def test_three_term_shapes(lib):
     assert {K.gemm_f32(lib, "apply", N, J, D)[::2] for J, D, N in x3.FP32_SHAPES} == {("128x64", True), ("128x64", False)}
 
 
-@pytest.mark.parametrize("kind", ["logits", "shrink", "residual"])
+@pytest.mark.parametrize("kind", ["projections", "shrink", "residual"])
 def test_three_term_shapes_of_contiguous_operands(lib, kind):
     import test_gpu_gemm_f32x3 as x3
-    plans = [K.gemm_f32x3(lib, kind, B, J, D) for J, D, B in (x3.LOGITS_SHAPES if kind == "logits" else x3.SC_SHAPES)]
+    plans = [K.gemm_f32x3(lib, kind, B, J, D) for J, D, B in (x3.LOGITS_SHAPES if kind == "projections" else x3.SC_SHAPES)]
     assert {(p[0], p[1] > 1) for p in plans if p} == {(t, s) for t in K.X3_TILES for s in (False, True)}
 
 
 def test_shapes_whose_row_kernels_add_up_the_splits(lib):
     import test_gpu_split_sums as s
 
-    assert all(K.split(lib, "logits", *shape) > 1 for shape in s.MLR_SHAPES[:-1] + s.DML_SHAPES[:-1])
-    assert K.split(lib, "logits", *s.MLR_SHAPES[-1]) == K.split(lib, "logits", *s.DML_SHAPES[-1]) == 1
+    for kind, shapes in (("logits", s.MLR_SHAPES), ("projections", s.DML_SHAPES)):
+        assert all(K.split(lib, kind, *shape) > 1 for shape in shapes[:-1])
+        assert K.split(lib, kind, *shapes[-1]) == 1
 
 
 def test_shapes_of_the_forward_on_rows(lib):
@@ -64,3 +65,12 @@ def test_shapes_of_the_forward_on_rows(lib):
     plans = [K.forward(lib, *s, copy) for s in SHAPES for copy in (False, True)]
     assert all(mt > 0 for mt, _, _ in plans), list(zip([s for s in SHAPES for _ in "ab"], plans))
     assert {mt for mt, _, _ in plans} == {1, 2, 4} and {split > 1 for _, _, split in plans} == {False, True}
+
+
+def test_adding_up_elsewhere_is_cheaper(lib):
+    """A k-split whose parts the row kernel adds up pays no launch for their sum: the same contraction is split at fewer products
+    where it is a projection than where it is a shrink step, and never estimated slower."""
+    for B, J in ((400, 300), (410, 292), (663, 60), (512, 1024)):
+        first = {kind: next(D for D in range(256, 40000, 32) if K.split(lib, kind, B, J, D) > 1) for kind in ("projections", "shrink")}
+        assert first["projections"] < first["shrink"], (B, J, first)
+        assert all(K.estimate(lib, "projections", B, J, D) <= K.estimate(lib, "shrink", B, J, D) for D in range(32, 10000, 500))
