@@ -251,7 +251,7 @@ int sfb_apply_signed(sfb_ctx* ctx, float* W, int64_t J, int64_t D, const void* U
  * pairs every column is touched by some pair).  fp32 factors, and bf16 ones with
  * more than about one per cent of non-zeros, few pairs or a small W, go through
  * the dense contraction; otherwise the products are formed over the pairs that
- * have entries in a group of sixteen columns only (the same override; results
+ * have entries in a group of sixteen columns only (chosen per call; results
  * agree to rounding: the order of summation differs).
  *
  * A stored entry with a column outside [0, cols) or a row range outside
@@ -278,7 +278,7 @@ int sfb_csr_check(sfb_ctx* ctx, const sfb_csr* m, int64_t* violations);
  * the second factors are the rows of X themselves.  y: int32 labels [B]. */
 int64_t sfb_mlr_sf_csr_workspace_bytes(int64_t J, int64_t D, int64_t B, int32_t dtype);
 int sfb_mlr_sf_csr(sfb_ctx* ctx, const float* W, int64_t J, int64_t D, const sfb_csr* X, const int32_t* y, void* U);
-/* Route of sfb_mlr_sf_csr and sfb_apply_csr on this context: 0 = chosen per call (the default), 1 = always the dense product,
+/* Route of sfb_mlr_sf_csr on this context: 0 = chosen per call (the default), 1 = always the dense product,
  * 2 = always over the stored entries (shapes that route cannot take still go the dense way).  For
  * measurements and tests; results agree to rounding (different summation order). */
 int sfb_set_csr_route(sfb_ctx* ctx, int route);

@@ -429,7 +429,7 @@ class Context:
         self._check(rc, "sfb_mlr_sf_csr")
 
     def sfb_set_csr_route(self, route: int = 0):
-        """0: sfb_mlr_sf_csr and sfb_apply_csr pick their route per call; 1: dense product; 2: over the stored entries."""
+        """0: sfb_mlr_sf_csr picks its route per call; 1: dense product; 2: over the stored entries."""
         self._check(lib().sfb_set_csr_route(self._h, int(route)), "sfb_set_csr_route")
 
     def sfb_apply_csr(self, W, U, indptr, indices, values, eta, coef=None):

@@ -64,8 +64,9 @@ struct sfb_ctx {
     uint16_t* split_lo;
     // CU / XCD counts of the device, per-device launch state, wait bound of the one-read softmax
     sfb::DeviceInfo dev;
-    // route of sfb_mlr_sf_csr and sfb_apply_csr: 0 chosen from the number of stored entries, 1 dense contraction, 2 over the non-zeros
-    int csr_route;
+    // route of sfb_mlr_sf_csr: 0 chosen from the number of stored entries, 1 dense contraction, 2 over the non-zeros; the same
+    // of sfb_apply_csr, which only the tests force
+    int csr_route, apply_csr_route;
     // this device's copy of the library's static scratch array (sfb_apply_static), resolved by sfb_create
     char* static_scratch;
     int static_scratch_err;
@@ -205,6 +206,10 @@ int check_batch(int32_t model, int64_t J, int64_t D, const sfb_batch* b)
 
 }  // namespace
 
+namespace sfb {
+void force_apply_csr_route(sfb_ctx* ctx, int route) { ctx->apply_csr_route = route; }      // (for the tests)
+}  // namespace sfb
+
 extern "C" {
 
 int sfb_create(sfb_ctx** out, int device_id, void* hip_stream)
@@ -230,7 +235,7 @@ int sfb_create(sfb_ctx** out, int device_id, void* hip_stream)
     c->shadow_buf = nullptr;
     c->shadow_J = c->shadow_D = 0;
     c->split_lo = nullptr;
-    c->csr_route = 0;
+    c->csr_route = c->apply_csr_route = 0;
     int cus = 0, xcds = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device_id) != hipSuccess || cus <= 0) {
         delete c;
@@ -865,8 +870,8 @@ static bool apply_csr_use_gather(const sfb_ctx* ctx, int64_t N, int64_t J, int64
 {
     // the lists must fit where U^T would be, in front of V^T
     const int64_t room = reinterpret_cast<const char*>(sfb::apply_bf16_vt(ctx->ws, N, J)) - ctx->ws;
-    if (ctx->csr_route == 1 || !sfb::apply_gather_supported(N, J, D) || sfb::apply_gather_workspace_bytes(N, D) > room) return false;
-    if (ctx->csr_route == 2) return true;
+    if (ctx->apply_csr_route == 1 || !sfb::apply_gather_supported(N, J, D) || sfb::apply_gather_workspace_bytes(N, D) > room) return false;
+    if (ctx->apply_csr_route == 2) return true;
     const double panels = (double)((J + 63) / 64), cus = (double)ctx->dev.cus;
     if (panels < 0.75 * cus || (double)J * (double)D < 33e6) return false;
     const double rounds = (double)(((J + 63) / 64 + ctx->dev.cus - 1) / ctx->dev.cus);

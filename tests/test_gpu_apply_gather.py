@@ -5,6 +5,8 @@ Tolerance: bf16 products are exact in fp32, and an fp32 sum of k products, in an
 their absolute values of the exact one (first order); the update adds one rounding of the product with eta and one of the
 result.
 """
+import ctypes
+
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -34,8 +36,11 @@ def factors(N, J, D, rho, seed):
 
 
 def context(sfb, layout, W, route):
+    """route of sfb_apply_csr: 0 chosen, 1 dense contraction, 2 over the stored entries"""
     c = sfb.Context(0)
-    c.sfb_set_csr_route(route)
+    force = sfb.lib()._ZN3sfb21force_apply_csr_routeEP7sfb_ctxi
+    force.restype, force.argtypes = None, [ctypes.c_void_p, ctypes.c_int]
+    force(c._h, route)
     if layout == "copy":
         c.sfb_shadow_attach(W)
     elif layout == "planes":
@@ -95,3 +100,20 @@ def test_picks_its_route(sfb, N, J, D, rho, gather):
     assert bool(torch.all((W - W1).abs() <= 2 * (N + 4) * EPS * size + 4 * EPS * W1.abs()))
     c.close()
     d.close()
+
+
+@pytest.mark.parametrize("route", [0, 1, 2])
+@pytest.mark.parametrize("rho,gather", [(0.005, True), (0.05, False)])
+def test_the_route_of_the_forward_is_not_the_applys(sfb, rho, gather, route):
+    """sfb_set_csr_route is about sfb_mlr_sf_csr: the apply keeps choosing for itself."""
+    N, J, D = 1024, 16384, 2056
+    U, V, W, csr = factors(N, J, D, rho, 6)
+    c = sfb.Context(0)
+    c.sfb_split_attach(W)
+    c.sfb_set_csr_route(route)
+    c.sfb_profile_enable(True)
+    c.sfb_profile_collect()
+    c.sfb_apply_csr(W, U, *csr, 0.01)
+    ran = c.sfb_profile_collect()
+    assert ("apply_gather" in ran) == gather, ran
+    c.close()
