@@ -12,6 +12,9 @@
 // lists (4.6 TB/s; dense product 6.12 and 0.26 for U^T); every further step of 32 pairs a tile 0.3 ms.  A request of the
 // list waits for an L2 hit, several times what a step's LDS reads and MFMAs take: one step at a time it was 0.48 ms a
 // step.
+// An infinite or NaN factor is NaN times the zeros that are left out, as in the dense product: a panel with one is gone over
+// again at the end.  (Looking for them costs 0.5 % there, 3 to 4 % of 51344 x 696 with 1191 pairs; the second pass, where
+// every factor is NaN, 100000 x 5000 with 512 pairs 0.67 -> 1.8 ms.)
 #include "planes.h"
 
 #include <type_traits>
@@ -22,6 +25,7 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 constexpr int PANEL = 64, CHUNK = 128, NT = 512;      // classes of a workgroup; columns of a wavefront's turn
 constexpr int AHEAD = 4;                              // steps requested at a time (2 or 3: 1 % slower at three steps a tile)
@@ -43,6 +47,7 @@ struct Params {
 // Column of element l16 of tile t (0 .. 7) of a chunk: a lane of the apply owns eight columns of its eight tiles, in a row
 // (planes) or as two groups of four 64 apart (fp32 array), that 16-byte accesses cover.
 __device__ __forceinline__ int tile_column(bool planes, int t, int l16) { return planes ? 8 * l16 + t : 4 * l16 + (t & 3) + 64 * (t >> 2); }
+__device__ __forceinline__ int tile_of_column(bool planes, int c) { return planes ? c & 7 : (c & 3) + 4 * (c >> 6); }
 
 // One workgroup per tile.  Vt: V^T as a bf16 operand of pitch Np (columns D .. of the last block of rows are zero).  The
 // listed pairs of each residue modulo 4 take every fourth place of the list (the gaps of the shorter ones are rows of
@@ -127,12 +132,16 @@ __global__ __launch_bounds__(NT, 2) void apply_gather_kernel(Params p)
         const uint32_t xcds = (uint32_t)p.num_xcd, x = blockIdx.x % xcds, q = (uint32_t)p.panels / xcds, r = (uint32_t)p.panels % xcds;
         m0 = (int64_t)(x * q + (x < r ? x : r) + blockIdx.x / xcds) * PANEL;
     }
+    u16x2 largest = {0, 0};      // from 0x7f80 on: a value that is not finite
     for (int i = tid >> 3; i < (p.N + 3) / 4 * 4 + 4; i += NT / 8) {
         const int piece = tid & 7;
         u32x4 v = {0u, 0u, 0u, 0u};
         if (i < p.N && m0 + 8 * piece < p.J) v = *reinterpret_cast<const u32x4*>(p.U + (int64_t)i * p.J + m0 + 8 * piece);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) largest = __builtin_elementwise_max(largest, __builtin_bit_cast(u16x2, v[k] & 0x7fff7fffu));
         *reinterpret_cast<u32x4*>(lds + i * 128 + (((piece >> 1) ^ (i & 3)) << 5) + ((piece & 1) << 4)) = v;
     }
+    const bool wave_bad = __builtin_amdgcn_ballot_w64(largest[0] >= 0x7f80 || largest[1] >= 0x7f80) != 0;
     __syncthreads();
 
     const int last_m = (int)(p.J - m0 < PANEL ? p.J - m0 : PANEL) - 1;
@@ -288,6 +297,58 @@ __global__ __launch_bounds__(NT, 2) void apply_gather_kernel(Params p)
                 store(std::integral_constant<int, ta + 2>{}, e_, w[ta][e]);
             });
         });
+    }
+
+    // ---- a factor that is not finite is NaN times the zeros of V that were left out: each wavefront goes over its chunks
+    // again, a lane a class, and makes NaN what belongs to a class and a tile with such a pair that is not listed there
+    // (the arguments and the lane read again: kept since the start they would take registers from the loop above)
+    uint64_t args = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    const int cls = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    const auto* q = (const __attribute__((address_space(4))) Params*)args;
+    const int N = q->N;
+    __syncthreads();
+    uint32_t* const flag = reinterpret_cast<uint32_t*>(lds + (N + 3) / 4 * 4 * 128);      // (in the rows of zeros)
+    if (wave_bad && cls == 0) *flag = 1u;
+    __syncthreads();
+    if (*flag == 0u) return;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    auto bad_of = [&](int i) -> int {
+        return (*reinterpret_cast<const uint16_t*>(lds + i * 128 + (((cls >> 4) ^ (i & 3)) << 5) + 2 * (cls & 15)) & 0x7f80) == 0x7f80 ? 1 : 0;
+    };
+    int all = 0;
+    for (int i = 0; i < N; ++i) all += bad_of(i);
+    const int64_t D = q->D;
+    const uint32_t nan_word = split_word(__builtin_nanf(""));
+    for (int chunk = wave; chunk < q->chunks; chunk += NT / 64) {
+        int unlisted = 0;      // bit t: tile t of the chunk lacks such a pair of this class
+        for (int t = 0; t < 8; ++t) {
+            const int64_t tile = 8 * (int64_t)chunk + t;
+            const int n = (int)q->steps[tile];
+            int listed = 0;
+            if (__builtin_amdgcn_ballot_w64(all > 0 && all <= 32 * n) != 0)      // (more than can be listed: need not be counted)
+                for (int j = 0; j < 16 * n; ++j) {
+                    const uint32_t two = q->rows[tile * q->max_steps * 16 + j];
+                    const int i0 = (int)(two & 0xffffu), i1 = (int)(two >> 16);
+                    if (i0 < N) listed += bad_of(i0);
+                    if (i1 < N) listed += bad_of(i1);
+                }
+            if (all > 32 * n || listed < all) unlisted |= 1 << t;
+        }
+        for (uint64_t rows = __builtin_amdgcn_ballot_w64(unlisted != 0 && m0 + cls < q->J); rows != 0; rows &= rows - 1) {
+            const int r = __builtin_ctzll(rows), tiles = __builtin_amdgcn_readlane(unlisted, r);
+            const int64_t m = m0 + r;
+            for (int e = 0; e < 2; ++e) {
+                const int c = 2 * cls + e;
+                const int64_t d = (int64_t)chunk * CHUNK + c;
+                if (d >= D || !(tiles >> tile_of_column(PLANES, c) & 1)) continue;
+                if (q->shadow) q->shadow[((m / BM) * (q->ld_shadow / BK) + d / BK) * (int64_t)(BM * BK) + (m % BM) * BK + d % BK] = (uint16_t)(nan_word >> 16);
+                if (PLANES)
+                    q->lo[((m / BM) * ((D + BN - 1) / BN) + d / BN) * (int64_t)(BM * BN) + (m % BM) * BN + d % BN] = (uint16_t)nan_word;
+                else
+                    q->C[m * q->ldc + d] = __builtin_nanf("");
+            }
+        }
     }
 }
 

@@ -102,6 +102,44 @@ def test_picks_its_route(sfb, N, J, D, rho, gather):
     d.close()
 
 
+@pytest.mark.parametrize("layout", ["plain", "copy", "planes"])
+@pytest.mark.parametrize("N,J,D,rho,bad", [
+    (1, 72, 24, 0.3, 3), (300, 520, 328, 0.01, 5), (300, 520, 328, 0.01, 4000), (64, 648, 136, 1.0, 9), (256, 704, 136, 0.0, 3),
+    (1024, 640, 1160, 0.005, 40), (1276, 520, 264, 0.05, 30), (1274, 520, 264, 0.3, 100),
+])
+def test_not_finite_factors(sfb, N, J, D, rho, bad, layout):
+    """An infinite or NaN factor times the zeros of V is NaN: it reaches every column, as in the dense contraction."""
+    print("apply_gather, not finite", N, J, D, rho, bad, layout, flush=True)
+    U, V, W, csr = factors(N, J, D, rho, N + J + 1)
+    g = torch.Generator().manual_seed(7)
+    at, what = torch.randint(N * J, (bad,), generator=g).to(DEV), torch.tensor([float("inf"), -float("inf"), float("nan")], device=DEV)
+    U.view(-1)[at] = what[torch.arange(bad, device=DEV) % 3].to(torch.bfloat16)
+    out = []
+    for route in (1, 2):
+        W1 = W.clone()
+        c = context(sfb, layout, W1, route)
+        c.sfb_apply_csr(W1, U, *csr, 0.01)
+        if layout == "copy":      # the copy's rows, by logits of unit samples
+            X, y = torch.eye(8, D, device=DEV).to(torch.bfloat16), torch.zeros(8, dtype=torch.int32, device=DEV)
+            P = torch.empty(8, J, dtype=torch.bfloat16, device=DEV)
+            c.sfb_compute_sf(sfb.SFB_MLR, W1, X, Y=y, U=P)
+            out.append(P)
+        if layout == "planes":
+            c.sfb_split_export(W1)
+        out.append(W1)
+        c.close()
+    ref = W.double() - 0.01 * (U.double().t() @ V.double())
+    assert not bool(torch.isfinite(ref).all())
+    for got in (out[-1], out[len(out) // 2 - 1]):
+        for test in (torch.isnan, torch.isposinf, torch.isneginf):
+            assert torch.equal(test(got), test(ref)), (test, (test(got) != test(ref)).nonzero()[:4])
+    if layout == "copy":
+        assert torch.equal(torch.isnan(out[0]), torch.isnan(out[2]))
+    fine = torch.isfinite(ref)
+    size = 0.01 * (U.abs().double().t() @ V.abs().double())
+    assert bool(torch.all(((out[-1].double() - ref).abs() <= (N + 4) * EPS * size + 4 * EPS * (ref.abs() + W.abs().double()))[fine]))
+
+
 @pytest.mark.parametrize("route", [0, 1, 2])
 @pytest.mark.parametrize("rho,gather", [(0.005, True), (0.05, False)])
 def test_the_route_of_the_forward_is_not_the_applys(sfb, rho, gather, route):
