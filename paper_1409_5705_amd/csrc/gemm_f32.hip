@@ -1,10 +1,9 @@
 // fp32 MFMA GEMM family for gfx950 (v_mfma_f32_16x16x4_f32), used by every
 // fp32 workload: MLR logits, DML projections, the two ISTA contractions of
 // sparse coding, and the reconstruction + application of the SF sum.  It keeps the
-// contractions of less than some 10 us and the ones with a k below 32; the larger ones go
-// to the bf16 matrix instructions on three terms per value (gemm_f32x3.hip) wherever the
-// two cost models find that faster, so the first, second, third and seventh line below
-// are the ones it no longer has (now 48, 29, 33 and 26 us).
+// contractions of less than some 10 us, the ones with a k below 32 and the k-contiguous
+// ones off 16-byte alignment; the larger ones go to the bf16 matrix instructions on three
+// terms per value (gemm_f32x3.hip) wherever the two cost models find that faster.
 //
 //   acc[m][n] = sum_k A(m,k) * B(n,k)
 //
@@ -23,19 +22,20 @@
 // What bounds it (MI355X, us of one launch in a row of dependent ones; in front of the
 // arrow the kernel this one replaced: four wavefronts of 32x32x2 MFMAs, a k-split over
 // workgroups with a second launch, rows off 16-byte alignment through a scalar path):
+//   256 x 1000 x 2048                        21 -> 12
+//   100 x 1000 x 300                         14 -> 4.9  launch, first loads, epilogue; two workgroups share a CU
+//   100 x 300 x 1000                         14 -> 5.7
+//   100 x 1003 x 2047 (nothing aligned)      20 -> 14
+// and, where it ran before gemm_f32x3.hip took them (now 48, 29, 34 and 25 us),
 //   1000 x 2048 x 2048 (both k-strided)      92 -> 74   64.7 us in the k-loop (54.5 at 2.4 GHz; the clock is 2.2
 //                                                       in kernels this short), 2.3 first loads, 2.5 epilogue
 //   512 x 4096 x 1024  (both k-contiguous)   45 -> 40   32 in the loop, 27.9 at 2.4 GHz
 //   512 x 1024 x 4096  (k-contiguous x strided) 47 -> 43   k divided inside the workgroup, no second launch
-//   256 x 1000 x 2048                        21 -> 12
-//   100 x 1000 x 300                         14 -> 4.9  launch, first loads, epilogue; two workgroups share a CU
-//   100 x 300 x 1000                         14 -> 5.7
 //   1003 x 2047 x 800 (nothing aligned)      60 -> 41
-//   100 x 1003 x 2047 (nothing aligned)      20 -> 14
 // 16x16x4 MFMAs rather than 32x32x2: in a kernel of 60 us a loop of nothing but MFMAs on
 // random operands runs at 2.40 GHz with the former and 2.23 with the latter.  Two
 // wavefronts per SIMD hide each other's LDS latency, barriers and load issue: a launch of
-// the first of these without any loads or reads in its loop takes 68 instead of 74 us.
+// 1000 x 2048 x 2048 without any loads or reads in its loop takes 68 instead of 74 us.
 #include "gemm_f32.h"
 
 #include <cmath>

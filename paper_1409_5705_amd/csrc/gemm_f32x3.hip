@@ -23,11 +23,13 @@
 //
 // 32x32x16 rather than 16x16x32 MFMAs: the latter hide two vector instructions each, and the loop has three times as many.
 //
-// What bounds it: power.  The launch of 1000 x 2048 over 2048 takes 79000 cycles of which the matrix pipes are busy for
-// 49000; on zeros the clock is 2.37 GHz and the launch takes 36 us, on N(0,1) values 1.65 to 1.8 GHz and 46 to 49.  Where k is
-// short the launch, first loads and epilogue (8 us in all) count as much.  The epilogue goes through buffer descriptors
-// because the branches of a bounds check per access made it wait for each old value in turn (24 instead of 29 us at
-// 1003 x 2047 over 800).
+// What bounds it: power and instruction issue.  The launch of 1000 x 2048 over 2048 takes 84600 cycles of which the matrix
+// pipes are busy for 49000; on zeros the clock is 2.35 GHz and the launch takes 36 us, on N(0,1) values 1.75 GHz and 47 to 49.
+// Where k is short the launch, first loads and epilogue (8 us in all) count as much.  The epilogue goes through buffer
+// descriptors because the branches of a bounds check per access made it wait for each old value in turn (24 instead of 29 us
+// at 1003 x 2047 over 800).  The launch takes 190 us where every sum is multiplied again (factors of nothing but NaN; the fp32
+// kernel 65).  Factors that rotate through 320 MB instead of coming from the caches: 48.2 / 49.0 us, 1003 x 2047 over 800
+// 24.9 / 26.1.
 #include "gemm_f32.h"
 
 #include <type_traits>
