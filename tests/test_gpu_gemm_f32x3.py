@@ -135,6 +135,9 @@ OVERFLOWS = [
     ((1 + 2.0 ** -7 - 2.0 ** -23) * 2.0 ** 64, 1.9921875 * 2.0 ** 63, True),
     (3.4028234663852886e38, 1.0, False), (1e38, 3.4, False), (1.9999 * 2.0 ** 70, 1.00004 * 2.0 ** 57, False),
 ]
+# whole and with a k-split, both tile shapes (test_kernel_plans.py), a partial block of k
+NOT_FINITE_APPLY = [(512, 4096, 1024), (364, 1707, 1148), (1025, 2113, 799), (131, 4367, 2491)]
+NOT_FINITE_LOGITS = [(512, 4096, 1024), (517, 1028, 4004), (177, 2732, 4148), (770, 2548, 716)]
 NANS = [0x7f800001, -0x7fffff, 0x7fc00000, 0x7f80ffff]      # (payloads in the low 16 bits only; -0x7fffff: 0xff800001)
 
 
@@ -155,9 +158,10 @@ def extremes(K, M, N):
     return a, b
 
 
-def test_overflow_and_nan_strided(ctx):
-    a, b = extremes(1024, 512, 4096)
-    C = torch.zeros(512, 4096, device="cuda:0")
+@pytest.mark.parametrize("M,N,K", NOT_FINITE_APPLY)
+def test_overflow_and_nan_strided(ctx, M, N, K):
+    a, b = extremes(K, M, N)
+    C = torch.zeros(M, N, device="cuda:0")
     ctx.sfb_apply(C, a, b, -1.0)
     for i, (x, y, overflow) in enumerate(OVERFLOWS):
         for at, sign in ((i, 1.0), (64 + i, -1.0)):
@@ -168,16 +172,17 @@ def test_overflow_and_nan_strided(ctx):
     assert torch.isposinf(C[50, 50])
 
 
-def test_overflow_and_nan_contiguous(ctx):
+@pytest.mark.parametrize("B,J,D", NOT_FINITE_LOGITS)
+def test_overflow_and_nan_contiguous(ctx, B, J, D):
     """Logits: the softmax of a row with an infinite one or NaN is NaN, with a finite one, however large, it is not."""
     import paper_1409_5705_amd as sfb
-    a, b = extremes(1024, 512, 4096)
+    a, b = extremes(D, B, J)
     b[:, 40:40 + len(NANS)] = 0.0                       # (NaN in every row otherwise)
     X, W = a.t().contiguous(), b.t().contiguous()
-    U = torch.empty(512, 4096, device="cuda:0")
-    ctx.sfb_compute_sf(sfb.SFB_MLR, W, X, Y=torch.zeros(512, dtype=torch.int32, device="cuda:0"), U=U)
+    U = torch.empty(B, J, device="cuda:0")
+    ctx.sfb_compute_sf(sfb.SFB_MLR, W, X, Y=torch.zeros(B, dtype=torch.int32, device="cuda:0"), U=U)
     nan = torch.isnan(U).any(dim=1)
-    want = torch.zeros(512, dtype=torch.bool)
+    want = torch.zeros(B, dtype=torch.bool)
     for i, (_, _, overflow) in enumerate(OVERFLOWS):
         want[i] = overflow
     want[32:32 + len(NANS)], want[50] = True, True
@@ -199,7 +204,7 @@ def test_not_finite_residual(ctx):
     for got, want in ((U, codes), (V, X.double() - codes @ W.double())):
         for test in (torch.isnan, torch.isposinf, torch.isneginf):
             assert torch.equal(test(got), test(want)), (test, (test(got) != test(want)).nonzero()[:4])
-    assert abs(U[5, 7].item() / 3e38 - 1) <= 1e-5
+    assert abs(U[5, 7].item() / 3e38 - 1) <= 1e-5 and float(V[5].abs().max()) <= 1e-5 * 3e38
 
 
 def test_rows_of_a_larger_matrix_and_alignment(ctx):

@@ -42,6 +42,9 @@ def test_three_term_shapes(lib):
     plans = [K.gemm_f32x3(lib, "apply", N, J, D) for J, D, N in x3.APPLY_SHAPES]
     assert all(plans) and all(K.gemm_f32x3(lib, "apply", N, J, D) for J, D, N in [(1003, 2047, 300), (1001, 2049, 333)]), list(zip(x3.APPLY_SHAPES, plans))
     assert {(t, split > 1) for t, split in plans} == {(t, s) for t in K.X3_TILES for s in (False, True)}
+    assert all(K.gemm_f32x3(lib, "apply", k, m, n) for m, n, k in x3.NOT_FINITE_APPLY)
+    reached = [K.gemm_f32x3(lib, "logits", B, J, D) for B, J, D in x3.NOT_FINITE_LOGITS]
+    assert all(reached) and {p[0] for p in reached} == set(K.X3_TILES) and {p[1] > 1 for p in reached} == {False, True}, reached
     assert {K.gemm_f32(lib, "apply", N, J, D)[::2] for J, D, N in x3.FP32_SHAPES} == {("128x64", True), ("128x64", False)}
 
 
