@@ -299,7 +299,7 @@ def main():
                     help="mlr_large_bf16: hand the samples over as CSR rows (sfb_mlr_sf_csr / sfb_apply_csr)")
     args = ap.parse_args()
     if args.gpus != 1 or int(os.environ.get("WORLD_SIZE", "1")) != 1:
-        print("bench.py measures one GPU: this build has no multi-GPU path (each GPU box has one GPU); "
+        print("bench.py measures one GPU: the library applies factors on one device and leaves their exchange to the caller; "
               "run with --gpus 1", file=sys.stderr)
         sys.exit(2)
 
